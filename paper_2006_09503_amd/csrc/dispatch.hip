@@ -12,6 +12,9 @@ void gemm_bf16_kernel_name(const GemmDesc* d, int count, char* out, size_t cap);
 hipError_t attention_fwd_simple(const AttnDesc& d, const void* qkv, void* o, float* lse, hipStream_t st);
 hipError_t attention_bwd_simple(const AttnDesc& d, const void* qkv, const void* o, const float* lse,
                                 const void* d_o, void* dqkv, float* delta, hipStream_t st);
+hipError_t attention_fwd_f32(const AttnDesc& d, const void* qkv, void* o, float* lse, hipStream_t st);
+hipError_t attention_bwd_f32(const AttnDesc& d, const void* qkv, const void* o, const float* lse, const void* d_o,
+                             void* dqkv, float* delta, hipStream_t st);
 hipError_t attention_fwd_mfma(const AttnDesc& d, const void* qkv, void* o, float* lse, hipStream_t st);
 hipError_t attention_bwd_mfma(const AttnDesc& d, const void* qkv, const void* o, const float* lse,
                               const void* d_o, void* dqkv, float* delta, hipStream_t st);
@@ -82,6 +85,7 @@ hipError_t attention_fwd(const AttnDesc& d, const void* qkv, void* o, float* lse
   if (e != hipSuccess) return e;
   if (!qkv || !o || !lse || !aligned16(qkv) || !aligned16(o)) return hipErrorInvalidValue;
   if (attention_mfma_supported(d)) return attention_fwd_mfma(d, qkv, o, lse, stream);
+  if (d.dtype == kF32) return attention_fwd_f32(d, qkv, o, lse, stream);
   return attention_fwd_simple(d, qkv, o, lse, stream);
 }
 
@@ -93,6 +97,7 @@ hipError_t attention_bwd(const AttnDesc& d, const void* qkv, const void* o, cons
   if (!aligned16(qkv) || !aligned16(o) || !aligned16(d_o) || !aligned16(dqkv)) return hipErrorInvalidValue;
   if (attention_mfma_supported(d)) return attention_bwd_mfma(d, qkv, o, lse, d_o, dqkv, delta, stream);
   if (d.colsum_partial) return hipErrorInvalidValue;   // only the MFMA kernels produce the column sums
+  if (d.dtype == kF32) return attention_bwd_f32(d, qkv, o, lse, d_o, dqkv, delta, stream);
   return attention_bwd_simple(d, qkv, o, lse, d_o, dqkv, delta, stream);
 }
 
