@@ -1,5 +1,13 @@
-// bf16 masked-softmax attention on the gfx950 matrix cores, forward and backward, for head
-// sizes 32, 64, 80 and 128.  fp32 scores, statistics and accumulators; no s x s matrix in HBM.
+// bf16 masked-softmax attention on the gfx950 matrix cores, forward and backward, for every head size that is a
+// multiple of 8 up to 128.  fp32 scores, statistics and accumulators; no s x s matrix in HBM.
+//
+// Two sets of instances.  Head sizes 32, 64, 80 and 128 have one each (ANY = false).  The others run on the next larger
+// of 32, 48, 64, 80, 96, 112, 128 with the true size at run time (ANY = true): tile columns past the head are fetched from
+// a zeroed chunk, rows past the sequence too.  These keep their probabilities (and dS) exact to 16 bits of mantissa:
+// a value enters the second product as the sum of two bf16 numbers, its rounding and the rounding of what that left,
+// two MFMAs instead of one; and a position that some rows of a tile may not see cannot reach them even if it holds
+// infinities or NaNs (accumulate_visible).  Measured at b=3 s=1000 a=16 dh=96 causal against one thread per row in fp32
+// on the vector ALU, which these sizes used to run on: forward 2892 -> 36 us, dQ with delta 2800 -> 46, dK/dV 13683 -> 81.
 //
 // All three kernels keep one query (forward, dQ) or one key (dK/dV) per lane of a 32-wide MFMA
 // column, so softmax statistics, lse and delta are per-lane scalars or short in-lane loops:
@@ -36,21 +44,20 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef short v4i16 __attribute__((ext_vector_type(4)));
 typedef short v8i16 __attribute__((ext_vector_type(8)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef __attribute__((address_space(3))) v4i16 lds_v4i16_t;
 typedef __attribute__((address_space(3))) void lds_void_t;
 typedef __attribute__((address_space(3))) char lds_char_t;
 typedef __attribute__((address_space(1))) const void glob_void_t;
 
-// Waves per workgroup, 32 rows (queries or keys) each.  Measured on MI355X with 2 / 4 / 8 waves
+// Waves per workgroup (NW), 32 rows (queries or keys) each.  Measured on MI355X with 2 / 4 / 8 waves
 // (s = 512, dh = 64: forward 27.9 / 20.7 / 19.5 us, backward 66.7 / 58.8 / 57.1 us; s = 2048,
 // dh = 128 causal: forward 270 / 258 / 152 us): more waves share each K/V tile and each barrier.
-constexpr int kWaves = 8;
-constexpr int kThreads = kWaves * 64;
-constexpr int kBlockRows = kWaves * 32;
+// That is with a workgroup for every CU; see waves_for for smaller launches.
 constexpr int kTile = 64;         // rows streamed through LDS per step
 constexpr float kLog2e = 1.4426950408889634f;
 
-template <int DH>
+template <int DH, bool ANY = false>
 struct Cfg {
   static constexpr int KS = DH / 16;               // MFMA k-steps over the head dimension
   static constexpr int DHP = (DH + 31) / 32 * 32;  // head dimension padded to whole 32-row blocks
@@ -58,22 +65,20 @@ struct Cfg {
   static constexpr int CH = DH / 8;                // 16-byte chunks per tile row
   static constexpr int kTileU4 = kTile * CH;       // uint4 per tile
   static constexpr int kPadU4 = 4;                 // transposing reads of the padded head columns run past a row
-  // Two waves per SIMD (which 8-wave workgroups imply) cap a lane at 256 registers; the compiler
-  // then keeps MFMA results in ordinary VGPRs.  With 512 available it parks them in the
-  // accumulator file and copies every score to a VGPR and back around the softmax arithmetic,
-  // which costs more than the MFMAs.
-  static constexpr int kMinWaves = 2;
-  static constexpr bool kDkvVInLds = DH == 128;   // dK/dV kernel: V fragments of the wave's keys in LDS, not registers
+  // dK/dV kernel: V (K) fragments of the wave's keys in LDS, not registers
+  static constexpr bool kDkvParts = ANY && DH >= 112;   // dK and dV in workgroups of their own
+  static constexpr bool kDkvVInLds = (DH == 128 && !ANY) || (ANY && DH == 96), kDkvKInLds = ANY && DH == 96;
 };
 
-// Chunk swizzle per head size (rows are 64 / 128 / 160 / 256 bytes; the LDS has 64 banks of 4 bytes).
+// Chunk swizzle per head size (rows are 64 / 96 / 128 / 160 / 192 / 224 / 256 bytes; the LDS has 64 banks of 4 bytes).
 // Checked against a bank model for both read patterns: 16-byte reads of 16 consecutive rows at one
 // logical chunk, and the transposing 8-byte reads (4 consecutive rows x 32 or 64 contiguous bytes).
 template <int DH>
 __device__ __forceinline__ int swz(int r) {
   if (DH == 32) return (r >> 2) & 3;
   if (DH == 64) { const int u = (r >> 1) & 7; return ((u & 1) << 2) | (u >> 1); }
-  if (DH == 80) return (r >> 3) & 1;
+  if (DH == 48 || DH == 80 || DH == 112) return (r >> 3) & 1;   // 8 rows start on 8 different even chunks of a bank line
+  if (DH == 96) return (r >> 2) & 3;                            // 4 rows start on every fourth chunk
   return ((r & 3) << 2) | ((r >> 2) & 3);
 }
 
@@ -82,49 +87,47 @@ constexpr int vmcnt_imm(int n) { return (n & 15) | ((n >> 4) << 14) | (7 << 4) |
 
 // Rows [row0, row0 + 64) x DH of a [*, ld] matrix -> LDS tile; lane i of a load instruction owns
 // LDS slot L0 + i and fetches the chunk that belongs there.  Rows >= row_end are fetched from row
-// row_end - 1 (finite data; whatever they produce is masked or never stored).
-template <int DH>
+// row_end - 1 (finite data; whatever they produce is masked or never stored).  ANY: those rows and the
+// columns past the head come from a chunk of zeros.
+__device__ const uint4 kZeroChunk = {0, 0, 0, 0};
+template <int DH, bool ANY, int NW>
 struct TileLoader {
   static constexpr int CH = DH / 8;
   static constexpr int kInstr = kTile * CH / 64;            // wave-instructions per tile
-  static constexpr int NI = (kInstr + kWaves - 1) / kWaves;  // per wave
+  static constexpr int NI = (kInstr + NW - 1) / NW;  // per wave
   int row[NI], coff[NI];
   int wave_;
-  __device__ __forceinline__ void init(int wave, int lane) {
+  __device__ __forceinline__ void init(int wave, int lane, int dh) {
     wave_ = wave;
 #pragma unroll
     for (int j = 0; j < NI; ++j) {
-      const int L = (j * kWaves + wave) * 64 + lane;
+      const int L = (j * NW + wave) * 64 + lane;
       const int r = L / CH, pc = L % CH;
       row[j] = r < kTile ? r : kTile - 1;
       coff[j] = (pc ^ swz<DH>(r)) * 8;
+      if (ANY && coff[j] >= dh) coff[j] = -1;
     }
   }
   __device__ __forceinline__ void issue(const bf16_t* __restrict__ src, int64_t ld, int row0, int row_end, uint4* tile) const {
 #pragma unroll
     for (int j = 0; j < NI; ++j) {
-      if ((j * kWaves + wave_) < kInstr) {   // wave-uniform
+      if ((j * NW + wave_) < kInstr) {   // wave-uniform
         const int r = min(row0 + row[j], row_end - 1);
-        __builtin_amdgcn_global_load_lds((glob_void_t*)(src + (int64_t)r * ld + coff[j]),
-                                         (lds_void_t*)(tile + (j * kWaves + wave_) * 64), 16, 0, 0);
+        const bf16_t* from = src + (int64_t)r * ld + (ANY ? max(coff[j], 0) : coff[j]);
+        if (ANY && (coff[j] < 0 || row0 + row[j] >= row_end)) from = reinterpret_cast<const bf16_t*>(&kZeroChunk);
+        __builtin_amdgcn_global_load_lds((glob_void_t*)from, (lds_void_t*)(tile + (j * NW + wave_) * 64), 16, 0, 0);
       }
     }
   }
 };
 
-// 64 floats starting at src[i0] -> LDS, by one wave (4 bytes per lane); entries past n_valid repeat the last one
-__device__ __forceinline__ void issue_floats(const float* __restrict__ src, int i0, int n_valid, float* dst, int lane) {
-  const int i = min(i0 + lane, n_valid - 1);
-  __builtin_amdgcn_global_load_lds((glob_void_t*)(src + i), (lds_void_t*)dst, 4, 0, 0);
-}
-
 // 16-byte k-fragment of a row of a [*, ld] matrix straight from HBM (second MFMA operand)
-template <int DH>
-__device__ __forceinline__ void load_frags(const bf16_t* __restrict__ row_ptr, bool ok, int hf, bf16x8 (&f)[Cfg<DH>::KS]) {
+template <int DH, bool ANY>
+__device__ __forceinline__ void load_frags(const bf16_t* __restrict__ row_ptr, bool ok, int hf, int dh, bf16x8 (&f)[Cfg<DH>::KS]) {
 #pragma unroll
   for (int ks = 0; ks < Cfg<DH>::KS; ++ks) {
     uint4 v = make_uint4(0, 0, 0, 0);
-    if (ok) v = *reinterpret_cast<const uint4*>(row_ptr + ks * 16 + hf * 8);
+    if (ok && (!ANY || ks * 16 + hf * 8 < dh)) v = *reinterpret_cast<const uint4*>(row_ptr + ks * 16 + hf * 8);
     f[ks] = __builtin_bit_cast(bf16x8, v);
   }
 }
@@ -142,6 +145,20 @@ __device__ __forceinline__ bf16x8 pack_half(const f32x16& v, int half) {
   w.x = pack_bf16x2(v[b + 0], v[b + 1]); w.y = pack_bf16x2(v[b + 2], v[b + 3]);
   w.z = pack_bf16x2(v[b + 4], v[b + 5]); w.w = pack_bf16x2(v[b + 6], v[b + 7]);
   return __builtin_bit_cast(bf16x8, w);
+}
+
+// The same as the sum of two operands: what rounding to bf16 gives, and the rounding of what it left (v - hi is exact)
+__device__ __forceinline__ void pack_half_split(const f32x16& v, int half, bf16x8& hi, bf16x8& lo) {
+  uint32_t wh[4], wl[4];
+  const int b = 8 * half;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const float x = v[b + 2 * i], y = v[b + 2 * i + 1];
+    wh[i] = pack_bf16x2(x, y);
+    wl[i] = pack_bf16x2(x - __uint_as_float(wh[i] << 16), y - __uint_as_float(wh[i] & 0xffff0000u));
+  }
+  hi = __builtin_bit_cast(bf16x8, make_uint4(wh[0], wh[1], wh[2], wh[3]));
+  lo = __builtin_bit_cast(bf16x8, make_uint4(wl[0], wl[1], wl[2], wl[3]));
 }
 
 // First operand, head columns of the tile as MFMA rows: this lane's row is head column
@@ -174,6 +191,51 @@ __device__ __forceinline__ uint2 pack4f(float a, float b, float c, float d) {
   return make_uint2(pack_bf16x2(a, b), pack_bf16x2(c, d));
 }
 
+// Does the 64-row tile hold an infinity or a NaN? (the same answer in every lane)
+template <int DH>
+__device__ __forceinline__ bool tile_not_finite(const uint4* tile, int lane) {
+  uint32_t top = 0;   // adding 1 to an exponent of all ones carries into the sign's place
+#pragma unroll 4
+  for (int i = 0; i < Cfg<DH>::CH; ++i) {
+    const uint4 v = tile[i * 64 + lane];
+    top |= ((v.x & 0x7f807f80u) + 0x00800080u) | ((v.y & 0x7f807f80u) + 0x00800080u) | ((v.z & 0x7f807f80u) + 0x00800080u) |
+           ((v.w & 0x7f807f80u) + 0x00800080u);
+  }
+  return __any((top & 0x80008000u) != 0);
+}
+
+// out += X^T P over the tile rows [row0, row0 + 32), row by row and only into the lanes whose query (key) sees the row: for
+// a tile that holds infinities or NaNs and is not visible as a whole (0 * inf would reach rows that must not see it).
+// Rare: the kernels only look for such tiles in their loop, and a workgroup that met one starts over in the EXACT form
+// (inside the one loop this path cost the dK/dV kernel hundreds of spilled registers: 299 us instead of 100 at head size 96, b=3 s=1000 a=16).
+template <int DH, typename Sees>
+__device__ __forceinline__ void accumulate_visible(const uint4* tile, int row0, const f32x16& p, f32x16 (&out)[Cfg<DH>::DB], int lane, Sees&& sees) {
+  const int hf = lane >> 5;
+#pragma unroll 1
+  for (int rr = 0; rr < 32; ++rr) {
+    const int reg = (rr >> 3) * 4 + (rr & 3), row = row0 + rr;
+    float w = p[0];
+#pragma unroll
+    for (int e = 1; e < 16; ++e) w = e == reg ? p[e] : w;
+    const float other = __shfl_xor(w, 32, 64);
+    w = ((rr >> 2) & 1) == hf ? w : other;
+    if (!sees(row)) continue;
+    const lds_char_t* x = (const lds_char_t*)(tile + row * Cfg<DH>::CH) + hf * 8;
+    const int sw = swz<DH>(row);
+#pragma unroll
+    for (int chunk = 0; chunk < Cfg<DH>::CH; ++chunk) {
+      const u32x2 v = *(const __attribute__((address_space(3))) u32x2*)(x + ((chunk ^ sw) << 4));
+      f32x16& o = out[chunk >> 2];
+      const int g = 4 * (chunk & 3);
+      o[g] = fmaf(w, __uint_as_float(v.x << 16), o[g]);
+      o[g + 1] = fmaf(w, __uint_as_float(v.x & 0xffff0000u), o[g + 1]);
+      o[g + 2] = fmaf(w, __uint_as_float(v.y << 16), o[g + 2]);
+      o[g + 3] = fmaf(w, __uint_as_float(v.y & 0xffff0000u), o[g + 3]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+}
+
 // Sum of v over the 16 lanes of a DPP row, left in every lane of the row: two quad permutes, then
 // the half-row and full-row mirrors (each step adds a lane that holds the other group's sum).
 __device__ __forceinline__ float row16_sum(float v) {
@@ -190,8 +252,8 @@ __device__ __forceinline__ float row16_sum(float v) {
 
 // Column sums over the workgroup's rows of a result held as acc[db][r] (lane = row, registers =
 // head columns db*32 + 8*(r/4) + 4*hf + r%4), scaled by `scale`, written to out[0 .. DH).
-// red: 16 * DHP floats of LDS that no wave still reads (one partial row per 16 lanes).
-template <int DH>
+// red: 2 * NW * DHP floats of LDS that no wave still reads (one partial row per 16 lanes).
+template <int DH, int NW>
 __device__ __forceinline__ void block_column_sums(const f32x16 (&acc)[Cfg<DH>::DB], float scale, float* red, float* out,
                                                   int tid, int lane, int wave) {
   using C = Cfg<DH>;
@@ -209,10 +271,10 @@ __device__ __forceinline__ void block_column_sums(const f32x16 (&acc)[Cfg<DH>::D
       if ((lane & 15) == 0) *reinterpret_cast<float4*>(mine + db * 32 + 8 * g) = v;
     }
   __syncthreads();
-  for (int d = tid; d < DH; d += kThreads) {
+  for (int d = tid; d < DH; d += NW * 64) {
     float t = 0.f;
 #pragma unroll
-    for (int w = 0; w < 2 * kWaves; ++w) t += red[w * C::DHP + d];
+    for (int w = 0; w < 2 * NW; ++w) t += red[w * C::DHP + d];
     out[d] = t * scale;
   }
 }
@@ -234,7 +296,7 @@ __device__ __forceinline__ void wave_lds_sync() {
 }
 template <int DH>
 __device__ __forceinline__ void store_rows(const f32x16 (&acc)[Cfg<DH>::DB], float scale, uint4* strip, bf16_t* out, int64_t ld,
-                                           int rows_valid, int lane) {
+                                           int rows_valid, int dh, int lane) {
   using C = Cfg<DH>;
   constexpr int STRIDE = 2 * DH + 16;   // bytes
   char* w = reinterpret_cast<char*>(strip);
@@ -254,7 +316,7 @@ __device__ __forceinline__ void store_rows(const f32x16 (&acc)[Cfg<DH>::DB], flo
   for (int it = 0; it < (TOTAL + 63) / 64; ++it) {
     const int L = it * 64 + lane;
     const int row = L / C::CH, ch = L % C::CH;
-    if (L < TOTAL && row < rows_valid)
+    if (L < TOTAL && row < rows_valid && ch * 8 < dh)
       *reinterpret_cast<uint4*>(out + row * ld + ch * 8) = *reinterpret_cast<const uint4*>(w + row * STRIDE + ch * 16);
   }
   wave_lds_sync();   // the strip may be written again
@@ -262,10 +324,11 @@ __device__ __forceinline__ void store_rows(const f32x16 (&acc)[Cfg<DH>::DB], flo
 
 // ------------------------------------------------------------------------------------------------
 // forward
-template <int DH>
-__global__ __launch_bounds__(kThreads, Cfg<DH>::kMinWaves) void attn_fwd_mfma_kernel(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ o,
-                                                                  float* __restrict__ lse, int s, int a, int mask_mode,
-                                                                  const int32_t* __restrict__ seqlens) {
+// (all kernels: two waves per SIMD, which 8-wave workgroups imply, cap a lane at 256 registers; the compiler then keeps
+// MFMA results in ordinary VGPRs.  With 512 available it parks them in the accumulator file and copies every score to a
+// VGPR and back around the softmax arithmetic, which costs more than the MFMAs.)
+template <int DH, int NW, bool ANY, bool EXACT>
+__device__ __forceinline__ bool attn_fwd(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ o, float* __restrict__ lse, int s, int a, int mask_mode, const int32_t* __restrict__ seqlens, int dh_) {
   using C = Cfg<DH>;
   extern __shared__ uint4 smem[];   // stage st: K tile at st * 2 * kTileU4, V tile behind it
 
@@ -275,28 +338,30 @@ __global__ __launch_bounds__(kThreads, Cfg<DH>::kMinWaves) void attn_fwd_mfma_ke
   // first: the workgroups that take longest start earliest and the launch does not end on one of them
   const int n = blockIdx.y, head = blockIdx.x;
   const int blk = mask_mode == 1 ? (int)(gridDim.z - 1 - blockIdx.z) : (int)blockIdx.z;
-  const int i0 = blk * kBlockRows;
-  const int h = a * DH;
+  const int i0 = blk * NW * 32;
+  const int dh = ANY ? dh_ : DH;
+  const int h = a * dh;
   const int64_t ld = 3 * (int64_t)h;
-  const bf16_t* base = qkv + (int64_t)n * s * ld + head * DH;
+  const bf16_t* base = qkv + (int64_t)n * s * ld + head * dh;
   const int kv_len = mask_mode == 2 ? min(max(seqlens[n], 1), s) : s;   // lengths outside [1, s] are clamped: no read past the sequence, no empty row
   const bool causal = mask_mode == 1;
   const int iw0 = i0 + wave * 32;
   const int i = iw0 + l32;
-  const float scale = 1.0f / sqrtf((float)DH);
+  const float scale = 1.0f / sqrtf((float)dh);
   const float c = scale * kLog2e;
 
   bf16x8 qf[C::KS];
-  load_frags<DH>(base + (int64_t)i * ld, i < s, hf, qf);
+  load_frags<DH, ANY>(base + (int64_t)i * ld, i < s, hf, dh, qf);
   f32x16 oacc[C::DB];
+  float m_i = -INFINITY, l_i = 0.f;
+  bool hidden = false;   // ANY: a tile that not every row sees holds infinities or NaNs
+
+  const int jend = causal ? min(i0 + NW * 32, s) : kv_len;
+  const int ntiles = (jend + kTile - 1) / kTile;
+  TileLoader<DH, ANY, NW> loader;
+  loader.init(wave, lane, dh);
 #pragma unroll
   for (int db = 0; db < C::DB; ++db) oacc[db] = zero16();
-  float m_i = -INFINITY, l_i = 0.f;
-
-  const int jend = causal ? min(i0 + kBlockRows, s) : kv_len;
-  const int ntiles = (jend + kTile - 1) / kTile;
-  TileLoader<DH> loader;
-  loader.init(wave, lane);
   loader.issue(base + h, ld, 0, jend, smem);
   loader.issue(base + 2 * h, ld, 0, jend, smem + C::kTileU4);
   for (int t = 0; t < ntiles; ++t) {
@@ -355,31 +420,57 @@ __global__ __launch_bounds__(kThreads, Cfg<DH>::kMinWaves) void attn_fwd_mfma_ke
     for (int db = 0; db < C::DB; ++db)
 #pragma unroll
       for (int r = 0; r < 16; ++r) oacc[db][r] *= alpha;
-    bf16x8 pb[4];
+    if constexpr (ANY) {
+      if (causal && j0 + kTile - 1 > iw0) {
+        if (EXACT) {
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk) pb[kk] = pack_half(sacc[kk >> 1], kk & 1);
+          for (int nb = 0; nb < 2; ++nb) accumulate_visible<DH>(v_lds, nb * 32, sacc[nb], oacc, lane, [&](int row) { return j0 + row <= i; });
+          continue;
+        }
+        hidden = hidden || tile_not_finite<DH>(v_lds, lane);
+      }
 #pragma unroll
-    for (int db = 0; db < C::DB; ++db)
+      for (int kk = 0; kk < 4; ++kk) {
+        bf16x8 hi, lo;
+        pack_half_split(sacc[kk >> 1], kk & 1, hi, lo);
 #pragma unroll
-      for (int kk = 0; kk < 4; ++kk)
-        oacc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(read_cols<DH>(v_lds, db * 32, kk, lane), pb[kk], oacc[db], 0, 0, 0);
+        for (int db = 0; db < C::DB; ++db) {
+          const bf16x8 v = read_cols<DH>(v_lds, db * 32, kk, lane);
+          oacc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v, hi, oacc[db], 0, 0, 0);
+          oacc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v, lo, oacc[db], 0, 0, 0);
+        }
+      }
+    } else {
+      bf16x8 pb[4];
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk) pb[kk] = pack_half(sacc[kk >> 1], kk & 1);
+#pragma unroll
+      for (int db = 0; db < C::DB; ++db)
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk)
+          oacc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(read_cols<DH>(v_lds, db * 32, kk, lane), pb[kk], oacc[db], 0, 0, 0);
+    }
   }
+  if constexpr (ANY && !EXACT)
+    if (__syncthreads_or(hidden)) return true;
 
   const float l_tot = l_i + __shfl_xor(l_i, 32, 64);
   __syncthreads();   // every wave is done with the K / V tiles, whose LDS the output strips re-use
   const float inv = 1.0f / l_tot;   // (rows past the sequence: never stored)
-  store_rows<DH>(oacc, inv, smem + wave * out_strip_u4<DH>(), o + ((int64_t)n * s + iw0) * h + head * DH, h, s - iw0, lane);
+  store_rows<DH>(oacc, inv, smem + wave * out_strip_u4<DH>(), o + ((int64_t)n * s + iw0) * h + head * dh, h, s - iw0, dh, lane);
   if (i < s && hf == 0) lse[((int64_t)n * a + head) * s + i] = m_i * scale + logf(l_tot);
+  return false;
+}
+template <int DH, int NW, bool ANY>
+__global__ __launch_bounds__(NW * 64, 2) void attn_fwd_mfma_kernel(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ o, float* __restrict__ lse, int s, int a, int mask_mode, const int32_t* __restrict__ seqlens, int dh_) {
+  if (attn_fwd<DH, NW, ANY, false>(qkv, o, lse, s, a, mask_mode, seqlens, dh_))
+    if constexpr (ANY) attn_fwd<DH, NW, ANY, true>(qkv, o, lse, s, a, mask_mode, seqlens, dh_);
 }
 
 // ------------------------------------------------------------------------------------------------
 // dQ (and delta = rowsum(dO * O), which the dK/dV kernel reads afterwards)
-template <int DH>
-__global__ __launch_bounds__(kThreads, Cfg<DH>::kMinWaves) void attn_dq_mfma_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ o,
-                                                                 const bf16_t* __restrict__ d_o, const float* __restrict__ lse,
-                                                                 float* __restrict__ delta, bf16_t* __restrict__ dqkv, int s,
-                                                                 int a, int mask_mode, const int32_t* __restrict__ seqlens,
-                                                                 float* __restrict__ colsum) {
+template <int DH, int NW, bool ANY, bool EXACT>
+__device__ __forceinline__ bool attn_dq(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ o, const bf16_t* __restrict__ d_o, const float* __restrict__ lse, float* __restrict__ delta, bf16_t* __restrict__ dqkv, int s, int a, int mask_mode, const int32_t* __restrict__ seqlens, float* __restrict__ colsum, int dh_) {
   using C = Cfg<DH>;
   extern __shared__ uint4 smem[];   // stage st: K tile at st * 2 * kTileU4, V tile behind it
 
@@ -389,32 +480,33 @@ __global__ __launch_bounds__(kThreads, Cfg<DH>::kMinWaves) void attn_dq_mfma_ker
   // first: the workgroups that take longest start earliest and the launch does not end on one of them
   const int n = blockIdx.y, head = blockIdx.x;
   const int blk = mask_mode == 1 ? (int)(gridDim.z - 1 - blockIdx.z) : (int)blockIdx.z;
-  const int i0 = blk * kBlockRows;
-  const int h = a * DH;
+  const int i0 = blk * NW * 32;
+  const int dh = ANY ? dh_ : DH;
+  const int h = a * dh;
   const int64_t ld = 3 * (int64_t)h;
-  const bf16_t* base = qkv + (int64_t)n * s * ld + head * DH;
+  const bf16_t* base = qkv + (int64_t)n * s * ld + head * dh;
   const int kv_len = mask_mode == 2 ? min(max(seqlens[n], 1), s) : s;   // lengths outside [1, s] are clamped: no read past the sequence, no empty row
   const bool causal = mask_mode == 1;
   const int iw0 = i0 + wave * 32;
   const int i = iw0 + l32;
   const bool row_ok = i < s;
-  const float scale = 1.0f / sqrtf((float)DH);
+  const float scale = 1.0f / sqrtf((float)dh);
   const float c = scale * kLog2e;
 
-  const int jend = causal ? min(i0 + kBlockRows, s) : kv_len;
+  const int jend = causal ? min(i0 + NW * 32, s) : kv_len;
   const int ntiles = (jend + kTile - 1) / kTile;
-  TileLoader<DH> loader;
-  loader.init(wave, lane);
+  TileLoader<DH, ANY, NW> loader;
+  loader.init(wave, lane, dh);
   loader.issue(base + h, ld, 0, jend, smem);
   loader.issue(base + 2 * h, ld, 0, jend, smem + C::kTileU4);
 
   bf16x8 qf[C::KS], dof[C::KS];
-  load_frags<DH>(base + (int64_t)i * ld, row_ok, hf, qf);
-  load_frags<DH>(d_o + ((int64_t)n * s + i) * h + head * DH, row_ok, hf, dof);
+  load_frags<DH, ANY>(base + (int64_t)i * ld, row_ok, hf, dh, qf);
+  load_frags<DH, ANY>(d_o + ((int64_t)n * s + i) * h + head * dh, row_ok, hf, dh, dof);
   float delta_i;
   {
     bf16x8 of[C::KS];
-    load_frags<DH>(o + ((int64_t)n * s + i) * h + head * DH, row_ok, hf, of);
+    load_frags<DH, ANY>(o + ((int64_t)n * s + i) * h + head * dh, row_ok, hf, dh, of);
     float part = 0.f;
 #pragma unroll
     for (int ks = 0; ks < C::KS; ++ks)
@@ -424,10 +516,13 @@ __global__ __launch_bounds__(kThreads, Cfg<DH>::kMinWaves) void attn_dq_mfma_ker
     if (row_ok && hf == 0) delta[((int64_t)n * a + head) * s + i] = delta_i;
   }
   const float lse_i = row_ok ? lse[((int64_t)n * a + head) * s + i] * kLog2e : INFINITY;
+  f32x16 minus_delta;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) minus_delta[r] = -delta_i;
   f32x16 dq[C::DB];
+  bool hidden = false;
 #pragma unroll
   for (int db = 0; db < C::DB; ++db) dq[db] = zero16();
-
   for (int t = 0; t < ntiles; ++t) {
     const int j0 = t * kTile;
     __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
@@ -441,7 +536,7 @@ __global__ __launch_bounds__(kThreads, Cfg<DH>::kMinWaves) void attn_dq_mfma_ker
     const uint4* k_lds = smem + (t & 1) * 2 * C::kTileU4;
     const uint4* v_lds = k_lds + C::kTileU4;
 
-    f32x16 sacc[2] = {zero16(), zero16()}, dp[2] = {zero16(), zero16()};
+    f32x16 sacc[2] = {zero16(), zero16()}, dp[2] = {minus_delta, minus_delta};   // dP - delta comes out of the product
 #pragma unroll
     for (int ks = 0; ks < C::KS; ++ks) {
 #pragma unroll
@@ -459,6 +554,7 @@ __global__ __launch_bounds__(kThreads, Cfg<DH>::kMinWaves) void attn_dq_mfma_ker
           const int key = j0 + nb * 32 + 8 * (r >> 2) + 4 * hf + (r & 3);
           const bool vis = key < kv_len && (!causal || key <= i);
           sacc[nb][r] = vis ? sacc[nb][r] : -INFINITY;
+          if (ANY) dp[nb][r] = vis ? dp[nb][r] : 0.f;   // dS is zero then, whatever the masked V holds
         }
     }
 #pragma unroll
@@ -466,33 +562,62 @@ __global__ __launch_bounds__(kThreads, Cfg<DH>::kMinWaves) void attn_dq_mfma_ker
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         const float pv = __builtin_amdgcn_exp2f(fmaf(sacc[nb][r], c, -lse_i));
-        sacc[nb][r] = pv * (dp[nb][r] - delta_i);   // dS^T (the 1/sqrt(dh) factor is applied at the end)
+        sacc[nb][r] = pv * dp[nb][r];   // dS^T (the 1/sqrt(dh) factor is applied at the end)
       }
-    bf16x8 dsb[4];
+    if constexpr (ANY) {
+      if (causal && j0 + kTile - 1 > iw0) {
+        if (EXACT) {
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk) dsb[kk] = pack_half(sacc[kk >> 1], kk & 1);
+          for (int nb = 0; nb < 2; ++nb) accumulate_visible<DH>(k_lds, nb * 32, sacc[nb], dq, lane, [&](int row) { return j0 + row <= i; });
+          continue;
+        }
+        hidden = hidden || tile_not_finite<DH>(k_lds, lane);
+      }
 #pragma unroll
-    for (int db = 0; db < C::DB; ++db)
+      for (int kk = 0; kk < 4; ++kk) {
+        bf16x8 hi, lo;
+        pack_half_split(sacc[kk >> 1], kk & 1, hi, lo);
 #pragma unroll
-      for (int kk = 0; kk < 4; ++kk)
-        dq[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(read_cols<DH>(k_lds, db * 32, kk, lane), dsb[kk], dq[db], 0, 0, 0);
+        for (int db = 0; db < C::DB; ++db) {
+          const bf16x8 k = read_cols<DH>(k_lds, db * 32, kk, lane);
+          dq[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k, hi, dq[db], 0, 0, 0);
+          dq[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k, lo, dq[db], 0, 0, 0);
+        }
+      }
+    } else {
+      bf16x8 dsb[4];
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk) dsb[kk] = pack_half(sacc[kk >> 1], kk & 1);
+#pragma unroll
+      for (int db = 0; db < C::DB; ++db)
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk)
+          dq[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(read_cols<DH>(k_lds, db * 32, kk, lane), dsb[kk], dq[db], 0, 0, 0);
+    }
   }
+  if constexpr (ANY && !EXACT)
+    if (__syncthreads_or(hidden)) return true;
   __syncthreads();   // every wave is done with the K / V tiles
-  if (colsum) {   // rows past the end of the sequence hold zeros
-    float* row = colsum + ((int64_t)n * gridDim.z + blk) * ld + head * DH;
-    block_column_sums<DH>(dq, scale, reinterpret_cast<float*>(smem), row, tid, lane, wave);
+  if (!ANY && colsum) {   // rows past the end of the sequence hold zeros
+    float* row = colsum + ((int64_t)n * gridDim.z + blk) * ld + head * dh;
+    block_column_sums<DH, NW>(dq, scale, reinterpret_cast<float*>(smem), row, tid, lane, wave);
     __syncthreads();   // ... and with the partial rows of the sums
   }
-  store_rows<DH>(dq, scale, smem + wave * out_strip_u4<DH>(), dqkv + ((int64_t)n * s + iw0) * ld + head * DH, ld, s - iw0, lane);
+  store_rows<DH>(dq, scale, smem + wave * out_strip_u4<DH>(), dqkv + ((int64_t)n * s + iw0) * ld + head * dh, ld, s - iw0, dh, lane);
+  return false;
+}
+template <int DH, int NW, bool ANY>
+__global__ __launch_bounds__(NW * 64, 2) void attn_dq_mfma_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ o, const bf16_t* __restrict__ d_o, const float* __restrict__ lse, float* __restrict__ delta, bf16_t* __restrict__ dqkv, int s, int a, int mask_mode, const int32_t* __restrict__ seqlens, float* __restrict__ colsum, int dh_) {
+  if (attn_dq<DH, NW, ANY, false>(qkv, o, d_o, lse, delta, dqkv, s, a, mask_mode, seqlens, colsum, dh_))
+    if constexpr (ANY) attn_dq<DH, NW, ANY, true>(qkv, o, d_o, lse, delta, dqkv, s, a, mask_mode, seqlens, colsum, dh_);
 }
 
 // ------------------------------------------------------------------------------------------------
 // dK, dV
-template <int DH>
-__global__ __launch_bounds__(kThreads, Cfg<DH>::kMinWaves) void attn_dkv_mfma_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ d_o,
-                                                                  const float* __restrict__ lse, const float* __restrict__ delta,
-                                                                  bf16_t* __restrict__ dqkv, int s, int a, int mask_mode,
-                                                                  const int32_t* __restrict__ seqlens, float* __restrict__ colsum) {
+// PART: 0 both results; 1 only dV, 2 only dK (the largest heads of the ANY set, where both accumulators, split operands and
+// fragments did not fit in the registers: a workgroup then makes one of the two, at the price of the scores twice)
+template <int DH, int NW, bool ANY, bool EXACT, int PART>
+__device__ __forceinline__ bool attn_dkv(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ d_o, const float* __restrict__ lse, const float* __restrict__ delta, bf16_t* __restrict__ dqkv, int s, int a, int mask_mode, const int32_t* __restrict__ seqlens, float* __restrict__ colsum, int dh_) {
   using C = Cfg<DH>;
   extern __shared__ uint4 smem[];
   // stage st: Q tile, dO tile, 64 lse, 64 delta
@@ -501,12 +626,14 @@ __global__ __launch_bounds__(kThreads, Cfg<DH>::kMinWaves) void attn_dkv_mfma_ke
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l32 = lane & 31, hf = lane >> 5;
   // grid = (heads, sequences, key blocks), key block slowest: under a causal mask the first keys are seen by
   // the most queries, and those workgroups are dispatched first (see the forward kernel)
-  const int n = blockIdx.y, head = blockIdx.x, blk = blockIdx.z;
-  const int j0 = blk * kBlockRows;
-  const int h = a * DH;
+  const int n = blockIdx.y, head = blockIdx.x, blk = PART ? (int)blockIdx.z >> 1 : (int)blockIdx.z;
+  constexpr bool DV = PART != 2, DK = PART != 1;
+  const int j0 = blk * NW * 32;
+  const int dh = ANY ? dh_ : DH;
+  const int h = a * dh;
   const int64_t ld = 3 * (int64_t)h;
-  const bf16_t* base = qkv + (int64_t)n * s * ld + head * DH;
-  const bf16_t* dobase = d_o + (int64_t)n * s * h + head * DH;
+  const bf16_t* base = qkv + (int64_t)n * s * ld + head * dh;
+  const bf16_t* dobase = d_o + (int64_t)n * s * h + head * dh;
   const float* lse_row = lse + ((int64_t)n * a + head) * s;
   const float* delta_row = delta + ((int64_t)n * a + head) * s;
   const int kv_len = mask_mode == 2 ? min(max(seqlens[n], 1), s) : s;   // lengths outside [1, s] are clamped: no read past the sequence, no empty row
@@ -514,43 +641,58 @@ __global__ __launch_bounds__(kThreads, Cfg<DH>::kMinWaves) void attn_dkv_mfma_ke
   const int jw0 = j0 + wave * 32;
   const int j = jw0 + l32;
   const bool row_ok = j < s;
-  const float scale = 1.0f / sqrtf((float)DH);
+  const float scale = 1.0f / sqrtf((float)dh);
   const float c = scale * kLog2e;
 
   bf16x8 kf[C::KS], vf[C::KS];
-  load_frags<DH>(base + h + (int64_t)j * ld, row_ok, hf, kf);
-  load_frags<DH>(base + 2 * h + (int64_t)j * ld, row_ok, hf, vf);
+  load_frags<DH, ANY>(base + h + (int64_t)j * ld, row_ok, hf, dh, kf);
+  load_frags<DH, ANY>(base + 2 * h + (int64_t)j * ld, row_ok, hf, dh, vf);
   // At head size 128 the two accumulators are 128 registers and the K and V fragments of the wave's keys 64 more: with
   // the scores on top the kernel spilled.  There the V fragments wait in a wave-private piece of LDS (16 bytes per
   // lane and k-step, read back in the order written: no bank conflicts, no barrier) and are fetched per use.
-  constexpr bool kVInLds = Cfg<DH>::kDkvVInLds;
+  // (ANY: two fragments per probability operand and the path for hidden infinities raise the count; there from 80 on, K too
+  // where LDS has room.)
+  constexpr bool kVInLds = Cfg<DH, ANY>::kDkvVInLds, kKInLds = Cfg<DH, ANY>::kDkvKInLds;
   uint4* vstore = smem + 2 * kStageU4 + C::kPadU4 + wave * (C::KS * 64);
   if (kVInLds) {
 #pragma unroll
     for (int ks = 0; ks < C::KS; ++ks) vstore[ks * 64 + lane] = __builtin_bit_cast(uint4, vf[ks]);
   }
-  f32x16 dk[C::DB], dv[C::DB];
+  uint4* kstore = smem + 2 * kStageU4 + C::kPadU4 + (NW + wave) * (C::KS * 64);
+  if (kKInLds) {
 #pragma unroll
-  for (int db = 0; db < C::DB; ++db) { dk[db] = zero16(); dv[db] = zero16(); }
+    for (int ks = 0; ks < C::KS; ++ks) kstore[ks * 64 + lane] = __builtin_bit_cast(uint4, kf[ks]);
+  }
+  f32x16 dk[C::DB], dv[C::DB];
 
   const bool wg_dead = j0 >= kv_len;                       // every key of the workgroup is padding
   const int istart = causal ? (j0 / kTile) * kTile : 0;    // earlier queries see none of these keys
   const int ntiles = wg_dead ? 0 : (s - istart + kTile - 1) / kTile;
-  TileLoader<DH> loader;
-  loader.init(wave, lane);
+  TileLoader<DH, ANY, NW> loader;
+  loader.init(wave, lane, dh);
   auto issue_tile = [&](int i0, uint4* stage) {
     loader.issue(base, ld, i0, s, stage);
     loader.issue(dobase, (int64_t)h, i0, s, stage + C::kTileU4);
-    float* f = reinterpret_cast<float*>(stage + 2 * C::kTileU4);
-    if (wave == 0) issue_floats(lse_row, i0, s, f, lane);
-    if (wave == 1) issue_floats(delta_row, i0, s, f + kTile, lane);
   };
-  if (ntiles > 0) issue_tile(istart, smem);
+  // lse and delta of the tile's queries travel through a register of two waves, which lets them enter LDS in the form the
+  // loop uses: -lse * log2(e), and -delta, the starting value of the accumulators of dP
+  float stat = 0.f;
+  auto load_stat = [&](int i0) {
+    if (wave < 2) stat = (wave == 0 ? lse_row : delta_row)[min(i0 + lane, s - 1)];
+  };
+  bool hidden = false;
+#pragma unroll
+  for (int db = 0; db < C::DB; ++db) { dk[db] = zero16(); dv[db] = zero16(); }
+  if (ntiles > 0) { load_stat(istart); issue_tile(istart, smem); }
   for (int t = 0; t < ntiles; ++t) {
     const int i0 = istart + t * kTile;
     __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+    if (wave < 2) {
+      float* f = reinterpret_cast<float*>(smem + (t & 1) * kStageU4 + 2 * C::kTileU4);
+      f[wave * kTile + lane] = wave == 0 ? -kLog2e * stat : -stat;   // (the stage's readers were done before the last barrier)
+    }
     __syncthreads();
-    if (t + 1 < ntiles) issue_tile(i0 + kTile, smem + ((t + 1) & 1) * kStageU4);
+    if (t + 1 < ntiles) { load_stat(i0 + kTile); issue_tile(i0 + kTile, smem + ((t + 1) & 1) * kStageU4); }
     const uint4* q_lds = smem + (t & 1) * kStageU4;
     const uint4* do_lds = q_lds + C::kTileU4;
     const float* lse_lds = reinterpret_cast<const float*>(q_lds + 2 * C::kTileU4);
@@ -560,61 +702,121 @@ __global__ __launch_bounds__(kThreads, Cfg<DH>::kMinWaves) void attn_dkv_mfma_ke
       const int ib = i0 + qb * 32;
       if (causal && ib + 31 < jw0) continue;   // all 32 queries lie before this wave's keys
       if (ib >= s) continue;                   // no query of the block exists
-      f32x16 sacc = zero16(), dp = zero16();
+      f32x16 sacc = zero16(), dp;
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const float4 d4 = *reinterpret_cast<const float4*>(delta_lds + qb * 32 + 8 * g + 4 * hf);
+        dp[4 * g] = d4.x; dp[4 * g + 1] = d4.y; dp[4 * g + 2] = d4.z; dp[4 * g + 3] = d4.w;
+      }
 #pragma unroll
       for (int ks = 0; ks < C::KS; ++ks) {
-        sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(read_rows<DH>(q_lds, qb * 32 + l32, ks, hf), kf[ks], sacc, 0, 0, 0);
+        const bf16x8 kfr = kKInLds ? __builtin_bit_cast(bf16x8, kstore[ks * 64 + lane]) : kf[ks];
+        sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(read_rows<DH>(q_lds, qb * 32 + l32, ks, hf), kfr, sacc, 0, 0, 0);
         const bf16x8 vfr = kVInLds ? __builtin_bit_cast(bf16x8, vstore[ks * 64 + lane]) : vf[ks];
-        dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(read_rows<DH>(do_lds, qb * 32 + l32, ks, hf), vfr, dp, 0, 0, 0);
+        if (DK) dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(read_rows<DH>(do_lds, qb * 32 + l32, ks, hf), vfr, dp, 0, 0, 0);
       }
       const bool need_mask = (jw0 + 32 > kv_len) || (causal && jw0 + 31 > ib) || (ib + 32 > s);
+      uint32_t seen = 0;   // ANY: per register, whether the key sees the query
       if (need_mask) {   // a masked score of -inf gives probability exactly 0
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
           const int iq = ib + 8 * (r >> 2) + 4 * hf + (r & 3);
           const bool vis = j < kv_len && (!causal || j <= iq) && iq < s;
           sacc[r] = vis ? sacc[r] : -INFINITY;
+          if (ANY) seen |= vis ? 1u << r : 0u;
         }
       }
       f32x16 pv16, ds16;
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
         const float4 l4 = *reinterpret_cast<const float4*>(lse_lds + qb * 32 + 8 * g + 4 * hf);
-        const float4 d4 = *reinterpret_cast<const float4*>(delta_lds + qb * 32 + 8 * g + 4 * hf);
-        const float lv[4] = {l4.x, l4.y, l4.z, l4.w}, dl[4] = {d4.x, d4.y, d4.z, d4.w};
+        const float lv[4] = {l4.x, l4.y, l4.z, l4.w};
 #pragma unroll
         for (int t4 = 0; t4 < 4; ++t4) {
           const int r = 4 * g + t4;
-          const float pv = __builtin_amdgcn_exp2f(fmaf(sacc[r], c, -lv[t4] * kLog2e));
+          const float pv = __builtin_amdgcn_exp2f(fmaf(sacc[r], c, lv[t4]));
           pv16[r] = pv;
-          ds16[r] = pv * (dp[r] - dl[t4]);
+          ds16[r] = pv * dp[r];
         }
       }
+      if constexpr (ANY) {
+        if (need_mask) {   // P and dS of unseen pairs are zero whatever lse, delta, dO and V hold there
 #pragma unroll
-      for (int half = 0; half < 2; ++half) {
-        const bf16x8 pb = pack_half(pv16, half), dsb = pack_half(ds16, half);
-        const int kk = qb * 2 + half;
+          for (int r = 0; r < 16; ++r) {
+            pv16[r] = (seen >> r) & 1 ? pv16[r] : 0.f;
+            ds16[r] = (seen >> r) & 1 ? ds16[r] : 0.f;
+          }
+        }
+        // (a key past the length sees no query at all: its lanes stay zero whatever the tile holds)
+        if (need_mask) {
+          if (EXACT) {
+            auto sees = [&](int row) { return j < kv_len && i0 + row < s && (!causal || j <= i0 + row); };
+            if (DV) accumulate_visible<DH>(do_lds, qb * 32, pv16, dv, lane, sees);
+            if (DK) accumulate_visible<DH>(q_lds, qb * 32, ds16, dk, lane, sees);
+            continue;
+          }
+          hidden = hidden || (DK && tile_not_finite<DH>(q_lds, lane)) || (DV && tile_not_finite<DH>(do_lds, lane));
+        }
 #pragma unroll
-        for (int db = 0; db < C::DB; ++db) {
-          dv[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(read_cols<DH>(do_lds, db * 32, kk, lane), pb, dv[db], 0, 0, 0);
-          dk[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(read_cols<DH>(q_lds, db * 32, kk, lane), dsb, dk[db], 0, 0, 0);
+        for (int half = 0; half < 2; ++half) {
+          const int kk = qb * 2 + half;
+          bf16x8 hi, lo;
+          if (DV) pack_half_split(pv16, half, hi, lo);
+#pragma unroll
+          for (int db = 0; DV && db < C::DB; ++db) {
+            const bf16x8 x = read_cols<DH>(do_lds, db * 32, kk, lane);
+            dv[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x, hi, dv[db], 0, 0, 0);
+            dv[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x, lo, dv[db], 0, 0, 0);
+          }
+          if (DK) pack_half_split(ds16, half, hi, lo);
+#pragma unroll
+          for (int db = 0; DK && db < C::DB; ++db) {
+            const bf16x8 x = read_cols<DH>(q_lds, db * 32, kk, lane);
+            dk[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x, hi, dk[db], 0, 0, 0);
+            dk[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x, lo, dk[db], 0, 0, 0);
+          }
+        }
+      } else {
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {
+          const bf16x8 pb = pack_half(pv16, half), dsb = pack_half(ds16, half);
+          const int kk = qb * 2 + half;
+#pragma unroll
+          for (int db = 0; db < C::DB; ++db) {
+            dv[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(read_cols<DH>(do_lds, db * 32, kk, lane), pb, dv[db], 0, 0, 0);
+            dk[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(read_cols<DH>(q_lds, db * 32, kk, lane), dsb, dk[db], 0, 0, 0);
+          }
         }
       }
     }
   }
+  if constexpr (ANY && !EXACT)
+    if (__syncthreads_or(hidden)) return true;
   __syncthreads();   // every wave is done with the Q / dO tiles
-  if (colsum) {   // masked and non-existent keys hold zeros
-    float* row = colsum + ((int64_t)n * gridDim.z + blk) * ld + head * DH;
+  if (!ANY && colsum) {   // masked and non-existent keys hold zeros
+    float* row = colsum + ((int64_t)n * gridDim.z + blk) * ld + head * dh;
     float* red = reinterpret_cast<float*>(smem);
-    block_column_sums<DH>(dk, scale, red, row + h, tid, lane, wave);
+    block_column_sums<DH, NW>(dk, scale, red, row + h, tid, lane, wave);
     __syncthreads();
-    block_column_sums<DH>(dv, 1.0f, red, row + 2 * h, tid, lane, wave);
+    block_column_sums<DH, NW>(dv, 1.0f, red, row + 2 * h, tid, lane, wave);
     __syncthreads();
   }
-  bf16_t* outk = dqkv + ((int64_t)n * s + jw0) * ld + h + head * DH;
+  bf16_t* outk = dqkv + ((int64_t)n * s + jw0) * ld + h + head * dh;
   uint4* strip = smem + wave * out_strip_u4<DH>();
-  store_rows<DH>(dk, scale, strip, outk, ld, s - jw0, lane);
-  store_rows<DH>(dv, 1.0f, strip, outk + h, ld, s - jw0, lane);
+  if (DK) store_rows<DH>(dk, scale, strip, outk, ld, s - jw0, dh, lane);
+  if (DV) store_rows<DH>(dv, 1.0f, strip, outk + h, ld, s - jw0, dh, lane);
+  return false;
+}
+template <int DH, int NW, bool ANY>
+__global__ __launch_bounds__(NW * 64, 2) void attn_dkv_mfma_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ d_o, const float* __restrict__ lse, const float* __restrict__ delta, bf16_t* __restrict__ dqkv, int s, int a, int mask_mode, const int32_t* __restrict__ seqlens, float* __restrict__ colsum, int dh_) {
+  auto run = [&](auto part) __attribute__((always_inline)) {
+    constexpr int PART = decltype(part)::value;
+    if (attn_dkv<DH, NW, ANY, false, PART>(qkv, d_o, lse, delta, dqkv, s, a, mask_mode, seqlens, colsum, dh_))
+      if constexpr (ANY) attn_dkv<DH, NW, ANY, true, PART>(qkv, d_o, lse, delta, dqkv, s, a, mask_mode, seqlens, colsum, dh_);
+  };
+  if constexpr (!Cfg<DH, ANY>::kDkvParts) run(std::integral_constant<int, 0>{});
+  else if (blockIdx.z & 1) run(std::integral_constant<int, 1>{});
+  else run(std::integral_constant<int, 2>{});
 }
 
 template <typename K>
@@ -626,73 +828,108 @@ hipError_t set_lds(K kern, size_t bytes, bool* done) {
   return e;
 }
 
-template <int DH>
+template <int DH, int NW, bool ANY>
 hipError_t fwd_launch(const AttnDesc& d, const void* qkv, void* o, float* lse, hipStream_t st) {
   using C = Cfg<DH>;
-  constexpr size_t lds_out = (size_t)kWaves * out_strip_u4<DH>() * sizeof(uint4);   // the output strips re-use the tiles' LDS
+  constexpr size_t lds_out = (size_t)NW * out_strip_u4<DH>() * sizeof(uint4);   // the output strips re-use the tiles' LDS
   constexpr size_t lds_tiles = (4 * C::kTileU4 + C::kPadU4) * sizeof(uint4);
   constexpr size_t lds = lds_tiles > lds_out ? lds_tiles : lds_out;
   static bool done = false;
-  hipError_t e = set_lds(attn_fwd_mfma_kernel<DH>, lds, &done);
+  hipError_t e = set_lds(attn_fwd_mfma_kernel<DH, NW, ANY>, lds, &done);
   if (e != hipSuccess) return e;
-  dim3 grid(d.a, d.b, ceil_div(d.s, kBlockRows));
-  hipLaunchKernelGGL(attn_fwd_mfma_kernel<DH>, grid, dim3(kThreads), lds, st, static_cast<const bf16_t*>(qkv),
-                     static_cast<bf16_t*>(o), lse, d.s, d.a, d.mask_mode, d.seqlens);
+  dim3 grid(d.a, d.b, ceil_div(d.s, NW * 32));
+  hipLaunchKernelGGL((attn_fwd_mfma_kernel<DH, NW, ANY>), grid, dim3(NW * 64), lds, st, static_cast<const bf16_t*>(qkv),
+                     static_cast<bf16_t*>(o), lse, d.s, d.a, d.mask_mode, d.seqlens, d.dh);
   return hipGetLastError();
 }
 
-template <int DH>
+template <int DH, int NW, bool ANY>
 hipError_t bwd_launch(const AttnDesc& d, const void* qkv, const void* o, const float* lse, const void* d_o, void* dqkv,
                       float* delta, hipStream_t st) {
   using C = Cfg<DH>;
-  constexpr size_t lds_out = (size_t)kWaves * out_strip_u4<DH>() * sizeof(uint4);   // the output strips re-use the tiles' LDS
+  constexpr size_t lds_out = (size_t)NW * out_strip_u4<DH>() * sizeof(uint4);   // the output strips re-use the tiles' LDS
   constexpr size_t lds_dq_tiles = (4 * C::kTileU4 + C::kPadU4) * sizeof(uint4);
   constexpr size_t lds_dq = lds_dq_tiles > lds_out ? lds_dq_tiles : lds_out;
-  constexpr size_t lds_dkv_tiles = (2 * (2 * C::kTileU4 + 2 * kTile / 4) + C::kPadU4 + (C::kDkvVInLds ? kWaves * C::KS * 64 : 0)) * sizeof(uint4);
+  constexpr size_t lds_dkv_tiles = (2 * (2 * C::kTileU4 + 2 * kTile / 4) + C::kPadU4 + (Cfg<DH, ANY>::kDkvVInLds + Cfg<DH, ANY>::kDkvKInLds) * NW * C::KS * 64) * sizeof(uint4);
   constexpr size_t lds_dkv = lds_dkv_tiles > lds_out ? lds_dkv_tiles : lds_out;
   static_assert(lds_dkv <= 160 * 1024, "LDS of a CU");
   static bool done_dq = false, done_dkv = false;
-  hipError_t e = set_lds(attn_dq_mfma_kernel<DH>, lds_dq, &done_dq);
+  hipError_t e = set_lds(attn_dq_mfma_kernel<DH, NW, ANY>, lds_dq, &done_dq);
   if (e != hipSuccess) return e;
-  e = set_lds(attn_dkv_mfma_kernel<DH>, lds_dkv, &done_dkv);
+  e = set_lds(attn_dkv_mfma_kernel<DH, NW, ANY>, lds_dkv, &done_dkv);
   if (e != hipSuccess) return e;
-  dim3 grid(d.a, d.b, ceil_div(d.s, kBlockRows));
-  hipLaunchKernelGGL(attn_dq_mfma_kernel<DH>, grid, dim3(kThreads), lds_dq, st, static_cast<const bf16_t*>(qkv),
+  dim3 grid(d.a, d.b, ceil_div(d.s, NW * 32));
+  hipLaunchKernelGGL((attn_dq_mfma_kernel<DH, NW, ANY>), grid, dim3(NW * 64), lds_dq, st, static_cast<const bf16_t*>(qkv),
                      static_cast<const bf16_t*>(o), static_cast<const bf16_t*>(d_o), lse, delta,
-                     static_cast<bf16_t*>(dqkv), d.s, d.a, d.mask_mode, d.seqlens, d.colsum_partial);
-  hipLaunchKernelGGL(attn_dkv_mfma_kernel<DH>, grid, dim3(kThreads), lds_dkv, st, static_cast<const bf16_t*>(qkv),
+                     static_cast<bf16_t*>(dqkv), d.s, d.a, d.mask_mode, d.seqlens, d.colsum_partial, d.dh);
+  if (Cfg<DH, ANY>::kDkvParts) grid.z *= 2;
+  hipLaunchKernelGGL((attn_dkv_mfma_kernel<DH, NW, ANY>), grid, dim3(NW * 64), lds_dkv, st, static_cast<const bf16_t*>(qkv),
                      static_cast<const bf16_t*>(d_o), lse, delta, static_cast<bf16_t*>(dqkv), d.s, d.a, d.mask_mode,
-                     d.seqlens, d.colsum_partial);
+                     d.seqlens, d.colsum_partial, d.dh);
   return hipGetLastError();
 }
 
 }  // namespace
 
-int attention_colsum_rows(int b, int s) { return b * ceil_div(s, kBlockRows); }
+// Workgroups of 8 waves (256 rows) share each K/V tile and barrier among more rows, workgroups of 4 (128 rows) are twice as
+// many: the latter up to half a workgroup of 8 per CU, and under a causal mask, where the blocks' work differs and a launch ends
+// on its longest, up to one per CU (7/8 of it from head size 96 on, whose tiles take longer to fetch).  Forward + backward, 4 | 8
+// waves: b=2 s=1024 a=16 (128 blocks of 256 rows) dh=64 84.6 | 99.3 us, dh=96 149 | 186, dh=128 126 | 145; b=3 s=1000 a=16 (192)
+// dh=96 290 | 231, causal 162 | 194; b=8 s=512 a=16 (256) dh=64 72.3 | 70.7, causal 59.7 | 65.9, dh=128 causal 104.5 | 101.2;
+// b=4 s=1024 a=32 (512) dh=128 436 | 341.
+namespace {
+int waves_for(const AttnDesc& d) {
+  const int64_t blocks = (int64_t)d.b * d.a * ceil_div(d.s, 256), cus = gemm_compute_units();
+  if (d.mask_mode == 1) return blocks <= (d.dh < 96 ? cus : cus * 7 / 8) ? 4 : 8;
+  return 2 * blocks <= cus ? 4 : 8;
+}
+}  // namespace
 
-bool attention_mfma_supported(const AttnDesc& d) {
+int attention_colsum_rows(const AttnDesc& d) { return d.b * ceil_div(d.s, 32 * waves_for(d)); }
+int attention_colsum_max_rows(int b, int s) { return b * ceil_div(s, 128); }
+
+bool attention_emits_colsum(const AttnDesc& d) {
   return d.dtype == kBF16 && (d.dh == 32 || d.dh == 64 || d.dh == 80 || d.dh == 128);
 }
 
-hipError_t attention_fwd_mfma(const AttnDesc& d, const void* qkv, void* o, float* lse, hipStream_t st) {
+namespace {
+// F<DH, NW, ANY>::run for the head size and workgroup size of a call
+template <template <int, int, bool> class F, int NW, typename... Args>
+hipError_t by_head(const AttnDesc& d, Args... args) {
   switch (d.dh) {
-    case 32: return fwd_launch<32>(d, qkv, o, lse, st);
-    case 64: return fwd_launch<64>(d, qkv, o, lse, st);
-    case 80: return fwd_launch<80>(d, qkv, o, lse, st);
-    case 128: return fwd_launch<128>(d, qkv, o, lse, st);
-    default: return hipErrorInvalidValue;
+    case 32: return F<32, NW, false>::run(d, args...);
+    case 64: return F<64, NW, false>::run(d, args...);
+    case 80: return F<80, NW, false>::run(d, args...);
+    case 128: return F<128, NW, false>::run(d, args...);
   }
+  if (d.dh < 32) return F<32, NW, true>::run(d, args...);
+  if (d.dh <= 48) return F<48, NW, true>::run(d, args...);
+  if (d.dh < 64) return F<64, NW, true>::run(d, args...);
+  if (d.dh < 80) return F<80, NW, true>::run(d, args...);
+  if (d.dh <= 96) return F<96, NW, true>::run(d, args...);
+  if (d.dh <= 112) return F<112, NW, true>::run(d, args...);
+  return F<128, NW, true>::run(d, args...);
+}
+template <int DH, int NW, bool ANY>
+struct Fwd {
+  static hipError_t run(const AttnDesc& d, const void* qkv, void* o, float* lse, hipStream_t st) { return fwd_launch<DH, NW, ANY>(d, qkv, o, lse, st); }
+};
+template <int DH, int NW, bool ANY>
+struct Bwd {
+  static hipError_t run(const AttnDesc& d, const void* qkv, const void* o, const float* lse, const void* d_o, void* dqkv, float* delta, hipStream_t st) {
+    return bwd_launch<DH, NW, ANY>(d, qkv, o, lse, d_o, dqkv, delta, st);
+  }
+};
+}  // namespace
+
+hipError_t attention_fwd_mfma(const AttnDesc& d, const void* qkv, void* o, float* lse, hipStream_t st) {
+  return waves_for(d) == 8 ? by_head<Fwd, 8>(d, qkv, o, lse, st) : by_head<Fwd, 4>(d, qkv, o, lse, st);
 }
 
 hipError_t attention_bwd_mfma(const AttnDesc& d, const void* qkv, const void* o, const float* lse, const void* d_o,
                               void* dqkv, float* delta, hipStream_t st) {
-  switch (d.dh) {
-    case 32: return bwd_launch<32>(d, qkv, o, lse, d_o, dqkv, delta, st);
-    case 64: return bwd_launch<64>(d, qkv, o, lse, d_o, dqkv, delta, st);
-    case 80: return bwd_launch<80>(d, qkv, o, lse, d_o, dqkv, delta, st);
-    case 128: return bwd_launch<128>(d, qkv, o, lse, d_o, dqkv, delta, st);
-    default: return hipErrorInvalidValue;
-  }
+  return waves_for(d) == 8 ? by_head<Bwd, 8>(d, qkv, o, lse, d_o, dqkv, delta, st)
+                                       : by_head<Bwd, 4>(d, qkv, o, lse, d_o, dqkv, delta, st);
 }
 
 }  // namespace k2bw

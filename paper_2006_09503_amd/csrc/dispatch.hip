@@ -9,9 +9,6 @@ hipError_t gemm_f32(const GemmDesc& d, hipStream_t stream);
 hipError_t gemm_bf16(const GemmDesc& d, hipStream_t stream);
 hipError_t gemm_bf16_grouped(const GemmDesc* d, int count, hipStream_t stream);
 void gemm_bf16_kernel_name(const GemmDesc* d, int count, char* out, size_t cap);
-hipError_t attention_fwd_simple(const AttnDesc& d, const void* qkv, void* o, float* lse, hipStream_t st);
-hipError_t attention_bwd_simple(const AttnDesc& d, const void* qkv, const void* o, const float* lse,
-                                const void* d_o, void* dqkv, float* delta, hipStream_t st);
 hipError_t attention_fwd_f32(const AttnDesc& d, const void* qkv, void* o, float* lse, hipStream_t st);
 hipError_t attention_bwd_f32(const AttnDesc& d, const void* qkv, const void* o, const float* lse, const void* d_o,
                              void* dqkv, float* delta, hipStream_t st);
@@ -84,9 +81,7 @@ hipError_t attention_fwd(const AttnDesc& d, const void* qkv, void* o, float* lse
   hipError_t e = check_attn(d);
   if (e != hipSuccess) return e;
   if (!qkv || !o || !lse || !aligned16(qkv) || !aligned16(o)) return hipErrorInvalidValue;
-  if (attention_mfma_supported(d)) return attention_fwd_mfma(d, qkv, o, lse, stream);
-  if (d.dtype == kF32) return attention_fwd_f32(d, qkv, o, lse, stream);
-  return attention_fwd_simple(d, qkv, o, lse, stream);
+  return d.dtype == kBF16 ? attention_fwd_mfma(d, qkv, o, lse, stream) : attention_fwd_f32(d, qkv, o, lse, stream);
 }
 
 hipError_t attention_bwd(const AttnDesc& d, const void* qkv, const void* o, const float* lse, const void* d_o,
@@ -95,10 +90,9 @@ hipError_t attention_bwd(const AttnDesc& d, const void* qkv, const void* o, cons
   if (e != hipSuccess) return e;
   if (!qkv || !o || !lse || !d_o || !dqkv || !delta) return hipErrorInvalidValue;
   if (!aligned16(qkv) || !aligned16(o) || !aligned16(d_o) || !aligned16(dqkv)) return hipErrorInvalidValue;
-  if (attention_mfma_supported(d)) return attention_bwd_mfma(d, qkv, o, lse, d_o, dqkv, delta, stream);
-  if (d.colsum_partial) return hipErrorInvalidValue;   // only the MFMA kernels produce the column sums
-  if (d.dtype == kF32) return attention_bwd_f32(d, qkv, o, lse, d_o, dqkv, delta, stream);
-  return attention_bwd_simple(d, qkv, o, lse, d_o, dqkv, delta, stream);
+  if (d.colsum_partial && !attention_emits_colsum(d)) return hipErrorInvalidValue;
+  return d.dtype == kBF16 ? attention_bwd_mfma(d, qkv, o, lse, d_o, dqkv, delta, stream)
+                          : attention_bwd_f32(d, qkv, o, lse, d_o, dqkv, delta, stream);
 }
 
 }  // namespace k2bw

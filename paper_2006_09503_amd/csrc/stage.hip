@@ -344,7 +344,7 @@ hipError_t run_forward(stage2bw* st, int buf, ActSet& acts, const int32_t* lens,
     g.prefetch = wptr(st, buf, o.wo); g.prefetch_bytes = (int64_t)h * h * st->esize;   // the next GEMM's weights
     e = run_gemm(st, STAGE_K_GEMM_FWD, g);
     if (e != hipSuccess) return e;
-    e = timed(st, STAGE_K_ATTN_FWD, st->dtype == kBF16 ? "attn_fwd_mfma_kernel" : "attn_fwd_simple", attn_flops, 0.0, [&] {
+    e = timed(st, STAGE_K_ATTN_FWD, st->dtype == kBF16 ? "attn_fwd_mfma_kernel" : "attn_f32_fwd_kernel", attn_flops, 0.0, [&] {
       return attention_fwd(attn_desc(st, lens), A.qkv, A.o, A.lse, st->cur);
     });
     if (e != hipSuccess) return e;
@@ -527,7 +527,7 @@ hipError_t run_backward(stage2bw* st, int buf, int set, int pos, const int32_t* 
     e = dgrad(dx1, h, kWo, o.wo, h, st->tmp_h, nullptr, l, kWqkv, o.wqkv, (int64_t)3 * h * h);   if (e != hipSuccess) return e;
     // attention
     AttnDesc ad = attn_desc(st, lens);
-    const bool fused_dqkv = attention_mfma_supported(ad);
+    const bool fused_dqkv = attention_emits_colsum(ad);
     if (fused_dqkv) ad.colsum_partial = st->attn_partial[l];
     e = timed(st, STAGE_K_ATTN_BWD, "attention backward (dq + dkv kernels)", attn_flops, 0.0, [&] {
       return attention_bwd(ad, A.qkv, A.o, A.lse, st->tmp_h, dqkv, st->delta, st->cur);
@@ -555,7 +555,7 @@ hipError_t run_backward(stage2bw* st, int buf, int set, int pos, const int32_t* 
       fin.push_back({partial, parts, ld, n, out});
       fin_elems += (double)parts * n;
     };
-    if (fused_dqkv) add_fin(st->attn_partial[l], attention_colsum_rows(c.microbatch, c.seq), 3 * h, 3 * h, st->G + o.bqkv);
+    if (fused_dqkv) add_fin(st->attn_partial[l], attention_colsum_rows(ad), 3 * h, 3 * h, st->G + o.bqkv);
     else add_fin(st->cs_partial[l] + col_dqkv, cs_parts, cs_cols, 3 * h, st->G + o.bqkv);
     if (fused_du) add_fin(st->du_partial[l], (T + 31) / 32, f, f, st->G + o.b1);
     else add_fin(st->cs_partial[l] + col_du, cs_parts, cs_cols, f, st->G + o.b1);
@@ -712,7 +712,7 @@ int stage_create(const stage_config_t* cfg, const float* init_weights_host, void
     ALLOC(st->ln_partial2[l], (int64_t)ln_bwd_max_parts() * 3 * h * 4, nullptr);
     if (st->dtype == kBF16) {
       ALLOC(st->du_partial[l], (int64_t)((T + 31) / 32) * f * 4, nullptr);
-      ALLOC(st->attn_partial[l], (int64_t)attention_colsum_rows(cfg->microbatch, cfg->seq) * 3 * h * 4, nullptr);
+      ALLOC(st->attn_partial[l], (int64_t)attention_colsum_max_rows(cfg->microbatch, cfg->seq) * 3 * h * 4, nullptr);
     }
     // the column-sum kernel serves the stage's incoming dy (top layer) and, in fp32 mode or for
     // head sizes without the fused attention kernels, du and dqkv of every layer
