@@ -1,11 +1,10 @@
 // Shape validation and routing of GEMM and attention calls to the kernel families.
-#include <cstdio>
-
 #include "kernels.hpp"
 
 namespace k2bw {
 
-hipError_t gemm_f32(const GemmDesc& d, hipStream_t stream);
+hipError_t gemm_f32_grouped(const GemmDesc* d, int count, hipStream_t stream);
+void gemm_f32_kernel_name(const GemmDesc* d, int count, char* out, size_t cap);
 hipError_t gemm_bf16(const GemmDesc& d, hipStream_t stream);
 hipError_t gemm_bf16_grouped(const GemmDesc* d, int count, hipStream_t stream);
 void gemm_bf16_kernel_name(const GemmDesc* d, int count, char* out, size_t cap);
@@ -44,12 +43,12 @@ hipError_t check_gemm(const GemmDesc& d) {
 hipError_t gemm(const GemmDesc& d, hipStream_t stream) {
   hipError_t e = check_gemm(d);
   if (e != hipSuccess) return e;
-  return d.dtype == kF32 ? gemm_f32(d, stream) : gemm_bf16(d, stream);
+  return d.dtype == kF32 ? gemm_f32_grouped(&d, 1, stream) : gemm_bf16(d, stream);
 }
 
 void gemm_kernel_name(const GemmDesc* d, int count, char* out, size_t cap) {
   if (d[0].dtype == kBF16) gemm_bf16_kernel_name(d, count, out, cap);
-  else snprintf(out, cap, "gemm_f32_kernel<%s, %s, %d>", d[0].trans_a ? "true" : "false", d[0].trans_b ? "true" : "false", d[0].epilogue);
+  else gemm_f32_kernel_name(d, count, out, cap);
 }
 
 hipError_t gemm_grouped(const GemmDesc* d, int count, hipStream_t stream) {
@@ -60,11 +59,7 @@ hipError_t gemm_grouped(const GemmDesc* d, int count, hipStream_t stream) {
     if (d[g].dtype != d[0].dtype) return hipErrorInvalidValue;
   }
   if (d[0].dtype == kBF16) return gemm_bf16_grouped(d, count, stream);
-  for (int g = 0; g < count; ++g) {
-    hipError_t e = gemm_f32(d[g], stream);
-    if (e != hipSuccess) return e;
-  }
-  return hipSuccess;
+  return gemm_f32_grouped(d, count, stream);
 }
 
 namespace {

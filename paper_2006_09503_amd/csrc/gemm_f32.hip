@@ -10,11 +10,16 @@
 // Any M, N, K: what lies outside the matrices is loaded as zero and never stored; operands whose leading
 // dimension or base address do not allow 16-byte loads take guarded 4-byte loads instead.
 //
+// Products whose 128 x 128 tiles do not fill the chip run on gemm_f32_split_kernel (further down): tiles of 64 x 64 or 32 x 32 whose reduction range
+// is split over the workgroup's waves.
+//
 // Lane layout of v_mfma_f32_32x32x2_f32: lane l supplies element (l % 32, l / 32) of the first operand
 // (32 x 2) and (l / 32, l % 32) of the second (2 x 32); it receives column l % 32 of D, rows
 // 8*(r/4) + 4*(l/32) + (r % 4) for accumulator register r.  As in the bf16 kernels the B tile is fed as the
 // first operand and the A tile as the second, so a lane owns one row m of C and four consecutive columns
 // per register quad: the epilogue's accesses are 16-byte vectors.
+#include <cstdio>
+
 #include "kernels.hpp"
 
 namespace k2bw {
@@ -88,6 +93,55 @@ struct TileMover {
   }
 };
 
+// Epilogue of four consecutive columns gn .. gn+3 of row gm (gm < M, gn < N)
+template <int EPI>
+__device__ __forceinline__ void finish4(const F32Params& p, int gm, int gn, const float (&acc)[4]) {
+  const int64_t idx = (int64_t)gm * p.ldc + gn;
+  float v[4] = {acc[0], acc[1], acc[2], acc[3]};
+  const bool whole = p.vec_c && gn + 3 < p.N;
+  auto rd4 = [&](const float* src, float (&o)[4]) {
+    if (whole) { const float4 q = *reinterpret_cast<const float4*>(src); o[0] = q.x; o[1] = q.y; o[2] = q.z; o[3] = q.w; }
+    else {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) o[i] = gn + i < p.N ? src[i] : 0.f;
+    }
+  };
+  auto wr4 = [&](float* dst, const float (&o)[4]) {
+    if (whole) *reinterpret_cast<float4*>(dst) = make_float4(o[0], o[1], o[2], o[3]);
+    else {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) if (gn + i < p.N) dst[i] = o[i];
+    }
+  };
+  if (EPI == kEpiStore) {
+    if (p.bias) { float b[4]; rd4(p.bias + gn, b);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) v[i] += b[i]; }
+    if (p.aux) { float r[4]; rd4(p.aux + idx, r);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) v[i] += r[i]; }
+    wr4(p.C + idx, v);
+  } else if (EPI == kEpiGelu) {
+    float b[4]; rd4(p.bias + gn, b);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] += b[i];
+    wr4(p.C + idx, v);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] = gelu_f(v[i]);
+    wr4(p.aux_out + idx, v);
+  } else if (EPI == kEpiGeluGrad) {
+    float u[4]; rd4(p.aux + idx, u);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] *= gelu_grad_f(u[i]);
+    wr4(p.C + idx, v);
+  } else {
+    if (p.accumulate) { float c[4]; rd4(p.C + idx, c);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) v[i] = c[i] + v[i]; }
+    wr4(p.C + idx, v);
+  }
+}
+
 template <bool TA, bool TB, int EPI>
 __global__ __launch_bounds__(kThreads) void gemm_f32_mfma_kernel(F32Params p) {
   __shared__ __attribute__((aligned(16))) float sA[2][BK * LDT];
@@ -152,71 +206,212 @@ __global__ __launch_bounds__(kThreads) void gemm_f32_mfma_kernel(F32Params p) {
       for (int g = 0; g < 4; ++g) {
         const int gn = n0 + wn * 64 + ni * 32 + 8 * g + 4 * half;
         if (gn >= p.N) continue;
-        const int64_t idx = (int64_t)gm * p.ldc + gn;
-        float v[4] = {acc[mi][ni][4 * g], acc[mi][ni][4 * g + 1], acc[mi][ni][4 * g + 2], acc[mi][ni][4 * g + 3]};
-        const bool whole = p.vec_c && gn + 3 < p.N;
-        auto rd4 = [&](const float* src, float (&o)[4]) {
-          if (whole) { const float4 q = *reinterpret_cast<const float4*>(src); o[0] = q.x; o[1] = q.y; o[2] = q.z; o[3] = q.w; }
-          else {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) o[i] = gn + i < p.N ? src[i] : 0.f;
-          }
-        };
-        auto wr4 = [&](float* dst, const float (&o)[4]) {
-          if (whole) *reinterpret_cast<float4*>(dst) = make_float4(o[0], o[1], o[2], o[3]);
-          else {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) if (gn + i < p.N) dst[i] = o[i];
-          }
-        };
-        if (EPI == kEpiStore) {
-          if (p.bias) { float b[4]; rd4(p.bias + gn, b);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) v[i] += b[i]; }
-          if (p.aux) { float r[4]; rd4(p.aux + idx, r);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) v[i] += r[i]; }
-          wr4(p.C + idx, v);
-        } else if (EPI == kEpiGelu) {
-          float b[4]; rd4(p.bias + gn, b);
-#pragma unroll
-          for (int i = 0; i < 4; ++i) v[i] += b[i];
-          wr4(p.C + idx, v);
-#pragma unroll
-          for (int i = 0; i < 4; ++i) v[i] = gelu_f(v[i]);
-          wr4(p.aux_out + idx, v);
-        } else if (EPI == kEpiGeluGrad) {
-          float u[4]; rd4(p.aux + idx, u);
-#pragma unroll
-          for (int i = 0; i < 4; ++i) v[i] *= gelu_grad_f(u[i]);
-          wr4(p.C + idx, v);
-        } else {
-          if (p.accumulate) { float c[4]; rd4(p.C + idx, c);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) v[i] = c[i] + v[i]; }
-          wr4(p.C + idx, v);
-        }
+        const float v[4] = {acc[mi][ni][4 * g], acc[mi][ni][4 * g + 1], acc[mi][ni][4 * g + 2], acc[mi][ni][4 * g + 3]};
+        finish4<EPI>(p, gm, gn, v);
       }
   }
 }
 
+// ------------------------------------------------------------------------------------------------
+// Small products.  128 x 128 tiles leave most CUs without work when M or N is a few hundred (the tiny parity stage: 1 to 4
+// workgroups), and each of them then walks the whole reduction range alone.  Here a workgroup owns a tile of 32*MB x 32*NB and
+// its kSplit waves take every kSplit-th chunk of 16 k, each for the whole tile; the partial sums meet in LDS once, in a fixed
+// order.  Nothing is shared inside the loop, so there is no LDS and no barrier in it: operands come straight into the
+// fragment registers (16 bytes per lane where k is contiguous, 128-byte rows otherwise), one chunk ahead of their use.
+// k-slots: instruction i of group j (8 k) takes k = 8j + i in lanes 0..31 and 8j + 4 + i in lanes 32..63, in both operands.
+constexpr int kChunk = 16;
+
+template <int NBLK, bool ROW_CONTIG>
+struct FragLoader {   // fragments of 32*NBLK rows x kChunk k: f[block][k-instruction]
+  const float* base[NBLK];
+  int ld;
+  __device__ __forceinline__ void init(const float* X, int ld_, int row0, int rows, int l32, int hf) {
+    ld = ld_;
+#pragma unroll
+    for (int b = 0; b < NBLK; ++b) {
+      const int r = min(row0 + 32 * b + l32, rows - 1);   // rows past the matrix: a copy, never stored
+      base[b] = ROW_CONTIG ? X + r + (int64_t)(4 * hf) * ld : X + (int64_t)r * ld + 4 * hf;
+    }
+  }
+  __device__ __forceinline__ void load(int k0, float (&f)[NBLK][kChunk / 2]) const {
+#pragma unroll
+    for (int b = 0; b < NBLK; ++b)
+#pragma unroll
+      for (int j = 0; j < kChunk / 8; ++j) {
+        if (ROW_CONTIG) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) f[b][4 * j + i] = base[b][(int64_t)(k0 + 8 * j + i) * ld];
+        } else {
+          const float4 v = *reinterpret_cast<const float4*>(base[b] + k0 + 8 * j);
+          f[b][4 * j] = v.x; f[b][4 * j + 1] = v.y; f[b][4 * j + 2] = v.z; f[b][4 * j + 3] = v.w;
+        }
+      }
+  }
+  // the last, partial chunk: what lies past K is zero
+  __device__ __forceinline__ void load_tail(int k0, int K, int hf, float (&f)[NBLK][kChunk / 2]) const {
+#pragma unroll
+    for (int b = 0; b < NBLK; ++b)
+#pragma unroll
+      for (int e = 0; e < kChunk / 2; ++e) {
+        const int k = k0 + 8 * (e / 4) + (e % 4);   // (base holds the 4*hf)
+        f[b][e] = 0.f;
+        if (k + 4 * hf < K) f[b][e] = ROW_CONTIG ? base[b][(int64_t)k * ld] : base[b][k];
+      }
+  }
+};
+
+constexpr int kGroupF32 = 24;   // products of one form that may share a launch
+struct GroupF32 {
+  F32Params p[kGroupF32];
+  int tile_start[kGroupF32 + 1];
+  int count;
+};
+
+template <int MB, int NB, int kSplit, bool TA, bool TB, int EPI>
+__global__ __launch_bounds__(kSplit * 64) void gemm_f32_split_kernel(GroupF32 gp) {
+  constexpr int TM = 32 * MB, TN = 32 * NB, LDS_LD = TN + 4;
+  extern __shared__ __attribute__((aligned(16))) float part[];   // [kSplit][TM][LDS_LD]
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l32 = lane & 31, hf = lane >> 5;
+  int g = 0;
+  for (int q = 1; q < gp.count; ++q) g = (int)blockIdx.x >= gp.tile_start[q] ? q : g;
+  const F32Params& p = gp.p[g];
+  const int t = (int)blockIdx.x - gp.tile_start[g], tiles_n = (p.N + TN - 1) / TN;
+  const int m0 = t / tiles_n * TM, n0 = t % tiles_n * TN;
+
+  FragLoader<MB, TA> la;
+  FragLoader<NB, !TB> lb;
+  la.init(p.A, p.lda, m0, p.M, l32, hf);
+  lb.init(p.B, p.ldb, n0, p.N, l32, hf);
+  f32x16 acc[MB][NB];
+#pragma unroll
+  for (int mi = 0; mi < MB; ++mi)
+#pragma unroll
+    for (int ni = 0; ni < NB; ++ni)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[mi][ni][r] = 0.f;
+  float a[2][MB][kChunk / 2], b[2][NB][kChunk / 2];
+  auto multiply = [&](int s) __attribute__((always_inline)) {
+#pragma unroll
+    for (int e = 0; e < kChunk / 2; ++e)
+#pragma unroll
+      for (int mi = 0; mi < MB; ++mi)
+#pragma unroll
+        for (int ni = 0; ni < NB; ++ni) acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x2f32(b[s][ni][e], a[s][mi][e], acc[mi][ni], 0, 0, 0);
+  };
+  const int full = p.K / kChunk;
+  int c = wave;
+  if (c < full) { la.load(c * kChunk, a[0]); lb.load(c * kChunk, b[0]); }
+  for (; c < full; c += 2 * kSplit) {
+    if (c + kSplit < full) { la.load((c + kSplit) * kChunk, a[1]); lb.load((c + kSplit) * kChunk, b[1]); }
+    __builtin_amdgcn_sched_barrier(0);
+    multiply(0);
+    if (c + kSplit >= full) break;
+    if (c + 2 * kSplit < full) { la.load((c + 2 * kSplit) * kChunk, a[0]); lb.load((c + 2 * kSplit) * kChunk, b[0]); }
+    __builtin_amdgcn_sched_barrier(0);
+    multiply(1);
+  }
+  if (full * kChunk < p.K && full % kSplit == wave) {
+    la.load_tail(full * kChunk, p.K, hf, a[0]);
+    lb.load_tail(full * kChunk, p.K, hf, b[0]);
+    multiply(0);
+  }
+  // a lane owns row m and four consecutive columns per register quad
+  float* mine = part + wave * TM * LDS_LD;
+#pragma unroll
+  for (int mi = 0; mi < MB; ++mi)
+#pragma unroll
+    for (int ni = 0; ni < NB; ++ni)
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        *reinterpret_cast<float4*>(mine + (mi * 32 + l32) * LDS_LD + ni * 32 + 8 * q + 4 * hf) =
+            make_float4(acc[mi][ni][4 * q], acc[mi][ni][4 * q + 1], acc[mi][ni][4 * q + 2], acc[mi][ni][4 * q + 3]);
+  __syncthreads();
+  for (int e = tid; e < TM * TN / 4; e += kSplit * 64) {
+    const int row = e / (TN / 4), col = e % (TN / 4) * 4;
+    if (m0 + row >= p.M || n0 + col >= p.N) continue;
+    float4 s = *reinterpret_cast<const float4*>(part + row * LDS_LD + col);
+#pragma unroll
+    for (int w = 1; w < kSplit; ++w) {
+      const float4 v = *reinterpret_cast<const float4*>(part + (w * TM + row) * LDS_LD + col);
+      s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
+    }
+    const float v[4] = {s.x, s.y, s.z, s.w};
+    finish4<EPI>(p, m0 + row, n0 + col, v);
+  }
+}
+
+// ------------------------------------------------------------------------------------------------
+template <int MB, int NB, int kSplit, bool TA, bool TB, int EPI>
+hipError_t launch_split(GroupF32& gp, hipStream_t s) {
+  constexpr size_t lds = (size_t)kSplit * 32 * MB * (32 * NB + 4) * sizeof(float);
+  static bool done = false;
+  if (!done && lds > 64 * 1024) {
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_f32_split_kernel<MB, NB, kSplit, TA, TB, EPI>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+    done = true;
+  }
+  int total = 0;
+  for (int g = 0; g < gp.count; ++g) {
+    gp.tile_start[g] = total;
+    total += ceil_div(gp.p[g].M, 32 * MB) * ceil_div(gp.p[g].N, 32 * NB);
+  }
+  gp.tile_start[gp.count] = total;
+  hipLaunchKernelGGL((gemm_f32_split_kernel<MB, NB, kSplit, TA, TB, EPI>), dim3(total), dim3(kSplit * 64), lds, s, gp);
+  return hipGetLastError();
+}
+
+// The split kernels load a K-contiguous operand 16 bytes at a time
+bool split_ok(const F32Params& p, bool ta, bool tb) { return (ta || p.vec_a) && (!tb || p.vec_b); }
+
+// Tile edge for `count` products of one form (128: one product per launch on the staged kernel).  The edge with the least
+// rounds of tiles over the CUs times the time of a tile, in units of what a 32 x 32 tile's matrix instructions take: a 64 x 64
+// tile takes 4, a 128 x 128 tile 16; 32 x 32 tiles fetch twice the operands of 64 x 64 ones (x 1.22), the staged kernel needs two
+// workgroups per CU to hide its latencies (x 0.95 with them, x 1.25 without).  Forward | data gradient | weight gradient in us,
+// edge 128, 64, 32 (tokens, in, out): (128,512,128) 54.2|17.5|18.6, 14.5|7.3|7.7, 6.4|4.1|4.4; (512,1024,3072) 102|289|57,
+// 50|63|46, 47|47|51; (2048,1024,1024) 103|102|180, 52|57|48, 59|62|68; (4096,1024,4096) 307|389|357, 371|317|333, 425|464|462;
+// (4096,4096,8192) 2261|2375|2218, 2744|2325|2771, 3619|3735|3560.
+int choose_f32(const F32Params* p, int count, bool ta, bool tb) {
+  int64_t t[3] = {0, 0, 0};
+  const int edge[3] = {128, 64, 32};
+  for (int g = 0; g < count; ++g) {
+    if (!split_ok(p[g], ta, tb)) return 128;
+    for (int e = 0; e < 3; ++e) t[e] += (int64_t)ceil_div(p[g].M, edge[e]) * ceil_div(p[g].N, edge[e]);
+  }
+  const int cus = gemm_compute_units();
+  const double cost[3] = {ceil_div(t[0], cus) * 16.0 * (t[0] >= 2 * cus ? 0.95 : 1.25), ceil_div(t[1], cus) * 4.0, ceil_div(t[2], cus) * 1.22};
+  return cost[0] <= cost[1] && cost[0] <= cost[2] ? 128 : cost[1] <= cost[2] ? 64 : 32;
+}
+
+template <bool TA, bool TB, int EPI>
+hipError_t launch_form(GroupF32& gp, hipStream_t s) {
+  switch (choose_f32(gp.p, gp.count, TA, TB)) {
+    case 64: return launch_split<2, 2, 4, TA, TB, EPI>(gp, s);
+    case 32: return launch_split<1, 1, 8, TA, TB, EPI>(gp, s);
+  }
+  for (int g = 0; g < gp.count; ++g) {
+    const F32Params& p = gp.p[g];
+    hipLaunchKernelGGL((gemm_f32_mfma_kernel<TA, TB, EPI>), dim3(ceil_div(p.N, BN), ceil_div(p.M, BM)), dim3(kThreads), 0, s, p);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
 template <bool TA, bool TB>
-hipError_t launch_epi(const F32Params& p, int epi, dim3 grid, hipStream_t s) {
+hipError_t launch_epi(GroupF32& gp, int epi, hipStream_t s) {
   switch (epi) {
-    case kEpiStore: hipLaunchKernelGGL((gemm_f32_mfma_kernel<TA, TB, kEpiStore>), grid, dim3(kThreads), 0, s, p); break;
-    case kEpiGelu: hipLaunchKernelGGL((gemm_f32_mfma_kernel<TA, TB, kEpiGelu>), grid, dim3(kThreads), 0, s, p); break;
-    case kEpiGeluGrad: hipLaunchKernelGGL((gemm_f32_mfma_kernel<TA, TB, kEpiGeluGrad>), grid, dim3(kThreads), 0, s, p); break;
-    case kEpiAccum: hipLaunchKernelGGL((gemm_f32_mfma_kernel<TA, TB, kEpiAccum>), grid, dim3(kThreads), 0, s, p); break;
+    case kEpiStore: return launch_form<TA, TB, kEpiStore>(gp, s);
+    case kEpiGelu: return launch_form<TA, TB, kEpiGelu>(gp, s);
+    case kEpiGeluGrad: return launch_form<TA, TB, kEpiGeluGrad>(gp, s);
+    case kEpiAccum: return launch_form<TA, TB, kEpiAccum>(gp, s);
     default: return hipErrorInvalidValue;
   }
-  return hipGetLastError();
 }
 
 bool vec16(const void* ptr, int ld) { return (reinterpret_cast<uintptr_t>(ptr) & 15) == 0 && ld % 4 == 0; }
 
-}  // namespace
-
-hipError_t gemm_f32(const GemmDesc& d, hipStream_t stream) {
+F32Params to_params(const GemmDesc& d) {
   F32Params p{static_cast<const float*>(d.A), static_cast<const float*>(d.B), static_cast<float*>(d.C),
               d.M, d.N, d.K, d.lda, d.ldb, d.ldc, static_cast<const float*>(d.bias), static_cast<const float*>(d.aux),
               static_cast<float*>(d.aux_out), d.accumulate ? 1 : 0, 0, 0, 0};
@@ -224,11 +419,36 @@ hipError_t gemm_f32(const GemmDesc& d, hipStream_t stream) {
   p.vec_b = vec16(d.B, d.ldb);
   p.vec_c = vec16(d.C, d.ldc) && (!d.aux || vec16(d.aux, d.ldc)) && (!d.aux_out || vec16(d.aux_out, d.ldc)) &&
             (!d.bias || vec16(d.bias, 4));
-  dim3 grid(ceil_div(d.N, BN), ceil_div(d.M, BM));
-  if (d.trans_a) return d.trans_b ? launch_epi<true, true>(p, d.epilogue, grid, stream)
-                                  : launch_epi<true, false>(p, d.epilogue, grid, stream);
-  return d.trans_b ? launch_epi<false, true>(p, d.epilogue, grid, stream)
-                   : launch_epi<false, false>(p, d.epilogue, grid, stream);
+  return p;
+}
+
+}  // namespace
+
+// `count` products of the same form and epilogue (1..kGemmMaxGroup); small ones share a launch
+hipError_t gemm_f32_grouped(const GemmDesc* d, int count, hipStream_t stream) {
+  static_assert(kGemmMaxGroup <= kGroupF32, "");
+  if (count < 1 || count > kGroupF32) return hipErrorInvalidValue;
+  GroupF32 gp;
+  gp.count = count;
+  for (int g = 0; g < count; ++g) {
+    if (d[g].trans_a != d[0].trans_a || d[g].trans_b != d[0].trans_b || d[g].epilogue != d[0].epilogue) return hipErrorInvalidValue;
+    gp.p[g] = to_params(d[g]);
+  }
+  if (d[0].trans_a) return d[0].trans_b ? launch_epi<true, true>(gp, d[0].epilogue, stream) : launch_epi<true, false>(gp, d[0].epilogue, stream);
+  return d[0].trans_b ? launch_epi<false, true>(gp, d[0].epilogue, stream) : launch_epi<false, false>(gp, d[0].epilogue, stream);
+}
+
+void gemm_f32_kernel_name(const GemmDesc* d, int count, char* out, size_t cap) {
+  F32Params p[kGroupF32];
+  const int n = count < kGroupF32 ? count : kGroupF32;
+  for (int g = 0; g < n; ++g) p[g] = to_params(d[g]);
+  const char* ta = d[0].trans_a ? "true" : "false";
+  const char* tb = d[0].trans_b ? "true" : "false";
+  switch (choose_f32(p, n, d[0].trans_a, d[0].trans_b)) {
+    case 64: snprintf(out, cap, "gemm_f32_split_kernel<2, 2, 4, %s, %s, %d>", ta, tb, d[0].epilogue); break;
+    case 32: snprintf(out, cap, "gemm_f32_split_kernel<1, 1, 8, %s, %s, %d>", ta, tb, d[0].epilogue); break;
+    default: snprintf(out, cap, "gemm_f32_mfma_kernel<%s, %s, %d>", ta, tb, d[0].epilogue); break;
+  }
 }
 
 }  // namespace k2bw
