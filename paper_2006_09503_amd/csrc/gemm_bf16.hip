@@ -1,13 +1,14 @@
 // bf16 GEMM on the gfx950 matrix cores (v_mfma_f32_32x32x16_bf16), fp32 accumulation.
 //
-// One workgroup computes a BM x BN tile of C.  Two kernel families share the tile order, the
+// One workgroup computes a BM x BN tile of C.  The kernel families share the tile order, the
 // fragment layout and the epilogue:
 //
 //   * the ring kernel (gemm_bf16_ring_kernel, further down): operand tiles go from HBM straight
 //     into LDS (global_load_lds) through a ring of four stages, K-strided operands stay in their
-//     HBM form and are transposed by the LDS read.  It serves every launch whose K is a multiple
-//     of its K tile, which is every GEMM of the workloads;
-//   * the register-staged kernel (gemm_bf16_kernel): K steps of 64 through two LDS stages, any K.
+//     HBM form and are transposed by the LDS read.  It serves every launch with enough tiles and at least one whole
+//     K tile; launches with few tiles run on the same scheme with tiles of 64 or 32 and the reduction range split over
+//     the waves (gemm_bf16_split_kernel);
+//   * the register-staged kernel (gemm_bf16_kernel): K steps of 64 through two LDS stages, any K, two workgroups per CU.
 //     Both operand tiles are staged in one common form -- [row][64 k] bf16, 128-byte rows, 16-byte
 //     chunks XOR-swizzled by row -- whatever the operand's layout in HBM:
 //       - K contiguous in HBM (activations as A, W read for the data gradient): 16-byte global
@@ -674,7 +675,7 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64 * KSPLIT) void gemm_bf16
 }
 
 // ------------------------------------------------------------------------------------------------
-// Asynchronous kernels (K a multiple of the K tile).  Tiles go from HBM straight into LDS with
+// Asynchronous kernels.  Tiles go from HBM straight into LDS with
 // global_load_lds (16 bytes per lane, a wave fills 1 KB of consecutive LDS), so no registers and
 // no LDS store instructions are spent on staging:
 //   * K-contiguous operand: LDS [row][8 chunks], chunk XOR-swizzled as above; lane i of a load
@@ -699,6 +700,10 @@ __device__ __forceinline__ uint64_t uniform_address(const void* ptr) {
   return ((uint64_t)b_hi << 32) | (uint64_t)b_lo;
 }
 
+// 16-byte piece swizzle of a K-strided tile with R rows of C per k row (rows of 32: four pieces)
+template <int R>
+__device__ __forceinline__ int swz_strided(int k) { return (k & (R >= 64 ? 3 : 1)) << 1; }
+
 template <int R, int NW, int BKA, bool K_CONTIG>
 struct AsyncLoader {
   static constexpr int CHK = BKA / 8;               // chunks per row of a K-contiguous tile
@@ -722,7 +727,7 @@ struct AsyncLoader {
       } else {
         constexpr int PPR = R / 8;                  // pieces per k row
         const int k = L / PPR, pp = L % PPR;
-        const int piece = pp ^ ((k & 3) << 1);
+        const int piece = pp ^ swz_strided<R>(k);
         int col = piece * 8;
         if (col >= rows_valid) col = rows_valid - 8;
         voff[j] = ((uint32_t)k * (uint32_t)ld + col) * 2u;
@@ -745,6 +750,27 @@ struct AsyncLoader {
                  :
                  : "s"(dst), "v"(voff[j]), "s"(tile_addr)
                  : "memory");   // (M0 is reserved: the compiler keeps nothing in it)
+  }
+  // The partial K tile at the end of a reduction range (rem < BKA elements of it exist): chunks and rows past the end are
+  // fetched from inside the matrix, and replaced by zeros once they have landed (zero_past_end).
+  __device__ __forceinline__ void issue_partial(int j, uint64_t tile_addr, uint32_t lds_tile, int rem, int lane) const {
+    const int L = first_slot_ + j * 64 + lane;
+    uint32_t off = voff[j];
+    if (K_CONTIG) {
+      const int c = (L % CHK) ^ swz<CHK>(L / CHK);
+      if (c * 8 >= rem) off -= (uint32_t)c * 16u;
+    } else {
+      const int k = L / (R / 8);
+      if (k >= rem) off -= (uint32_t)(k - rem + 1) * (uint32_t)ld_ * 2u;
+    }
+    const uint32_t dst = __builtin_amdgcn_readfirstlane(lds_tile + (uint32_t)(first_slot_ + j * 64) * 16u);
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(dst), "v"(off), "s"(tile_addr) : "memory");
+  }
+  static __device__ __forceinline__ void zero_past_end(uint4* tile, int rem, int first, int step) {
+    for (int L = first; L < kSlots; L += step) {
+      const bool past = K_CONTIG ? ((L % CHK) ^ swz<CHK>(L / CHK)) * 8 >= rem : L / (R / 8) >= rem;
+      if (past) tile[L] = make_uint4(0, 0, 0, 0);
+    }
   }
   // bytes from one K tile to the next inside a contiguous piece of the reduction range
   __device__ __forceinline__ uint32_t tile_step_bytes() const {
@@ -802,7 +828,7 @@ __device__ __forceinline__ bf16x8 read_frag(const uint4* tile, int row0, int ks,
     const int r = lane & 15, a = r & 3, t = r >> 2;
     const int k = ks * 16 + (lane >> 5) * 8 + t;
     const int col = row0 + ((lane >> 4) & 1) * 16 + 4 * a;
-    const int piece = (col >> 3) ^ (t << 1);        // (k & 3) == t
+    const int piece = (col >> 3) ^ swz_strided<R>(t);   // (k & 3) == t
     const int byte = k * (R * 2) + piece * 16 + ((col >> 2) & 1) * 8;
     const lds_v4i16_t* p0 = (const lds_v4i16_t*)((const __attribute__((address_space(3))) char*)tile + byte);
     const lds_v4i16_t* p1 = (const lds_v4i16_t*)((const __attribute__((address_space(3))) char*)tile + byte + 4 * R * 2);
@@ -866,12 +892,15 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void gemm_bf16_ring_ker
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[mi][ni][r] = 0.f;
 
-  const int nk = p.K / BKA;   // K is a multiple of BKA
+  // K >= BKA.  A range that is not whole K tiles (plain problems only) starts with its partial tile, so that the loop below
+  // knows whole ones only.
+  const int nk_whole = p.K / BKA, rem = p.K % BKA;
+  const int nk = nk_whole + (rem > 0);
   // tile t (past the end: the last one again, never read) goes to stage t & (NS - 1);
   // a stage's LDS byte address: the low half of a generic pointer into LDS is its LDS address
   const uint32_t lds_base = __builtin_amdgcn_readfirstlane((uint32_t)reinterpret_cast<uintptr_t>(smem));
   TileWalk walk;   // the tile the next loads fetch
-  walk.init(ld_a.base_, ld_b.base_, ld_a.tile_step_bytes(), ld_b.tile_step_bytes(), p, nk);
+  walk.init(ld_a.base_, ld_b.base_, ld_a.tile_step_bytes(), ld_b.tile_step_bytes(), p, nk_whole);
   auto issue = [&](int v, uint32_t stage_bytes) {
     if (v < IPA) ld_a.issue_one_untracked(v, walk.a_addr, stage_bytes);
     else ld_b.issue_one_untracked(v - IPA, walk.b_addr, stage_bytes + (uint32_t)(BM * CHK) * 16u);
@@ -890,6 +919,15 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void gemm_bf16_ring_ker
   }
 #pragma unroll
   for (int t = 0; t < NS - 1; ++t) {
+    if (t == 0 && rem > 0) {   // uniform
+      const uint64_t a_tail = walk.a_addr + (uint64_t)walk.a_step * (uint32_t)nk_whole, b_tail = walk.b_addr + (uint64_t)walk.b_step * (uint32_t)nk_whole;
+#pragma unroll
+      for (int v = 0; v < NV; ++v) {
+        if (v < IPA) ld_a.issue_partial(v, a_tail, lds_base, rem, lane);
+        else ld_b.issue_partial(v - IPA, b_tail, lds_base + (uint32_t)(BM * CHK) * 16u, rem, lane);
+      }
+      continue;
+    }
 #pragma unroll
     for (int v = 0; v < NV; ++v) issue(v, lds_base + (uint32_t)(t * kStage) * 16u);
     walk.advance();
@@ -897,6 +935,11 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void gemm_bf16_ring_ker
   __builtin_amdgcn_s_waitcnt(vmcnt_imm((NS - 2) * NV));
   asm volatile("" : "+v"(touched));   // the touch has landed: last use of its register
   __syncthreads();
+  if (rem > 0) {
+    decltype(ld_a)::zero_past_end(smem, rem, tid, NW * 64);
+    decltype(ld_b)::zero_past_end(smem + BM * CHK, rem, tid, NW * 64);
+    __syncthreads();
+  }
   bf16x8 af[2][MI], bfr[2][NI];
 #pragma unroll
   for (int mi = 0; mi < MI; ++mi) af[0][mi] = read_frag<BM, BKA, !TA>(smem, wm * WM + mi * 32, 0, lane);
@@ -978,6 +1021,173 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void gemm_bf16_ring_ker
   epilogue<MI, NI, WM, WN, EPI>(acc, gp.p[g], m0, n0, wm, wn, lane, smem, wave, 0, MI);
 }
 
+
+// ------------------------------------------------------------------------------------------------
+// Products with few tiles.  A workgroup owns a tile of 32*MB x 32*NB and its kSplit waves share the reduction range: wave w takes
+// the K tiles w, w + kSplit, ... of 32 for the whole tile, each wave through a ring of four LDS stages of its own (the ring
+// kernel's loads and layouts), so the loop has no barrier and every wave keeps three tiles in flight; the partial sums meet in
+// LDS once, in a fixed order.  Such products are bound by the bytes a chip can have in flight, not by the matrix cores: small
+// tiles put more CUs to work, and splitting K inside the workgroup does it without partial sums in HBM.
+template <int MB, int NB, int kSplit, bool TA, bool TB, int EPI>
+__global__ __launch_bounds__(kSplit * 64) void gemm_bf16_split_kernel(GroupParams gp) {
+  constexpr int BM = 32 * MB, BN = 32 * NB, BKA = 32, NS = 4, CHK = BKA / 8, KS = BKA / 16, NT = kSplit * 64;
+  constexpr int kStage = (BM + BN) * CHK;   // uint4 per stage
+  extern __shared__ uint4 smem[];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  int wg, g;
+  const BfParams p = select_problem(gp, wg, g);
+  int bm, bn;
+  tile_coords(wg, p.tiles_m, p.tiles_n, bm, bn);
+  const int m0 = bm * BM, n0 = bn * BN;
+
+  AsyncLoader<BM, 1, BKA, !TA> ld_a;
+  AsyncLoader<BN, 1, BKA, TB> ld_b;
+  ld_a.init(TA ? p.A + m0 : p.A + (int64_t)m0 * p.lda, p.lda, min(p.M - m0, BM), 0, lane);
+  ld_b.init(TB ? p.B + (int64_t)n0 * p.ldb : p.B + n0, p.ldb, min(p.N - n0, BN), 0, lane);
+  constexpr int IPA = decltype(ld_a)::IPW, NV = IPA + decltype(ld_b)::IPW;
+  uint4* ring = smem + wave * (NS * kStage);
+  const uint32_t lds_ring = __builtin_amdgcn_readfirstlane((uint32_t)reinterpret_cast<uintptr_t>(ring));
+  const uint64_t a0 = uniform_address(ld_a.base_), b0 = uniform_address(ld_b.base_);
+  const uint32_t a_step = ld_a.tile_step_bytes(), b_step = ld_b.tile_step_bytes();
+  const int nk_whole = p.K / BKA, rem = p.K % BKA;
+  const int mine = nk_whole > wave ? (nk_whole - wave + kSplit - 1) / kSplit : 0;   // whole K tiles of this wave
+  auto issue = [&](int i) {   // this wave's i-th tile, into stage i & (NS - 1); past the end nothing
+    if (i >= mine) return;
+    const uint32_t kt = (uint32_t)(wave + i * kSplit), dst = lds_ring + (uint32_t)((i & (NS - 1)) * kStage) * 16u;
+#pragma unroll
+    for (int v = 0; v < IPA; ++v) ld_a.issue_one_untracked(v, a0 + (uint64_t)a_step * kt, dst);
+#pragma unroll
+    for (int v = 0; v < NV - IPA; ++v) ld_b.issue_one_untracked(v, b0 + (uint64_t)b_step * kt, dst + (uint32_t)(BM * CHK) * 16u);
+  };
+  f32x16 acc[MB][NB];
+#pragma unroll
+  for (int mi = 0; mi < MB; ++mi)
+#pragma unroll
+    for (int ni = 0; ni < NB; ++ni)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[mi][ni][r] = 0.f;
+  auto multiply = [&](const uint4* stage) __attribute__((always_inline)) {
+    bf16x8 af[KS][MB], bfr[KS][NB];
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+#pragma unroll
+      for (int mi = 0; mi < MB; ++mi) af[ks][mi] = read_frag<BM, BKA, !TA>(stage, mi * 32, ks, lane);
+#pragma unroll
+      for (int ni = 0; ni < NB; ++ni) bfr[ks][ni] = read_frag<BN, BKA, TB>(stage + BM * CHK, ni * 32, ks, lane);
+    }
+    // the stage may be overwritten by the loads issued after this point
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+      for (int mi = 0; mi < MB; ++mi)
+#pragma unroll
+        for (int ni = 0; ni < NB; ++ni)
+          acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[ks][ni], af[ks][mi], acc[mi][ni], 0, 0, 0);
+  };
+  issue(0); issue(1); issue(2);
+  for (int i = 0; i < mine; ++i) {
+    // tile i has landed once at most the loads of the (up to two) tiles behind it are outstanding
+    if (i + 2 < mine) __builtin_amdgcn_s_waitcnt(vmcnt_imm(2 * NV));
+    else __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+    asm volatile("" ::: "memory");
+    multiply(ring + (i & (NS - 1)) * kStage);
+    issue(i + 3);   // into the stage read in the previous trip
+  }
+  if (rem > 0 && nk_whole % kSplit == wave) {   // the partial tile at the end of the range: the next wave in turn takes it
+    const uint32_t dst = lds_ring;
+#pragma unroll
+    for (int v = 0; v < IPA; ++v) ld_a.issue_partial(v, a0 + (uint64_t)a_step * (uint32_t)nk_whole, dst, rem, lane);
+#pragma unroll
+    for (int v = 0; v < NV - IPA; ++v) ld_b.issue_partial(v, b0 + (uint64_t)b_step * (uint32_t)nk_whole, dst + (uint32_t)(BM * CHK) * 16u, rem, lane);
+    __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+    asm volatile("" ::: "memory");
+    decltype(ld_a)::zero_past_end(ring, rem, lane, 64);
+    decltype(ld_b)::zero_past_end(ring + BM * CHK, rem, lane, 64);
+    wave_lds_sync();
+    multiply(ring);
+  }
+
+  // partial sums: a lane owns row m and four consecutive columns per register quad
+  constexpr int LD = BN + 4;   // floats per row
+  __syncthreads();             // every wave is done with its ring
+  float* part = reinterpret_cast<float*>(smem);
+#pragma unroll
+  for (int mi = 0; mi < MB; ++mi)
+#pragma unroll
+    for (int ni = 0; ni < NB; ++ni)
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        *reinterpret_cast<float4*>(part + (wave * BM + mi * 32 + (lane & 31)) * LD + ni * 32 + 8 * q + 4 * (lane >> 5)) =
+            make_float4(acc[mi][ni][4 * q], acc[mi][ni][4 * q + 1], acc[mi][ni][4 * q + 2], acc[mi][ni][4 * q + 3]);
+  __syncthreads();
+  const BfParams& q = gp.p[g];
+  for (int e = tid; e < BM * BN / 8; e += NT) {
+    const int row = e / (BN / 8), col = e % (BN / 8) * 8;
+    float v[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int w = 0; w < kSplit; ++w) {
+      const float4 lo = *reinterpret_cast<const float4*>(part + (w * BM + row) * LD + col);
+      const float4 hi = *reinterpret_cast<const float4*>(part + (w * BM + row) * LD + col + 4);
+      v[0] += lo.x; v[1] += lo.y; v[2] += lo.z; v[3] += lo.w;
+      v[4] += hi.x; v[5] += hi.y; v[6] += hi.z; v[7] += hi.w;
+    }
+    const bool inside = m0 + row < q.M && n0 + col < q.N;   // N is a multiple of 8
+    if (inside) {
+      const int64_t idx = (int64_t)(m0 + row) * q.ldc + n0 + col;
+      if (EPI == kEpiAccum) {
+        float* dst = static_cast<float*>(q.C) + idx;
+        if (q.accumulate) {
+          const float4 lo = *reinterpret_cast<const float4*>(dst), hi = *reinterpret_cast<const float4*>(dst + 4);
+          v[0] += lo.x; v[1] += lo.y; v[2] += lo.z; v[3] += lo.w;
+          v[4] += hi.x; v[5] += hi.y; v[6] += hi.z; v[7] += hi.w;
+        }
+        *reinterpret_cast<float4*>(dst) = make_float4(v[0], v[1], v[2], v[3]);
+        *reinterpret_cast<float4*>(dst + 4) = make_float4(v[4], v[5], v[6], v[7]);
+      } else {
+        float t[8];
+        if ((EPI == kEpiStore || EPI == kEpiGelu) && q.bias) {
+          unpack8(*reinterpret_cast<const uint4*>(q.bias + n0 + col), t);
+#pragma unroll
+          for (int j = 0; j < 8; ++j) v[j] += t[j];
+        }
+        if (EPI == kEpiStore && q.aux) {
+          unpack8(*reinterpret_cast<const uint4*>(q.aux + idx), t);
+#pragma unroll
+          for (int j = 0; j < 8; ++j) v[j] += t[j];
+        }
+        if (EPI == kEpiGeluGrad) {
+          unpack8(*reinterpret_cast<const uint4*>(q.aux + idx), t);
+#pragma unroll
+          for (int j = 0; j < 8; ++j) v[j] *= gelu_grad_fast(t[j]);
+        }
+        *reinterpret_cast<uint4*>(static_cast<bf16_t*>(q.C) + idx) = pack8(v);
+        if (EPI == kEpiGelu) {
+#pragma unroll
+          for (int j = 0; j < 8; ++j) v[j] = gelu_fast(v[j]);
+          *reinterpret_cast<uint4*>(q.aux_out + idx) = pack8(v);
+        }
+      }
+    }
+    if (EPI == kEpiGeluGrad && q.colsum) {   // the values before rounding, for the sums below (rows past the matrix: zero)
+      float* mine_out = part + row * LD + col;
+      *reinterpret_cast<float4*>(mine_out) = inside ? make_float4(v[0], v[1], v[2], v[3]) : make_float4(0.f, 0.f, 0.f, 0.f);
+      *reinterpret_cast<float4*>(mine_out + 4) = inside ? make_float4(v[4], v[5], v[6], v[7]) : make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+  }
+  if (EPI == kEpiGeluGrad && q.colsum) {   // column sums of every 32-row strip
+    __syncthreads();
+    for (int e = tid; e < MB * BN; e += NT) {
+      const int strip = e / BN, col = e % BN;
+      if (m0 + strip * 32 >= q.M || n0 + col >= q.N) continue;
+      float t = 0.f;
+#pragma unroll 8
+      for (int r = 0; r < 32; ++r) t += part[(strip * 32 + r) * LD + col];
+      q.colsum[(int64_t)((m0 >> 5) + strip) * q.N + n0 + col] = t;
+    }
+  }
+}
 
 int compute_units() {
   static int n = 0;
@@ -1106,6 +1316,35 @@ hipError_t launch(GroupParams gp, hipStream_t s) {
   return hipGetLastError();
 }
 
+template <int MB, int NB, int kSplit, bool TA, bool TB, int EPI>
+hipError_t launch_split(GroupParams gp, hipStream_t s) {
+  constexpr size_t ring = (size_t)kSplit * 4 * (32 * MB + 32 * NB) * 4 * sizeof(uint4);
+  constexpr size_t part = (size_t)kSplit * 32 * MB * (32 * NB + 4) * sizeof(float);
+  constexpr size_t lds = ring > part ? ring : part;
+  static_assert(lds <= 160 * 1024, "LDS of a CU");
+  auto kern = gemm_bf16_split_kernel<MB, NB, kSplit, TA, TB, EPI>;
+  static bool configured = false;
+  if (!configured) {
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+    configured = true;
+  }
+  int total = 0;
+  for (int g = 0; g < gp.count; ++g) {
+    gp.p[g].tiles_m = ceil_div(gp.p[g].M, 32 * MB);
+    gp.p[g].tiles_n = ceil_div(gp.p[g].N, 32 * NB);
+    gp.tile_start[g] = total;
+    total += gp.p[g].tiles_m * gp.p[g].tiles_n;
+  }
+  for (int g = gp.count; g <= kMaxProblems; ++g) gp.tile_start[g] = total;
+  gp.n_tiles = total;
+  gp.seg0 = 0;
+  gp.seg1 = total / 8 * 8;
+  gp.seg2 = 0;
+  hipLaunchKernelGGL(kern, dim3(total), dim3(kSplit * 64), lds, s, gp);
+  return hipGetLastError();
+}
+
 int g_tile_override = 0;  // 0: heuristic; else force a tile shape (tuning aid)
 
 // Tile choice for a (grouped) problem; ta/tb as in GemmDesc.
@@ -1113,27 +1352,47 @@ int choose_tile(const BfParams* p, int count, bool ta, bool tb) {
   int tile = g_tile_override;
   if (tile == 0) {
     // Measured on MI355X (M = 2048..8192): once 256x256 tiles give about 5/8 of the CUs a tile
-    // (160 tiles: N = 2560 at M = 4096) the 8-wave 256x256 kernels win, by 15..30 % at 160..192
-    // tiles and more above, and among them the ring kernel by 10..25 %.  Below that, 128x128
-    // tiles: with about one tile per CU the ring kernel with K tiles of 64 (a little ahead of the
-    // register-staged variant with two K groups per workgroup), with more tiles two register-staged
-    // workgroups per CU.  The ring kernels need K to be a multiple of their K tile and fall back to
-    // the register-staged kernel of the same tile otherwise.
-    int64_t big = 0, small = 0;
+    // (160 tiles: N = 2560 at M = 4096) the 8-wave 256x256 ring kernel wins, by 15..30 % at 160..192 tiles and more
+    // above.  Below that the tile with the least estimated time, in microseconds: rounds of tiles over the CUs times a
+    // fixed part and a part per k of the reduction range, fitted to launches of 8 to 1024 tiles with K = 32 .. 4608:
+    //   32x32, K split over 8 waves   3.0 + 1.25e-3 K per round
+    //   64x64, K split over 4 waves   3.5 + 3.3e-3 K per round
+    //   128x128 ring                  3 once, 1.5 + 7.5e-3 K per round (4.8e-3 K while half the CUs are idle)
+    // and the accumulator's trip through HBM at 20 KB per microsecond and CU.  Forward | data | weight gradient, tiles 128 (the
+    // register-staged kernel used before), 128 ring, 64, 32 in us: 128 tokens 1024 -> 3072: 17.3|35.0|8.7, 9.9|17.9|7.7,
+    // 7.2|10.6|11.1, 7.9|6.1|24.8; 1000 tokens 768 -> 2304: 14.9|27.3|17.4, 9.8|16.0|13.2, 15.3|10.0|14.0, 26.6|15.5|32.8;
+    // 3000 tokens 1536 -> 4608 (256x256: 46|86|69): 69|77|66, 62|66|61, 99|96|89, 251|164|241.
+    // Among 128x128 tiles two register-staged workgroups per CU win where a launch of several rounds of short products lives
+    // on its accumulator (300 tokens 2048 -> 4096, weight gradient: 18.5 against 24.7 us), the ring kernel elsewhere.
+    int64_t big = 0, t128 = 0, t64 = 0, t32 = 0;
+    int K = 0;
     for (int g = 0; g < count; ++g) {
       big += (int64_t)ceil_div(p[g].M, 256) * ceil_div(p[g].N, 256);
-      small += (int64_t)ceil_div(p[g].M, 128) * ceil_div(p[g].N, 128);
+      t128 += (int64_t)ceil_div(p[g].M, 128) * ceil_div(p[g].N, 128);
+      t64 += (int64_t)ceil_div(p[g].M, 64) * ceil_div(p[g].N, 64);
+      t32 += (int64_t)ceil_div(p[g].M, 32) * ceil_div(p[g].N, 32);
+      K = p[g].K > K ? p[g].K : K;
     }
-    tile = big >= 144 ? 23 : small <= 256 ? 22 : 2;
-    (void)ta; (void)tb;
+    const int cus = compute_units();
+    const bool accum = ta;   // the weight-gradient form
+    const double c32 = ceil_div(t32, cus) * (3.0 + 1.25e-3 * K + (accum ? 0.4 : 0.0));
+    const double c64 = ceil_div(t64, cus) * (3.5 + 3.3e-3 * K + (accum ? 1.6 : 0.0));
+    const double c128 = 3.0 + ceil_div(t128, cus) * (1.5 + (t128 * 2 <= cus ? 4.8e-3 : 7.5e-3) * K + (accum ? 6.5 : 0.0));
+    if (big >= 144) tile = 23;
+    else if (c32 < c64 && c32 < c128) tile = 32;
+    else if (c64 < c128) tile = 64;
+    else tile = accum && t128 > cus && K <= 1024 ? 2 : 22;
+    (void)tb;
   }
   bool segmented = false;
   for (int g = 0; g < count; ++g) segmented = segmented || p[g].seg_tiles > 1;
-  if (segmented && tile < 20) tile = 22;   // only the ring kernels walk a segmented reduction range
-  if (tile > 20) {   // the ring kernels need whole K tiles (in every piece of a segmented range)
+  if (segmented && tile != 23) tile = 22;   // only the ring kernels walk a segmented reduction range
+  if (tile == 22 || tile == 23) {   // the ring kernels need a whole K tile (and nothing but whole ones in the pieces of a segmented range)
     const int bk = tile == 22 ? 64 : 32;
-    for (int g = 0; g < count; ++g)
-      if ((p[g].K / (p[g].seg_tiles > 1 ? p[g].seg_tiles : 1)) % bk) { tile = segmented ? -1 : tile == 22 ? 6 : 3; break; }
+    for (int g = 0; g < count; ++g) {
+      const bool ok = p[g].seg_tiles > 1 ? (p[g].K / p[g].seg_tiles) % bk == 0 : p[g].K >= bk;
+      if (!ok) { tile = segmented ? -1 : tile == 22 ? 6 : 3; break; }
+    }
   }
   return tile;
 }
@@ -1147,6 +1406,8 @@ hipError_t pick_tile(const GroupParams& gp, hipStream_t s) {
     case 6: return launch<128, 128, 64, 64, 64, TA, TB, EPI, 2>(gp, s);   // two K groups of 4 waves
     case 22: return launch_ring<128, 128, 32, 64, 64, 4, TA, TB, EPI>(gp, s);   // 8 waves
     case 23: return launch_ring<256, 256, 128, 64, 32, 4, TA, TB, EPI>(gp, s);
+    case 32: return launch_split<1, 1, 8, TA, TB, EPI>(gp, s);
+    case 64: return launch_split<2, 2, 4, TA, TB, EPI>(gp, s);
     default: return hipErrorInvalidValue;
   }
 }
@@ -1210,6 +1471,8 @@ void gemm_bf16_kernel_name(const GemmDesc* d, int count, char* out, size_t cap) 
     case 6: snprintf(out, cap, "gemm_bf16_kernel<128, 128, 64, 64, 64, %s, %s, %d, 2>", ta, tb, d[0].epilogue); break;
     case 22: snprintf(out, cap, "gemm_bf16_ring_kernel<128, 128, 32, 64, 64, 4, %s, %s, %d>", ta, tb, d[0].epilogue); break;
     case 23: snprintf(out, cap, "gemm_bf16_ring_kernel<256, 256, 128, 64, 32, 4, %s, %s, %d>", ta, tb, d[0].epilogue); break;
+    case 32: snprintf(out, cap, "gemm_bf16_split_kernel<1, 1, 8, %s, %s, %d>", ta, tb, d[0].epilogue); break;
+    case 64: snprintf(out, cap, "gemm_bf16_split_kernel<2, 2, 4, %s, %s, %d>", ta, tb, d[0].epilogue); break;
     default: snprintf(out, cap, "gemm_bf16 tile %d <%s, %s, %d>", tile, ta, tb, d[0].epilogue); break;
   }
 }

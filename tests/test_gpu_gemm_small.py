@@ -1,12 +1,18 @@
-"""fp32 products at the edges of the tiles and of the split reduction range: one row, one column, 31/32/33, 63/64/65, reduction
+"""Products at the edges of their kernels' tiles.
+
+fp32: at the edges of the tiles and of the split reduction range: one row, one column, 31/32/33, 63/64/65, reduction
 ranges from 1 to a few chunks of 16 with every kind of remainder, leading dimensions that allow no 16-byte loads; all forms and
-epilogues, and several products in one launch through the weight-gradient accumulation of a stage."""
+epilogues, and several products in one launch through the weight-gradient accumulation of a stage.
+bf16: partial K tiles of the direct-to-LDS kernels (every remainder class of their K tiles, with NaNs behind the matrices, which
+must not show), and the kernels that split the reduction range over a workgroup's waves."""
 import numpy as np
 import pytest
 import torch
 
 from oracle import block as ob
 from paper_2006_09503_amd import binding as B
+
+from paper_2006_09503_amd.synth import round_to_bf16
 
 from gpu_util import rel, to_host
 
@@ -50,3 +56,73 @@ def test_fp32_products_at_tile_edges(M, N, K, ta, tb, pad):
         if epi == 1:
             assert rel(to_host(G)[:, :N], ob.gelu(full)) < tol
         assert bool(torch.isnan(C[:, N:]).all())
+
+
+BF16 = 1
+
+
+def bf16_matrix(rng, rows, cols, ld, scale=1.0):
+    """A bf16 matrix with rows `ld` apart and NaN everywhere else, a row's worth behind the end included."""
+    a = round_to_bf16((rng.standard_normal((rows, cols)) * scale).astype(np.float32))
+    d = torch.full((rows + 1, ld), float("nan"), device="cuda", dtype=torch.bfloat16)
+    d[:rows, :cols] = torch.from_numpy(a).cuda().to(torch.bfloat16)
+    return a.astype(np.float64), d
+
+
+@pytest.mark.parametrize("tile", [0, 22, 23, 32, 64])
+@pytest.mark.parametrize("M,N,K", [(8, 8, 8), (40, 72, 40), (264, 136, 72), (136, 264, 104), (96, 520, 200), (328, 272, 1016), (72, 64, 2056)])
+def test_bf16_partial_k_tiles(tile, M, N, K):
+    rng = np.random.default_rng(M + N + K + tile)
+    L = B.lib()
+    assert L.k2bw_tune_gemm_tile(tile) == 0
+    try:
+        x, X = bf16_matrix(rng, M, K, K + 8)
+        w, W = bf16_matrix(rng, K, N, N + 8, 0.1)
+        wt, Wt = bf16_matrix(rng, N, K, K + 8, 0.1)
+        bias, Bi = bf16_matrix(rng, 1, N, N)
+        aux, U = bf16_matrix(rng, M, N, N)
+        C = torch.empty((M, N), device="cuda", dtype=torch.bfloat16)
+        G = torch.empty_like(C)
+        for tb, (m, dev, ld) in ((0, (w, W, N + 8)), (1, (wt.T, Wt, K + 8))):
+            want = x @ m
+            for epi in (0, 1, 2):
+                if tb and epi == 1:
+                    continue   # a form nobody issues
+                assert L.k2bw_gemm(BF16, 0, tb, epi, M, N, K, X.data_ptr(), K + 8, dev.data_ptr(), ld, C.data_ptr(), N,
+                                   Bi.data_ptr() if epi < 2 else None, U.data_ptr() if epi != 1 else None,
+                                   G.data_ptr() if epi == 1 else None, 0, None) == 0
+                torch.cuda.synchronize()
+                full = {0: want + bias + aux, 1: want + bias, 2: want * ob.gelu_grad(aux)}[epi]
+                assert rel(to_host(C), full) < 3e-3      # one rounding to bf16: 2^-9 / sqrt(3), and the fast GELU
+                if epi == 1:
+                    assert rel(to_host(G), ob.gelu(full)) < 3e-3
+        # the fused bias gradient: column sums of the unrounded values
+        db = torch.full((N,), float("nan"), device="cuda")
+        ws = torch.empty(L.k2bw_gemm_dgrad_gelu_bias_workspace(M, N), device="cuda")
+        assert L.k2bw_gemm_dgrad_gelu_bias(M, N, K, X.data_ptr(), K + 8, Wt.data_ptr(), K + 8, C.data_ptr(), N, U.data_ptr(), db.data_ptr(),
+                                           0, ws.data_ptr(), None) == 0
+        torch.cuda.synchronize()
+        full = (x @ wt.T) * ob.gelu_grad(aux)
+        assert np.abs(to_host(db) - full.sum(0)).max() < 1e-4 * np.sqrt((full ** 2).sum(0)).max() * np.sqrt(M)
+    finally:
+        assert L.k2bw_tune_gemm_tile(0) == 0
+
+
+@pytest.mark.parametrize("tile", [0, 22, 23, 32, 64])
+@pytest.mark.parametrize("M,N,K", [(72, 40, 1), (136, 264, 33), (264, 136, 65), (256, 520, 127), (520, 264, 1000), (64, 64, 4099)])
+def test_bf16_weight_gradient_of_any_number_of_tokens(tile, M, N, K):
+    rng = np.random.default_rng(M + N + K + tile)
+    L = B.lib()
+    assert L.k2bw_tune_gemm_tile(tile) == 0
+    try:
+        x, X = bf16_matrix(rng, K, M, M + 8)
+        dy, D = bf16_matrix(rng, K, N, N + 8)
+        g0 = rng.standard_normal((M, N)).astype(np.float32)
+        for acc in (0, 1):
+            G = torch.from_numpy(g0.copy()).cuda()
+            assert L.k2bw_gemm(BF16, 1, 0, 3, M, N, K, X.data_ptr(), M + 8, D.data_ptr(), N + 8, G.data_ptr(), N, None, None, None, acc,
+                               None) == 0
+            torch.cuda.synchronize()
+            assert rel(to_host(G), x.T @ dy + (g0 if acc else 0)) < 2e-6
+    finally:
+        assert L.k2bw_tune_gemm_tile(0) == 0
