@@ -53,7 +53,7 @@ struct GemmDesc {
   int dtype = kF32;
 };
 hipError_t gemm(const GemmDesc& d, hipStream_t stream);
-// 1..4 independent GEMMs of the same form, epilogue and dtype; bf16 runs them in one launch.
+// Independent GEMMs of the same form, epilogue and dtype in one launch where the kernels allow it; more than one: kEpiAccum only.
 constexpr int kGemmMaxGroup = 24;   // GEMMs of one form and epilogue that may share a launch
 hipError_t gemm_grouped(const GemmDesc* d, int count, hipStream_t stream);
 // CUs of the current device (a launch of T tiles takes ceil(T / CUs) rounds of one tile per CU).
@@ -84,6 +84,9 @@ hipError_t colsum_partial(const void* y, int rows, int n, int ldy, float* partia
 // out[n] = (accumulate ? out[n] : 0) + sum_p partial[p][n]
 hipError_t colsum_finalize(const float* partial, int parts, int n, float* out, bool accumulate,
                            hipStream_t stream);
+
+// Both steps (or one launch for few rows): out[n] = (accumulate ? out[n] : 0) + column sums of y [rows, n], contiguous; partial as above.
+hipError_t column_sums(const void* y, int rows, int n, float* partial, float* out, bool accumulate, int dtype, hipStream_t stream);
 
 // Grouped forms: column sums of up to 4 matrices [rows, n_i] in one launch into
 // partial[parts][sum n_i] (segment i starts at column sum_{j<i} n_j), and the final reduction

@@ -104,11 +104,7 @@ int64_t k2bw_bias_grad_workspace(int n) {
 int k2bw_bias_grad(int dtype, int rows, int n, const void* y, float* out, int accumulate, float* workspace,
                    void* stream) {
   if (!dtype_ok(dtype) || !out || !workspace) return STAGE_ERR_INVALID_ARG;
-  int parts = 0;
-  hipStream_t s = static_cast<hipStream_t>(stream);
-  hipError_t e = colsum_partial(y, rows, n, n, workspace, &parts, dtype, s);
-  if (e != hipSuccess) return rc_of(e);
-  return rc_of(colsum_finalize(workspace, parts, n, out, accumulate != 0, s));
+  return rc_of(column_sums(y, rows, n, workspace, out, accumulate != 0, dtype, static_cast<hipStream_t>(stream)));
 }
 
 int k2bw_bias_grad_static_max_cols(void) { return kStaticMaxCols; }
@@ -126,13 +122,8 @@ int k2bw_bias_grad_static(int dtype, int rows, int n, const void* y, float* out,
       return STAGE_ERR_HIP;
     scratch_ptr[dev] = p;
   }
-  float* partial = scratch_ptr[dev];
-  int parts = 0;
-  hipStream_t s = static_cast<hipStream_t>(stream);
-  // Every partial row the second kernel reads is written in full by the first: nothing needs clearing.
-  hipError_t e = colsum_partial(y, rows, n, n, partial, &parts, dtype, s);
-  if (e != hipSuccess) return rc_of(e);
-  return rc_of(colsum_finalize(partial, parts, n, out, accumulate != 0, s));
+  // Every partial row that is read is written in full by the same call: nothing needs clearing.
+  return rc_of(column_sums(y, rows, n, scratch_ptr[dev], out, accumulate != 0, dtype, static_cast<hipStream_t>(stream)));
 }
 
 int k2bw_attention_fwd(int dtype, int b, int s, int a, int dh, int mask_mode, const int32_t* seqlens,

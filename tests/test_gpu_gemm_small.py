@@ -126,3 +126,20 @@ def test_bf16_weight_gradient_of_any_number_of_tokens(tile, M, N, K):
             assert rel(to_host(G), x.T @ dy + (g0 if acc else 0)) < 2e-6
     finally:
         assert L.k2bw_tune_gemm_tile(0) == 0
+
+
+@pytest.mark.parametrize("dtype", [0, BF16])
+@pytest.mark.parametrize("rows,n", [(1, 8), (127, 40), (129, 24), (513, 264), (1024, 72), (1025, 4104), (2048, 4096), (2049, 32)])
+def test_column_sums_on_both_sides_of_the_one_launch_rule(dtype, rows, n):
+    rng = np.random.default_rng(rows + n)
+    y = rng.standard_normal((rows, n)).astype(np.float32)
+    y = round_to_bf16(y) if dtype else y
+    Y = torch.from_numpy(y).cuda().to(torch.bfloat16 if dtype else torch.float32)
+    L = B.lib()
+    ws = torch.empty(L.k2bw_bias_grad_workspace(n), device="cuda")
+    out = torch.full((n,), float("nan"), device="cuda")
+    for acc in (0, 1):
+        assert L.k2bw_bias_grad(dtype, rows, n, Y.data_ptr(), out.data_ptr(), acc, ws.data_ptr(), None) == 0
+    torch.cuda.synchronize()
+    # sums of `rows` terms of size 1, each addition rounded to 2^-24 of a running sum of about sqrt(rows)
+    assert np.abs(to_host(out) - 2 * y.astype(np.float64).sum(0)).max() < 1e-6 * rows + 1e-6
