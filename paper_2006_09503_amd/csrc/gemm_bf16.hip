@@ -64,9 +64,10 @@ struct BfParams {
 // Up to kMaxGroup independent GEMMs of the same form in one launch: workgroup ids
 // [tile_start[g], tile_start[g+1]) belong to problem g.
 constexpr int kMaxProblems = kMaxGroup + 1;   // + one problem split in two for the balanced tail
-struct GroupParams {
-  BfParams p[kMaxProblems];
-  int tile_start[kMaxProblems + 1];
+template <int CAP>
+struct GroupOf {
+  BfParams p[CAP];
+  int tile_start[CAP + 1];
   int count;
   int n_tiles;   // = tile_start[count] = the launch's workgroups
   // workgroup id -> tile number (see select_problem): [0, seg0) in blocks of 32 tiles dealt to the XCDs in turn
@@ -74,6 +75,21 @@ struct GroupParams {
   // runs (multiples of 8), the rest as they come
   int seg0, seg1, seg2;
 };
+using GroupParams = GroupOf<kMaxProblems>;   // on the host
+// What a launch carries: only weight-gradient products share launches.  The runtime copies a launch's arguments on the host's
+// time (3.4 KB for 25 problems: 4.4 us per launch against 3.7 with the two a single product needs).
+template <int EPI>
+constexpr int kLaunchCap = EPI == kEpiAccum ? kMaxProblems : 2;
+template <int EPI>
+using LaunchParams = GroupOf<kLaunchCap<EPI>>;
+template <int EPI>
+LaunchParams<EPI> launch_params(const GroupParams& gp) {
+  LaunchParams<EPI> l;
+  for (int g = 0; g < kLaunchCap<EPI>; ++g) { l.p[g] = gp.p[g]; l.tile_start[g] = gp.tile_start[g]; }
+  l.tile_start[kLaunchCap<EPI>] = gp.tile_start[kLaunchCap<EPI>];
+  l.count = gp.count; l.n_tiles = gp.n_tiles; l.seg0 = gp.seg0; l.seg1 = gp.seg1; l.seg2 = gp.seg2;
+  return l;
+}
 
 // Chunk swizzle.  Three LDS access patterns have to avoid bank conflicts at once: fragment
 // reads (32 consecutive rows, same logical chunk, 16 bytes per lane), direct stores (the 8 or 16
@@ -285,7 +301,8 @@ __device__ __forceinline__ void tile_coords(int t, int tiles_m, int tiles_n, int
 // Returns a copy of the problem for the code in front of the K loop (only the fields used there
 // are kept); the epilogue reads its operands through gp.p[g], where their latency does not matter
 // and they occupy no registers during the loop.
-__device__ __forceinline__ BfParams select_problem(const GroupParams& gp, int& wg, int& g) {
+template <int CAP>
+__device__ __forceinline__ BfParams select_problem(const GroupOf<CAP>& gp, int& wg, int& g) {
   BfParams p = gp.p[0];
   const int count = gp.count;
   // (mask arithmetic, not branches: all the loads above stay in one round)
@@ -299,7 +316,7 @@ __device__ __forceinline__ BfParams select_problem(const GroupParams& gp, int& w
   g = 0;
   if (count > 1) {
 #pragma unroll
-    for (int q = 1; q < kMaxProblems; ++q)
+    for (int q = 1; q < CAP; ++q)
       if (q < count && wg >= gp.tile_start[q]) g = q;
     if (g > 0) {
       p = gp.p[g];
@@ -514,7 +531,7 @@ __device__ __forceinline__ void interleave_reads_with_mfma() {
 // MFMAs of the other) without shrinking the tile; the sum order is fixed, so results do not
 // depend on timing.
 template <int BM, int BN, int WM, int WN, int BK, bool TA, bool TB, int EPI, int KSPLIT>
-__global__ __launch_bounds__((BM / WM) * (BN / WN) * 64 * KSPLIT) void gemm_bf16_kernel(GroupParams gp) {
+__global__ __launch_bounds__((BM / WM) * (BN / WN) * 64 * KSPLIT) void gemm_bf16_kernel(LaunchParams<EPI> gp) {
   constexpr int NT = (BM / WM) * (BN / WN) * 64;   // threads of one K group
   constexpr int CH = BK / 8;
   constexpr int MI = WM / 32, NI = WN / 32;
@@ -856,7 +873,7 @@ constexpr int vmcnt_imm(int n) { return (n & 15) | ((n >> 4) << 14) | (7 << 4) |
 // row and load) that tile is 10..15 % slower once the operands come from HBM, as they do inside
 // the stage, with four stages or with eight.
 template <int BM, int BN, int WM, int WN, int BKA, int NS, bool TA, bool TB, int EPI>
-__global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void gemm_bf16_ring_kernel(GroupParams gp) {
+__global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void gemm_bf16_ring_kernel(LaunchParams<EPI> gp) {
   constexpr int CHK = BKA / 8, KS = BKA / 16;
   constexpr int NW = (BM / WM) * (BN / WN);
   constexpr int MI = WM / 32, NI = WN / 32;
@@ -1029,7 +1046,7 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void gemm_bf16_ring_ker
 // LDS once, in a fixed order.  Such products are bound by the bytes a chip can have in flight, not by the matrix cores: small
 // tiles put more CUs to work, and splitting K inside the workgroup does it without partial sums in HBM.
 template <int MB, int NB, int kSplit, bool TA, bool TB, int EPI>
-__global__ __launch_bounds__(kSplit * 64) void gemm_bf16_split_kernel(GroupParams gp) {
+__global__ __launch_bounds__(kSplit * 64) void gemm_bf16_split_kernel(LaunchParams<EPI> gp) {
   constexpr int BM = 32 * MB, BN = 32 * NB, BKA = 32, NS = 4, CHK = BKA / 8, KS = BKA / 16, NT = kSplit * 64;
   constexpr int kStage = (BM + BN) * CHK;   // uint4 per stage
   extern __shared__ uint4 smem[];
@@ -1283,7 +1300,7 @@ hipError_t launch_ring(GroupParams gp, hipStream_t s) {
   gp.seg0 = full_tiles / 256 * 256;
   gp.seg1 = (full_tiles - gp.seg0) / 8 * 8;
   gp.seg2 = (total - gp.seg0 - gp.seg1) / 8 * 8;
-  hipLaunchKernelGGL(kern, dim3(total), dim3(NT), lds, s, gp);
+  hipLaunchKernelGGL(kern, dim3(total), dim3(NT), lds, s, launch_params<EPI>(gp));
   return hipGetLastError();
 }
 
@@ -1312,7 +1329,7 @@ hipError_t launch(GroupParams gp, hipStream_t s) {
   gp.seg0 = 0;
   gp.seg1 = total / 8 * 8;
   gp.seg2 = 0;
-  hipLaunchKernelGGL(kern, dim3(total), dim3(NT), lds, s, gp);
+  hipLaunchKernelGGL(kern, dim3(total), dim3(NT), lds, s, launch_params<EPI>(gp));
   return hipGetLastError();
 }
 
@@ -1341,7 +1358,7 @@ hipError_t launch_split(GroupParams gp, hipStream_t s) {
   gp.seg0 = 0;
   gp.seg1 = total / 8 * 8;
   gp.seg2 = 0;
-  hipLaunchKernelGGL(kern, dim3(total), dim3(kSplit * 64), lds, s, gp);
+  hipLaunchKernelGGL(kern, dim3(total), dim3(kSplit * 64), lds, s, launch_params<EPI>(gp));
   return hipGetLastError();
 }
 
@@ -1477,7 +1494,7 @@ void gemm_bf16_kernel_name(const GemmDesc* d, int count, char* out, size_t cap) 
   }
 }
 
-// `count` GEMMs (1..4) with the same form and epilogue in one launch.
+// `count` GEMMs (1..kGemmMaxGroup) with the same form and epilogue in one launch; more than one: weight-gradient form only.
 hipError_t gemm_bf16_grouped(const GemmDesc* d, int count, hipStream_t stream) {
   if (count < 1 || count > kMaxGroup) return hipErrorInvalidValue;
   GroupParams gp{};
@@ -1488,6 +1505,7 @@ hipError_t gemm_bf16_grouped(const GemmDesc* d, int count, hipStream_t stream) {
     const int64_t a_rows = d[g].trans_a ? d[g].K / d[g].n_seg : d[g].M, b_rows = d[g].trans_b ? d[g].N : d[g].K / d[g].n_seg;
     if (a_rows * (int64_t)d[g].lda * 2 >= (1ll << 31) || b_rows * (int64_t)d[g].ldb * 2 >= (1ll << 31))
       return hipErrorInvalidValue;
+    if (count > 1 && d[g].epilogue != kEpiAccum) return hipErrorInvalidValue;   // one per launch
     if (d[g].trans_a != d[0].trans_a || d[g].trans_b != d[0].trans_b || d[g].epilogue != d[0].epilogue)
       return hipErrorInvalidValue;
     gp.p[g] = to_params(d[g]);

@@ -261,19 +261,25 @@ struct FragLoader {   // fragments of 32*NBLK rows x kChunk k: f[block][k-instru
 };
 
 constexpr int kGroupF32 = 24;   // products of one form that may share a launch
-struct GroupF32 {
-  F32Params p[kGroupF32];
-  int tile_start[kGroupF32 + 1];
+template <int CAP>
+struct GroupOfF32 {
+  F32Params p[CAP];
+  int tile_start[CAP + 1];
   int count;
 };
+using GroupF32 = GroupOfF32<kGroupF32>;   // on the host
+// What a launch carries (its arguments are copied on the host's time): only weight-gradient products share launches
+template <int EPI>
+constexpr int kLaunchCap = EPI == kEpiAccum ? kGroupF32 : 1;
 
 template <int MB, int NB, int kSplit, bool TA, bool TB, int EPI>
-__global__ __launch_bounds__(kSplit * 64) void gemm_f32_split_kernel(GroupF32 gp) {
+__global__ __launch_bounds__(kSplit * 64) void gemm_f32_split_kernel(GroupOfF32<kLaunchCap<EPI>> gp) {
   constexpr int TM = 32 * MB, TN = 32 * NB, LDS_LD = TN + 4;
   extern __shared__ __attribute__((aligned(16))) float part[];   // [kSplit][TM][LDS_LD]
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l32 = lane & 31, hf = lane >> 5;
   int g = 0;
-  for (int q = 1; q < gp.count; ++q) g = (int)blockIdx.x >= gp.tile_start[q] ? q : g;
+  if (kLaunchCap<EPI> > 1)
+    for (int q = 1; q < gp.count; ++q) g = (int)blockIdx.x >= gp.tile_start[q] ? q : g;
   const F32Params& p = gp.p[g];
   const int t = (int)blockIdx.x - gp.tile_start[g], tiles_n = (p.N + TN - 1) / TN;
   const int m0 = t / tiles_n * TM, n0 = t % tiles_n * TN;
@@ -357,7 +363,11 @@ hipError_t launch_split(GroupF32& gp, hipStream_t s) {
     total += ceil_div(gp.p[g].M, 32 * MB) * ceil_div(gp.p[g].N, 32 * NB);
   }
   gp.tile_start[gp.count] = total;
-  hipLaunchKernelGGL((gemm_f32_split_kernel<MB, NB, kSplit, TA, TB, EPI>), dim3(total), dim3(kSplit * 64), lds, s, gp);
+  GroupOfF32<kLaunchCap<EPI>> l;
+  l.count = gp.count;
+  for (int g = 0; g < gp.count; ++g) { l.p[g] = gp.p[g]; l.tile_start[g] = gp.tile_start[g]; }
+  l.tile_start[gp.count] = total;
+  hipLaunchKernelGGL((gemm_f32_split_kernel<MB, NB, kSplit, TA, TB, EPI>), dim3(total), dim3(kSplit * 64), lds, s, l);
   return hipGetLastError();
 }
 
@@ -385,6 +395,7 @@ int choose_f32(const F32Params* p, int count, bool ta, bool tb) {
 
 template <bool TA, bool TB, int EPI>
 hipError_t launch_form(GroupF32& gp, hipStream_t s) {
+  if (gp.count > kLaunchCap<EPI>) return hipErrorInvalidValue;
   switch (choose_f32(gp.p, gp.count, TA, TB)) {
     case 64: return launch_split<2, 2, 4, TA, TB, EPI>(gp, s);
     case 32: return launch_split<1, 1, 8, TA, TB, EPI>(gp, s);
