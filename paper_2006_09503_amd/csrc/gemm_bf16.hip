@@ -721,21 +721,25 @@ __device__ __forceinline__ uint64_t uniform_address(const void* ptr) {
 template <int R>
 __device__ __forceinline__ int swz_strided(int k) { return (k & (R >= 64 ? 3 : 1)) << 1; }
 
+// (Tiles of 192 rows: 12 load instructions for 8 waves, so four waves issue one more than the others.)
 template <int R, int NW, int BKA, bool K_CONTIG>
 struct AsyncLoader {
   static constexpr int CHK = BKA / 8;               // chunks per row of a K-contiguous tile
   static constexpr int kSlots = R * CHK;            // 16-byte slots per tile
-  static constexpr int IPW = kSlots / 64 / NW;      // load instructions per wave
-  static_assert(kSlots % (64 * NW) == 0, "tile/waves mismatch");
+  static constexpr int kInstr = kSlots / 64;        // load instructions per tile
+  static constexpr bool kEven = kInstr % NW == 0;   // else the last one of the waves from kInstr % NW on is left out
+  static constexpr int IPW = (kInstr + NW - 1) / NW;   // load instructions per wave
+  static_assert(kSlots % 64 == 0, "tile/waves mismatch");
   const bf16_t* base_;
   uint32_t voff[IPW];   // byte offsets from the tile's base
   int ld_, first_slot_;
+  __device__ __forceinline__ int slot(int j) const { return first_slot_ + j * (kEven ? 64 : NW * 64); }
   __device__ __forceinline__ void init(const bf16_t* base, int ld, int rows_valid, int wave, int lane) {
     base_ = base; ld_ = ld;
-    first_slot_ = wave * IPW * 64;
+    first_slot_ = wave * (kEven ? IPW : 1) * 64;
 #pragma unroll
     for (int j = 0; j < IPW; ++j) {
-      const int L = first_slot_ + j * 64 + lane;
+      const int L = kEven ? slot(j) + lane : min(slot(j), kSlots - 64) + lane;
       if (K_CONTIG) {
         const int row = L / CHK, pc = L % CHK;
         const int c = pc ^ swz<CHK>(row);
@@ -762,7 +766,7 @@ struct AsyncLoader {
   // lds_tile: byte address of the stage's tile in LDS, wave-uniform.
   // tile_addr: address of the tile's element (row0, k0), wave-uniform.
   __device__ __forceinline__ void issue_one_untracked(int j, uint64_t tile_addr, uint32_t lds_tile) const {
-    const uint32_t dst = __builtin_amdgcn_readfirstlane(lds_tile + (uint32_t)(first_slot_ + j * 64) * 16u);
+    const uint32_t dst = __builtin_amdgcn_readfirstlane(lds_tile + (uint32_t)slot(j) * 16u);
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
                  :
                  : "s"(dst), "v"(voff[j]), "s"(tile_addr)
@@ -771,7 +775,7 @@ struct AsyncLoader {
   // The partial K tile at the end of a reduction range (rem < BKA elements of it exist): chunks and rows past the end are
   // fetched from inside the matrix, and replaced by zeros once they have landed (zero_past_end).
   __device__ __forceinline__ void issue_partial(int j, uint64_t tile_addr, uint32_t lds_tile, int rem, int lane) const {
-    const int L = first_slot_ + j * 64 + lane;
+    const int L = slot(j) + lane;
     uint32_t off = voff[j];
     if (K_CONTIG) {
       const int c = (L % CHK) ^ swz<CHK>(L / CHK);
@@ -780,7 +784,7 @@ struct AsyncLoader {
       const int k = L / (R / 8);
       if (k >= rem) off -= (uint32_t)(k - rem + 1) * (uint32_t)ld_ * 2u;
     }
-    const uint32_t dst = __builtin_amdgcn_readfirstlane(lds_tile + (uint32_t)(first_slot_ + j * 64) * 16u);
+    const uint32_t dst = __builtin_amdgcn_readfirstlane(lds_tile + (uint32_t)slot(j) * 16u);
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(dst), "v"(off), "s"(tile_addr) : "memory");
   }
   static __device__ __forceinline__ void zero_past_end(uint4* tile, int rem, int first, int step) {
@@ -899,6 +903,10 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void gemm_bf16_ring_ker
   ld_a.init(TA ? p.A + m0 : p.A + (int64_t)m0 * p.lda, p.lda, min(p.M - m0, tile_m), wave, lane);
   ld_b.init(TB ? p.B + (int64_t)n0 * p.ldb : p.B + n0, p.ldb, p.N - n0, wave, lane);
   constexpr int IPA = decltype(ld_a)::IPW, NV = IPA + decltype(ld_b)::IPW;   // loads per wave and tile
+  // A tile of A whose loads do not divide evenly: the first waves issue one load (number IPA - 1) more than the others
+  constexpr bool kEven = decltype(ld_a)::kEven;
+  static_assert(decltype(ld_b)::kEven, "only A tiles come in uneven shares");
+  const bool extra = kEven || wave < decltype(ld_a)::kInstr % NW;   // wave-uniform
 
   constexpr int kStage = (BM + BN) * CHK;  // uint4 per stage
   f32x16 acc[MI][NI];
@@ -919,6 +927,7 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void gemm_bf16_ring_ker
   TileWalk walk;   // the tile the next loads fetch
   walk.init(ld_a.base_, ld_b.base_, ld_a.tile_step_bytes(), ld_b.tile_step_bytes(), p, nk_whole);
   auto issue = [&](int v, uint32_t stage_bytes) {
+    if (!kEven && v == IPA - 1 && !extra) return;
     if (v < IPA) ld_a.issue_one_untracked(v, walk.a_addr, stage_bytes);
     else ld_b.issue_one_untracked(v - IPA, walk.b_addr, stage_bytes + (uint32_t)(BM * CHK) * 16u);
   };
@@ -940,6 +949,7 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void gemm_bf16_ring_ker
       const uint64_t a_tail = walk.a_addr + (uint64_t)walk.a_step * (uint32_t)nk_whole, b_tail = walk.b_addr + (uint64_t)walk.b_step * (uint32_t)nk_whole;
 #pragma unroll
       for (int v = 0; v < NV; ++v) {
+        if (!kEven && v == IPA - 1 && !extra) continue;
         if (v < IPA) ld_a.issue_partial(v, a_tail, lds_base, rem, lane);
         else ld_b.issue_partial(v - IPA, b_tail, lds_base + (uint32_t)(BM * CHK) * 16u, rem, lane);
       }
@@ -949,7 +959,8 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void gemm_bf16_ring_ker
     for (int v = 0; v < NV; ++v) issue(v, lds_base + (uint32_t)(t * kStage) * 16u);
     walk.advance();
   }
-  __builtin_amdgcn_s_waitcnt(vmcnt_imm((NS - 2) * NV));
+  if (extra) __builtin_amdgcn_s_waitcnt(vmcnt_imm((NS - 2) * NV));
+  else __builtin_amdgcn_s_waitcnt(vmcnt_imm((NS - 2) * (NV - 1)));
   asm volatile("" : "+v"(touched));   // the touch has landed: last use of its register
   __syncthreads();
   if (rem > 0) {
@@ -970,13 +981,15 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void gemm_bf16_ring_ker
   static_assert((KS * NM) % NV == 0, "one load every (KS * NM / NV)-th MFMA");
   constexpr int EVERY = KS * NM / NV;
   constexpr int NV_PRE = ((KS - 1) * NM + EVERY - 1) / EVERY;   // loads issued before the barrier
+  static_assert(kEven || NV_PRE >= IPA, "the load that some waves leave out is one of those");
   static_assert((NS - 3) * NV + NV_PRE <= 63, "vmcnt range");
   if (!active) {
     // same loads, waits and barriers as below, no fragments and no MFMAs: the step's loads follow its
     // barrier, so at the wait the tiles kt+2 .. kt+NS-2 may be outstanding
     for (int kt = 0; kt < nk; ++kt) {
       const uint32_t l_stage = lds_base + (uint32_t)(((kt + NS - 1) & (NS - 1)) * kStage) * 16u;
-      __builtin_amdgcn_s_waitcnt(vmcnt_imm((NS - 3) * NV));
+      if (extra) __builtin_amdgcn_s_waitcnt(vmcnt_imm((NS - 3) * NV));
+      else __builtin_amdgcn_s_waitcnt(vmcnt_imm((NS - 3) * (NV - 1)));
       __syncthreads();
 #pragma unroll
       for (int v = 0; v < NV; ++v) issue(v, l_stage);
@@ -1005,7 +1018,8 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void gemm_bf16_ring_ker
         // tile kt+1 has landed once at most the loads issued after it are outstanding: all of
         // tiles kt+2 .. kt+NS-2 and what this step has issued of tile kt+NS-1 so far; the barrier
         // also tells that nobody reads stage kt any more (its last fragments are in registers)
-        __builtin_amdgcn_s_waitcnt(vmcnt_imm((NS - 3) * NV + NV_PRE) & ~(15 << 8));   // and lgkmcnt(0)
+        if (extra) __builtin_amdgcn_s_waitcnt(vmcnt_imm((NS - 3) * NV + NV_PRE) & ~(15 << 8));   // and lgkmcnt(0)
+        else __builtin_amdgcn_s_waitcnt(vmcnt_imm((NS - 3) * (NV - 1) + NV_PRE - 1) & ~(15 << 8));
         __syncthreads();
       }
 #pragma unroll
@@ -1369,7 +1383,7 @@ int choose_tile(const BfParams* p, int count, bool ta, bool tb) {
   int tile = g_tile_override;
   if (tile == 0) {
     // Measured on MI355X (M = 2048..8192): once 256x256 tiles give about 5/8 of the CUs a tile
-    // (160 tiles: N = 2560 at M = 4096) the 8-wave 256x256 ring kernel wins, by 15..30 % at 160..192 tiles and more
+    // (160 tiles: N = 2560 at M = 4096) the 8-wave ring kernels of that size win, by 15..30 % at 160..192 tiles and more
     // above.  Below that the tile with the least estimated time, in microseconds: rounds of tiles over the CUs times a
     // fixed part and a part per k of the reduction range, fitted to launches of 8 to 1024 tiles with K = 32 .. 4608:
     //   32x32, K split over 8 waves   3.0 + 1.25e-3 K per round
@@ -1381,10 +1395,16 @@ int choose_tile(const BfParams* p, int count, bool ta, bool tb) {
     // 3000 tokens 1536 -> 4608 (256x256: 46|86|69): 69|77|66, 62|66|61, 99|96|89, 251|164|241.
     // Among 128x128 tiles two register-staged workgroups per CU win where a launch of several rounds of short products lives
     // on its accumulator (300 tokens 2048 -> 4096, weight gradient: 18.5 against 24.7 us), the ring kernel elsewhere.
-    int64_t big = 0, t128 = 0, t64 = 0, t32 = 0;
+    // Where 192x256 tiles still fit into one round they spread the same work over a third more CUs: they are ahead of 256x256
+    // tiles, and of 128x128 ones from 132 tiles on, in the forms whose B is read along its rows (us, tile 256 | 192 | 128):
+    // 4096 x 2560 x 2560 60.5 | 55.4 | 66.6 (220 tiles); weight gradient 3072 x 3072 x 4096 92.5 | 76.4 | 107 (192); 2000 x 3000 x 3000
+    // 64.3 | 53.0 | 58.8 (132); 3000 x 2048 x 2048 41.8 | 35.8 | 34.8 (128).  With both operands contiguous along K they gain
+    // nothing (4096 x 2560 x 10240 198 | 206): that form is bound by its loads, of which a smaller tile needs more.
+    int64_t big = 0, t192 = 0, t128 = 0, t64 = 0, t32 = 0;
     int K = 0;
     for (int g = 0; g < count; ++g) {
       big += (int64_t)ceil_div(p[g].M, 256) * ceil_div(p[g].N, 256);
+      t192 += (int64_t)ceil_div(p[g].M, 192) * ceil_div(p[g].N, 256);
       t128 += (int64_t)ceil_div(p[g].M, 128) * ceil_div(p[g].N, 128);
       t64 += (int64_t)ceil_div(p[g].M, 64) * ceil_div(p[g].N, 64);
       t32 += (int64_t)ceil_div(p[g].M, 32) * ceil_div(p[g].N, 32);
@@ -1395,16 +1415,16 @@ int choose_tile(const BfParams* p, int count, bool ta, bool tb) {
     const double c32 = ceil_div(t32, cus) * (3.0 + 1.25e-3 * K + (accum ? 0.4 : 0.0));
     const double c64 = ceil_div(t64, cus) * (3.5 + 3.3e-3 * K + (accum ? 1.6 : 0.0));
     const double c128 = 3.0 + ceil_div(t128, cus) * (1.5 + (t128 * 2 <= cus ? 4.8e-3 : 7.5e-3) * K + (accum ? 6.5 : 0.0));
-    if (big >= 144) tile = 23;
+    if (!tb && t192 >= 132 && t192 <= cus && big < cus) tile = 24;
+    else if (big >= 144) tile = 23;
     else if (c32 < c64 && c32 < c128) tile = 32;
     else if (c64 < c128) tile = 64;
     else tile = accum && t128 > cus && K <= 1024 ? 2 : 22;
-    (void)tb;
   }
   bool segmented = false;
   for (int g = 0; g < count; ++g) segmented = segmented || p[g].seg_tiles > 1;
-  if (segmented && tile != 23) tile = 22;   // only the ring kernels walk a segmented reduction range
-  if (tile == 22 || tile == 23) {   // the ring kernels need a whole K tile (and nothing but whole ones in the pieces of a segmented range)
+  if (segmented && tile != 23 && tile != 24) tile = 22;   // only the ring kernels walk a segmented reduction range
+  if (tile >= 22 && tile <= 24) {   // the ring kernels need a whole K tile (and nothing but whole ones in the pieces of a segmented range)
     const int bk = tile == 22 ? 64 : 32;
     for (int g = 0; g < count; ++g) {
       const bool ok = p[g].seg_tiles > 1 ? (p[g].K / p[g].seg_tiles) % bk == 0 : p[g].K >= bk;
@@ -1423,6 +1443,7 @@ hipError_t pick_tile(const GroupParams& gp, hipStream_t s) {
     case 6: return launch<128, 128, 64, 64, 64, TA, TB, EPI, 2>(gp, s);   // two K groups of 4 waves
     case 22: return launch_ring<128, 128, 32, 64, 64, 4, TA, TB, EPI>(gp, s);   // 8 waves
     case 23: return launch_ring<256, 256, 128, 64, 32, 4, TA, TB, EPI>(gp, s);
+    case 24: return launch_ring<192, 256, 96, 64, 32, 4, TA, TB, EPI>(gp, s);
     case 32: return launch_split<1, 1, 8, TA, TB, EPI>(gp, s);
     case 64: return launch_split<2, 2, 4, TA, TB, EPI>(gp, s);
     default: return hipErrorInvalidValue;
@@ -1488,6 +1509,7 @@ void gemm_bf16_kernel_name(const GemmDesc* d, int count, char* out, size_t cap) 
     case 6: snprintf(out, cap, "gemm_bf16_kernel<128, 128, 64, 64, 64, %s, %s, %d, 2>", ta, tb, d[0].epilogue); break;
     case 22: snprintf(out, cap, "gemm_bf16_ring_kernel<128, 128, 32, 64, 64, 4, %s, %s, %d>", ta, tb, d[0].epilogue); break;
     case 23: snprintf(out, cap, "gemm_bf16_ring_kernel<256, 256, 128, 64, 32, 4, %s, %s, %d>", ta, tb, d[0].epilogue); break;
+    case 24: snprintf(out, cap, "gemm_bf16_ring_kernel<192, 256, 96, 64, 32, 4, %s, %s, %d>", ta, tb, d[0].epilogue); break;
     case 32: snprintf(out, cap, "gemm_bf16_split_kernel<1, 1, 8, %s, %s, %d>", ta, tb, d[0].epilogue); break;
     case 64: snprintf(out, cap, "gemm_bf16_split_kernel<2, 2, 4, %s, %s, %d>", ta, tb, d[0].epilogue); break;
     default: snprintf(out, cap, "gemm_bf16 tile %d <%s, %s, %d>", tile, ta, tb, d[0].epilogue); break;

@@ -69,7 +69,7 @@ def bf16_matrix(rng, rows, cols, ld, scale=1.0):
     return a.astype(np.float64), d
 
 
-@pytest.mark.parametrize("tile", [0, 22, 23, 32, 64])
+@pytest.mark.parametrize("tile", [0, 22, 23, 24, 32, 64])
 @pytest.mark.parametrize("M,N,K", [(8, 8, 8), (40, 72, 40), (264, 136, 72), (136, 264, 104), (96, 520, 200), (328, 272, 1016), (72, 64, 2056)])
 def test_bf16_partial_k_tiles(tile, M, N, K):
     rng = np.random.default_rng(M + N + K + tile)
@@ -108,7 +108,7 @@ def test_bf16_partial_k_tiles(tile, M, N, K):
         assert L.k2bw_tune_gemm_tile(0) == 0
 
 
-@pytest.mark.parametrize("tile", [0, 22, 23, 32, 64])
+@pytest.mark.parametrize("tile", [0, 22, 23, 24, 32, 64])
 @pytest.mark.parametrize("M,N,K", [(72, 40, 1), (136, 264, 33), (264, 136, 65), (256, 520, 127), (520, 264, 1000), (64, 64, 4099)])
 def test_bf16_weight_gradient_of_any_number_of_tokens(tile, M, N, K):
     rng = np.random.default_rng(M + N + K + tile)
