@@ -65,9 +65,8 @@ struct Cfg {
   static constexpr int CH = DH / 8;                // 16-byte chunks per tile row
   static constexpr int kTileU4 = kTile * CH;       // uint4 per tile
   static constexpr int kPadU4 = 4;                 // transposing reads of the padded head columns run past a row
-  // dK/dV kernel: V (K) fragments of the wave's keys in LDS, not registers
-  static constexpr bool kDkvParts = ANY && DH >= 112;   // dK and dV in workgroups of their own
-  static constexpr bool kDkvVInLds = (DH == 128 && !ANY) || (ANY && DH == 96), kDkvKInLds = ANY && DH == 96;
+  static constexpr bool kDkvParts = ANY && DH >= 80;   // dK and dV always in workgroups of their own
+  static constexpr bool kDkvVInLds = DH == 128 && !ANY;   // dK/dV kernel: V fragments of the wave's keys in LDS, not registers
 };
 
 // Chunk swizzle per head size (rows are 64 / 96 / 128 / 160 / 192 / 224 / 256 bytes; the LDS has 64 banks of 4 bytes).
@@ -614,8 +613,11 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_dq_mfma_kernel(const bf16_t* 
 
 // ------------------------------------------------------------------------------------------------
 // dK, dV
-// PART: 0 both results; 1 only dV, 2 only dK (the largest heads of the ANY set, where both accumulators, split operands and
-// fragments did not fit in the registers: a workgroup then makes one of the two, at the price of the scores twice)
+// PART: 0 both results; 1 only dV, 2 only dK: a workgroup makes one of the two, at the price of the scores twice.  For heads of
+// the ANY set from 72 on both accumulators, the split operands and the fragments do not fit in the registers (and a spill in the
+// loop waits for the next tile's loads: backward at b=3 s=1000 a=16 causal, head size 96 119 -> 100 us, 72 145 -> 91); and launches
+// that leave half of the CUs idle gain the second half's work (b=4 s=300 a=8 without mask: dh=128 39.4 -> 35.7,
+// 48 36.5 -> 31.2; b=1 s=1024 a=8 dh=128 causal 88 -> 76).
 template <int DH, int NW, bool ANY, bool EXACT, int PART>
 __device__ __forceinline__ bool attn_dkv(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ d_o, const float* __restrict__ lse, const float* __restrict__ delta, bf16_t* __restrict__ dqkv, int s, int a, int mask_mode, const int32_t* __restrict__ seqlens, float* __restrict__ colsum, int dh_) {
   using C = Cfg<DH>;
@@ -650,18 +652,11 @@ __device__ __forceinline__ bool attn_dkv(const bf16_t* __restrict__ qkv, const b
   // At head size 128 the two accumulators are 128 registers and the K and V fragments of the wave's keys 64 more: with
   // the scores on top the kernel spilled.  There the V fragments wait in a wave-private piece of LDS (16 bytes per
   // lane and k-step, read back in the order written: no bank conflicts, no barrier) and are fetched per use.
-  // (ANY: two fragments per probability operand and the path for hidden infinities raise the count; there from 80 on, K too
-  // where LDS has room.)
-  constexpr bool kVInLds = Cfg<DH, ANY>::kDkvVInLds, kKInLds = Cfg<DH, ANY>::kDkvKInLds;
+  constexpr bool kVInLds = Cfg<DH, ANY>::kDkvVInLds && DK;
   uint4* vstore = smem + 2 * kStageU4 + C::kPadU4 + wave * (C::KS * 64);
   if (kVInLds) {
 #pragma unroll
     for (int ks = 0; ks < C::KS; ++ks) vstore[ks * 64 + lane] = __builtin_bit_cast(uint4, vf[ks]);
-  }
-  uint4* kstore = smem + 2 * kStageU4 + C::kPadU4 + (NW + wave) * (C::KS * 64);
-  if (kKInLds) {
-#pragma unroll
-    for (int ks = 0; ks < C::KS; ++ks) kstore[ks * 64 + lane] = __builtin_bit_cast(uint4, kf[ks]);
   }
   f32x16 dk[C::DB], dv[C::DB];
 
@@ -710,8 +705,7 @@ __device__ __forceinline__ bool attn_dkv(const bf16_t* __restrict__ qkv, const b
       }
 #pragma unroll
       for (int ks = 0; ks < C::KS; ++ks) {
-        const bf16x8 kfr = kKInLds ? __builtin_bit_cast(bf16x8, kstore[ks * 64 + lane]) : kf[ks];
-        sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(read_rows<DH>(q_lds, qb * 32 + l32, ks, hf), kfr, sacc, 0, 0, 0);
+        sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(read_rows<DH>(q_lds, qb * 32 + l32, ks, hf), kf[ks], sacc, 0, 0, 0);
         const bf16x8 vfr = kVInLds ? __builtin_bit_cast(bf16x8, vstore[ks * 64 + lane]) : vf[ks];
         if (DK) dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(read_rows<DH>(do_lds, qb * 32 + l32, ks, hf), vfr, dp, 0, 0, 0);
       }
@@ -783,8 +777,8 @@ __device__ __forceinline__ bool attn_dkv(const bf16_t* __restrict__ qkv, const b
           const int kk = qb * 2 + half;
 #pragma unroll
           for (int db = 0; db < C::DB; ++db) {
-            dv[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(read_cols<DH>(do_lds, db * 32, kk, lane), pb, dv[db], 0, 0, 0);
-            dk[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(read_cols<DH>(q_lds, db * 32, kk, lane), dsb, dk[db], 0, 0, 0);
+            if (DV) dv[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(read_cols<DH>(do_lds, db * 32, kk, lane), pb, dv[db], 0, 0, 0);
+            if (DK) dk[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(read_cols<DH>(q_lds, db * 32, kk, lane), dsb, dk[db], 0, 0, 0);
           }
         }
       }
@@ -794,12 +788,16 @@ __device__ __forceinline__ bool attn_dkv(const bf16_t* __restrict__ qkv, const b
     if (__syncthreads_or(hidden)) return true;
   __syncthreads();   // every wave is done with the Q / dO tiles
   if (!ANY && colsum) {   // masked and non-existent keys hold zeros
-    float* row = colsum + ((int64_t)n * gridDim.z + blk) * ld + head * dh;
+    float* row = colsum + ((int64_t)n * (gridDim.z >> (PART ? 1 : 0)) + blk) * ld + head * dh;
     float* red = reinterpret_cast<float*>(smem);
-    block_column_sums<DH, NW>(dk, scale, red, row + h, tid, lane, wave);
-    __syncthreads();
-    block_column_sums<DH, NW>(dv, 1.0f, red, row + 2 * h, tid, lane, wave);
-    __syncthreads();
+    if (DK) {
+      block_column_sums<DH, NW>(dk, scale, red, row + h, tid, lane, wave);
+      __syncthreads();
+    }
+    if (DV) {
+      block_column_sums<DH, NW>(dv, 1.0f, red, row + 2 * h, tid, lane, wave);
+      __syncthreads();
+    }
   }
   bf16_t* outk = dqkv + ((int64_t)n * s + jw0) * ld + h + head * dh;
   uint4* strip = smem + wave * out_strip_u4<DH>();
@@ -807,14 +805,14 @@ __device__ __forceinline__ bool attn_dkv(const bf16_t* __restrict__ qkv, const b
   if (DV) store_rows<DH>(dv, 1.0f, strip, outk + h, ld, s - jw0, dh, lane);
   return false;
 }
-template <int DH, int NW, bool ANY>
+template <int DH, int NW, bool ANY, bool PARTS>
 __global__ __launch_bounds__(NW * 64, 2) void attn_dkv_mfma_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ d_o, const float* __restrict__ lse, const float* __restrict__ delta, bf16_t* __restrict__ dqkv, int s, int a, int mask_mode, const int32_t* __restrict__ seqlens, float* __restrict__ colsum, int dh_) {
   auto run = [&](auto part) __attribute__((always_inline)) {
     constexpr int PART = decltype(part)::value;
     if (attn_dkv<DH, NW, ANY, false, PART>(qkv, d_o, lse, delta, dqkv, s, a, mask_mode, seqlens, colsum, dh_))
       if constexpr (ANY) attn_dkv<DH, NW, ANY, true, PART>(qkv, d_o, lse, delta, dqkv, s, a, mask_mode, seqlens, colsum, dh_);
   };
-  if constexpr (!Cfg<DH, ANY>::kDkvParts) run(std::integral_constant<int, 0>{});
+  if constexpr (!PARTS) run(std::integral_constant<int, 0>{});
   else if (blockIdx.z & 1) run(std::integral_constant<int, 1>{});
   else run(std::integral_constant<int, 2>{});
 }
@@ -843,30 +841,44 @@ hipError_t fwd_launch(const AttnDesc& d, const void* qkv, void* o, float* lse, h
   return hipGetLastError();
 }
 
+template <int DH, int NW, bool ANY, bool PARTS>
+hipError_t dkv_launch(const AttnDesc& d, const void* qkv, const float* lse, const void* d_o, void* dqkv, const float* delta, hipStream_t st) {
+  using C = Cfg<DH>;
+  constexpr size_t lds_out = (size_t)NW * out_strip_u4<DH>() * sizeof(uint4);   // the output strips re-use the tiles' LDS
+  constexpr size_t lds_tiles = (2 * (2 * C::kTileU4 + 2 * kTile / 4) + C::kPadU4 + Cfg<DH, ANY>::kDkvVInLds * NW * C::KS * 64) * sizeof(uint4);
+  constexpr size_t lds = lds_tiles > lds_out ? lds_tiles : lds_out;
+  static_assert(lds <= 160 * 1024, "LDS of a CU");
+  static bool done = false;
+  hipError_t e = set_lds(attn_dkv_mfma_kernel<DH, NW, ANY, PARTS>, lds, &done);
+  if (e != hipSuccess) return e;
+  dim3 grid(d.a, d.b, ceil_div(d.s, NW * 32) * (PARTS ? 2 : 1));
+  hipLaunchKernelGGL((attn_dkv_mfma_kernel<DH, NW, ANY, PARTS>), grid, dim3(NW * 64), lds, st, static_cast<const bf16_t*>(qkv),
+                     static_cast<const bf16_t*>(d_o), lse, delta, static_cast<bf16_t*>(dqkv), d.s, d.a, d.mask_mode,
+                     d.seqlens, d.colsum_partial, d.dh);
+  return hipGetLastError();
+}
+
 template <int DH, int NW, bool ANY>
 hipError_t bwd_launch(const AttnDesc& d, const void* qkv, const void* o, const float* lse, const void* d_o, void* dqkv,
                       float* delta, hipStream_t st) {
   using C = Cfg<DH>;
-  constexpr size_t lds_out = (size_t)NW * out_strip_u4<DH>() * sizeof(uint4);   // the output strips re-use the tiles' LDS
+  constexpr size_t lds_out = (size_t)NW * out_strip_u4<DH>() * sizeof(uint4);
   constexpr size_t lds_dq_tiles = (4 * C::kTileU4 + C::kPadU4) * sizeof(uint4);
   constexpr size_t lds_dq = lds_dq_tiles > lds_out ? lds_dq_tiles : lds_out;
-  constexpr size_t lds_dkv_tiles = (2 * (2 * C::kTileU4 + 2 * kTile / 4) + C::kPadU4 + (Cfg<DH, ANY>::kDkvVInLds + Cfg<DH, ANY>::kDkvKInLds) * NW * C::KS * 64) * sizeof(uint4);
-  constexpr size_t lds_dkv = lds_dkv_tiles > lds_out ? lds_dkv_tiles : lds_out;
-  static_assert(lds_dkv <= 160 * 1024, "LDS of a CU");
-  static bool done_dq = false, done_dkv = false;
+  static bool done_dq = false;
   hipError_t e = set_lds(attn_dq_mfma_kernel<DH, NW, ANY>, lds_dq, &done_dq);
-  if (e != hipSuccess) return e;
-  e = set_lds(attn_dkv_mfma_kernel<DH, NW, ANY>, lds_dkv, &done_dkv);
   if (e != hipSuccess) return e;
   dim3 grid(d.a, d.b, ceil_div(d.s, NW * 32));
   hipLaunchKernelGGL((attn_dq_mfma_kernel<DH, NW, ANY>), grid, dim3(NW * 64), lds_dq, st, static_cast<const bf16_t*>(qkv),
                      static_cast<const bf16_t*>(o), static_cast<const bf16_t*>(d_o), lse, delta,
                      static_cast<bf16_t*>(dqkv), d.s, d.a, d.mask_mode, d.seqlens, d.colsum_partial, d.dh);
-  if (Cfg<DH, ANY>::kDkvParts) grid.z *= 2;
-  hipLaunchKernelGGL((attn_dkv_mfma_kernel<DH, NW, ANY>), grid, dim3(NW * 64), lds_dkv, st, static_cast<const bf16_t*>(qkv),
-                     static_cast<const bf16_t*>(d_o), lse, delta, static_cast<bf16_t*>(dqkv), d.s, d.a, d.mask_mode,
-                     d.seqlens, d.colsum_partial, d.dh);
-  return hipGetLastError();
+  e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  // few blocks: dK and dV in workgroups of their own (see attn_dkv)
+  constexpr bool kAlways = Cfg<DH, ANY>::kDkvParts;
+  const int64_t blocks = (int64_t)d.a * d.b * ceil_div(d.s, NW * 32);
+  if (kAlways || (NW == 4 && 2 * blocks <= gemm_compute_units())) return dkv_launch<DH, NW, ANY, kAlways || NW == 4>(d, qkv, lse, d_o, dqkv, delta, st);
+  return dkv_launch<DH, NW, ANY, kAlways>(d, qkv, lse, d_o, dqkv, delta, st);
 }
 
 }  // namespace
