@@ -7,7 +7,7 @@
 // a value enters the second product as the sum of two bf16 numbers, its rounding and the rounding of what that left,
 // two MFMAs instead of one; and a position that some rows of a tile may not see cannot reach them even if it holds
 // infinities or NaNs (accumulate_visible).  Measured at b=3 s=1000 a=16 dh=96 causal against one thread per row in fp32
-// on the vector ALU, which these sizes used to run on: forward 2892 -> 36 us, dQ with delta 2800 -> 46, dK/dV 13683 -> 81.
+// on the vector ALU, which these sizes used to run on: forward 2892 -> 29 us, backward 16480 -> 100.
 //
 // All three kernels keep one query (forward, dQ) or one key (dK/dV) per lane of a 32-wide MFMA
 // column, so softmax statistics, lse and delta are per-lane scalars or short in-lane loops:
@@ -51,9 +51,9 @@ typedef __attribute__((address_space(3))) char lds_char_t;
 typedef __attribute__((address_space(1))) const void glob_void_t;
 
 // Waves per workgroup (NW), 32 rows (queries or keys) each.  Measured on MI355X with 2 / 4 / 8 waves
-// (s = 512, dh = 64: forward 27.9 / 20.7 / 19.5 us, backward 66.7 / 58.8 / 57.1 us; s = 2048,
+// (one split, s = 512, dh = 64: forward 27.9 / 20.7 / 19.5 us, backward 66.7 / 58.8 / 57.1 us; s = 2048,
 // dh = 128 causal: forward 270 / 258 / 152 us): more waves share each K/V tile and each barrier.
-// That is with a workgroup for every CU; see waves_for for smaller launches.
+// That is with a workgroup for every CU; see shape_for for smaller launches.
 constexpr int kTile = 64;         // rows streamed through LDS per step
 constexpr float kLog2e = 1.4426950408889634f;
 
@@ -184,6 +184,27 @@ __device__ __forceinline__ f32x16 zero16() {
 #pragma unroll
   for (int r = 0; r < 16; ++r) z[r] = 0.f;
   return z;
+}
+
+// A wave's result blocks through LDS (64 lanes x 16*DB floats, a lane's own), from one half of a workgroup to the other
+template <int DB>
+__device__ __forceinline__ void give(const f32x16 (&acc)[DB], float* buf, int lane) {
+#pragma unroll
+  for (int db = 0; db < DB; ++db)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) buf[(db * 16 + r) * 64 + lane] = acc[db][r];
+}
+template <int DB>
+__device__ __forceinline__ void take(f32x16 (&acc)[DB], const float* buf, int lane) {
+#pragma unroll
+  for (int db = 0; db < DB; ++db)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[db][r] += buf[(db * 16 + r) * 64 + lane];
+}
+template <int DB>
+__device__ __forceinline__ void clear(f32x16 (&acc)[DB]) {
+#pragma unroll
+  for (int db = 0; db < DB; ++db) acc[db] = zero16();
 }
 
 __device__ __forceinline__ uint2 pack4f(float a, float b, float c, float d) {
@@ -326,25 +347,29 @@ __device__ __forceinline__ void store_rows(const f32x16 (&acc)[Cfg<DH>::DB], flo
 // (all kernels: two waves per SIMD, which 8-wave workgroups imply, cap a lane at 256 registers; the compiler then keeps
 // MFMA results in ordinary VGPRs.  With 512 available it parks them in the accumulator file and copies every score to a
 // VGPR and back around the softmax arithmetic, which costs more than the MFMAs.)
-template <int DH, int NW, bool ANY, bool EXACT>
+template <int DH, int NW, int KSPL, bool ANY, bool EXACT>
 __device__ __forceinline__ bool attn_fwd(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ o, float* __restrict__ lse, int s, int a, int mask_mode, const int32_t* __restrict__ seqlens, int dh_) {
   using C = Cfg<DH>;
   extern __shared__ uint4 smem[];   // stage st: K tile at st * 2 * kTileU4, V tile behind it
 
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l32 = lane & 31, hf = lane >> 5;
+  // wave = (part of the streamed rows, group of own rows): with KSPL = 2 each half of the waves takes every second tile,
+  // through tiles of its own in LDS, and the halves' results meet at the end
+  constexpr int RW = NW / KSPL;
+  const int kg = KSPL == 1 ? 0 : wave / RW, rw = KSPL == 1 ? wave : wave % RW;
   // grid = (heads, sequences, row blocks): the row block varies slowest, so all heads' copies of a block are
   // dispatched together, and under a causal mask the blocks with the most keys to visit (the last queries) go
   // first: the workgroups that take longest start earliest and the launch does not end on one of them
   const int n = blockIdx.y, head = blockIdx.x;
   const int blk = mask_mode == 1 ? (int)(gridDim.z - 1 - blockIdx.z) : (int)blockIdx.z;
-  const int i0 = blk * NW * 32;
+  const int i0 = blk * RW * 32;
   const int dh = ANY ? dh_ : DH;
   const int h = a * dh;
   const int64_t ld = 3 * (int64_t)h;
   const bf16_t* base = qkv + (int64_t)n * s * ld + head * dh;
   const int kv_len = mask_mode == 2 ? min(max(seqlens[n], 1), s) : s;   // lengths outside [1, s] are clamped: no read past the sequence, no empty row
   const bool causal = mask_mode == 1;
-  const int iw0 = i0 + wave * 32;
+  const int iw0 = i0 + rw * 32;
   const int i = iw0 + l32;
   const float scale = 1.0f / sqrtf((float)dh);
   const float c = scale * kLog2e;
@@ -355,25 +380,29 @@ __device__ __forceinline__ bool attn_fwd(const bf16_t* __restrict__ qkv, bf16_t*
   float m_i = -INFINITY, l_i = 0.f;
   bool hidden = false;   // ANY: a tile that not every row sees holds infinities or NaNs
 
-  const int jend = causal ? min(i0 + NW * 32, s) : kv_len;
+  const int jend = causal ? min(i0 + RW * 32, s) : kv_len;
   const int ntiles = (jend + kTile - 1) / kTile;
-  TileLoader<DH, ANY, NW> loader;
-  loader.init(wave, lane, dh);
+  TileLoader<DH, ANY, RW> loader;
+  loader.init(rw, lane, dh);
 #pragma unroll
   for (int db = 0; db < C::DB; ++db) oacc[db] = zero16();
-  loader.issue(base + h, ld, 0, jend, smem);
-  loader.issue(base + 2 * h, ld, 0, jend, smem + C::kTileU4);
-  for (int t = 0; t < ntiles; ++t) {
-    const int j0 = t * kTile;
+  uint4* const tiles = smem + kg * (4 * C::kTileU4 + C::kPadU4);
+  if (kg < ntiles) {
+    loader.issue(base + h, ld, kg * kTile, jend, tiles);
+    loader.issue(base + 2 * h, ld, kg * kTile, jend, tiles + C::kTileU4);
+  }
+  for (int st = 0; st * KSPL < ntiles; ++st) {
+    const int t = st * KSPL + kg, j0 = t * kTile;
     __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));   // this wave's share of tile t has landed
-    __syncthreads();                            // ... and everyone's; all waves are done with tile t-1
-    if (t + 1 < ntiles) {
-      uint4* nxt = smem + ((t + 1) & 1) * 2 * C::kTileU4;
-      loader.issue(base + h, ld, j0 + kTile, jend, nxt);
-      loader.issue(base + 2 * h, ld, j0 + kTile, jend, nxt + C::kTileU4);
+    __syncthreads();                            // ... and everyone's; all waves are done with the tile before
+    if (t + KSPL < ntiles) {
+      uint4* nxt = tiles + ((st + 1) & 1) * 2 * C::kTileU4;
+      loader.issue(base + h, ld, j0 + KSPL * kTile, jend, nxt);
+      loader.issue(base + 2 * h, ld, j0 + KSPL * kTile, jend, nxt + C::kTileU4);
     }
+    if (KSPL > 1 && t >= ntiles) continue;   // (the last step of an odd number of tiles)
     if (causal && j0 > iw0 + 31) continue;   // every key of the tile lies after this wave's queries
-    const uint4* k_lds = smem + (t & 1) * 2 * C::kTileU4;
+    const uint4* k_lds = tiles + (st & 1) * 2 * C::kTileU4;
     const uint4* v_lds = k_lds + C::kTileU4;
 
     f32x16 sacc[2] = {zero16(), zero16()};
@@ -453,51 +482,79 @@ __device__ __forceinline__ bool attn_fwd(const bf16_t* __restrict__ qkv, bf16_t*
   if constexpr (ANY && !EXACT)
     if (__syncthreads_or(hidden)) return true;
 
+  __syncthreads();   // every wave is done with the K / V tiles, whose LDS is used again below
+  if constexpr (KSPL == 2) {
+    float* buf = reinterpret_cast<float*>(smem) + rw * ((C::DB * 16 + 2) * 64);
+    if (kg == 1) {
+      give<C::DB>(oacc, buf, lane);
+      buf[C::DB * 16 * 64 + lane] = m_i;
+      buf[(C::DB * 16 + 1) * 64 + lane] = l_i;
+    }
+    __syncthreads();
+    if (kg == 0) {   // both halves to the larger of the two maxima (a half without a visible key adds nothing)
+      const float m1 = buf[C::DB * 16 * 64 + lane], l1 = buf[(C::DB * 16 + 1) * 64 + lane];
+      const float m = fmaxf(m_i, m1);
+      const float f0 = m_i == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m_i - m) * c), f1 = m1 == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m1 - m) * c);
+      l_i = l_i * f0 + l1 * f1;
+      m_i = m;
+#pragma unroll
+      for (int db = 0; db < C::DB; ++db)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) oacc[db][r] = oacc[db][r] * f0 + buf[(db * 16 + r) * 64 + lane] * f1;
+    }
+    __syncthreads();
+  }
   const float l_tot = l_i + __shfl_xor(l_i, 32, 64);
-  __syncthreads();   // every wave is done with the K / V tiles, whose LDS the output strips re-use
   const float inv = 1.0f / l_tot;   // (rows past the sequence: never stored)
-  store_rows<DH>(oacc, inv, smem + wave * out_strip_u4<DH>(), o + ((int64_t)n * s + iw0) * h + head * dh, h, s - iw0, dh, lane);
-  if (i < s && hf == 0) lse[((int64_t)n * a + head) * s + i] = m_i * scale + logf(l_tot);
+  store_rows<DH>(oacc, inv, smem + wave * out_strip_u4<DH>(), o + ((int64_t)n * s + iw0) * h + head * dh, h, kg == 0 ? s - iw0 : 0, dh, lane);
+  if (i < s && hf == 0 && kg == 0) lse[((int64_t)n * a + head) * s + i] = m_i * scale + logf(l_tot);
   return false;
 }
-template <int DH, int NW, bool ANY>
+template <int DH, int NW, int KSPL, bool ANY>
 __global__ __launch_bounds__(NW * 64, 2) void attn_fwd_mfma_kernel(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ o, float* __restrict__ lse, int s, int a, int mask_mode, const int32_t* __restrict__ seqlens, int dh_) {
-  if (attn_fwd<DH, NW, ANY, false>(qkv, o, lse, s, a, mask_mode, seqlens, dh_))
-    if constexpr (ANY) attn_fwd<DH, NW, ANY, true>(qkv, o, lse, s, a, mask_mode, seqlens, dh_);
+  if (attn_fwd<DH, NW, KSPL, ANY, false>(qkv, o, lse, s, a, mask_mode, seqlens, dh_))
+    if constexpr (ANY) attn_fwd<DH, NW, KSPL, ANY, true>(qkv, o, lse, s, a, mask_mode, seqlens, dh_);
 }
 
 // ------------------------------------------------------------------------------------------------
 // dQ (and delta = rowsum(dO * O), which the dK/dV kernel reads afterwards)
-template <int DH, int NW, bool ANY, bool EXACT>
+template <int DH, int NW, int KSPL, bool ANY, bool EXACT>
 __device__ __forceinline__ bool attn_dq(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ o, const bf16_t* __restrict__ d_o, const float* __restrict__ lse, float* __restrict__ delta, bf16_t* __restrict__ dqkv, int s, int a, int mask_mode, const int32_t* __restrict__ seqlens, float* __restrict__ colsum, int dh_) {
   using C = Cfg<DH>;
   extern __shared__ uint4 smem[];   // stage st: K tile at st * 2 * kTileU4, V tile behind it
 
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l32 = lane & 31, hf = lane >> 5;
+  // wave = (part of the streamed rows, group of own rows): with KSPL = 2 each half of the waves takes every second tile,
+  // through tiles of its own in LDS, and the halves' results meet at the end
+  constexpr int RW = NW / KSPL;
+  const int kg = KSPL == 1 ? 0 : wave / RW, rw = KSPL == 1 ? wave : wave % RW;
   // grid = (heads, sequences, row blocks): the row block varies slowest, so all heads' copies of a block are
   // dispatched together, and under a causal mask the blocks with the most keys to visit (the last queries) go
   // first: the workgroups that take longest start earliest and the launch does not end on one of them
   const int n = blockIdx.y, head = blockIdx.x;
   const int blk = mask_mode == 1 ? (int)(gridDim.z - 1 - blockIdx.z) : (int)blockIdx.z;
-  const int i0 = blk * NW * 32;
+  const int i0 = blk * RW * 32;
   const int dh = ANY ? dh_ : DH;
   const int h = a * dh;
   const int64_t ld = 3 * (int64_t)h;
   const bf16_t* base = qkv + (int64_t)n * s * ld + head * dh;
   const int kv_len = mask_mode == 2 ? min(max(seqlens[n], 1), s) : s;   // lengths outside [1, s] are clamped: no read past the sequence, no empty row
   const bool causal = mask_mode == 1;
-  const int iw0 = i0 + wave * 32;
+  const int iw0 = i0 + rw * 32;
   const int i = iw0 + l32;
   const bool row_ok = i < s;
   const float scale = 1.0f / sqrtf((float)dh);
   const float c = scale * kLog2e;
 
-  const int jend = causal ? min(i0 + NW * 32, s) : kv_len;
+  const int jend = causal ? min(i0 + RW * 32, s) : kv_len;
   const int ntiles = (jend + kTile - 1) / kTile;
-  TileLoader<DH, ANY, NW> loader;
-  loader.init(wave, lane, dh);
-  loader.issue(base + h, ld, 0, jend, smem);
-  loader.issue(base + 2 * h, ld, 0, jend, smem + C::kTileU4);
+  TileLoader<DH, ANY, RW> loader;
+  loader.init(rw, lane, dh);
+  uint4* const tiles = smem + kg * (4 * C::kTileU4 + C::kPadU4);
+  if (kg < ntiles) {
+    loader.issue(base + h, ld, kg * kTile, jend, tiles);
+    loader.issue(base + 2 * h, ld, kg * kTile, jend, tiles + C::kTileU4);
+  }
 
   bf16x8 qf[C::KS], dof[C::KS];
   load_frags<DH, ANY>(base + (int64_t)i * ld, row_ok, hf, dh, qf);
@@ -512,7 +569,7 @@ __device__ __forceinline__ bool attn_dq(const bf16_t* __restrict__ qkv, const bf
 #pragma unroll
       for (int e = 0; e < 8; ++e) part = fmaf((float)dof[ks][e], (float)of[ks][e], part);
     delta_i = part + __shfl_xor(part, 32, 64);
-    if (row_ok && hf == 0) delta[((int64_t)n * a + head) * s + i] = delta_i;
+    if (row_ok && hf == 0 && kg == 0) delta[((int64_t)n * a + head) * s + i] = delta_i;
   }
   const float lse_i = row_ok ? lse[((int64_t)n * a + head) * s + i] * kLog2e : INFINITY;
   f32x16 minus_delta;
@@ -522,17 +579,18 @@ __device__ __forceinline__ bool attn_dq(const bf16_t* __restrict__ qkv, const bf
   bool hidden = false;
 #pragma unroll
   for (int db = 0; db < C::DB; ++db) dq[db] = zero16();
-  for (int t = 0; t < ntiles; ++t) {
-    const int j0 = t * kTile;
+  for (int st = 0; st * KSPL < ntiles; ++st) {
+    const int t = st * KSPL + kg, j0 = t * kTile;
     __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
     __syncthreads();
-    if (t + 1 < ntiles) {
-      uint4* nxt = smem + ((t + 1) & 1) * 2 * C::kTileU4;
-      loader.issue(base + h, ld, j0 + kTile, jend, nxt);
-      loader.issue(base + 2 * h, ld, j0 + kTile, jend, nxt + C::kTileU4);
+    if (t + KSPL < ntiles) {
+      uint4* nxt = tiles + ((st + 1) & 1) * 2 * C::kTileU4;
+      loader.issue(base + h, ld, j0 + KSPL * kTile, jend, nxt);
+      loader.issue(base + 2 * h, ld, j0 + KSPL * kTile, jend, nxt + C::kTileU4);
     }
+    if (KSPL > 1 && t >= ntiles) continue;   // (the last step of an odd number of tiles)
     if (causal && j0 > iw0 + 31) continue;
-    const uint4* k_lds = smem + (t & 1) * 2 * C::kTileU4;
+    const uint4* k_lds = tiles + (st & 1) * 2 * C::kTileU4;
     const uint4* v_lds = k_lds + C::kTileU4;
 
     f32x16 sacc[2] = {zero16(), zero16()}, dp[2] = {minus_delta, minus_delta};   // dP - delta comes out of the product
@@ -597,18 +655,25 @@ __device__ __forceinline__ bool attn_dq(const bf16_t* __restrict__ qkv, const bf
   if constexpr (ANY && !EXACT)
     if (__syncthreads_or(hidden)) return true;
   __syncthreads();   // every wave is done with the K / V tiles
+  if constexpr (KSPL == 2) {
+    float* buf = reinterpret_cast<float*>(smem) + rw * (C::DB * 16 * 64);
+    if (kg == 1) { give<C::DB>(dq, buf, lane); clear<C::DB>(dq); }
+    __syncthreads();
+    if (kg == 0) take<C::DB>(dq, buf, lane);
+    __syncthreads();
+  }
   if (!ANY && colsum) {   // rows past the end of the sequence hold zeros
     float* row = colsum + ((int64_t)n * gridDim.z + blk) * ld + head * dh;
     block_column_sums<DH, NW>(dq, scale, reinterpret_cast<float*>(smem), row, tid, lane, wave);
     __syncthreads();   // ... and with the partial rows of the sums
   }
-  store_rows<DH>(dq, scale, smem + wave * out_strip_u4<DH>(), dqkv + ((int64_t)n * s + iw0) * ld + head * dh, ld, s - iw0, dh, lane);
+  store_rows<DH>(dq, scale, smem + wave * out_strip_u4<DH>(), dqkv + ((int64_t)n * s + iw0) * ld + head * dh, ld, kg == 0 ? s - iw0 : 0, dh, lane);
   return false;
 }
-template <int DH, int NW, bool ANY>
+template <int DH, int NW, int KSPL, bool ANY>
 __global__ __launch_bounds__(NW * 64, 2) void attn_dq_mfma_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ o, const bf16_t* __restrict__ d_o, const float* __restrict__ lse, float* __restrict__ delta, bf16_t* __restrict__ dqkv, int s, int a, int mask_mode, const int32_t* __restrict__ seqlens, float* __restrict__ colsum, int dh_) {
-  if (attn_dq<DH, NW, ANY, false>(qkv, o, d_o, lse, delta, dqkv, s, a, mask_mode, seqlens, colsum, dh_))
-    if constexpr (ANY) attn_dq<DH, NW, ANY, true>(qkv, o, d_o, lse, delta, dqkv, s, a, mask_mode, seqlens, colsum, dh_);
+  if (attn_dq<DH, NW, KSPL, ANY, false>(qkv, o, d_o, lse, delta, dqkv, s, a, mask_mode, seqlens, colsum, dh_))
+    if constexpr (ANY) attn_dq<DH, NW, KSPL, ANY, true>(qkv, o, d_o, lse, delta, dqkv, s, a, mask_mode, seqlens, colsum, dh_);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -616,9 +681,9 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_dq_mfma_kernel(const bf16_t* 
 // PART: 0 both results; 1 only dV, 2 only dK: a workgroup makes one of the two, at the price of the scores twice.  For heads of
 // the ANY set from 72 on both accumulators, the split operands and the fragments do not fit in the registers (and a spill in the
 // loop waits for the next tile's loads: backward at b=3 s=1000 a=16 causal, head size 96 119 -> 100 us, 72 145 -> 91); and launches
-// that leave half of the CUs idle gain the second half's work (b=4 s=300 a=8 without mask: dh=128 39.4 -> 35.7,
-// 48 36.5 -> 31.2; b=1 s=1024 a=8 dh=128 causal 88 -> 76).
-template <int DH, int NW, bool ANY, bool EXACT, int PART>
+// that leave half of the CUs idle gain the second half's work (backward, 64-row blocks: b=1 s=1024 a=8 dh=64 30.2 -> 28.2 us,
+// b=1 s=2048 a=4 causal 51.3 -> 47.4).
+template <int DH, int NW, int KSPL, bool ANY, bool EXACT, int PART>
 __device__ __forceinline__ bool attn_dkv(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ d_o, const float* __restrict__ lse, const float* __restrict__ delta, bf16_t* __restrict__ dqkv, int s, int a, int mask_mode, const int32_t* __restrict__ seqlens, float* __restrict__ colsum, int dh_) {
   using C = Cfg<DH>;
   extern __shared__ uint4 smem[];
@@ -628,9 +693,12 @@ __device__ __forceinline__ bool attn_dkv(const bf16_t* __restrict__ qkv, const b
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l32 = lane & 31, hf = lane >> 5;
   // grid = (heads, sequences, key blocks), key block slowest: under a causal mask the first keys are seen by
   // the most queries, and those workgroups are dispatched first (see the forward kernel)
+  // (halves of the waves: see the forward kernel)
+  constexpr int RW = NW / KSPL;
+  const int kg = KSPL == 1 ? 0 : wave / RW, rw = KSPL == 1 ? wave : wave % RW;
   const int n = blockIdx.y, head = blockIdx.x, blk = PART ? (int)blockIdx.z >> 1 : (int)blockIdx.z;
   constexpr bool DV = PART != 2, DK = PART != 1;
-  const int j0 = blk * NW * 32;
+  const int j0 = blk * RW * 32;
   const int dh = ANY ? dh_ : DH;
   const int h = a * dh;
   const int64_t ld = 3 * (int64_t)h;
@@ -640,7 +708,7 @@ __device__ __forceinline__ bool attn_dkv(const bf16_t* __restrict__ qkv, const b
   const float* delta_row = delta + ((int64_t)n * a + head) * s;
   const int kv_len = mask_mode == 2 ? min(max(seqlens[n], 1), s) : s;   // lengths outside [1, s] are clamped: no read past the sequence, no empty row
   const bool causal = mask_mode == 1;
-  const int jw0 = j0 + wave * 32;
+  const int jw0 = j0 + rw * 32;
   const int j = jw0 + l32;
   const bool row_ok = j < s;
   const float scale = 1.0f / sqrtf((float)dh);
@@ -652,7 +720,7 @@ __device__ __forceinline__ bool attn_dkv(const bf16_t* __restrict__ qkv, const b
   // At head size 128 the two accumulators are 128 registers and the K and V fragments of the wave's keys 64 more: with
   // the scores on top the kernel spilled.  There the V fragments wait in a wave-private piece of LDS (16 bytes per
   // lane and k-step, read back in the order written: no bank conflicts, no barrier) and are fetched per use.
-  constexpr bool kVInLds = Cfg<DH, ANY>::kDkvVInLds && DK;
+  constexpr bool kVInLds = Cfg<DH, ANY>::kDkvVInLds && PART == 0;
   uint4* vstore = smem + 2 * kStageU4 + C::kPadU4 + wave * (C::KS * 64);
   if (kVInLds) {
 #pragma unroll
@@ -663,8 +731,8 @@ __device__ __forceinline__ bool attn_dkv(const bf16_t* __restrict__ qkv, const b
   const bool wg_dead = j0 >= kv_len;                       // every key of the workgroup is padding
   const int istart = causal ? (j0 / kTile) * kTile : 0;    // earlier queries see none of these keys
   const int ntiles = wg_dead ? 0 : (s - istart + kTile - 1) / kTile;
-  TileLoader<DH, ANY, NW> loader;
-  loader.init(wave, lane, dh);
+  TileLoader<DH, ANY, RW> loader;
+  loader.init(rw, lane, dh);
   auto issue_tile = [&](int i0, uint4* stage) {
     loader.issue(base, ld, i0, s, stage);
     loader.issue(dobase, (int64_t)h, i0, s, stage + C::kTileU4);
@@ -673,22 +741,24 @@ __device__ __forceinline__ bool attn_dkv(const bf16_t* __restrict__ qkv, const b
   // loop uses: -lse * log2(e), and -delta, the starting value of the accumulators of dP
   float stat = 0.f;
   auto load_stat = [&](int i0) {
-    if (wave < 2) stat = (wave == 0 ? lse_row : delta_row)[min(i0 + lane, s - 1)];
+    if (rw < 2) stat = (rw == 0 ? lse_row : delta_row)[min(i0 + lane, s - 1)];
   };
   bool hidden = false;
 #pragma unroll
   for (int db = 0; db < C::DB; ++db) { dk[db] = zero16(); dv[db] = zero16(); }
-  if (ntiles > 0) { load_stat(istart); issue_tile(istart, smem); }
-  for (int t = 0; t < ntiles; ++t) {
-    const int i0 = istart + t * kTile;
+  uint4* const tiles = smem + kg * (2 * kStageU4 + C::kPadU4);
+  if (kg < ntiles) { load_stat(istart + kg * kTile); issue_tile(istart + kg * kTile, tiles); }
+  for (int st = 0; st * KSPL < ntiles; ++st) {
+    const int t = st * KSPL + kg, i0 = istart + t * kTile;
     __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
-    if (wave < 2) {
-      float* f = reinterpret_cast<float*>(smem + (t & 1) * kStageU4 + 2 * C::kTileU4);
-      f[wave * kTile + lane] = wave == 0 ? -kLog2e * stat : -stat;   // (the stage's readers were done before the last barrier)
+    if (rw < 2) {
+      float* f = reinterpret_cast<float*>(tiles + (st & 1) * kStageU4 + 2 * C::kTileU4);
+      f[rw * kTile + lane] = rw == 0 ? -kLog2e * stat : -stat;   // (the stage's readers were done before the last barrier)
     }
     __syncthreads();
-    if (t + 1 < ntiles) { load_stat(i0 + kTile); issue_tile(i0 + kTile, smem + ((t + 1) & 1) * kStageU4); }
-    const uint4* q_lds = smem + (t & 1) * kStageU4;
+    if (t + KSPL < ntiles) { load_stat(i0 + KSPL * kTile); issue_tile(i0 + KSPL * kTile, tiles + ((st + 1) & 1) * kStageU4); }
+    if (KSPL > 1 && t >= ntiles) continue;
+    const uint4* q_lds = tiles + (st & 1) * kStageU4;
     const uint4* do_lds = q_lds + C::kTileU4;
     const float* lse_lds = reinterpret_cast<const float*>(q_lds + 2 * C::kTileU4);
     const float* delta_lds = lse_lds + kTile;
@@ -787,6 +857,21 @@ __device__ __forceinline__ bool attn_dkv(const bf16_t* __restrict__ qkv, const b
   if constexpr (ANY && !EXACT)
     if (__syncthreads_or(hidden)) return true;
   __syncthreads();   // every wave is done with the Q / dO tiles
+  if constexpr (KSPL == 2) {
+    constexpr int kSlots = (DK + DV) * C::DB * 16;
+    float* buf = reinterpret_cast<float*>(smem) + rw * (kSlots * 64);
+    float* buf_v = buf + (DK ? C::DB * 16 * 64 : 0);
+    if (kg == 1) {
+      if (DK) { give<C::DB>(dk, buf, lane); clear<C::DB>(dk); }
+      if (DV) { give<C::DB>(dv, buf_v, lane); clear<C::DB>(dv); }
+    }
+    __syncthreads();
+    if (kg == 0) {
+      if (DK) take<C::DB>(dk, buf, lane);
+      if (DV) take<C::DB>(dv, buf_v, lane);
+    }
+    __syncthreads();
+  }
   if (!ANY && colsum) {   // masked and non-existent keys hold zeros
     float* row = colsum + ((int64_t)n * (gridDim.z >> (PART ? 1 : 0)) + blk) * ld + head * dh;
     float* red = reinterpret_cast<float*>(smem);
@@ -801,16 +886,16 @@ __device__ __forceinline__ bool attn_dkv(const bf16_t* __restrict__ qkv, const b
   }
   bf16_t* outk = dqkv + ((int64_t)n * s + jw0) * ld + h + head * dh;
   uint4* strip = smem + wave * out_strip_u4<DH>();
-  if (DK) store_rows<DH>(dk, scale, strip, outk, ld, s - jw0, dh, lane);
-  if (DV) store_rows<DH>(dv, 1.0f, strip, outk + h, ld, s - jw0, dh, lane);
+  if (DK) store_rows<DH>(dk, scale, strip, outk, ld, kg == 0 ? s - jw0 : 0, dh, lane);
+  if (DV) store_rows<DH>(dv, 1.0f, strip, outk + h, ld, kg == 0 ? s - jw0 : 0, dh, lane);
   return false;
 }
-template <int DH, int NW, bool ANY, bool PARTS>
+template <int DH, int NW, int KSPL, bool ANY, bool PARTS>
 __global__ __launch_bounds__(NW * 64, 2) void attn_dkv_mfma_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ d_o, const float* __restrict__ lse, const float* __restrict__ delta, bf16_t* __restrict__ dqkv, int s, int a, int mask_mode, const int32_t* __restrict__ seqlens, float* __restrict__ colsum, int dh_) {
   auto run = [&](auto part) __attribute__((always_inline)) {
     constexpr int PART = decltype(part)::value;
-    if (attn_dkv<DH, NW, ANY, false, PART>(qkv, d_o, lse, delta, dqkv, s, a, mask_mode, seqlens, colsum, dh_))
-      if constexpr (ANY) attn_dkv<DH, NW, ANY, true, PART>(qkv, d_o, lse, delta, dqkv, s, a, mask_mode, seqlens, colsum, dh_);
+    if (attn_dkv<DH, NW, KSPL, ANY, false, PART>(qkv, d_o, lse, delta, dqkv, s, a, mask_mode, seqlens, colsum, dh_))
+      if constexpr (ANY) attn_dkv<DH, NW, KSPL, ANY, true, PART>(qkv, d_o, lse, delta, dqkv, s, a, mask_mode, seqlens, colsum, dh_);
   };
   if constexpr (!PARTS) run(std::integral_constant<int, 0>{});
   else if (blockIdx.z & 1) run(std::integral_constant<int, 1>{});
@@ -826,122 +911,149 @@ hipError_t set_lds(K kern, size_t bytes, bool* done) {
   return e;
 }
 
-template <int DH, int NW, bool ANY>
+constexpr size_t max_of(size_t a, size_t b) { return a > b ? a : b; }
+
+template <int DH, int NW, int KSPL, bool ANY>
 hipError_t fwd_launch(const AttnDesc& d, const void* qkv, void* o, float* lse, hipStream_t st) {
   using C = Cfg<DH>;
   constexpr size_t lds_out = (size_t)NW * out_strip_u4<DH>() * sizeof(uint4);   // the output strips re-use the tiles' LDS
-  constexpr size_t lds_tiles = (4 * C::kTileU4 + C::kPadU4) * sizeof(uint4);
-  constexpr size_t lds = lds_tiles > lds_out ? lds_tiles : lds_out;
+  constexpr size_t lds_merge = KSPL == 1 ? 0 : NW / KSPL * (C::DB * 16 + 2) * 64 * sizeof(float);   // ... and so do the halves' results
+  constexpr size_t lds = max_of(max_of(KSPL * (4 * C::kTileU4 + C::kPadU4) * sizeof(uint4), lds_out), lds_merge);
+  static_assert(lds <= 160 * 1024, "LDS of a CU");
   static bool done = false;
-  hipError_t e = set_lds(attn_fwd_mfma_kernel<DH, NW, ANY>, lds, &done);
+  hipError_t e = set_lds(attn_fwd_mfma_kernel<DH, NW, KSPL, ANY>, lds, &done);
   if (e != hipSuccess) return e;
-  dim3 grid(d.a, d.b, ceil_div(d.s, NW * 32));
-  hipLaunchKernelGGL((attn_fwd_mfma_kernel<DH, NW, ANY>), grid, dim3(NW * 64), lds, st, static_cast<const bf16_t*>(qkv),
+  dim3 grid(d.a, d.b, ceil_div(d.s, NW / KSPL * 32));
+  hipLaunchKernelGGL((attn_fwd_mfma_kernel<DH, NW, KSPL, ANY>), grid, dim3(NW * 64), lds, st, static_cast<const bf16_t*>(qkv),
                      static_cast<bf16_t*>(o), lse, d.s, d.a, d.mask_mode, d.seqlens, d.dh);
   return hipGetLastError();
 }
 
-template <int DH, int NW, bool ANY, bool PARTS>
+template <int DH, int NW, int KSPL, bool ANY, bool PARTS>
 hipError_t dkv_launch(const AttnDesc& d, const void* qkv, const float* lse, const void* d_o, void* dqkv, const float* delta, hipStream_t st) {
   using C = Cfg<DH>;
-  constexpr size_t lds_out = (size_t)NW * out_strip_u4<DH>() * sizeof(uint4);   // the output strips re-use the tiles' LDS
-  constexpr size_t lds_tiles = (2 * (2 * C::kTileU4 + 2 * kTile / 4) + C::kPadU4 + Cfg<DH, ANY>::kDkvVInLds * NW * C::KS * 64) * sizeof(uint4);
-  constexpr size_t lds = lds_tiles > lds_out ? lds_tiles : lds_out;
+  constexpr size_t lds_out = (size_t)NW * out_strip_u4<DH>() * sizeof(uint4);
+  constexpr size_t lds_merge = KSPL == 1 ? 0 : NW / KSPL * (PARTS ? 1 : 2) * C::DB * 16 * 64 * sizeof(float);
+  constexpr size_t lds_tiles = (KSPL * (2 * (2 * C::kTileU4 + 2 * kTile / 4) + C::kPadU4) +
+                                (!PARTS && Cfg<DH, ANY>::kDkvVInLds ? NW * C::KS * 64 : 0)) * sizeof(uint4);
+  constexpr size_t lds = max_of(max_of(lds_tiles, lds_out), lds_merge);
   static_assert(lds <= 160 * 1024, "LDS of a CU");
   static bool done = false;
-  hipError_t e = set_lds(attn_dkv_mfma_kernel<DH, NW, ANY, PARTS>, lds, &done);
+  hipError_t e = set_lds(attn_dkv_mfma_kernel<DH, NW, KSPL, ANY, PARTS>, lds, &done);
   if (e != hipSuccess) return e;
-  dim3 grid(d.a, d.b, ceil_div(d.s, NW * 32) * (PARTS ? 2 : 1));
-  hipLaunchKernelGGL((attn_dkv_mfma_kernel<DH, NW, ANY, PARTS>), grid, dim3(NW * 64), lds, st, static_cast<const bf16_t*>(qkv),
+  dim3 grid(d.a, d.b, ceil_div(d.s, NW / KSPL * 32) * (PARTS ? 2 : 1));
+  hipLaunchKernelGGL((attn_dkv_mfma_kernel<DH, NW, KSPL, ANY, PARTS>), grid, dim3(NW * 64), lds, st, static_cast<const bf16_t*>(qkv),
                      static_cast<const bf16_t*>(d_o), lse, delta, static_cast<bf16_t*>(dqkv), d.s, d.a, d.mask_mode,
                      d.seqlens, d.colsum_partial, d.dh);
   return hipGetLastError();
 }
 
-template <int DH, int NW, bool ANY>
+template <int DH, int NW, int KSPL, bool ANY>
 hipError_t bwd_launch(const AttnDesc& d, const void* qkv, const void* o, const float* lse, const void* d_o, void* dqkv,
                       float* delta, hipStream_t st) {
   using C = Cfg<DH>;
   constexpr size_t lds_out = (size_t)NW * out_strip_u4<DH>() * sizeof(uint4);
-  constexpr size_t lds_dq_tiles = (4 * C::kTileU4 + C::kPadU4) * sizeof(uint4);
-  constexpr size_t lds_dq = lds_dq_tiles > lds_out ? lds_dq_tiles : lds_out;
-  static bool done_dq = false;
-  hipError_t e = set_lds(attn_dq_mfma_kernel<DH, NW, ANY>, lds_dq, &done_dq);
+  constexpr size_t lds_merge = KSPL == 1 ? 0 : NW / KSPL * C::DB * 16 * 64 * sizeof(float);
+  constexpr size_t lds = max_of(max_of(KSPL * (4 * C::kTileU4 + C::kPadU4) * sizeof(uint4), lds_out), lds_merge);
+  static_assert(lds <= 160 * 1024, "LDS of a CU");
+  static bool done = false;
+  hipError_t e = set_lds(attn_dq_mfma_kernel<DH, NW, KSPL, ANY>, lds, &done);
   if (e != hipSuccess) return e;
-  dim3 grid(d.a, d.b, ceil_div(d.s, NW * 32));
-  hipLaunchKernelGGL((attn_dq_mfma_kernel<DH, NW, ANY>), grid, dim3(NW * 64), lds_dq, st, static_cast<const bf16_t*>(qkv),
+  dim3 grid(d.a, d.b, ceil_div(d.s, NW / KSPL * 32));
+  hipLaunchKernelGGL((attn_dq_mfma_kernel<DH, NW, KSPL, ANY>), grid, dim3(NW * 64), lds, st, static_cast<const bf16_t*>(qkv),
                      static_cast<const bf16_t*>(o), static_cast<const bf16_t*>(d_o), lse, delta,
                      static_cast<bf16_t*>(dqkv), d.s, d.a, d.mask_mode, d.seqlens, d.colsum_partial, d.dh);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
+  // (two sets of tiles and the V fragments of head size 128 do not fit in LDS together)
+  constexpr bool kAlways = Cfg<DH, ANY>::kDkvParts || (KSPL == 2 && Cfg<DH, ANY>::kDkvVInLds), kMay = kAlways || (NW == 4 && KSPL == 2);
   // few blocks: dK and dV in workgroups of their own (see attn_dkv)
-  constexpr bool kAlways = Cfg<DH, ANY>::kDkvParts;
-  const int64_t blocks = (int64_t)d.a * d.b * ceil_div(d.s, NW * 32);
-  if (kAlways || (NW == 4 && 2 * blocks <= gemm_compute_units())) return dkv_launch<DH, NW, ANY, kAlways || NW == 4>(d, qkv, lse, d_o, dqkv, delta, st);
-  return dkv_launch<DH, NW, ANY, kAlways>(d, qkv, lse, d_o, dqkv, delta, st);
+  const int64_t blocks = (int64_t)d.a * d.b * ceil_div(d.s, NW / KSPL * 32);
+  if (kAlways || (kMay && 2 * blocks <= gemm_compute_units())) return dkv_launch<DH, NW, KSPL, ANY, kMay>(d, qkv, lse, d_o, dqkv, delta, st);
+  return dkv_launch<DH, NW, KSPL, ANY, kAlways>(d, qkv, lse, d_o, dqkv, delta, st);
 }
 
 }  // namespace
 
-// Workgroups of 8 waves (256 rows) share each K/V tile and barrier among more rows, workgroups of 4 (128 rows) are twice as
-// many: the latter up to half a workgroup of 8 per CU, and under a causal mask, where the blocks' work differs and a launch ends
-// on its longest, up to one per CU (7/8 of it from head size 96 on, whose tiles take longer to fetch).  Forward + backward, 4 | 8
-// waves: b=2 s=1024 a=16 (128 blocks of 256 rows) dh=64 84.6 | 99.3 us, dh=96 149 | 186, dh=128 126 | 145; b=3 s=1000 a=16 (192)
-// dh=96 290 | 231, causal 162 | 194; b=8 s=512 a=16 (256) dh=64 72.3 | 70.7, causal 59.7 | 65.9, dh=128 causal 104.5 | 101.2;
-// b=4 s=1024 a=32 (512) dh=128 436 | 341.
+// How many rows a workgroup owns, and how often the rows it streams are split between its waves (see the three kernels):
+//   8 x 1  256 rows: each streamed tile and barrier is shared among the most rows
+//   8 x 2  128 rows, two halves of 4 waves
+//   4 x 2   64 rows, two halves of 2 waves
+// The smaller ones are two and four times as many workgroups with half the steps each: 8 x 1 from more than half a workgroup per
+// CU on, 4 x 2 while 8 x 2 would not fill half of the CUs.  Under a causal mask the blocks' work differs and a launch ends on its
+// longest, which 8 x 2 halves: there 8 x 1 from more than one workgroup per CU on (backward at head size 128, whose dK and dV
+// then are workgroups of their own: from 7/8).  Forward | backward in us, 8 x 1, 8 x 2, 4 x 2 (without the split, 4 waves of
+// 128 rows: the last column):
+//   b=1 s=1024 a=8  dh=64          32 blocks of 256 rows   23.8 | 59.6   14.8 | 34.8   11.4 | 28.2     19.3 | 47.0
+//   b=2 s=512  a=16 dh=64 padding  64                      14.3 | 41.8   10.0 | 27.2    8.1 | 23.8
+//   b=3 s=512  a=16 dh=64 padding  96                      14.6 | 42.8   10.2 | 29.3   11.0 | 31.0
+//   b=2 s=1024 a=16 dh=64          128                     25.6 | 62.4   16.3 | 42.9   17.4 | 45.7     21.4 | 54.3
+//   b=5 s=512  a=16 dh=64 padding  160                     16.2 | 46.0   17.0 | 54.6   17.5 | 48.2
+//   b=3 s=1024 a=16 dh=128 causal  192                     35.8 | 101    27.6 | 92.5   36.1 | 130
+//   b=4 s=1024 a=16 dh=64 causal   256                     26.4 | 64.1   19.8 | 54.7   21.3 | 57.0
+//   b=4 s=1024 a=16 dh=128 causal  256                     36.9 | 103    32.3 | 114    47.8 | 168
+//   b=5 s=1024 a=16 dh=64 causal   320                     27.7 | 66.0   24.9 | 74.8   26.5 | 71.9
 namespace {
-int waves_for(const AttnDesc& d) {
+enum Shape { k8x1, k8x2, k4x2 };
+Shape shape_for(const AttnDesc& d, bool bwd) {
   const int64_t blocks = (int64_t)d.b * d.a * ceil_div(d.s, 256), cus = gemm_compute_units();
-  if (d.mask_mode == 1) return blocks <= (d.dh < 96 ? cus : cus * 7 / 8) ? 4 : 8;
-  return 2 * blocks <= cus ? 4 : 8;
+  const int64_t most = d.mask_mode != 1 ? cus / 2 : bwd && d.dh == 128 ? cus * 7 / 8 : cus;
+  if (blocks > most) return k8x1;
+  return (int64_t)d.b * d.a * ceil_div(d.s, 128) * 2 > cus ? k8x2 : k4x2;
 }
+int rows_of(Shape sh) { return sh == k8x1 ? 256 : sh == k8x2 ? 128 : 64; }
 }  // namespace
 
-int attention_colsum_rows(const AttnDesc& d) { return d.b * ceil_div(d.s, 32 * waves_for(d)); }
-int attention_colsum_max_rows(int b, int s) { return b * ceil_div(s, 128); }
+int attention_colsum_rows(const AttnDesc& d) { return d.b * ceil_div(d.s, rows_of(shape_for(d, true))); }
+int attention_colsum_max_rows(int b, int s) { return b * ceil_div(s, 64); }
 
 bool attention_emits_colsum(const AttnDesc& d) {
   return d.dtype == kBF16 && (d.dh == 32 || d.dh == 64 || d.dh == 80 || d.dh == 128);
 }
 
 namespace {
-// F<DH, NW, ANY>::run for the head size and workgroup size of a call
-template <template <int, int, bool> class F, int NW, typename... Args>
+// F<DH, NW, KSPL, ANY>::run for the head size and shape of a call
+template <template <int, int, int, bool> class F, int NW, int KSPL, typename... Args>
 hipError_t by_head(const AttnDesc& d, Args... args) {
   switch (d.dh) {
-    case 32: return F<32, NW, false>::run(d, args...);
-    case 64: return F<64, NW, false>::run(d, args...);
-    case 80: return F<80, NW, false>::run(d, args...);
-    case 128: return F<128, NW, false>::run(d, args...);
+    case 32: return F<32, NW, KSPL, false>::run(d, args...);
+    case 64: return F<64, NW, KSPL, false>::run(d, args...);
+    case 80: return F<80, NW, KSPL, false>::run(d, args...);
+    case 128: return F<128, NW, KSPL, false>::run(d, args...);
   }
-  if (d.dh < 32) return F<32, NW, true>::run(d, args...);
-  if (d.dh <= 48) return F<48, NW, true>::run(d, args...);
-  if (d.dh < 64) return F<64, NW, true>::run(d, args...);
-  if (d.dh < 80) return F<80, NW, true>::run(d, args...);
-  if (d.dh <= 96) return F<96, NW, true>::run(d, args...);
-  if (d.dh <= 112) return F<112, NW, true>::run(d, args...);
-  return F<128, NW, true>::run(d, args...);
+  if (d.dh < 32) return F<32, NW, KSPL, true>::run(d, args...);
+  if (d.dh <= 48) return F<48, NW, KSPL, true>::run(d, args...);
+  if (d.dh < 64) return F<64, NW, KSPL, true>::run(d, args...);
+  if (d.dh < 80) return F<80, NW, KSPL, true>::run(d, args...);
+  if (d.dh <= 96) return F<96, NW, KSPL, true>::run(d, args...);
+  if (d.dh <= 112) return F<112, NW, KSPL, true>::run(d, args...);
+  return F<128, NW, KSPL, true>::run(d, args...);
 }
-template <int DH, int NW, bool ANY>
+template <template <int, int, int, bool> class F, typename... Args>
+hipError_t by_shape(const AttnDesc& d, bool bwd, Args... args) {
+  switch (shape_for(d, bwd)) {
+    case k8x1: return by_head<F, 8, 1>(d, args...);
+    case k8x2: return by_head<F, 8, 2>(d, args...);
+    default: return by_head<F, 4, 2>(d, args...);
+  }
+}
+template <int DH, int NW, int KSPL, bool ANY>
 struct Fwd {
-  static hipError_t run(const AttnDesc& d, const void* qkv, void* o, float* lse, hipStream_t st) { return fwd_launch<DH, NW, ANY>(d, qkv, o, lse, st); }
+  static hipError_t run(const AttnDesc& d, const void* qkv, void* o, float* lse, hipStream_t st) { return fwd_launch<DH, NW, KSPL, ANY>(d, qkv, o, lse, st); }
 };
-template <int DH, int NW, bool ANY>
+template <int DH, int NW, int KSPL, bool ANY>
 struct Bwd {
   static hipError_t run(const AttnDesc& d, const void* qkv, const void* o, const float* lse, const void* d_o, void* dqkv, float* delta, hipStream_t st) {
-    return bwd_launch<DH, NW, ANY>(d, qkv, o, lse, d_o, dqkv, delta, st);
+    return bwd_launch<DH, NW, KSPL, ANY>(d, qkv, o, lse, d_o, dqkv, delta, st);
   }
 };
 }  // namespace
 
-hipError_t attention_fwd_mfma(const AttnDesc& d, const void* qkv, void* o, float* lse, hipStream_t st) {
-  return waves_for(d) == 8 ? by_head<Fwd, 8>(d, qkv, o, lse, st) : by_head<Fwd, 4>(d, qkv, o, lse, st);
-}
+hipError_t attention_fwd_mfma(const AttnDesc& d, const void* qkv, void* o, float* lse, hipStream_t st) { return by_shape<Fwd>(d, false, qkv, o, lse, st); }
 
 hipError_t attention_bwd_mfma(const AttnDesc& d, const void* qkv, const void* o, const float* lse, const void* d_o,
                               void* dqkv, float* delta, hipStream_t st) {
-  return waves_for(d) == 8 ? by_head<Bwd, 8>(d, qkv, o, lse, d_o, dqkv, delta, st)
-                                       : by_head<Bwd, 4>(d, qkv, o, lse, d_o, dqkv, delta, st);
+  return by_shape<Bwd>(d, true, qkv, o, lse, d_o, dqkv, delta, st);
 }
 
 }  // namespace k2bw

@@ -100,3 +100,48 @@ def test_what_nobody_sees_does_not_show(dtype, dh, bad):
     poisoned[0, 50:, h:] = bad
     O4, lse4, D4 = run_attention(dtype, b, s, a, dh, 2, poisoned, d_o, lens)
     assert np.array_equal(O3, O4) and np.array_equal(lse3, lse4) and np.array_equal(D3, D4)
+
+
+@pytest.mark.parametrize("dh", [32, 64, 80, 96, 128])
+@pytest.mark.parametrize("b,s,a,mask", [(1, 200, 2, 1), (1, 330, 2, 0), (3, 300, 16, 0), (3, 330, 16, 2), (5, 300, 16, 1), (5, 270, 16, 0)])
+def test_attention_at_every_split_of_the_streamed_rows(dh, b, s, a, mask):
+    """Few, some and many workgroups: blocks of 64 and 128 rows whose two halves of waves take every second tile of the other
+    side (odd and even numbers of tiles, halves that see nothing), and blocks of 256 rows that take all; with the bias gradient."""
+    h = a * dh
+    qkv, d_o, lens = draw(BF16, b, s, a, dh, mask)
+    if lens is not None:
+        lens[:2] = 1, 65
+    L = B.lib()
+    fused = dh != 96
+    QKV, DO = to_dev(qkv, BF16), to_dev(d_o, BF16)
+    lp = None if lens is None else (LEN := torch.from_numpy(lens).cuda()).data_ptr()
+    n_ws = L.k2bw_attention_bwd_workspace(b, s, a, dh)
+    ws = torch.full((n_ws + 64,), 7.0, device="cuda")
+    db = torch.ones(3 * h, device="cuda")
+    O = torch.full((b, s, h), float("nan"), device="cuda", dtype=torch.bfloat16)
+    D = torch.full((b, s, 3 * h), float("nan"), device="cuda", dtype=torch.bfloat16)
+    lse, delta = torch.empty((b, a, s), device="cuda"), torch.empty((b, a, s), device="cuda")
+    assert L.k2bw_attention_fwd(BF16, b, s, a, dh, mask, lp, QKV.data_ptr(), O.data_ptr(), lse.data_ptr(), None) == 0
+    assert L.k2bw_attention_bwd(BF16, b, s, a, dh, mask, lp, QKV.data_ptr(), O.data_ptr(), lse.data_ptr(), DO.data_ptr(), D.data_ptr(),
+                                delta.data_ptr(), db.data_ptr() if fused else None, 1, ws.data_ptr() if fused else None, None) == 0
+    torch.cuda.synchronize()
+    assert bool((ws[n_ws:] == 7.0).all())
+    split = lambda z: z.reshape(s, a, dh).transpose(1, 0, 2).astype(np.float64)
+    back = lambda z: z.transpose(1, 0, 2).reshape(s, h)
+    tol = 6e-3 if fused else TOL[BF16]
+    got_o, got_lse, got_d = to_host(O), to_host(lse), to_host(D)
+    for n in range(b):
+        q, k, v = (split(qkv[n, :, i * h:(i + 1) * h]) for i in range(3))
+        vis = ob.visibility(mask, s, None if lens is None else int(lens[n]))
+        o, P = ob.attention_fwd(q, k, v, vis)
+        grads = ob.attention_bwd(split(d_o[n]), q, k, v, P)
+        S = np.where(vis[None], q @ k.transpose(0, 2, 1) / math.sqrt(dh), -np.inf)
+        assert rel(got_o[n], back(o)) < tol
+        assert np.abs(got_lse[n] - np.log(np.exp(S - S.max(-1, keepdims=True)).sum(-1)) - S.max(-1)).max() < 1e-4
+        size = max(np.linalg.norm(g) for g in grads)
+        for i, g in enumerate(grads):
+            assert np.linalg.norm(got_d[n, :, i * h:(i + 1) * h] - back(g)) < 2 * tol * size
+    if fused:   # b*s values, each within 2^-8 of its own rounded one: their rounding errors add up like sqrt
+        want = got_d.astype(np.float64).reshape(-1, 3 * h)
+        bound = 2.0 ** -9 * np.sqrt((want ** 2).sum(0)) * 4 + 1e-5 * np.abs(want).sum(0) + 1e-6
+        assert np.all(np.abs(to_host(db) - 1.0 - want.sum(0)) < bound)
