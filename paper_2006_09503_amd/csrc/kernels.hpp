@@ -64,17 +64,24 @@ void gemm_kernel_name(const GemmDesc* d, int count, char* out, size_t cap);
 // ---------------------------------------------------------------------------- LayerNorm
 // y = gain * (x - mean) * rstd + shift over rows of length h; saves mean, rstd (fp32 per row).
 // gain, shift: element type = dtype (the weight version buffers hold every parameter in it).
+// keep (may be null): the same launch also copies x to keep->x ([rows, h], not x itself) and keep->n integers.
+struct LnKeep {
+  void* x = nullptr;
+  const int32_t* n_in = nullptr;
+  int32_t* n_out = nullptr;
+  int n = 0;
+};
 hipError_t layernorm_fwd(const void* x, const void* gain, const void* shift, void* y,
                          float* mean, float* rstd, int rows, int h, float eps, int dtype,
-                         hipStream_t stream);
+                         hipStream_t stream, const LnKeep* keep = nullptr);
 // dx = dres + rstd * (dxhat - mean(dxhat) - xhat * mean(dxhat * xhat)), dxhat = dy * gain;
-// dres may be null.  Column sums go to partial[parts][3h] (fp32: sum_r dy*xhat | sum_r dy | sum_r dx);
+// dres may be null.  dres_keep (may be null; needs dres): the same launch also copies dres there.  Column sums go to partial[parts][3h] (fp32: sum_r dy*xhat | sum_r dy | sum_r dx);
 // *parts_out receives the number of partial rows written.  partial must hold
 // 3 * ln_bwd_max_parts() * h floats.
 int ln_bwd_max_parts();
 hipError_t layernorm_bwd(const void* dy, const void* x, const float* mean, const float* rstd,
                          const void* gain, const void* dres, void* dx, float* partial,
-                         int* parts_out, int rows, int h, int dtype, hipStream_t stream);
+                         int* parts_out, int rows, int h, int dtype, hipStream_t stream, void* dres_keep = nullptr);
 
 // ---------------------------------------------------------------------------- column sums
 // partial[parts][n] = per-slab column sums of y[rows, n] (ld = ldy); parts <= colsum_max_parts().

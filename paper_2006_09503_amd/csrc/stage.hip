@@ -297,21 +297,21 @@ hipError_t run_gemm(stage2bw* st, int cls, const GemmDesc& d) {
 }
 
 hipError_t run_ln_fwd(stage2bw* st, const void* x, const void* gain, const void* shift, void* y, float* mean,
-                      float* rstd) {
-  const double bytes = 2.0 * st->T * st->cfg.hidden * st->esize + 8.0 * st->T;
+                      float* rstd, const LnKeep* keep = nullptr) {
+  const double bytes = (keep ? 3.0 : 2.0) * st->T * st->cfg.hidden * st->esize + 8.0 * st->T;
   return timed(st, STAGE_K_LN_FWD, "ln_fwd_kernel", 0.0, bytes, [&] {
-    return layernorm_fwd(x, gain, shift, y, mean, rstd, st->T, st->cfg.hidden, st->cfg.ln_eps, st->dtype, st->cur);
+    return layernorm_fwd(x, gain, shift, y, mean, rstd, st->T, st->cfg.hidden, st->cfg.ln_eps, st->dtype, st->cur, keep);
   });
 }
 
 // LayerNorm backward; its two parameter gradients (gain | shift are adjacent in G) are left as
 // per-workgroup partial rows in `partial` and reduced at the end of the layer.
 hipError_t run_ln_bwd(stage2bw* st, const void* dy, const void* x, const float* mean, const float* rstd,
-                      const void* gain, const void* dres, void* dx, float* partial, int* parts) {
+                      const void* gain, const void* dres, void* dx, float* partial, int* parts, void* dres_keep = nullptr) {
   const int h = st->cfg.hidden;
-  const double bytes = 4.0 * st->T * h * st->esize + 8.0 * st->T;
+  const double bytes = (dres_keep ? 5.0 : 4.0) * st->T * h * st->esize + 8.0 * st->T;
   return timed(st, STAGE_K_LN_BWD, h >= 2048 ? "ln_bwd_wide_kernel" : "ln_bwd_kernel", 0.0, bytes, [&] {
-    return layernorm_bwd(dy, x, mean, rstd, gain, dres, dx, partial, parts, st->T, h, st->dtype, st->cur);
+    return layernorm_bwd(dy, x, mean, rstd, gain, dres, dx, partial, parts, st->T, h, st->dtype, st->cur, dres_keep);
   });
 }
 
@@ -322,11 +322,12 @@ AttnDesc attn_desc(const stage2bw* st, const int32_t* lens) {
   return d;
 }
 
-// Forward of all layers on weight buffer `buf`.  acts.layer[0].x already holds the stage input.
+// Forward of all layers on weight buffer `buf`.  x_in: the stage input; `keep` (may be null) says where the first kernel that
+// reads it leaves a copy: acts.layer[0].x, which the later ones read.  Without it acts.layer[0].x already holds the input.
 // y_out == nullptr: the stage output is not wanted (the forward re-run inside a backward pass with
 // recomputation): the last layer stops after FC1 + GELU, whose outputs the backward pass reads; its FC2
 // product would only produce the output that was already sent on.
-hipError_t run_forward(stage2bw* st, int buf, ActSet& acts, const int32_t* lens, void* y_out) {
+hipError_t run_forward(stage2bw* st, int buf, ActSet& acts, const int32_t* lens, void* y_out, const void* x_in = nullptr, const LnKeep* keep = nullptr) {
   const stage_config_t& c = st->cfg;
   const int T = st->T, h = c.hidden, f = c.ffn;
   const double attn_flops = 4.0 * c.microbatch * (double)c.seq * c.seq * h;
@@ -335,7 +336,7 @@ hipError_t run_forward(stage2bw* st, int buf, ActSet& acts, const int32_t* lens,
     LayerActs& A = acts.layer[l];
     void* y = (l == c.n_layers - 1) ? y_out : static_cast<void*>(acts.layer[l + 1].x);
     hipError_t e;
-    e = run_ln_fwd(st, A.x, wptr(st, buf, o.ln1_g), wptr(st, buf, o.ln1_b), A.a, A.mean1, A.rstd1);
+    e = run_ln_fwd(st, l == 0 && keep ? x_in : A.x, wptr(st, buf, o.ln1_g), wptr(st, buf, o.ln1_b), A.a, A.mean1, A.rstd1, l == 0 ? keep : nullptr);
     if (e != hipSuccess) return e;
     GemmDesc g;
     g.dtype = st->dtype;
@@ -467,15 +468,10 @@ hipError_t run_backward(stage2bw* st, int buf, int set, int pos, const int32_t* 
   const bool acc = !first;
   const double attn_flops = 10.0 * c.microbatch * (double)c.seq * c.seq * h;
   ActSet& acts = st->sets[set];
-  // the top layer's weight-gradient product reads the incoming gradient after this call has returned:
-  // keep a copy (one launch's worth of traffic per pass)
+  // the top layer's weight-gradient product reads the incoming gradient after this call has returned: the LayerNorm backward
+  // kernel, which reads it too, leaves a copy, and what comes after reads that (the caller's dx may overlap its dy)
   char* dy_keep = st->dy_top + (int64_t)pos * T * h * E;
-  {
-    const int64_t bytes = (int64_t)T * h * E;
-    hipError_t e = timed(st, STAGE_K_OTHER, "copy16_kernel", 0.0, 2.0 * bytes, [&] { return copy_bytes(dy_in, dy_keep, bytes, st->cur); });
-    if (e != hipSuccess) return e;
-  }
-  const void* dy = dy_keep;
+  const void* dy = dy_in;
   std::vector<FinalizeItem> fin;
   fin.reserve(8 * c.n_layers);
   double fin_elems = 0.0;
@@ -521,8 +517,10 @@ hipError_t run_backward(stage2bw* st, int buf, int set, int pos, const int32_t* 
     e = dgrad(du, f, kW1, o.w1, h, st->tmp_h, nullptr, l, kWo, o.wo, (int64_t)h * h);   if (e != hipSuccess) return e;
     // c = LN2(x1); dx1 = dy + LN2'(dc)
     int ln2_parts = 0, ln1_parts = 0;
-    e = run_ln_bwd(st, st->tmp_h, A.x1, A.mean2, A.rstd2, wptr(st, buf, o.ln2_g), dy, dx1, st->ln_partial[l], &ln2_parts);
+    e = run_ln_bwd(st, st->tmp_h, A.x1, A.mean2, A.rstd2, wptr(st, buf, o.ln2_g), dy, dx1, st->ln_partial[l], &ln2_parts,
+                   l == c.n_layers - 1 ? dy_keep : nullptr);
     if (e != hipSuccess) return e;
+    if (l == c.n_layers - 1) dy = dy_keep;
     // x1 = x + o Wo + bo
     e = dgrad(dx1, h, kWo, o.wo, h, st->tmp_h, nullptr, l, kWqkv, o.wqkv, (int64_t)3 * h * h);   if (e != hipSuccess) return e;
     // attention
@@ -752,7 +750,6 @@ int stage_forward(stage_t* st, int64_t mb, const void* x_dev, const int32_t* seq
   int rc = st->sched.check_forward(mb, &slot);
   if (rc != STAGE_OK) return rc;
   const int buf = st->sched.buffer_of(st->sched.read_version());
-  const int64_t in_bytes = (int64_t)st->T * st->cfg.hidden * st->esize;
   st->cur = st->stream;
   // full stash: the microbatch takes the activation set that has been free the longest
   if (!st->cfg.recompute && st->free_sets.empty()) return STAGE_ERR_BAD_STATE;   // (cannot happen: sets = slots + wg_j - 1)
@@ -767,22 +764,22 @@ int stage_forward(stage_t* st, int64_t mb, const void* x_dev, const int32_t* seq
   ActSet& acts = st->sets[set];
   // stash the stage input (with recompute it is the only thing kept)
   char* x_keep = st->cfg.recompute ? st->slot_x0[slot] : acts.layer[0].x;
-  HIP_TRY(timed(st, STAGE_K_OTHER, "copy16_kernel", 0.0, 2.0 * in_bytes, [&] { return copy_bytes(x_dev, x_keep, in_bytes, st->stream); }));
   const int32_t* lens = nullptr;
+  LnKeep keep;
+  keep.x = x_keep;
   if (st->cfg.mask_mode == STAGE_MASK_PADDING) {
-    HIP_TRY(hipMemcpyAsync(st->slot_lens[slot], seqlens_dev, (size_t)st->cfg.microbatch * 4, hipMemcpyDeviceToDevice,
-                           st->stream));
+    keep.n_in = seqlens_dev; keep.n_out = st->slot_lens[slot]; keep.n = st->cfg.microbatch;
     lens = st->slot_lens[slot];
   }
   if (st->cfg.recompute) {
     // the shared activation set is scratch here; its layer-0 input is read from the stash
     char* saved = acts.layer[0].x;
     acts.layer[0].x = x_keep;
-    hipError_t e = run_forward(st, buf, acts, lens, y_dev);
+    hipError_t e = run_forward(st, buf, acts, lens, y_dev, x_dev, &keep);
     acts.layer[0].x = saved;
     HIP_TRY(e);
   } else {
-    HIP_TRY(run_forward(st, buf, acts, lens, y_dev));
+    HIP_TRY(run_forward(st, buf, acts, lens, y_dev, x_dev, &keep));
   }
   if (st->two_streams) HIP_TRY(hipEventRecord(st->fwd_done[slot], st->stream));
   if (!st->cfg.recompute) {

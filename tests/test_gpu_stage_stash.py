@@ -1,0 +1,58 @@
+"""What a stage keeps of its inputs: the activation, the key lengths and the output gradient are stashed by the kernels that read
+them first, so the caller's buffers may be overwritten as soon as the call's work on the stream is done."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2006_09503_amd import binding as B
+from paper_2006_09503_amd import synth
+
+from gpu_util import tdtype, to_dev, to_host
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("precision", [synth.PREC_FP32, synth.PREC_BF16])
+@pytest.mark.parametrize("hidden,heads,seq,micro,layers,recompute",
+                         [(64, 2, 33, 3, 1, 0), (1024, 16, 20, 1, 2, 1), (2560, 32, 9, 1, 1, 0),
+                          (72, 1, 7, 300, 1, 0), (8320, 65, 5, 1, 1, 0)])
+def test_inputs_may_be_overwritten_after_the_call(precision, hidden, heads, seq, micro, layers, recompute):
+    """Two microbatches, one grouped weight-gradient launch: with x, the lengths and dy overwritten after each call (and an odd
+    bit pattern among the activations) every result is bit for bit the one with the buffers left alone."""
+    cfg = synth.StageConfig(layers, hidden, heads, 128, seq, micro, 2, 2, synth.MASK_PADDING, precision, recompute=recompute,
+                            wgrad_group=2, min_len=1)
+    gen = synth.StageInputs(cfg, 3)
+    w0 = gen.weights()
+    mbs = gen.microbatches(2)
+
+    def run(spoil):
+        st = B.Stage(cfg, w0)
+        shape = (micro, seq, hidden)
+        y = [torch.empty(shape, device="cuda", dtype=tdtype(precision)) for _ in range(2)]
+        dx = [torch.empty(shape, device="cuda", dtype=tdtype(precision)) for _ in range(2)]
+        x = [to_dev(m[0], precision) for m in mbs]
+        for t in x:
+            t.view(-1)[3] = -0.0
+        dy = [to_dev(m[1], precision) for m in mbs]
+        lens = [torch.from_numpy(m[2]).cuda() for m in mbs]
+        for k in range(2):
+            st.forward(k + 1, x[k], lens[k], y[k])
+            if spoil:
+                torch.cuda.synchronize()
+                x[k].fill_(float("nan")); lens[k].fill_(1)
+                torch.cuda.synchronize()
+        for k in range(2):
+            st.backward(k + 1, dy[k], dx[k])
+            if spoil:
+                torch.cuda.synchronize()
+                dy[k].fill_(float("nan"))
+                torch.cuda.synchronize()
+        torch.cuda.synchronize()
+        g = st.read_grad_accum()
+        st.close()
+        return [to_host(t) for t in y + dx] + [g]
+
+    a, b = run(False), run(True)
+    assert all(np.isfinite(t).all() for t in a)
+    for p, q in zip(a, b):
+        assert np.array_equal(p, q)
