@@ -612,6 +612,16 @@ __global__ __launch_bounds__(kWg) void colsum_partial_grouped_kernel(ColsumGroup
   }
 }
 
+// Sum of N float4 (a power of two) as a tree: log2 N roundings deep
+template <int N>
+__device__ __forceinline__ float4 pairwise(float4 (&v)[N]) {
+#pragma unroll
+  for (int w = N / 2; w > 0; w /= 2)
+#pragma unroll
+    for (int i = 0; i < w; ++i) { v[i].x += v[i + w].x; v[i].y += v[i + w].y; v[i].z += v[i + w].z; v[i].w += v[i + w].w; }
+  return v[0];
+}
+
 // out_s[n_s] (+)= sum over parts_s rows of partial_s, for up to kFinalizeMaxItems segments in one launch.
 // A workgroup owns 64 columns: 16 threads x 16 bytes cover 256 contiguous bytes of a row (whole cache lines; with
 // one float per thread a workgroup used half of every line it touched), 16 such groups walk the rows.
@@ -631,8 +641,8 @@ __global__ __launch_bounds__(kWg) void colsum_finalize_grouped_kernel(FinalizeGr
       float4 v[8];
 #pragma unroll
       for (int i = 0; i < 8; ++i) v[i] = *reinterpret_cast<const float4*>(partial + (int64_t)(p + i * 16) * ld + col);
-#pragma unroll
-      for (int i = 0; i < 8; ++i) { s.x += v[i].x; s.y += v[i].y; s.z += v[i].z; s.w += v[i].w; }
+      const float4 t = pairwise(v);
+      s.x += t.x; s.y += t.y; s.z += t.z; s.w += t.w;
     }
     for (; p < parts; p += 16) {
       const float4 v = *reinterpret_cast<const float4*>(partial + (int64_t)p * ld + col);
@@ -642,9 +652,10 @@ __global__ __launch_bounds__(kWg) void colsum_finalize_grouped_kernel(FinalizeGr
   red[pl][c] = s;
   __syncthreads();
   if (pl == 0 && col < n) {
-    float4 t = make_float4(0.f, 0.f, 0.f, 0.f);
+    float4 v[16];
 #pragma unroll
-    for (int i = 0; i < 16; ++i) { const float4 v = red[i][c]; t.x += v.x; t.y += v.y; t.z += v.z; t.w += v.w; }
+    for (int i = 0; i < 16; ++i) v[i] = red[i][c];
+    float4 t = pairwise(v);
     float4* out = reinterpret_cast<float4*>(g.out[sidx] + col);
     if (g.accumulate) { const float4 o = *out; t.x += o.x; t.y += o.y; t.z += o.z; t.w += o.w; }
     *out = t;

@@ -539,9 +539,14 @@ hipError_t run_backward(stage2bw* st, int buf, int set, int pos, const int32_t* 
     if (e != hipSuccess) return e;
     ColsumItem cs[3];
     int n_cs = 0, col_dqkv = -1, col_du = -1, col_dy = -1, cols = 0;
-    if (!fused_dqkv) { col_dqkv = cols; cs[n_cs++] = {dqkv, 3 * h, 3 * h}; cols += 3 * h; }
-    if (!fused_du) { col_du = cols; cs[n_cs++] = {du, f, f}; cols += f; }
-    if (l == c.n_layers - 1) { col_dy = cols; cs[n_cs++] = {dy, h, h}; cols += h; }
+    // fp32 mode, few tokens: the matrices themselves are partial rows that the stage's last reduction can sum, no more of them
+    // than the LayerNorm backward kernels leave (512); a launch less per layer (2 layers,
+    // h=128, 128 tokens, three batches of 4 microbatches: 2234 -> 2122 us).  Beyond, its few workgroups would walk too many rows
+    const bool direct = st->dtype == kF32 && T <= 512;
+    const bool sum_dqkv = !fused_dqkv && !direct, sum_du = !fused_du && !direct, sum_dy = l == c.n_layers - 1 && !direct;
+    if (sum_dqkv) { col_dqkv = cols; cs[n_cs++] = {dqkv, 3 * h, 3 * h}; cols += 3 * h; }
+    if (sum_du) { col_du = cols; cs[n_cs++] = {du, f, f}; cols += f; }
+    if (sum_dy) { col_dy = cols; cs[n_cs++] = {dy, h, h}; cols += h; }
     int cs_parts = 0, cs_cols = 0;
     if (n_cs > 0) {
       e = timed(st, STAGE_K_BIAS_GRAD, "colsum_partial_grouped_kernel", 0.0, (double)T * cols * st->esize, [&] {
@@ -553,11 +558,17 @@ hipError_t run_backward(stage2bw* st, int buf, int set, int pos, const int32_t* 
       fin.push_back({partial, parts, ld, n, out});
       fin_elems += (double)parts * n;
     };
+    auto rows = [](const void* p) { return static_cast<const float*>(p); };
     if (fused_dqkv) add_fin(st->attn_partial[l], attention_colsum_rows(ad), 3 * h, 3 * h, st->G + o.bqkv);
+    else if (direct) add_fin(rows(dqkv), T, 3 * h, 3 * h, st->G + o.bqkv);
     else add_fin(st->cs_partial[l] + col_dqkv, cs_parts, cs_cols, 3 * h, st->G + o.bqkv);
     if (fused_du) add_fin(st->du_partial[l], (T + 31) / 32, f, f, st->G + o.b1);
+    else if (direct) add_fin(rows(du), T, f, f, st->G + o.b1);
     else add_fin(st->cs_partial[l] + col_du, cs_parts, cs_cols, f, st->G + o.b1);
-    if (col_dy >= 0) add_fin(st->cs_partial[l] + col_dy, cs_parts, cs_cols, h, st->G + o.b2);
+    if (l == c.n_layers - 1) {
+      if (direct) add_fin(rows(dy), T, h, h, st->G + o.b2);
+      else add_fin(st->cs_partial[l] + col_dy, cs_parts, cs_cols, h, st->G + o.b2);
+    }
     add_fin(st->ln_partial[l], ln2_parts, 3 * h, 2 * h, st->G + o.ln2_g);
     add_fin(st->ln_partial[l] + 2 * h, ln2_parts, 3 * h, h, st->G + o.bo);
     add_fin(st->ln_partial2[l], ln1_parts, 3 * h, 2 * h, st->G + o.ln1_g);

@@ -7,7 +7,7 @@ import torch
 from paper_2006_09503_amd import binding as B
 from paper_2006_09503_amd import synth
 
-from gpu_util import tdtype, to_dev, to_host
+from gpu_util import run_stage_gpu, run_stage_oracle, tdtype, to_dev, to_host
 
 pytestmark = pytest.mark.gpu
 
@@ -56,3 +56,21 @@ def test_inputs_may_be_overwritten_after_the_call(precision, hidden, heads, seq,
     assert all(np.isfinite(t).all() for t in a)
     for p, q in zip(a, b):
         assert np.array_equal(p, q)
+
+
+@pytest.mark.parametrize("seq,micro", [(1, 1), (33, 3), (64, 8), (57, 9)])
+@pytest.mark.parametrize("layers", [1, 2])
+def test_fp32_bias_gradients_around_the_token_limit(layers, seq, micro):
+    """fp32 mode sums the bias gradients of up to 512 tokens straight from the gradient matrices, more through partial rows: both
+    sides of the limit against the oracle, relative to the largest entry of each (a sum of T fp32 terms, upstream rounding 1e-6)."""
+    cfg = synth.StageConfig(layers, 72, 3, 136, seq, micro, 2, 1, synth.MASK_CAUSAL, synth.PREC_FP32)
+    gen = synth.StageInputs(cfg, 5)
+    w0 = gen.weights()
+    mbs = gen.microbatches(2)
+    got = run_stage_gpu(cfg, w0, mbs, 1)["snaps"][0]["G"]
+    want = run_stage_oracle(cfg, w0, mbs).G[0]
+    for slices in synth.param_slices(cfg):
+        for name in ("bqkv", "bo", "b1", "b2"):
+            off, shape = slices[name]
+            w = want[off:off + shape[0]]
+            assert np.abs(got[off:off + shape[0]] - w).max() < 1e-5 * np.abs(w).max(), name
