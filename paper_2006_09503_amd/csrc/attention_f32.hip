@@ -296,8 +296,9 @@ __global__ __launch_bounds__(kThreads, 1) void attn_f32_fwd_kernel(const float* 
   float m = m_lds[l32];
 #pragma unroll
   for (int w = 1; w < kNW; ++w) m = fmaxf(m, m_lds[w * kRows + l32]);
-  const float f = m_i == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m_i - m) * c);   // a wave without a visible key adds nothing
-  if (hf == 0) l_lds[wave * kRows + l32] = m_i == -INFINITY ? 0.f : l_i * f;
+  // a wave without a visible key adds nothing; one whose scores are all NaN has the same maximum, and its l, which is NaN, stays
+  const float f = m_i == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m_i - m) * c);
+  if (hf == 0) l_lds[wave * kRows + l32] = l_i * f;
   put_strip<DH>(oacc, f, smem + wave * kRows * C::LD, l32, hf);
   __syncthreads();
   auto total = [&](int row) {

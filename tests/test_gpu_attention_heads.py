@@ -102,6 +102,26 @@ def test_what_nobody_sees_does_not_show(dtype, dh, bad):
     assert np.array_equal(O3, O4) and np.array_equal(lse3, lse4) and np.array_equal(D3, D4)
 
 
+@pytest.mark.parametrize("dtype,dh", [(F32, 32), (F32, 72), (BF16, 64), (BF16, 40)])
+@pytest.mark.parametrize("s,key", [(33, 32), (33, 0), (200, 130)])
+def test_a_visible_nan_reaches_the_log_sum(dtype, dh, s, key):
+    """A NaN in a visible key makes o and lse of every row NaN, also where it is the only key of its tile (s = 33, key 32) and the
+    waves that share the keys see nothing but it; a NaN in a query makes that row's NaN and leaves the others alone."""
+    h = 2 * dh
+    qkv, d_o, _ = draw(dtype, 1, s, 2, dh, 0)
+    O0, lse0, _ = run_attention(dtype, 1, s, 2, dh, 0, qkv, d_o, None)
+    bad = qkv.copy()
+    bad[0, key, h:2 * h] = float("nan")
+    O, lse, _ = run_attention(dtype, 1, s, 2, dh, 0, bad, d_o, None)
+    assert np.isnan(O).all() and np.isnan(lse).all()
+    bad = qkv.copy()
+    bad[0, 5, :h] = float("nan")
+    O, lse, _ = run_attention(dtype, 1, s, 2, dh, 0, bad, d_o, None)
+    others = np.arange(s) != 5
+    assert np.isnan(O[0, 5]).all() and np.isnan(lse[0, :, 5]).all()
+    assert np.array_equal(O[0, others], O0[0, others]) and np.array_equal(lse[0][:, others], lse0[0][:, others])
+
+
 @pytest.mark.parametrize("dh", [32, 64, 80, 96, 128])
 @pytest.mark.parametrize("b,s,a,mask", [(1, 200, 2, 1), (1, 330, 2, 0), (3, 300, 16, 0), (3, 330, 16, 2), (5, 300, 16, 1), (5, 270, 16, 0)])
 def test_attention_at_every_split_of_the_streamed_rows(dh, b, s, a, mask):
