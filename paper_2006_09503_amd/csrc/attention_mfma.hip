@@ -3,11 +3,12 @@
 //
 // Two sets of instances.  Head sizes 32, 64, 80 and 128 have one each (ANY = false).  The others run on the next larger
 // of 32, 48, 64, 80, 96, 112, 128 with the true size at run time (ANY = true): tile columns past the head are fetched from
-// a zeroed chunk, rows past the sequence too.  These keep their probabilities (and dS) exact to 16 bits of mantissa:
-// a value enters the second product as the sum of two bf16 numbers, its rounding and the rounding of what that left,
-// two MFMAs instead of one; and a position that some rows of a tile may not see cannot reach them even if it holds
-// infinities or NaNs (accumulate_visible).  Measured at b=3 s=1000 a=16 dh=96 causal against one thread per row in fp32
-// on the vector ALU, which these sizes used to run on: forward 2892 -> 29 us, backward 16480 -> 100.
+// a zeroed chunk, rows past the sequence too.  These keep their probabilities (and dS) in 32 bits, as the kernels did that these
+// sizes used to run on (one thread per row in fp32 on the vector ALU): a value enters the second product as the sum of three bf16
+// numbers that hold its 24 bits, three MFMAs instead of one; and a position that some rows of a tile may not see cannot reach them
+// even if it holds infinities or NaNs (accumulate_visible).  Measured at b=3 s=1000 a=16 dh=96 causal against those kernels:
+// forward 2892 -> 36 us, backward 16480 -> 118.  (With two numbers, 16 bits, 32 and 107 us; but a sum whose terms cancel to a
+// thousandth then shows it: 1 % off instead of bf16's rounding.)
 //
 // All three kernels keep one query (forward, dQ) or one key (dK/dV) per lane of a 32-wide MFMA
 // column, so softmax statistics, lse and delta are per-lane scalars or short in-lane loops:
@@ -146,18 +147,31 @@ __device__ __forceinline__ bf16x8 pack_half(const f32x16& v, int half) {
   return __builtin_bit_cast(bf16x8, w);
 }
 
-// The same as the sum of two operands: what rounding to bf16 gives, and the rounding of what it left (v - hi is exact)
-__device__ __forceinline__ void pack_half_split(const f32x16& v, int half, bf16x8& hi, bf16x8& lo) {
-  uint32_t wh[4], wl[4];
+// The same as the sum of three operands that together hold all 24 bits of the values: what rounding to bf16 gives, the rounding
+// of what that left, and the rest (the differences are exact, and the rest has at most 6 bits)
+struct Exact8 { bf16x8 part[3]; };
+__device__ __forceinline__ Exact8 pack_half_exact(const f32x16& v, int half) {
+  uint32_t w[3][4];
   const int b = 8 * half;
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    const float x = v[b + 2 * i], y = v[b + 2 * i + 1];
-    wh[i] = pack_bf16x2(x, y);
-    wl[i] = pack_bf16x2(x - __uint_as_float(wh[i] << 16), y - __uint_as_float(wh[i] & 0xffff0000u));
+    float x = v[b + 2 * i], y = v[b + 2 * i + 1];
+#pragma unroll
+    for (int p = 0; p < 3; ++p) {
+      w[p][i] = pack_bf16x2(x, y);
+      x -= __uint_as_float(w[p][i] << 16);
+      y -= __uint_as_float(w[p][i] & 0xffff0000u);
+    }
   }
-  hi = __builtin_bit_cast(bf16x8, make_uint4(wh[0], wh[1], wh[2], wh[3]));
-  lo = __builtin_bit_cast(bf16x8, make_uint4(wl[0], wl[1], wl[2], wl[3]));
+  Exact8 e;
+#pragma unroll
+  for (int p = 0; p < 3; ++p) e.part[p] = __builtin_bit_cast(bf16x8, make_uint4(w[p][0], w[p][1], w[p][2], w[p][3]));
+  return e;
+}
+// acc += X P for such a P
+__device__ __forceinline__ void mul_exact(const bf16x8& x, const Exact8& p, f32x16& acc) {
+#pragma unroll
+  for (int i = 0; i < 3; ++i) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x, p.part[i], acc, 0, 0, 0);
 }
 
 // First operand, head columns of the tile as MFMA rows: this lane's row is head column
@@ -438,7 +452,7 @@ __device__ __forceinline__ bool attn_fwd(const bf16_t* __restrict__ qkv, bf16_t*
     for (int nb = 0; nb < 2; ++nb)
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        const float pv = __builtin_amdgcn_exp2f(fmaf(sacc[nb][r], c, -mc));
+        const float pv = __builtin_amdgcn_exp2f(ANY ? (sacc[nb][r] - m_use) * c : fmaf(sacc[nb][r], c, -mc));
         sacc[nb][r] = pv;
         rowsum += pv;
       }
@@ -459,14 +473,9 @@ __device__ __forceinline__ bool attn_fwd(const bf16_t* __restrict__ qkv, bf16_t*
       }
 #pragma unroll
       for (int kk = 0; kk < 4; ++kk) {
-        bf16x8 hi, lo;
-        pack_half_split(sacc[kk >> 1], kk & 1, hi, lo);
+        const Exact8 pe = pack_half_exact(sacc[kk >> 1], kk & 1);
 #pragma unroll
-        for (int db = 0; db < C::DB; ++db) {
-          const bf16x8 v = read_cols<DH>(v_lds, db * 32, kk, lane);
-          oacc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v, hi, oacc[db], 0, 0, 0);
-          oacc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v, lo, oacc[db], 0, 0, 0);
-        }
+        for (int db = 0; db < C::DB; ++db) mul_exact(read_cols<DH>(v_lds, db * 32, kk, lane), pe, oacc[db]);
       }
     } else {
       bf16x8 pb[4];
@@ -571,7 +580,7 @@ __device__ __forceinline__ bool attn_dq(const bf16_t* __restrict__ qkv, const bf
     delta_i = part + __shfl_xor(part, 32, 64);
     if (row_ok && hf == 0 && kg == 0) delta[((int64_t)n * a + head) * s + i] = delta_i;
   }
-  const float lse_i = row_ok ? lse[((int64_t)n * a + head) * s + i] * kLog2e : INFINITY;
+  const float lse_i = row_ok ? lse[((int64_t)n * a + head) * s + i] * (ANY ? 1.f : kLog2e) : INFINITY;
   f32x16 minus_delta;
 #pragma unroll
   for (int r = 0; r < 16; ++r) minus_delta[r] = -delta_i;
@@ -618,7 +627,7 @@ __device__ __forceinline__ bool attn_dq(const bf16_t* __restrict__ qkv, const bf
     for (int nb = 0; nb < 2; ++nb)
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        const float pv = __builtin_amdgcn_exp2f(fmaf(sacc[nb][r], c, -lse_i));
+        const float pv = __builtin_amdgcn_exp2f(ANY ? fmaf(sacc[nb][r], scale, -lse_i) * kLog2e : fmaf(sacc[nb][r], c, -lse_i));
         sacc[nb][r] = pv * dp[nb][r];   // dS^T (the 1/sqrt(dh) factor is applied at the end)
       }
     if constexpr (ANY) {
@@ -632,14 +641,9 @@ __device__ __forceinline__ bool attn_dq(const bf16_t* __restrict__ qkv, const bf
       }
 #pragma unroll
       for (int kk = 0; kk < 4; ++kk) {
-        bf16x8 hi, lo;
-        pack_half_split(sacc[kk >> 1], kk & 1, hi, lo);
+        const Exact8 dse = pack_half_exact(sacc[kk >> 1], kk & 1);
 #pragma unroll
-        for (int db = 0; db < C::DB; ++db) {
-          const bf16x8 k = read_cols<DH>(k_lds, db * 32, kk, lane);
-          dq[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k, hi, dq[db], 0, 0, 0);
-          dq[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k, lo, dq[db], 0, 0, 0);
-        }
+        for (int db = 0; db < C::DB; ++db) mul_exact(read_cols<DH>(k_lds, db * 32, kk, lane), dse, dq[db]);
       }
     } else {
       bf16x8 dsb[4];
@@ -738,7 +742,7 @@ __device__ __forceinline__ bool attn_dkv(const bf16_t* __restrict__ qkv, const b
     loader.issue(dobase, (int64_t)h, i0, s, stage + C::kTileU4);
   };
   // lse and delta of the tile's queries travel through a register of two waves, which lets them enter LDS in the form the
-  // loop uses: -lse * log2(e), and -delta, the starting value of the accumulators of dP
+  // loop uses: -lse * log2(e) (ANY: -lse), and -delta, the starting value of the accumulators of dP
   float stat = 0.f;
   auto load_stat = [&](int i0) {
     if (rw < 2) stat = (rw == 0 ? lse_row : delta_row)[min(i0 + lane, s - 1)];
@@ -753,7 +757,7 @@ __device__ __forceinline__ bool attn_dkv(const bf16_t* __restrict__ qkv, const b
     __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
     if (rw < 2) {
       float* f = reinterpret_cast<float*>(tiles + (st & 1) * kStageU4 + 2 * C::kTileU4);
-      f[rw * kTile + lane] = rw == 0 ? -kLog2e * stat : -stat;   // (the stage's readers were done before the last barrier)
+      f[rw * kTile + lane] = rw == 0 && !ANY ? -kLog2e * stat : -stat;   // (the stage's readers were done before the last barrier)
     }
     __syncthreads();
     if (t + KSPL < ntiles) { load_stat(i0 + KSPL * kTile); issue_tile(i0 + KSPL * kTile, tiles + ((st + 1) & 1) * kStageU4); }
@@ -798,7 +802,7 @@ __device__ __forceinline__ bool attn_dkv(const bf16_t* __restrict__ qkv, const b
 #pragma unroll
         for (int t4 = 0; t4 < 4; ++t4) {
           const int r = 4 * g + t4;
-          const float pv = __builtin_amdgcn_exp2f(fmaf(sacc[r], c, lv[t4]));
+          const float pv = __builtin_amdgcn_exp2f(ANY ? fmaf(sacc[r], scale, lv[t4]) * kLog2e : fmaf(sacc[r], c, lv[t4]));
           pv16[r] = pv;
           ds16[r] = pv * dp[r];
         }
@@ -824,20 +828,15 @@ __device__ __forceinline__ bool attn_dkv(const bf16_t* __restrict__ qkv, const b
 #pragma unroll
         for (int half = 0; half < 2; ++half) {
           const int kk = qb * 2 + half;
-          bf16x8 hi, lo;
-          if (DV) pack_half_split(pv16, half, hi, lo);
+          if (DV) {
+            const Exact8 pe = pack_half_exact(pv16, half);
 #pragma unroll
-          for (int db = 0; DV && db < C::DB; ++db) {
-            const bf16x8 x = read_cols<DH>(do_lds, db * 32, kk, lane);
-            dv[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x, hi, dv[db], 0, 0, 0);
-            dv[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x, lo, dv[db], 0, 0, 0);
+            for (int db = 0; db < C::DB; ++db) mul_exact(read_cols<DH>(do_lds, db * 32, kk, lane), pe, dv[db]);
           }
-          if (DK) pack_half_split(ds16, half, hi, lo);
+          if (DK) {
+            const Exact8 dse = pack_half_exact(ds16, half);
 #pragma unroll
-          for (int db = 0; DK && db < C::DB; ++db) {
-            const bf16x8 x = read_cols<DH>(q_lds, db * 32, kk, lane);
-            dk[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x, hi, dk[db], 0, 0, 0);
-            dk[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x, lo, dk[db], 0, 0, 0);
+            for (int db = 0; db < C::DB; ++db) mul_exact(read_cols<DH>(q_lds, db * 32, kk, lane), dse, dk[db]);
           }
         }
       } else {

@@ -102,6 +102,37 @@ def test_what_nobody_sees_does_not_show(dtype, dh, bad):
     assert np.array_equal(O3, O4) and np.array_equal(lse3, lse4) and np.array_equal(D3, D4)
 
 
+@pytest.mark.parametrize("dh", [24, 40, 56, 72, 96, 112, 120])
+@pytest.mark.parametrize("b,a", [(1, 2), (4, 16), (9, 16)])
+def test_probabilities_keep_their_32_bits(dh, b, a):
+    """bf16 at the head sizes without bf16 probabilities: P and dS enter the second products with all their bits.  Rows of
+    +-1 or +-1024 in turn against nearly equal P or dS: what remains of each sum is some 1e-3 of its terms, so 16 bits of P or dS
+    would show as 2^-17 * 1e3 = 8e-3, while rounding the result to bf16 is at most 2^-9 and 32-bit terms leave 2^-24 * 1e3."""
+    s, h = 256, a * dh
+    rng = np.random.default_rng(dh + b)
+    alt = np.where(np.arange(s) % 2 == 0, 1024.0, -1024.0)
+    q, k, v, g = (rng.standard_normal((b, a, s, dh)) for _ in range(4))
+    q *= 4e-4
+    q[..., 0] = 0.0                                  # column 0 of the keys does not enter the scores
+    k[..., 0] = alt
+    v[..., 1::2, :] = v[..., 0::2, :]                # neighbours share dP but for column 0,
+    v[..., 0] = alt / 1024
+    g[..., 0] *= 4e-4                                # which adds as little as P differs by
+    g[..., 1] = alt / 1024
+    q, k, v, g = (round_to_bf16(t.astype(np.float32)).astype(np.float64) for t in (q, k, v, g))
+    join = lambda t: t.transpose(0, 2, 1, 3).reshape(b, s, h).astype(np.float32)
+    O, lse, D = run_attention(BF16, b, s, a, dh, 0, np.concatenate([join(q), join(k), join(v)], -1), join(g), None)
+    split = lambda t: t.reshape(b, s, a, dh).transpose(0, 2, 1, 3).astype(np.float64)
+    S = q @ k.transpose(0, 1, 3, 2) / math.sqrt(dh)
+    P = np.exp(S - S.max(-1, keepdims=True))
+    P /= P.sum(-1, keepdims=True)
+    dS = P * (g @ v.transpose(0, 1, 3, 2) - (g * split(O)).sum(-1, keepdims=True))
+    tol = 2.0 ** -9 + 6e-4
+    assert rel(split(O)[..., 0], (P @ v)[..., 0]) < tol
+    assert rel(split(D[..., 2 * h:])[..., 1], (P.transpose(0, 1, 3, 2) @ g)[..., 1]) < tol
+    assert rel(split(D[..., :h])[..., 0], (dS @ k)[..., 0] / math.sqrt(dh)) < tol
+
+
 @pytest.mark.parametrize("dtype,dh", [(F32, 32), (F32, 72), (BF16, 64), (BF16, 40)])
 @pytest.mark.parametrize("s,key", [(33, 32), (33, 0), (200, 130)])
 def test_a_visible_nan_reaches_the_log_sum(dtype, dh, s, key):
