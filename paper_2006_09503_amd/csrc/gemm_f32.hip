@@ -18,6 +18,7 @@
 // 8*(r/4) + 4*(l/32) + (r % 4) for accumulator register r.  As in the bf16 kernels the B tile is fed as the
 // first operand and the A tile as the second, so a lane owns one row m of C and four consecutive columns
 // per register quad: the epilogue's accesses are 16-byte vectors.
+#include <cmath>
 #include <cstdio>
 
 #include "kernels.hpp"
@@ -374,23 +375,37 @@ hipError_t launch_split(GroupF32& gp, hipStream_t s) {
 // The split kernels load a K-contiguous operand 16 bytes at a time
 bool split_ok(const F32Params& p, bool ta, bool tb) { return (ta || p.vec_a) && (!tb || p.vec_b); }
 
-// Tile edge for `count` products of one form (128: one product per launch on the staged kernel).  The edge with the least
-// rounds of tiles over the CUs times the time of a tile, in units of what a 32 x 32 tile's matrix instructions take: a 64 x 64
-// tile takes 4, a 128 x 128 tile 16; 32 x 32 tiles fetch twice the operands of 64 x 64 ones (x 1.22), the staged kernel needs two
-// workgroups per CU to hide its latencies (x 0.95 with them, x 1.25 without).  Forward | data gradient | weight gradient in us,
-// edge 128, 64, 32 (tokens, in, out): (128,512,128) 54.2|17.5|18.6, 14.5|7.3|7.7, 6.4|4.1|4.4; (512,1024,3072) 102|289|57,
-// 50|63|46, 47|47|51; (2048,1024,1024) 103|102|180, 52|57|48, 59|62|68; (4096,1024,4096) 307|389|357, 371|317|333, 425|464|462;
-// (4096,4096,8192) 2261|2375|2218, 2744|2325|2771, 3619|3735|3560.
+// Tile edge for `count` products of one form (128: one product per launch on the staged kernel): the one with the least estimated
+// time.  In microseconds, with R tiles per CU, C = ceil(R) rounds and K in thousands: a launch has a fixed part, a part per tile of a
+// CU (its first loads, its sums and its trip through C) and a part per k, which the split kernels pay by whole rounds; so does the
+// staged kernel up to two workgroups per CU, where the part per tile also shrinks with what of a tile exists (`fill`).  Fitted to
+// launches of 260 random sizes (M, N, K of 8 to 8192) with each edge forced: 6 to 12 % off each time, and the choice costs 0.4 % over
+// the best edge on average.  What keeps short reduction ranges on 128 x 128 tiles is the part per tile.  Edge 128, 64, 32 in us:
+// forward 4620 x 5408 x 8 37, 83, 63; 1438 x 5208 x 16 16, 30, 22; 2702 x 5584 x 216 82, 119, -; weight gradient 4620 x 5408 x 8
+// 53, 119, 100; 4036 x 1920 x 48 25, 46, 38; 4278 x 7992 x 181 165, 273, -.  Small products, forward | data gradient | weight
+// gradient (tokens, in, out): (128,512,128) 54|18|19, 14|7.3|7.7, 6.4|4.1|4.4; (512,1024,3072) 102|289|57, 50|63|46, 47|47|51;
+// (2048,1024,1024) 103|102|180, 52|57|48, 59|62|68; (4096,1024,4096) 307|389|357, 371|317|333, 425|464|462.
+struct EdgeCost { double few0, few_tile, few_k, many0, many_tile, many_k, t64_0, t64_tile, t64_k, t32_0, t32_tile, t32_k; };
 int choose_f32(const F32Params* p, int count, bool ta, bool tb) {
-  int64_t t[3] = {0, 0, 0};
-  const int edge[3] = {128, 64, 32};
+  static constexpr EdgeCost kCost[3] = {
+      {2.75, 3.4, 92.0, 6.8, 3.9, 72.0, 3.6, 2.9, 18.6, 3.3, 0.50, 6.1},   // rows of B along N (forward)
+      {2.75, 3.7, 87.6, 6.3, 4.0, 69.3, 3.6, 1.5, 17.6, 3.3, 0.42, 5.5},   // both along K (data gradient)
+      {3.25, 6.5, 95.6, 7.0, 7.3, 67.2, 5.0, 4.3, 19.2, 3.6, 0.91, 6.7}};  // A along M (weight gradient: C is read and written)
+  const EdgeCost& q = kCost[ta ? 2 : tb ? 1 : 0];
+  const double cus = gemm_compute_units();
+  double c128 = 0, r64 = 0, k64 = 0, r32 = 0, k32 = 0;
   for (int g = 0; g < count; ++g) {
     if (!split_ok(p[g], ta, tb)) return 128;
-    for (int e = 0; e < 3; ++e) t[e] += (int64_t)ceil_div(p[g].M, edge[e]) * ceil_div(p[g].N, edge[e]);
+    auto per_cu = [&](int edge) { return (double)ceil_div(p[g].M, edge) * ceil_div(p[g].N, edge) / cus; };
+    const double r = per_cu(128), k = p[g].K * 1e-3;
+    const double fill = (p[g].M < 128 ? p[g].M / 128.0 : 1.0) * (p[g].N < 128 ? p[g].N / 128.0 : 1.0);
+    c128 += r <= 2 ? q.few0 + std::ceil(r) * (q.few_tile * fill + q.few_k * k) : q.many0 + r * (q.many_tile + q.many_k * k);
+    r64 += per_cu(64); k64 += per_cu(64) * k;
+    r32 += per_cu(32); k32 += per_cu(32) * k;
   }
-  const int cus = gemm_compute_units();
-  const double cost[3] = {ceil_div(t[0], cus) * 16.0 * (t[0] >= 2 * cus ? 0.95 : 1.25), ceil_div(t[1], cus) * 4.0, ceil_div(t[2], cus) * 1.22};
-  return cost[0] <= cost[1] && cost[0] <= cost[2] ? 128 : cost[1] <= cost[2] ? 64 : 32;
+  const double c64 = q.t64_0 + q.t64_tile * r64 + q.t64_k * std::ceil(r64) * (k64 / r64);
+  const double c32 = q.t32_0 + q.t32_tile * r32 + q.t32_k * std::ceil(r32) * (k32 / r32);
+  return c128 <= c64 && c128 <= c32 ? 128 : c64 <= c32 ? 64 : 32;
 }
 
 template <bool TA, bool TB, int EPI>
