@@ -1382,24 +1382,22 @@ int g_tile_override = 0;  // 0: heuristic; else force a tile shape (tuning aid)
 int choose_tile(const BfParams* p, int count, bool ta, bool tb) {
   int tile = g_tile_override;
   if (tile == 0) {
-    // Measured on MI355X (M = 2048..8192): once 256x256 tiles give about 5/8 of the CUs a tile
-    // (160 tiles: N = 2560 at M = 4096) the 8-wave ring kernels of that size win, by 15..30 % at 160..192 tiles and more
-    // above.  Below that the tile with the least estimated time, in microseconds: rounds of tiles over the CUs times a
-    // fixed part and a part per k of the reduction range, fitted to launches of 8 to 1024 tiles with K = 32 .. 4608:
-    //   32x32, K split over 8 waves   3.0 + 1.25e-3 K per round
-    //   64x64, K split over 4 waves   3.5 + 3.3e-3 K per round
-    //   128x128 ring                  3 once, 1.5 + 7.5e-3 K per round (4.8e-3 K while half the CUs are idle)
-    // and the accumulator's trip through HBM at 20 KB per microsecond and CU.  Forward | data | weight gradient, tiles 128 (the
-    // register-staged kernel used before), 128 ring, 64, 32 in us: 128 tokens 1024 -> 3072: 17.3|35.0|8.7, 9.9|17.9|7.7,
-    // 7.2|10.6|11.1, 7.9|6.1|24.8; 1000 tokens 768 -> 2304: 14.9|27.3|17.4, 9.8|16.0|13.2, 15.3|10.0|14.0, 26.6|15.5|32.8;
-    // 3000 tokens 1536 -> 4608 (256x256: 46|86|69): 69|77|66, 62|66|61, 99|96|89, 251|164|241.
-    // Among 128x128 tiles two register-staged workgroups per CU win where a launch of several rounds of short products lives
-    // on its accumulator (300 tokens 2048 -> 4096, weight gradient: 18.5 against 24.7 us), the ring kernel elsewhere.
-    // Where 192x256 tiles still fit into one round they spread the same work over a third more CUs: they are ahead of 256x256
-    // tiles, and of 128x128 ones from 132 tiles on, in the forms whose B is read along its rows (us, tile 256 | 192 | 128):
-    // 4096 x 2560 x 2560 60.5 | 55.4 | 66.6 (220 tiles); weight gradient 3072 x 3072 x 4096 92.5 | 76.4 | 107 (192); 2000 x 3000 x 3000
-    // 64.3 | 53.0 | 58.8 (132); 3000 x 2048 x 2048 41.8 | 35.8 | 34.8 (128).  With both operands contiguous along K they gain
-    // nothing (4096 x 2560 x 10240 198 | 206): that form is bound by its loads, of which a smaller tile needs more.
+    // Every line below was drawn from launches of 660 random sizes (M, N, K of 8 to 16384, half of them near the lines) with each
+    // tile forced; over these the choice costs 1.3 % over the best tile on average.
+    //
+    // 192x256 where they fit into one round and the forms read B along its rows: against 256x256 tiles 5..14 % less time (4096 x
+    // 2560 x 2560 60.5 -> 55.4 us).  Against two 128x128 workgroups per CU, time of 192x256 over that of 128x128: forward K < 128
+    // 1.05, from there 0.97 (K < 512), 0.89, 0.85, 0.80 (K >= 2048); weight gradient, which pays for C by the tile, K < 512 1.14,
+    // < 1024 1.02, < 2048 0.92, above 0.83.  Beyond two 128x128 tiles per CU, a third round of those, 0.9 down to 0.55.  (With both
+    // operands along K they gain nothing over 256x256: 4096 x 2560 x 10240 198 -> 206 us.)
+    // 256x256 from 144 tiles on.  With both operands along K and a partial K tile the register-staged kernel of that tile: the rows
+    // then start off the 128-byte lines, which the direct-to-LDS loads pay for twice (staged over ring 0.97, elsewhere 1.02..1.2).
+    // More 128x128 tiles than CUs: two register-staged workgroups per CU while their overlap is worth more than the ring; ring over
+    // staged: forward K < 128 1.18, < 512 1.01 (off the lines 1.09), < 1024 0.90 (1.02), above 0.83 (0.93); both along K 1.19, 1.05
+    // (1.16), 0.95 (1.15), 0.87 (1.05); weight gradient K < 512 1.2, < 1024 1.07, < 2048 1.0, above 0.90.
+    // Fewer: the least estimated time of 128x128, of 64x64 and of 32x32 tiles with K split over the waves, below.  Forward | data |
+    // weight gradient, tiles 128 (register-staged), 128 ring, 64, 32 in us: 128 tokens 1024 -> 3072: 17.3|35.0|8.7, 9.9|17.9|7.7,
+    // 7.2|10.6|11.1, 7.9|6.1|24.8; 1000 tokens 768 -> 2304: 14.9|27.3|17.4, 9.8|16.0|13.2, 15.3|10.0|14.0, 26.6|15.5|32.8.
     int64_t big = 0, t192 = 0, t128 = 0, t64 = 0, t32 = 0;
     int K = 0;
     for (int g = 0; g < count; ++g) {
@@ -1411,15 +1409,32 @@ int choose_tile(const BfParams* p, int count, bool ta, bool tb) {
       K = p[g].K > K ? p[g].K : K;
     }
     const int cus = compute_units();
-    const bool accum = ta;   // the weight-gradient form
-    const double c32 = ceil_div(t32, cus) * (3.0 + 1.25e-3 * K + (accum ? 0.4 : 0.0));
-    const double c64 = ceil_div(t64, cus) * (3.5 + 3.3e-3 * K + (accum ? 1.6 : 0.0));
-    const double c128 = 3.0 + ceil_div(t128, cus) * (1.5 + (t128 * 2 <= cus ? 4.8e-3 : 7.5e-3) * K + (accum ? 6.5 : 0.0));
-    if (!tb && t192 >= 132 && t192 <= cus && big < cus) tile = 24;
-    else if (big >= 144) tile = 23;
-    else if (c32 < c64 && c32 < c128) tile = 32;
-    else if (c64 < c128) tile = 64;
-    else tile = accum && t128 > cus && K <= 1024 ? 2 : 22;
+    const bool off_lines = K % 64 != 0;   // rows along K that are not whole 128-byte lines
+    if (!tb && t192 >= 132 && t192 <= cus && big < cus && (big >= 144 || t128 > 2 * cus || K >= (ta ? 1024 : 128))) {
+      tile = 24;
+    } else if (big >= 144) {
+      tile = tb && K % 32 ? 3 : 23;
+    } else if (t128 > cus) {
+      tile = K < (ta ? 1536 : off_lines ? 1024 : 512) || (tb && off_lines) ? 2 : 22;
+    } else {
+      // In microseconds, with R tiles per CU, C = ceil(R) rounds and K in thousands: a fixed part, one per round, and per k a part
+      // by rounds and one by tiles (bytes); 7 to 13 % off the measured times
+      struct TileCost { double c0, round, round_k, tile_k; };
+      static constexpr TileCost kCost[3][3] = {
+          {{2.8, 1.7, 5.6, 3.5}, {1.45, 2.4, 2.7, 2.0}, {1.4, 1.6, 0.97, 1.4}},    // forward
+          {{2.6, 1.8, 5.2, 5.7}, {1.65, 2.2, 2.5, 2.4}, {1.55, 1.55, 0.83, 1.1}},  // both operands along K
+          {{3.2, 2.6, 5.6, 2.6}, {1.3, 3.05, 2.6, 1.9}, {1.4, 1.9, 0.93, 1.9}}};   // weight gradient
+      const int64_t tiles[3] = {t128, t64, t32};
+      double cost[3];
+      for (int e = 0; e < 3; ++e) {
+        const TileCost& q = kCost[ta ? 2 : tb ? 1 : 0][e];
+        const double r = (double)tiles[e] / cus, c = ceil_div(tiles[e], cus);
+        cost[e] = q.c0 + q.round * c + (q.round_k * c + q.tile_k * r) * K * 1e-3;
+      }
+      if (cost[2] < cost[1] && cost[2] < cost[0]) tile = 32;
+      else if (cost[1] < cost[0]) tile = 64;
+      else tile = tb && off_lines && K >= 4096 ? 6 : 22;   // (ring over two K groups: 1.02 there, 0.98 from 2048, below 0.83)
+    }
   }
   bool segmented = false;
   for (int g = 0; g < count; ++g) segmented = segmented || p[g].seg_tiles > 1;

@@ -58,6 +58,13 @@ def test_fp32_products_at_tile_edges(M, N, K, ta, tb, pad):
         assert bool(torch.isnan(C[:, N:]).all())
 
 
+@pytest.mark.parametrize("M,N,K", [(930, 1030, 601), (1450, 2600, 9), (2049, 1290, 40), (130, 4100, 200)])
+def test_fp32_products_on_both_sides_of_the_tile_rule(M, N, K):
+    """64 x 64 tiles (one round, long reduction), and wide outputs whose short reductions stay on 128 x 128 tiles."""
+    for ta, tb in ((0, 0), (0, 1), (1, 0), (1, 1)):
+        test_fp32_products_at_tile_edges(M, N, K, ta, tb, 0)
+
+
 BF16 = 1
 
 
@@ -126,6 +133,16 @@ def test_bf16_weight_gradient_of_any_number_of_tokens(tile, M, N, K):
             assert rel(to_host(G), x.T @ dy + (g0 if acc else 0)) < 2e-6
     finally:
         assert L.k2bw_tune_gemm_tile(0) == 0
+
+
+@pytest.mark.parametrize("M,N,K", [(200, 17000, 72), (1168, 3304, 1544), (648, 11960, 40), (4104, 2056, 96), (968, 5944, 520), (392, 8536, 1032),
+                                   (1000, 2312, 2104), (3080, 3592, 40), (136, 10296, 264)])
+def test_bf16_products_on_both_sides_of_the_tile_rule(M, N, K):
+    """The tile the library picks, around its lines: 128 x 128 tiles in several rounds of short and long reductions, 192 x 256 and
+    256 x 256 tiles, reductions that are whole 128-byte lines and that are not; the partial K tiles and NaNs of the tests above."""
+    for k in (K, K + (-K) % 64):
+        test_bf16_partial_k_tiles(0, M, N, k)
+        test_bf16_weight_gradient_of_any_number_of_tokens(0, M, N, k - 3)
 
 
 @pytest.mark.parametrize("dtype", [0, BF16])
