@@ -499,8 +499,6 @@ __global__ __launch_bounds__(kWg) void colsum_partial_kernel(const T* __restrict
   }
 }
 
-// 16 columns x 16 part-lanes per workgroup: 64-byte segments per part row, 8 loads in flight per
-// thread, then an LDS tree over the part-lanes.
 // Column sums of 32 columns over all rows by one workgroup of 512 threads (4 threads to a row, 8 columns each), four rows of a
 // thread in flight at a time
 template <typename T>
@@ -545,6 +543,8 @@ __global__ __launch_bounds__(512) void colsum_direct_kernel(const T* __restrict_
   }
 }
 
+// 16 columns x 16 part-lanes per workgroup: 64-byte segments per part row, 8 loads in flight per
+// thread, then an LDS tree over the part-lanes.
 __global__ __launch_bounds__(kWg) void colsum_finalize_kernel(const float* __restrict__ partial, int parts, int n,
                                                                int ld, float* __restrict__ out, int accumulate) {
   __shared__ float red[16][17];
@@ -798,11 +798,17 @@ hipError_t colsum_partial(const void* y, int rows, int n, int ldy, float* partia
 }
 
 // Column sums in one launch where a workgroup of 32 columns can take all rows: two launches of a small matrix cost more in
-// fixed parts than the sums themselves.  Two launches | one, us: bf16 128 x 3072 6.2 | 3.8, 1000 x 4608 7.0 | 5.8, 2048 x 512 6.1 | 4.2,
-// 2000 x 3000 7.6 | 7.3, 4096 x 1024 6.4 | 10.1, 4096 x 8192 15.5 | 20.7; fp32 1024 x 1536 6.2 | 4.1, 2000 x 3000 8.3 | 8.5.
+// fixed parts than the sums themselves.  A workgroup reads 64 (bf16) or 128 bytes of each row, so it stays ahead while the caches
+// serve the other half of a line: up to 16 MiB, 14 where the rows do not start on lines of 128 bytes; fp32 rows that do are read in
+// whole lines and have no such limit.  Two launches | one, us: bf16 128 x 3072 6.2 | 3.8, 1024 x 8192 (16 MiB) 5.8 | 3.3, 768 x 12288
+// 5.8 | 7.2, 256 x 32768 (16 MiB) 6.3 | 3.8, 384 x 32768 6.4 | 9.1, 520 x 13912 (13.8) 6.5 | 6.3, 640 x 13912 (17) 7.1 | 8.4, 1000 x 22184
+// 12 | 18; fp32 1024 x 4104 (16) 6.6 | 3.9, 1500 x 4104 (23.5) 7.2 | 8.1, 640 x 28256 13.9 | 11.4, 640 x 28232 (off the lines) 15.1 | 18.5.
+// By rows: bf16 2048 x 512 6.1 | 4.2, 2000 x 3000 7.6 | 7.3, 4096 x 1024 6.4 | 10.1, 4096 x 8192 15.5 | 20.7; fp32 2000 x 3000 8.3 | 8.5.
 hipError_t column_sums(const void* y, int rows, int n, float* partial, float* out, bool accumulate, int dtype, hipStream_t stream) {
   if (rows <= 0 || n <= 0 || n % 8 || !y || !partial || !out || !aligned16(y) || !aligned16(partial)) return hipErrorInvalidValue;
-  if (rows <= 1024 || (rows <= 2048 && n <= 4096)) {
+  const int64_t row_bytes = (int64_t)n * (dtype == kBF16 ? 2 : 4);
+  const bool on_lines = row_bytes % 128 == 0;
+  if ((rows <= 1024 || (rows <= 2048 && n <= 4096)) && ((on_lines && dtype == kF32) || rows * row_bytes <= (on_lines ? 16ll : 14ll) << 20)) {
     if (dtype == kBF16)
       hipLaunchKernelGGL((colsum_direct_kernel<bf16_t>), dim3(ceil_div(n, 32)), dim3(512), 0, stream, static_cast<const bf16_t*>(y), rows, n, out,
                          accumulate ? 1 : 0);

@@ -146,7 +146,8 @@ def test_bf16_products_on_both_sides_of_the_tile_rule(M, N, K):
 
 
 @pytest.mark.parametrize("dtype", [0, BF16])
-@pytest.mark.parametrize("rows,n", [(1, 8), (127, 40), (129, 24), (513, 264), (1024, 72), (1025, 4104), (2048, 4096), (2049, 32)])
+@pytest.mark.parametrize("rows,n", [(1, 8), (127, 40), (129, 24), (513, 264), (1024, 72), (1025, 4104), (2048, 4096), (2049, 32),
+                                    (256, 32768), (257, 28672), (511, 14336), (520, 13912), (1024, 8200), (1500, 2504)])
 def test_column_sums_on_both_sides_of_the_one_launch_rule(dtype, rows, n):
     rng = np.random.default_rng(rows + n)
     y = rng.standard_normal((rows, n)).astype(np.float32)
