@@ -31,8 +31,10 @@ namespace {
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
-constexpr int kNW = 4;                  // waves per workgroup: they split the streamed rows
-constexpr int kThreads = kNW * 64;
+// Waves per workgroup (NW): they split the streamed rows.  Four; one in launches of more blocks than CUs whose sequences are a
+// single tile: three waves would only wait, and a CU takes four workgroups instead of one (b=46 s=17 a=12 dh=64: forward
+// 17.9 -> 7.6 us, backward 57 -> 23; b=57 s=1 a=32 dh=32 12.8 -> 6.7, 67 -> 22).
+constexpr int kManyWaves = 4;
 constexpr int kRows = 32;               // rows a workgroup owns
 constexpr float kLog2e = 1.4426950408889634f;
 
@@ -105,18 +107,18 @@ __device__ __forceinline__ void mul_rows(const float (&a)[CfgF<DH>::NF], const f
 // The operand a workgroup keeps for its own 32 rows (Q and dO in dQ, K and V in dK/dV), the same for all four waves: in
 // fragment registers, or for large heads, where the accumulators and the streamed operands need those, in LDS (rows of
 // DH + 4 floats: the 16-byte reads of 16 consecutive rows fall on all banks).
-template <int DH, bool IN_LDS>
+template <int DH, int NW, bool IN_LDS>
 struct Resident {
   float f[CfgF<DH>::NF];
   __device__ __forceinline__ void load(const float* __restrict__ row, int dh, int, int hf, int, float*) { load_row<DH>(row, dh, hf, f); }
   __device__ __forceinline__ void mul(const float (&x)[CfgF<DH>::NF], f32x16& acc, const float*, int, int) const { mul_rows<DH>(x, f, acc); }
 };
-template <int DH>
-struct Resident<DH, true> {
+template <int DH, int NW>
+struct Resident<DH, NW, true> {
   static constexpr int LDR = DH + 4;
-  // every wave writes a quarter of the columns of all 32 rows; the caller synchronises
+  // every wave writes its share of the columns of all 32 rows; the caller synchronises
   __device__ __forceinline__ void load(const float* __restrict__ row, int dh, int l32, int hf, int wave, float* rows) {
-    for (int j = wave; j < DH / 8; j += kNW) {
+    for (int j = wave; j < DH / 8; j += NW) {
       float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
       if (8 * j < dh) v = *reinterpret_cast<const float4*>(row + 8 * j + 4 * hf);
       *reinterpret_cast<float4*>(rows + l32 * LDR + 8 * j + 4 * hf) = v;
@@ -133,7 +135,7 @@ struct Resident<DH, true> {
     }
   }
 };
-template <int DH> constexpr int strip_floats() { return kNW * kRows * CfgF<DH>::LD; }
+template <int DH, int NW> constexpr int strip_floats() { return NW * kRows * CfgF<DH>::LD; }
 template <int DH> constexpr int resident_floats() { return kRows * (DH + 4); }
 template <int DH> constexpr bool kDqLds = DH >= 112;
 template <int DH> constexpr bool kDkvLds = DH >= 48;
@@ -201,17 +203,17 @@ __device__ __forceinline__ void put_strip(const f32x16 (&acc)[CfgF<DH>::DB], flo
 }
 
 // Sum of the waves' strips, times row_scale(row), to out[row][0 .. dh) for the first `rows` rows
-template <int DH, typename Scale>
+template <int DH, int NW, typename Scale>
 __device__ __forceinline__ void sum_strips(const float* strips, float* __restrict__ out, int64_t ld, int rows, int dh, int tid,
                                            Scale&& row_scale) {
   constexpr int kStrip = kRows * CfgF<DH>::LD;
   const int per_row = dh / 4;
-  for (int e = tid; e < kRows * per_row; e += kThreads) {
+  for (int e = tid; e < kRows * per_row; e += NW * 64) {
     const int row = e / per_row, c = e % per_row;
     if (row >= rows) break;
     float4 t = *reinterpret_cast<const float4*>(strips + row * CfgF<DH>::LD + 4 * c);
 #pragma unroll
-    for (int w = 1; w < kNW; ++w) {
+    for (int w = 1; w < NW; ++w) {
       const float4 v = *reinterpret_cast<const float4*>(strips + w * kStrip + row * CfgF<DH>::LD + 4 * c);
       t.x += v.x; t.y += v.y; t.z += v.z; t.w += v.w;
     }
@@ -222,11 +224,11 @@ __device__ __forceinline__ void sum_strips(const float* strips, float* __restric
 
 // ------------------------------------------------------------------------------------------------
 // forward: lane = query, registers = keys (S^T = K Q^T, O^T = V^T P^T)
-template <int DH>
-__global__ __launch_bounds__(kThreads, 1) void attn_f32_fwd_kernel(const float* __restrict__ qkv, float* __restrict__ o, float* __restrict__ lse,
+template <int DH, int NW>
+__global__ __launch_bounds__(NW * 64, 1) void attn_f32_fwd_kernel(const float* __restrict__ qkv, float* __restrict__ o, float* __restrict__ lse,
                                                                     int s, int a, int dh, int mask_mode, const int32_t* __restrict__ seqlens) {
   using C = CfgF<DH>;
-  extern __shared__ __attribute__((aligned(16))) float smem[];   // strips, then m[kNW][32], l[kNW][32]
+  extern __shared__ __attribute__((aligned(16))) float smem[];   // strips, then m[NW][32], l[NW][32]
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l32 = lane & 31, hf = lane >> 5;
   const int n = blockIdx.y, head = blockIdx.x;
   const bool causal = mask_mode == 1;
@@ -248,14 +250,14 @@ __global__ __launch_bounds__(kThreads, 1) void attn_f32_fwd_kernel(const float* 
   const int ntiles = (jend + 31) / 32;
   auto load_k = [&](int t) { load_row<DH>(base + h + (int64_t)min(t * 32 + l32, jend - 1) * ld, dh, hf, kf); };
   if (wave < ntiles) load_k(wave);
-  for (int t = wave; t < ntiles; t += kNW) {
+  for (int t = wave; t < ntiles; t += NW) {
     const int j0 = t * 32;
     load_cols<DH>(base + 2 * h + (int64_t)j0 * ld, (int)ld, jend - j0, dh, l32, hf, vc);
     __builtin_amdgcn_sched_barrier(0);   // V travels while the scores are computed
     f32x16 sc = zero16();
     mul_rows<DH>(kf, qf, sc);
     __builtin_amdgcn_sched_barrier(0);
-    if (t + kNW < ntiles) load_k(t + kNW);   // the next tile's K travels under the softmax and the second product
+    if (t + NW < ntiles) load_k(t + NW);   // the next tile's K travels under the softmax and the second product
     __builtin_amdgcn_sched_barrier(0);
     const bool diag = causal && j0 + 31 > i0;
     if (diag || j0 + 32 > jend) {
@@ -288,14 +290,14 @@ __global__ __launch_bounds__(kThreads, 1) void attn_f32_fwd_kernel(const float* 
     else mul_cols<DH>(vc, sc, oacc);
   }
   // the waves' maxima meet, every partial result is rescaled to the common one
-  float* m_lds = smem + kNW * kRows * C::LD;
-  float* l_lds = m_lds + kNW * kRows;
+  float* m_lds = smem + NW * kRows * C::LD;
+  float* l_lds = m_lds + NW * kRows;
   l_i += __shfl_xor(l_i, 32, 64);
   if (hf == 0) m_lds[wave * kRows + l32] = m_i;
   __syncthreads();
   float m = m_lds[l32];
 #pragma unroll
-  for (int w = 1; w < kNW; ++w) m = fmaxf(m, m_lds[w * kRows + l32]);
+  for (int w = 1; w < NW; ++w) m = fmaxf(m, m_lds[w * kRows + l32]);
   // a wave without a visible key adds nothing; one whose scores are all NaN has the same maximum, and its l, which is NaN, stays
   const float f = m_i == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m_i - m) * c);
   if (hf == 0) l_lds[wave * kRows + l32] = l_i * f;
@@ -304,17 +306,17 @@ __global__ __launch_bounds__(kThreads, 1) void attn_f32_fwd_kernel(const float* 
   auto total = [&](int row) {
     float t = l_lds[row];
 #pragma unroll
-    for (int w = 1; w < kNW; ++w) t += l_lds[w * kRows + row];
+    for (int w = 1; w < NW; ++w) t += l_lds[w * kRows + row];
     return t;
   };
-  sum_strips<DH>(smem, o + ((int64_t)n * s + i0) * h + head * dh, h, s - i0, dh, tid, [&](int row) { return 1.0f / total(row); });
+  sum_strips<DH, NW>(smem, o + ((int64_t)n * s + i0) * h + head * dh, h, s - i0, dh, tid, [&](int row) { return 1.0f / total(row); });
   if (wave == 0 && hf == 0 && i < s) lse[((int64_t)n * a + head) * s + i] = m * scale + logf(total(l32));
 }
 
 // ------------------------------------------------------------------------------------------------
 // dQ (and delta = rowsum(dO * O), which the dK/dV kernel reads): the forward's orientation
-template <int DH>
-__global__ __launch_bounds__(kThreads, 1) void attn_f32_dq_kernel(const float* __restrict__ qkv, const float* __restrict__ o,
+template <int DH, int NW>
+__global__ __launch_bounds__(NW * 64, 1) void attn_f32_dq_kernel(const float* __restrict__ qkv, const float* __restrict__ o,
                                                                    const float* __restrict__ d_o, const float* __restrict__ lse,
                                                                    float* __restrict__ delta, float* __restrict__ dqkv, int s, int a, int dh,
                                                                    int mask_mode, const int32_t* __restrict__ seqlens) {
@@ -332,8 +334,8 @@ __global__ __launch_bounds__(kThreads, 1) void attn_f32_dq_kernel(const float* _
   const float scale = 1.0f / sqrtf((float)dh), c = scale * kLog2e;
 
   float kf[C::NF], vf[C::NF], kc[C::DB][16];
-  Resident<DH, kDqLds<DH>> q, g;
-  float* q_lds = smem + strip_floats<DH>();
+  Resident<DH, NW, kDqLds<DH>> q, g;
+  float* q_lds = smem + strip_floats<DH, NW>();
   float* g_lds = q_lds + resident_floats<DH>();
   const float* g_row = d_o + ((int64_t)n * s + ic) * h + head * dh;
   q.load(base + (int64_t)ic * ld, dh, l32, hf, wave, q_lds);
@@ -364,7 +366,7 @@ __global__ __launch_bounds__(kThreads, 1) void attn_f32_dq_kernel(const float* _
   // large heads: rows of the next tile are not requested ahead, and the column operand only once the rows are used up
   constexpr bool kAhead = DH <= 96;
   if (kAhead && wave < ntiles) load_kv(wave);
-  for (int t = wave; t < ntiles; t += kNW) {
+  for (int t = wave; t < ntiles; t += NW) {
     const int j0 = t * 32;
     if (!kAhead) load_kv(t);
     auto load_k_cols = [&] { load_cols<DH>(base + h + (int64_t)j0 * ld, (int)ld, jend - j0, dh, l32, hf, kc); };
@@ -375,7 +377,7 @@ __global__ __launch_bounds__(kThreads, 1) void attn_f32_dq_kernel(const float* _
     g.mul(vf, dp, g_lds, l32, hf);
     __builtin_amdgcn_sched_barrier(0);
     if (!kAhead) load_k_cols();
-    if (kAhead && t + kNW < ntiles) load_kv(t + kNW);
+    if (kAhead && t + NW < ntiles) load_kv(t + NW);
     __builtin_amdgcn_sched_barrier(0);
     const bool diag = causal && j0 + 31 > i0;
 #pragma unroll
@@ -390,13 +392,13 @@ __global__ __launch_bounds__(kThreads, 1) void attn_f32_dq_kernel(const float* _
   }
   put_strip<DH>(dq, scale, smem + wave * kRows * C::LD, l32, hf);
   __syncthreads();
-  sum_strips<DH>(smem, dqkv + ((int64_t)n * s + i0) * ld + head * dh, ld, s - i0, dh, tid, [](int) { return 1.0f; });
+  sum_strips<DH, NW>(smem, dqkv + ((int64_t)n * s + i0) * ld + head * dh, ld, s - i0, dh, tid, [](int) { return 1.0f; });
 }
 
 // ------------------------------------------------------------------------------------------------
 // dK, dV: lane = key, registers = queries (S = Q K^T, dV^T = dO^T P, dK^T = Q^T dS)
-template <int DH>
-__global__ __launch_bounds__(kThreads, 1) void attn_f32_dkv_kernel(const float* __restrict__ qkv, const float* __restrict__ d_o,
+template <int DH, int NW>
+__global__ __launch_bounds__(NW * 64, 1) void attn_f32_dkv_kernel(const float* __restrict__ qkv, const float* __restrict__ d_o,
                                                                     const float* __restrict__ lse, const float* __restrict__ delta,
                                                                     float* __restrict__ dqkv, int s, int a, int dh, int mask_mode,
                                                                     const int32_t* __restrict__ seqlens) {
@@ -416,8 +418,8 @@ __global__ __launch_bounds__(kThreads, 1) void attn_f32_dkv_kernel(const float* 
   const float scale = 1.0f / sqrtf((float)dh);
 
   float qf[C::NF], gf[C::NF], qc[C::DB][16], gc[C::DB][16];
-  Resident<DH, kDkvLds<DH>> k, v;
-  float* k_lds = smem + strip_floats<DH>();
+  Resident<DH, NW, kDkvLds<DH>> k, v;
+  float* k_lds = smem + strip_floats<DH, NW>();
   float* v_lds = k_lds + resident_floats<DH>();
   k.load(base + h + (int64_t)jc * ld, dh, l32, hf, wave, k_lds);
   v.load(base + 2 * h + (int64_t)jc * ld, dh, l32, hf, wave, v_lds);
@@ -437,7 +439,7 @@ __global__ __launch_bounds__(kThreads, 1) void attn_f32_dkv_kernel(const float* 
   // registers allow it
   constexpr bool kColsFirst = DH <= 64, kAhead = DH <= 64;
   if (kAhead && t0 + wave < t1) load_qg(t0 + wave);
-  for (int t = t0 + wave; t < t1; t += kNW) {
+  for (int t = t0 + wave; t < t1; t += NW) {
     const int i0 = t * 32;
     if (!kAhead) load_qg(t);
     auto load_g_cols = [&] { load_cols<DH>(gbase + (int64_t)i0 * h, h, s - i0, dh, l32, hf, gc); };
@@ -456,7 +458,7 @@ __global__ __launch_bounds__(kThreads, 1) void attn_f32_dkv_kernel(const float* 
     v.mul(gf, dp, v_lds, l32, hf);
     __builtin_amdgcn_sched_barrier(0);
     if (!kColsFirst) load_g_cols();
-    if (kAhead && t + kNW < t1) load_qg(t + kNW);
+    if (kAhead && t + NW < t1) load_qg(t + NW);
     __builtin_amdgcn_sched_barrier(0);
     const bool diag = causal && i0 < j0 + 31;
 #pragma unroll
@@ -480,72 +482,88 @@ __global__ __launch_bounds__(kThreads, 1) void attn_f32_dkv_kernel(const float* 
   float* out = dqkv + ((int64_t)n * s + j0) * ld + h + head * dh;
   put_strip<DH>(dk, scale, smem + wave * kRows * C::LD, l32, hf);
   __syncthreads();
-  sum_strips<DH>(smem, out, ld, s - j0, dh, tid, [](int) { return 1.0f; });
+  sum_strips<DH, NW>(smem, out, ld, s - j0, dh, tid, [](int) { return 1.0f; });
   __syncthreads();
   put_strip<DH>(dv, 1.0f, smem + wave * kRows * C::LD, l32, hf);
   __syncthreads();
-  sum_strips<DH>(smem, out + h, ld, s - j0, dh, tid, [](int) { return 1.0f; });
+  sum_strips<DH, NW>(smem, out + h, ld, s - j0, dh, tid, [](int) { return 1.0f; });
 }
 
-template <int DH>
+template <int DH, int NW>
 hipError_t fwd_launch(const AttnDesc& d, const void* qkv, void* o, float* lse, hipStream_t st) {
-  constexpr size_t lds = (strip_floats<DH>() + 2 * kNW * kRows) * sizeof(float);
+  constexpr size_t lds = (strip_floats<DH, NW>() + 2 * NW * kRows) * sizeof(float);
   static bool done = false;
   if (!done) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(attn_f32_fwd_kernel<DH>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(attn_f32_fwd_kernel<DH, NW>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     done = true;
   }
   dim3 grid(d.a, d.b, ceil_div(d.s, kRows));
-  hipLaunchKernelGGL(attn_f32_fwd_kernel<DH>, grid, dim3(kThreads), lds, st, static_cast<const float*>(qkv), static_cast<float*>(o), lse,
+  hipLaunchKernelGGL((attn_f32_fwd_kernel<DH, NW>), grid, dim3(NW * 64), lds, st, static_cast<const float*>(qkv), static_cast<float*>(o), lse,
                      d.s, d.a, d.dh, d.mask_mode, d.seqlens);
   return hipGetLastError();
 }
 
-template <int DH>
+template <int DH, int NW>
 hipError_t bwd_launch(const AttnDesc& d, const void* qkv, const void* o, const float* lse, const void* d_o, void* dqkv, float* delta,
                       hipStream_t st) {
-  constexpr size_t lds_dq = (strip_floats<DH>() + (kDqLds<DH> ? 2 * resident_floats<DH>() : 0)) * sizeof(float);
-  constexpr size_t lds_dkv = (strip_floats<DH>() + (kDkvLds<DH> ? 2 * resident_floats<DH>() : 0)) * sizeof(float);
+  constexpr size_t lds_dq = (strip_floats<DH, NW>() + (kDqLds<DH> ? 2 * resident_floats<DH>() : 0)) * sizeof(float);
+  constexpr size_t lds_dkv = (strip_floats<DH, NW>() + (kDkvLds<DH> ? 2 * resident_floats<DH>() : 0)) * sizeof(float);
   static_assert(lds_dq <= 160 * 1024 && lds_dkv <= 160 * 1024, "LDS of a CU");
   static bool done = false;
   if (!done) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(attn_f32_dq_kernel<DH>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_dq);
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(attn_f32_dq_kernel<DH, NW>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_dq);
     if (e == hipSuccess)
-      e = hipFuncSetAttribute(reinterpret_cast<const void*>(attn_f32_dkv_kernel<DH>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_dkv);
+      e = hipFuncSetAttribute(reinterpret_cast<const void*>(attn_f32_dkv_kernel<DH, NW>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_dkv);
     if (e != hipSuccess) return e;
     done = true;
   }
   dim3 grid(d.a, d.b, ceil_div(d.s, kRows));
-  hipLaunchKernelGGL(attn_f32_dq_kernel<DH>, grid, dim3(kThreads), lds_dq, st, static_cast<const float*>(qkv), static_cast<const float*>(o),
+  hipLaunchKernelGGL((attn_f32_dq_kernel<DH, NW>), grid, dim3(NW * 64), lds_dq, st, static_cast<const float*>(qkv), static_cast<const float*>(o),
                      static_cast<const float*>(d_o), lse, delta, static_cast<float*>(dqkv), d.s, d.a, d.dh, d.mask_mode, d.seqlens);
-  hipLaunchKernelGGL(attn_f32_dkv_kernel<DH>, grid, dim3(kThreads), lds_dkv, st, static_cast<const float*>(qkv), static_cast<const float*>(d_o),
+  hipLaunchKernelGGL((attn_f32_dkv_kernel<DH, NW>), grid, dim3(NW * 64), lds_dkv, st, static_cast<const float*>(qkv), static_cast<const float*>(d_o),
                      lse, delta, static_cast<float*>(dqkv), d.s, d.a, d.dh, d.mask_mode, d.seqlens);
   return hipGetLastError();
 }
 
 }  // namespace
 
-// The head size is rounded up to a multiple of 16 (fragments) and 32 (result blocks); what lies past it is zero.
+namespace {
+// F<DH, NW>::run for the head size, rounded up to a multiple of 16 (fragments) and 32 (result blocks; what lies past it is zero),
+// and the waves of a call
+template <template <int, int> class F, int NW, typename... Args>
+hipError_t by_head(const AttnDesc& d, Args... args) {
+  if (d.dh <= 32) return F<32, NW>::run(d, args...);
+  if (d.dh <= 48) return F<48, NW>::run(d, args...);
+  if (d.dh <= 64) return F<64, NW>::run(d, args...);
+  if (d.dh <= 80) return F<80, NW>::run(d, args...);
+  if (d.dh <= 96) return F<96, NW>::run(d, args...);
+  if (d.dh <= 112) return F<112, NW>::run(d, args...);
+  return F<128, NW>::run(d, args...);
+}
+template <int DH, int NW>
+struct Fwd {
+  static hipError_t run(const AttnDesc& d, const void* qkv, void* o, float* lse, hipStream_t st) { return fwd_launch<DH, NW>(d, qkv, o, lse, st); }
+};
+template <int DH, int NW>
+struct Bwd {
+  static hipError_t run(const AttnDesc& d, const void* qkv, const void* o, const float* lse, const void* d_o, void* dqkv, float* delta, hipStream_t st) {
+    return bwd_launch<DH, NW>(d, qkv, o, lse, d_o, dqkv, delta, st);
+  }
+};
+}  // namespace
+
+namespace {
+bool one_wave(const AttnDesc& d) { return d.s <= kRows && (int64_t)d.b * d.a > gemm_compute_units(); }
+}  // namespace
+
 hipError_t attention_fwd_f32(const AttnDesc& d, const void* qkv, void* o, float* lse, hipStream_t st) {
-  if (d.dh <= 32) return fwd_launch<32>(d, qkv, o, lse, st);
-  if (d.dh <= 48) return fwd_launch<48>(d, qkv, o, lse, st);
-  if (d.dh <= 64) return fwd_launch<64>(d, qkv, o, lse, st);
-  if (d.dh <= 80) return fwd_launch<80>(d, qkv, o, lse, st);
-  if (d.dh <= 96) return fwd_launch<96>(d, qkv, o, lse, st);
-  if (d.dh <= 112) return fwd_launch<112>(d, qkv, o, lse, st);
-  return fwd_launch<128>(d, qkv, o, lse, st);
+  return one_wave(d) ? by_head<Fwd, 1>(d, qkv, o, lse, st) : by_head<Fwd, kManyWaves>(d, qkv, o, lse, st);
 }
 
 hipError_t attention_bwd_f32(const AttnDesc& d, const void* qkv, const void* o, const float* lse, const void* d_o, void* dqkv, float* delta,
                              hipStream_t st) {
-  if (d.dh <= 32) return bwd_launch<32>(d, qkv, o, lse, d_o, dqkv, delta, st);
-  if (d.dh <= 48) return bwd_launch<48>(d, qkv, o, lse, d_o, dqkv, delta, st);
-  if (d.dh <= 64) return bwd_launch<64>(d, qkv, o, lse, d_o, dqkv, delta, st);
-  if (d.dh <= 80) return bwd_launch<80>(d, qkv, o, lse, d_o, dqkv, delta, st);
-  if (d.dh <= 96) return bwd_launch<96>(d, qkv, o, lse, d_o, dqkv, delta, st);
-  if (d.dh <= 112) return bwd_launch<112>(d, qkv, o, lse, d_o, dqkv, delta, st);
-  return bwd_launch<128>(d, qkv, o, lse, d_o, dqkv, delta, st);
+  return one_wave(d) ? by_head<Bwd, 1>(d, qkv, o, lse, d_o, dqkv, delta, st) : by_head<Bwd, kManyWaves>(d, qkv, o, lse, d_o, dqkv, delta, st);
 }
 
 }  // namespace k2bw
