@@ -4,6 +4,7 @@ go unnoticed at run time.  Compiles the kernel file to gfx950 assembly (no GPU n
 resource usage the compiler reports per kernel."""
 import os
 import re
+import struct
 import subprocess
 import tempfile
 
@@ -26,3 +27,50 @@ def test_ring_gemm_kernels_use_no_scratch_and_fit_two_waves_per_simd():
         assert field("private_segment_fixed_size") == 0, name       # no scratch: nothing spilled
         assert field("vgpr_spill_count") == 0 and field("sgpr_spill_count") == 0, name
         assert field("vgpr_count") <= 256, name                     # 8 waves per workgroup = 2 per SIMD
+
+
+def built_kernels(pattern):
+    """(demangled name, field reader) of the kernels whose name holds `pattern` in the library as it is built, from the notes of its
+    gfx950 code objects."""
+    llvm = os.path.join(os.path.dirname(os.path.dirname(B.HIPCC)), "llvm", "bin")
+    if not os.path.exists(B.LIB):
+        B.build()
+    data, out, at = open(B.LIB, "rb").read(), [], 0
+    magic = b"__CLANG_OFFLOAD_BUNDLE__"
+    with tempfile.TemporaryDirectory() as tmp:
+        while (at := data.find(magic, at)) >= 0:
+            n, p = struct.unpack_from("<Q", data, at + len(magic))[0], at + len(magic) + 8
+            for _ in range(n):
+                offset, size, length = struct.unpack_from("<QQQ", data, p)
+                target, p = data[p + 24:p + 24 + length], p + 24 + length
+                if b"gfx950" not in target or size == 0:
+                    continue
+                path = os.path.join(tmp, "code.o")
+                with open(path, "wb") as f:
+                    f.write(data[at + offset:at + offset + size])
+                out.append(subprocess.run([os.path.join(llvm, "llvm-readelf"), "--notes", path], check=True, capture_output=True,
+                                          text=True).stdout)
+            at += len(magic)
+    kernels = re.findall(r"\.name:\s+(\S+)\n(.*?)\.wavefront_size", "\n".join(out), flags=re.S)
+    names = subprocess.run(["c++filt"], input="\n".join(n for n, _ in kernels), capture_output=True, text=True).stdout.split("\n")
+    return [(name, lambda k, body=body: int(re.search(r"\." + k + r":\s+(\d+)", body).group(1)))
+            for name, (_, body) in zip(names, kernels) if re.search(pattern, name)]
+
+
+def test_small_head_attention_kernels_leave_room_for_two_workgroups_per_cu():
+    """256-row workgroups are 8 waves; with at most 128 registers a CU holds two.  A dQ kernel of 141 cost the backward pass at head
+    size 32 up to a quarter of its speed."""
+    for kernel, head in (("fwd", 32), ("fwd", 64), ("dq", 32), ("dkv", 32)):
+        found = built_kernels(rf"attn_{kernel}_mfma_kernel<{head}, 8, 1, false")
+        assert found, (kernel, head)
+        for name, field in found:
+            assert field("vgpr_count") <= 128 and field("private_segment_fixed_size") == 0, name
+
+
+def test_fixed_head_attention_kernels_do_not_spill():
+    """The instances of head sizes 32, 64, 80 and 128 (those of the padded sizes hold a second, row-by-row copy of their loop, which
+    spills).  Two registers in front of the loop of the 64-row dQ kernel at head size 128 are the exception."""
+    found = built_kernels(r"attn_(fwd|dq|dkv)_mfma_kernel<\d+, \d, \d, false")
+    assert len(found) >= 30
+    for name, field in found:
+        assert field("vgpr_spill_count") <= (2 if "attn_dq_mfma_kernel<128, 4, 2" in name else 0), name
