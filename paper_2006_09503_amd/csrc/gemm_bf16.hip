@@ -876,6 +876,11 @@ constexpr int vmcnt_imm(int n) { return (n & 15) | ((n >> 4) << 14) | (7 << 4) |
 // of K = 32 (128 KB).  128x128 tiles: four stages of K = 64; with K = 32 (half a 128-byte line per
 // row and load) that tile is 10..15 % slower once the operands come from HBM, as they do inside
 // the stage, with four stages or with eight.
+// Whether a launch of such tiles may end with tiles of half the height (see launch_ring): 256x256 ones, whose loads divide evenly
+// among the waves.  (192x256 tiles are only taken where they fit into one round.)
+template <int BM, int BN, int WM, int WN, int BKA>
+constexpr bool kHalves = BM == 2 * WM && BM * (BKA / 8) % (64 * (BM / WM) * (BN / WN)) == 0;
+
 template <int BM, int BN, int WM, int WN, int BKA, int NS, bool TA, bool TB, int EPI>
 __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void gemm_bf16_ring_kernel(LaunchParams<EPI> gp) {
   constexpr int CHK = BKA / 8, KS = BKA / 16;
@@ -893,7 +898,7 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void gemm_bf16_ring_ker
   tile_coords(wg, p.tiles_m, p.tiles_n, bm, bn);
   // A launch may end with tiles of BM/2 rows (see launch_ring): the waves of the lower half then only
   // take part in the loads and barriers.
-  constexpr bool kCanHalve = BM == 2 * WM;
+  constexpr bool kCanHalve = kHalves<BM, BN, WM, WN, BKA>;
   const int tile_m = kCanHalve ? p.tile_m : BM;
   const bool active = !kCanHalve || wm * WM < tile_m;   // wave-uniform
   const int m0 = bm * tile_m, n0 = bn * BN;
@@ -988,8 +993,7 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void gemm_bf16_ring_ker
     // barrier, so at the wait the tiles kt+2 .. kt+NS-2 may be outstanding
     for (int kt = 0; kt < nk; ++kt) {
       const uint32_t l_stage = lds_base + (uint32_t)(((kt + NS - 1) & (NS - 1)) * kStage) * 16u;
-      if (extra) __builtin_amdgcn_s_waitcnt(vmcnt_imm((NS - 3) * NV));
-      else __builtin_amdgcn_s_waitcnt(vmcnt_imm((NS - 3) * (NV - 1)));
+      __builtin_amdgcn_s_waitcnt(vmcnt_imm((NS - 3) * NV));
       __syncthreads();
 #pragma unroll
       for (int v = 0; v < NV; ++v) issue(v, l_stage);
@@ -1275,7 +1279,7 @@ hipError_t launch_ring(GroupParams gp, hipStream_t s) {
     full += (int64_t)gp.p[g].tiles_m * gp.p[g].tiles_n;
   }
   int first_half = gp.count;   // problems [first_half, count) get tiles of BM/2 rows
-  if (BM == 2 * WM) {
+  if (kHalves<BM, BN, WM, WN, BKA>) {
     const int n_cu = compute_units();
     int64_t need = full % n_cu;
     if (full > n_cu && need > 0 && need <= n_cu / 2) {
@@ -1438,6 +1442,7 @@ int choose_tile(const BfParams* p, int count, bool ta, bool tb) {
   }
   bool segmented = false;
   for (int g = 0; g < count; ++g) segmented = segmented || p[g].seg_tiles > 1;
+  if (tile == 24 && tb) tile = 23;   // (a forced one)
   if (segmented && tile != 23 && tile != 24) tile = 22;   // only the ring kernels walk a segmented reduction range
   if (tile >= 22 && tile <= 24) {   // the ring kernels need a whole K tile (and nothing but whole ones in the pieces of a segmented range)
     const int bk = tile == 22 ? 64 : 32;
@@ -1458,7 +1463,9 @@ hipError_t pick_tile(const GroupParams& gp, hipStream_t s) {
     case 6: return launch<128, 128, 64, 64, 64, TA, TB, EPI, 2>(gp, s);   // two K groups of 4 waves
     case 22: return launch_ring<128, 128, 32, 64, 64, 4, TA, TB, EPI>(gp, s);   // 8 waves
     case 23: return launch_ring<256, 256, 128, 64, 32, 4, TA, TB, EPI>(gp, s);
-    case 24: return launch_ring<192, 256, 96, 64, 32, 4, TA, TB, EPI>(gp, s);
+    case 24:
+      if constexpr (!TB) return launch_ring<192, 256, 96, 64, 32, 4, TA, TB, EPI>(gp, s);
+      return hipErrorInvalidValue;
     case 32: return launch_split<1, 1, 8, TA, TB, EPI>(gp, s);
     case 64: return launch_split<2, 2, 4, TA, TB, EPI>(gp, s);
     default: return hipErrorInvalidValue;
