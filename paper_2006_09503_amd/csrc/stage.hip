@@ -492,10 +492,12 @@ hipError_t run_backward(stage2bw* st, int buf, int set, int pos, const int32_t* 
     const bool bf16 = st->dtype == kBF16;
     auto dgrad = [&](const void* grad, int N, int which, int64_t w_off, int K, void* out, const void* u, int next_layer,
                      int next_which, int64_t next_off, int64_t next_elems) {
-      // out[T,K] = grad[T,N] * W[K,N]^T.  Where the product runs on 256 x 256 tiles (bf16, at least 144 of them)
-      // it reads the transposed copy W^T [N,K] in the forward's operand form: measured 2 % (contraction 8192) to
-      // 16..28 % (16384 and up) faster there, while the 128 x 128 kernel of the small products, whose K tiles of 64
-      // already fetch whole 128-byte lines, is 10 % faster on W as it is stored.  fp32: W as it is stored.
+      // out[T,K] = grad[T,N] * W[K,N]^T.  Where the result has at least 144 tiles of 256 x 256 (bf16) the product reads the
+      // transposed copy W^T [N,K] in the forward's operand form: measured on those tiles 2 % (contraction 8192) to 16..28 %
+      // (16384 and up) faster, while the 128 x 128 kernel of the small products, whose K tiles of 64 already fetch whole
+      // 128-byte lines, is 10 % faster on W as it is stored.  Some of the former then run on 192 x 256 tiles, which exist in
+      // the forward's form only; a result between this line and theirs (132 of those tiles in one round) stays on W as it is
+      // stored.  fp32: W as it is stored.
       // next_*: the weights of the chain's next data-gradient GEMM, in the form that GEMM will read
       GemmDesc d;
       d.dtype = st->dtype;
@@ -540,8 +542,9 @@ hipError_t run_backward(stage2bw* st, int buf, int set, int pos, const int32_t* 
     ColsumItem cs[3];
     int n_cs = 0, col_dqkv = -1, col_du = -1, col_dy = -1, cols = 0;
     // fp32 mode, few tokens: the matrices themselves are partial rows that the stage's last reduction can sum, no more of them
-    // than the LayerNorm backward kernels leave (512); a launch less per layer (2 layers,
-    // h=128, 128 tokens, three batches of 4 microbatches: 2234 -> 2122 us).  Beyond, its few workgroups would walk too many rows
+    // than the LayerNorm backward kernels leave (512); a launch less per layer.  A batch of 4 microbatches and its update, one layer, in
+    // us: h=64 32 tokens 295 -> 282, 512 tokens 356 -> 344; h=256 128 tokens 463 -> 445, 512 tokens 596 -> 583; h=1024 512 tokens
+    // 2468 -> 2448.  Beyond, its few workgroups would walk too many rows
     const bool direct = st->dtype == kF32 && T <= 512;
     const bool sum_dqkv = !fused_dqkv && !direct, sum_du = !fused_du && !direct, sum_dy = l == c.n_layers - 1 && !direct;
     if (sum_dqkv) { col_dqkv = cols; cs[n_cs++] = {dqkv, 3 * h, 3 * h}; cols += 3 * h; }

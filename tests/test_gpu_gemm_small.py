@@ -18,7 +18,7 @@ from gpu_util import rel, to_host
 
 pytestmark = pytest.mark.gpu
 
-# the last two pick 64 x 64 tiles, and 128 x 128 tiles, by the rule on sizes
+# the last two pick 32 x 32 tiles in several rounds, and 128 x 128 tiles, by the rule on sizes
 SHAPES = [(1, 8, 1), (31, 33, 17), (32, 32, 16), (33, 65, 31), (64, 63, 128), (65, 128, 130), (129, 40, 7), (1024, 1030, 40), (4100, 2052, 24)]
 
 

@@ -335,7 +335,8 @@ def test_bias_gradient_column_sums(dtype, rows, n):
 @pytest.mark.parametrize("M,N,T,idx_a,idx_b", [
     (520, 264, 128, [3, 0, 2], [0, 1, 2]),                 # 128x128 ring tiles, K tiles of 64
     (264, 520, 64, [1], [2]),                              # one piece: the plain product
-    (3080, 3072, 96, [5, 1, 4, 0], [3, 2, 1, 0]),          # 256x256 ring tiles (K tiles of 32), ragged M
+    (3080, 3072, 96, [5, 1, 4, 0], [3, 2, 1, 0]),          # 204 tiles of 192x256 (K tiles of 32), ragged M: one round
+    (3080, 4352, 96, [5, 1, 4, 0], [3, 2, 1, 0]),          # 289 of those would not fit a round: 256x256 ring tiles, ragged M
     (2048, 2304, 64, [0, 1, 2, 3, 4, 5, 6, 7], [7, 6, 5, 4, 3, 2, 1, 0]),   # the maximum number of pieces
 ])
 def test_gemm_weight_gradient_over_several_microbatches(M, N, T, idx_a, idx_b):
@@ -412,7 +413,7 @@ def test_momentum_sgd_kernel():
 
 # ----------------------------------------------------------------------------- attention
 
-ATTN_SHAPES = [  # b, s, a, dh   (the last: three 256-row blocks per head, several heads and sequences)
+ATTN_SHAPES = [  # b, s, a, dh   (bf16: launches this small run on 64-row workgroups; test_gpu_attention_shapes.py has the others)
     (2, 50, 3, 24), (1, 200, 2, 64), (2, 130, 2, 80), (1, 257, 2, 128), (3, 64, 4, 32), (2, 700, 3, 64),
 ]
 
