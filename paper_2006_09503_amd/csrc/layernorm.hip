@@ -514,9 +514,7 @@ __global__ __launch_bounds__(512) void colsum_direct_kernel(const T* __restrict_
 #pragma unroll
       for (int u = 0; u < 4; ++u) load8(y + (int64_t)(r + u * 128) * n + col, v[u]);
 #pragma unroll
-      for (int u = 0; u < 4; ++u)
-#pragma unroll
-        for (int i = 0; i < 8; ++i) s[i] += v[u][i];
+      for (int i = 0; i < 8; ++i) s[i] += (v[0][i] + v[2][i]) + (v[1][i] + v[3][i]);
     }
     for (; r < rows; r += 128) {
       float v[8];
@@ -528,18 +526,27 @@ __global__ __launch_bounds__(512) void colsum_direct_kernel(const T* __restrict_
 #pragma unroll
   for (int i = 0; i < 8; ++i) part[rl][cc * 8 + i] = s[i];
   __syncthreads();
+  // the 128 partial sums of a column as a tree: 7 roundings deep (one after the other, eight and then sixteen, they left 6 % more
+  // error in fp32 than the two-launch form)
   const int c = tid & 31, g = tid >> 5;
-  float t = 0.f;
+  float t[16];
 #pragma unroll
-  for (int k = 0; k < 8; ++k) t += part[g * 8 + k][c];
-  part2[g][c] = t;
+  for (int k = 0; k < 8; ++k) t[k] = part[g * 8 + k][c];
+#pragma unroll
+  for (int w = 4; w > 0; w /= 2)
+#pragma unroll
+    for (int k = 0; k < w; ++k) t[k] += t[k + w];
+  part2[g][c] = t[0];
   __syncthreads();
   const int oc = blockIdx.x * 32 + tid;
   if (tid < 32 && oc < n) {
-    t = part2[0][tid];
 #pragma unroll
-    for (int k = 1; k < 16; ++k) t += part2[k][tid];
-    out[oc] = accumulate ? out[oc] + t : t;
+    for (int k = 0; k < 16; ++k) t[k] = part2[k][tid];
+#pragma unroll
+    for (int w = 8; w > 0; w /= 2)
+#pragma unroll
+      for (int k = 0; k < w; ++k) t[k] += t[k + w];
+    out[oc] = accumulate ? out[oc] + t[0] : t[0];
   }
 }
 

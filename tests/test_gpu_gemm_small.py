@@ -161,3 +161,20 @@ def test_column_sums_on_both_sides_of_the_one_launch_rule(dtype, rows, n):
     torch.cuda.synchronize()
     # sums of `rows` terms of size 1, each addition rounded to 2^-24 of a running sum of about sqrt(rows)
     assert np.abs(to_host(out) - 2 * y.astype(np.float64).sum(0)).max() < 1e-6 * rows + 1e-6
+
+
+def test_column_sums_of_one_launch_round_no_more_than_a_tree():
+    """128 rows, one to a thread: a tree of 7 additions per column, each off by 2^-24 / sqrt(3) of its result, leaves sqrt(7) of that;
+    eight and then sixteen partial sums one after the other leave more."""
+    L = B.lib()
+    n, err, size = 3072, 0.0, 0.0
+    ws = torch.empty(L.k2bw_bias_grad_workspace(n), device="cuda")
+    out = torch.empty(n, device="cuda")
+    for seed in range(6):
+        y = torch.randn((128, n), device="cuda", generator=torch.Generator(device="cuda").manual_seed(seed))
+        assert L.k2bw_bias_grad(0, 128, n, y.data_ptr(), out.data_ptr(), 0, ws.data_ptr(), None) == 0
+        torch.cuda.synchronize()
+        want = y.double().sum(0)
+        err += float(((out.double() - want) ** 2).sum())
+        size += float((want ** 2).sum())
+    assert (err / size) ** 0.5 < 7 ** 0.5 * 2.0 ** -24 / 3 ** 0.5
