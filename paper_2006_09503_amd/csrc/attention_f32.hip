@@ -31,9 +31,7 @@ namespace {
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
-// Waves per workgroup (NW): they split the streamed rows.  Four; one in launches of more blocks than CUs whose sequences are a
-// single tile: three waves would only wait, and a CU takes four workgroups instead of one (b=46 s=17 a=12 dh=64: forward
-// 17.9 -> 7.6 us, backward 57 -> 23; b=57 s=1 a=32 dh=32 12.8 -> 6.7, 67 -> 22).
+// Waves per workgroup (NW): four, which split the streamed rows, or one where a launch has blocks enough without that (one_wave)
 constexpr int kManyWaves = 4;
 constexpr int kRows = 32;               // rows a workgroup owns
 constexpr float kLog2e = 1.4426950408889634f;
@@ -533,6 +531,7 @@ namespace {
 // and the waves of a call
 template <template <int, int> class F, int NW, typename... Args>
 hipError_t by_head(const AttnDesc& d, Args... args) {
+  if (d.dh <= 16) return F<16, NW>::run(d, args...);   // (half of the score products of 32: b=60 s=178 a=32 dh=8 backward 560 -> 493 us)
   if (d.dh <= 32) return F<32, NW>::run(d, args...);
   if (d.dh <= 48) return F<48, NW>::run(d, args...);
   if (d.dh <= 64) return F<64, NW>::run(d, args...);
@@ -554,16 +553,33 @@ struct Bwd {
 }  // namespace
 
 namespace {
-bool one_wave(const AttnDesc& d) { return d.s <= kRows && (int64_t)d.b * d.a > gemm_compute_units(); }
+// A CU holds one workgroup of four waves (their registers fill it) or four of one wave (three in the backward pass of heads above 112,
+// whose LDS fills it).  With t tiles of 32 rows to stream and an overhead of about 1.2 tiles, `blocks` blocks take ceil(blocks / CUs)
+// rounds of ceil(t / 4) + 1.2 tiles, or ceil(blocks / 4 CUs) rounds of t + 1.2, each of those 1.2 times as long as it would be alone;
+// 1.35 times more under a causal mask in a launch of one round, which ends on its longest blocks; 1.4 times more in the forward pass of
+// heads up to 32, of whose four-wave workgroups a CU holds two.  One wave over four, forward | backward, dh=64: s=64 384 blocks
+// 0.83 | 0.81, 640 0.62 | 0.61; s=100 512 1.15 | 1.20, 1024 0.70 | 0.71; s=300 640 0.89 | 0.92 (causal 1.24 | 1.31), 1600 causal
+// 0.60 | 0.60; s=512 768 1.07 | 1.07, 1024 0.85 | 0.82; dh=32 s=160 640 causal 1.28 | 1.01; dh=128 s=300 960 0.73 | 1.35.  Over the 336
+// launches behind these the choice costs 0.8 % over the better one, and none is more than 5 % behind four waves.  Where one thread
+// per row had been ahead of four waves (us, one thread, four, one): b=60 s=40 a=32 dh=32 29 | 73, 30 | 148, 21 | 75; b=46 s=17 a=12
+// dh=64 21 | 52, 18 | 57, 7.6 | 23.
+bool one_wave(const AttnDesc& d, bool bwd) {
+  const int64_t tiles = ceil_div(d.s, kRows), blocks = (int64_t)d.b * d.a * tiles, cus = gemm_compute_units();
+  const int64_t at_once = cus * (bwd && d.dh > 112 ? 3 : 4);
+  double one = 1.2 * ceil_div(blocks, at_once) * (tiles + 1.2);
+  if (d.mask_mode == 1 && blocks <= at_once && tiles > 2) one *= 1.35;
+  if (!bwd && d.dh <= 32) one *= 1.4;
+  return one < ceil_div(blocks, cus) * (ceil_div(tiles, kManyWaves) + 1.2);
+}
 }  // namespace
 
 hipError_t attention_fwd_f32(const AttnDesc& d, const void* qkv, void* o, float* lse, hipStream_t st) {
-  return one_wave(d) ? by_head<Fwd, 1>(d, qkv, o, lse, st) : by_head<Fwd, kManyWaves>(d, qkv, o, lse, st);
+  return one_wave(d, false) ? by_head<Fwd, 1>(d, qkv, o, lse, st) : by_head<Fwd, kManyWaves>(d, qkv, o, lse, st);
 }
 
 hipError_t attention_bwd_f32(const AttnDesc& d, const void* qkv, const void* o, const float* lse, const void* d_o, void* dqkv, float* delta,
                              hipStream_t st) {
-  return one_wave(d) ? by_head<Bwd, 1>(d, qkv, o, lse, d_o, dqkv, delta, st) : by_head<Bwd, kManyWaves>(d, qkv, o, lse, d_o, dqkv, delta, st);
+  return one_wave(d, true) ? by_head<Bwd, 1>(d, qkv, o, lse, d_o, dqkv, delta, st) : by_head<Bwd, kManyWaves>(d, qkv, o, lse, d_o, dqkv, delta, st);
 }
 
 }  // namespace k2bw
