@@ -119,9 +119,10 @@ int k2bw_adam(int64_t n, const float* w_cur, float* w_next, void* w_next_bf16, f
 /* Tuning aid: force the bf16 GEMM's kernel variant (0 = built-in choice).  Register-staged:
  * 2: 128x128 tile / 4 waves, 3: 256x256 / 8 waves, 6: 128x128 with two K groups of 4 waves.
  * Direct-to-LDS loads through a ring of four LDS stages: 22: 128x128 / 8 waves, K tiles of 64;
- * 23: 256x256 / 8 waves, 24: 192x256 / 8 waves, K tiles of 32 (K below one K tile: 6 and 3 instead; 24 with both operands
- * contiguous along K: 23).  The same loads with the reduction range split over the waves of a workgroup: 32: 32x32 / 8 waves,
- * 64: 64x64 / 4 waves.
+ * 23: 256x256 / 8 waves, 24: 192x256 / 8 waves, K tiles of 32.  The same loads, K tiles of 64, two groups of four waves taking
+ * turns: 25: 256x256, 26: 192x256, 27: 128x256.  The same loads with the reduction range split over the waves of a workgroup:
+ * 32: 32x32 / 8 waves, 64: 64x64 / 4 waves.  Where the operand form or K (below one K tile) does not have the variant, the
+ * built-in choice runs.
  * Other ids: INVALID_ARG.  Process-wide. */
 int k2bw_tune_gemm_tile(int id);
 

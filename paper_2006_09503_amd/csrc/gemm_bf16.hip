@@ -722,7 +722,8 @@ template <int R>
 __device__ __forceinline__ int swz_strided(int k) { return (k & (R >= 64 ? 3 : 1)) << 1; }
 
 // (Tiles of 192 rows: 12 load instructions for 8 waves, so four waves issue one more than the others.)
-template <int R, int NW, int BKA, bool K_CONTIG>
+// S < R: the tile's rows are strips of S rows, each S2 rows further down the matrix than the one before.
+template <int R, int NW, int BKA, bool K_CONTIG, int S = R, int S2 = R>
 struct AsyncLoader {
   static constexpr int CHK = BKA / 8;               // chunks per row of a K-contiguous tile
   static constexpr int kSlots = R * CHK;            // 16-byte slots per tile
@@ -734,7 +735,8 @@ struct AsyncLoader {
   uint32_t voff[IPW];   // byte offsets from the tile's base
   int ld_, first_slot_;
   __device__ __forceinline__ int slot(int j) const { return first_slot_ + j * (kEven ? 64 : NW * 64); }
-  __device__ __forceinline__ void init(const bf16_t* base, int ld, int rows_valid, int wave, int lane) {
+  // first: the matrix row of the tile's first one, counted from base
+  __device__ __forceinline__ void init(const bf16_t* base, int ld, int rows_valid, int wave, int lane, int first = 0) {
     base_ = base; ld_ = ld;
     first_slot_ = wave * (kEven ? IPW : 1) * 64;
 #pragma unroll
@@ -743,13 +745,14 @@ struct AsyncLoader {
       if (K_CONTIG) {
         const int row = L / CHK, pc = L % CHK;
         const int c = pc ^ swz<CHK>(row);
-        const int rc = row < rows_valid ? row : rows_valid - 1;
+        const int rs = first + (S == R ? row : row / S * S2 + row % S);
+        const int rc = rs < rows_valid ? rs : rows_valid - 1;
         voff[j] = ((uint32_t)rc * (uint32_t)ld + c * 8) * 2u;
       } else {
         constexpr int PPR = R / 8;                  // pieces per k row
         const int k = L / PPR, pp = L % PPR;
         const int piece = pp ^ swz_strided<R>(k);
-        int col = piece * 8;
+        int col = first + (S == R ? piece * 8 : piece * 8 / S * S2 + piece * 8 % S);
         if (col >= rows_valid) col = rows_valid - 8;
         voff[j] = ((uint32_t)k * (uint32_t)ld + col) * 2u;
       }
@@ -873,10 +876,10 @@ constexpr int vmcnt_imm(int n) { return (n & 15) | ((n >> 4) << 14) | (7 << 4) |
 // the other 24).  With more than two stages the stage that tile kt+NS-1 goes to is already free
 // during the whole of step kt, so its loads are issued one at a time between the MFMAs of all
 // sub-steps and the queue never fills; a load has NS-2 steps to land.  256x256 tiles: four stages
-// of K = 32 (128 KB).  128x128 tiles: four stages of K = 64; with K = 32 (half a 128-byte line per
+// of K = 32 (128 KB); the phased kernel took over their forms with an operand along K.  128x128 tiles: four stages of K = 64; with K = 32 (half a 128-byte line per
 // row and load) that tile is 10..15 % slower once the operands come from HBM, as they do inside
 // the stage, with four stages or with eight.
-// Whether a launch of such tiles may end with tiles of half the height (see launch_ring): 256x256 ones, whose loads divide evenly
+// Whether a launch of such tiles may end with tiles of half the height (see launch_tiles): 256x256 ones, whose loads divide evenly
 // among the waves.  (192x256 tiles are only taken where they fit into one round.)
 template <int BM, int BN, int WM, int WN, int BKA>
 constexpr bool kHalves = BM == 2 * WM && BM * (BKA / 8) % (64 * (BM / WM) * (BN / WN)) == 0;
@@ -896,7 +899,7 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void gemm_bf16_ring_ker
   const BfParams p = select_problem(gp, wg, g);
   int bm, bn;
   tile_coords(wg, p.tiles_m, p.tiles_n, bm, bn);
-  // A launch may end with tiles of BM/2 rows (see launch_ring): the waves of the lower half then only
+  // A launch may end with tiles of BM/2 rows (see launch_tiles): the waves of the lower half then only
   // take part in the loads and barriers.
   constexpr bool kCanHalve = kHalves<BM, BN, WM, WN, BKA>;
   const int tile_m = kCanHalve ? p.tile_m : BM;
@@ -1056,6 +1059,180 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void gemm_bf16_ring_ker
   epilogue<MI, NI, WM, WN, EPI>(acc, gp.p[g], m0, n0, wm, wn, lane, smem, wave, 0, MI);
 }
 
+
+// ------------------------------------------------------------------------------------------------
+// The phased kernel: K tiles of 64 through two LDS stages, the eight waves in two groups of four (one of each group on every
+// SIMD) that are half a step apart: while one group runs its MFMAs, the other reads its next fragments and issues loads, and
+// barriers keep the two from drifting.  In the ring kernel both waves of a SIMD arrive at the same barrier together and the matrix
+// pipe drains there; and its K tiles of 32 make 64-byte row pieces of an operand that is contiguous along K, for which the L1 fetches
+// every line twice (time, and on long launches power).  K tiles of 64 leave room for two stages only, so a stage must come free
+// early for its refill to have time: a step works on the wave's rows in two parts, one after the other, with all fragments of B in
+// registers.  Per step k and wave:
+//   read B and the first part of A of tile k; issue the second part of A of tile k + 1
+//   MFMAs of the first part
+//   read the second part of A; issue B and the first part of A of tile k + 2, which go where those of tile k were
+//   MFMAs of the second part
+// with a barrier after each.  What a group reads in a phase was waited for, by the waves that had loaded it, before the barrier in
+// front of it; what it overwrites had been read (lgkmcnt) by both groups before that.  Every load has four phases, about a
+// microsecond, to land.  Rows of the two parts alternate in strips of a wave's share (AsyncLoader's S, S2).
+// Bound by power on long launches (see the tile table for sizes).  TFLOP/s before (ring) | now, N(0,1) operands: both operands along
+// K 8192^3 1285 | 1452, 2048 x 8192 x 32768 1079 | 1421, 2048 x 32768 x 8192 1233 | 1375, 4096 x 2560 x 10240 1090 | 1218; forward
+// 8192^3 1341 | 1409, 2048 x 32768 x 8192 1289 | 1389; weight gradient 8192^3 1279 | 1300.
+constexpr int kPhasedK = 64;
+
+template <int BM, int BN, int WM, int WN, bool TA, bool TB, int EPI>
+__device__ __forceinline__ void phased_tile(const BfParams& p, const BfParams& p_epi, int m0, int n0, uint4* smem) {
+  constexpr int BKA = kPhasedK, CHK = BKA / 8, KS = BKA / 16, NW = 8;
+  static_assert((BM / WM) * (BN / WN) == NW, "two groups of four waves");
+  constexpr int MI = WM / 32, NI = WN / 32, WAVES_N = BN / WN;
+  constexpr int MI0 = (MI + 1) / 2, MI1 = MI / 2;            // blocks of 32 rows of a wave in either part of the A tile
+  constexpr int R0 = BM / WM * MI0 * 32, R1 = BM / WM * MI1 * 32;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave / WAVES_N, wn = wave % WAVES_N;
+
+  AsyncLoader<R0, NW, BKA, !TA, MI0 * 32, WM> ld_a0;
+  AsyncLoader<R1, NW, BKA, !TA, MI1 * 32, WM> ld_a1;
+  AsyncLoader<BN, NW, BKA, TB> ld_b;
+  const int rows_a = p.M - m0;
+  const bf16_t* a_base = TA ? p.A + m0 : p.A + (int64_t)m0 * p.lda;
+  ld_a0.init(a_base, p.lda, rows_a, wave, lane);
+  ld_a1.init(a_base, p.lda, rows_a, wave, lane, MI0 * 32);
+  ld_b.init(TB ? p.B + (int64_t)n0 * p.ldb : p.B + n0, p.ldb, p.N - n0, wave, lane);
+  constexpr int IP0 = decltype(ld_a0)::IPW, IP1 = decltype(ld_a1)::IPW, IPB = decltype(ld_b)::IPW, NV = IP0 + IP1 + IPB;
+  static_assert(decltype(ld_a0)::kEven && decltype(ld_a1)::kEven && decltype(ld_b)::kEven, "every wave issues the same loads");
+
+  // LDS, in uint4: A as [stage][part], B as [stage]
+  constexpr int kA = BM * CHK, kA0 = R0 * CHK, kB = BN * CHK;
+  f32x16 acc[MI][NI];
+#pragma unroll
+  for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+    for (int ni = 0; ni < NI; ++ni)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[mi][ni][r] = 0.f;
+
+  const int nk_whole = p.K / BKA, rem = p.K % BKA;
+  const int nk = nk_whole + (rem > 0);
+  const uint32_t lds_a = __builtin_amdgcn_readfirstlane((uint32_t)reinterpret_cast<uintptr_t>(smem));
+  const uint32_t lds_b = lds_a + (uint32_t)(2 * kA) * 16u;
+  TileWalk walk;
+  walk.init(a_base, ld_b.base_, ld_a0.tile_step_bytes(), ld_b.tile_step_bytes(), p, nk_whole);
+  auto issue_b_a0 = [&](int st) __attribute__((always_inline)) {
+#pragma unroll
+    for (int v = 0; v < IPB; ++v) ld_b.issue_one_untracked(v, walk.b_addr, lds_b + (uint32_t)(st * kB) * 16u);
+#pragma unroll
+    for (int v = 0; v < IP0; ++v) ld_a0.issue_one_untracked(v, walk.a_addr, lds_a + (uint32_t)(st * kA) * 16u);
+  };
+  auto issue_a1 = [&](int st) __attribute__((always_inline)) {
+#pragma unroll
+    for (int v = 0; v < IP1; ++v) ld_a1.issue_one_untracked(v, walk.a_addr, lds_a + (uint32_t)(st * kA + kA0) * 16u);
+  };
+  uint32_t touched = 0;   // as in the ring kernel
+  if (p.prefetch != nullptr) {
+    const uint32_t line = ((uint32_t)blockIdx.x * NW + (uint32_t)wave) * 64u + (uint32_t)lane;
+    const uint32_t off = min(line * 128u, p.prefetch_bytes - 4u);
+    asm volatile("global_load_dword %0, %1, %2" : "=v"(touched) : "v"(off), "s"(uniform_address(p.prefetch)) : "memory");
+  }
+  if (rem > 0) {   // uniform; the partial tile comes first, as in the ring kernel
+    const uint64_t a_tail = walk.a_addr + (uint64_t)walk.a_step * (uint32_t)nk_whole, b_tail = walk.b_addr + (uint64_t)walk.b_step * (uint32_t)nk_whole;
+#pragma unroll
+    for (int v = 0; v < IPB; ++v) ld_b.issue_partial(v, b_tail, lds_b, rem, lane);
+#pragma unroll
+    for (int v = 0; v < IP0; ++v) ld_a0.issue_partial(v, a_tail, lds_a, rem, lane);
+#pragma unroll
+    for (int v = 0; v < IP1; ++v) ld_a1.issue_partial(v, a_tail, lds_a + (uint32_t)kA0 * 16u, rem, lane);
+  } else {
+    issue_b_a0(0);
+    issue_a1(0);
+    walk.advance();
+  }
+  issue_b_a0(1);
+  if (rem > 0) __builtin_amdgcn_s_waitcnt(vmcnt_imm(IPB + IP0));   // all of tile 0
+  else __builtin_amdgcn_s_waitcnt(vmcnt_imm(NV));                  // its B and first A part
+  asm volatile("" : "+v"(touched));   // the touch has landed: last use of its register
+  __syncthreads();
+  if (rem > 0) {
+    decltype(ld_a0)::zero_past_end(smem, rem, tid, NW * 64);
+    decltype(ld_a1)::zero_past_end(smem + kA0, rem, tid, NW * 64);
+    decltype(ld_b)::zero_past_end(smem + 2 * kA, rem, tid, NW * 64);
+    __syncthreads();
+  }
+  auto barrier = [&]() __attribute__((always_inline)) {
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_barrier" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  // everything this wave has issued but the newest NV loads has landed, and its LDS reads are done
+  auto settle = [&]() __attribute__((always_inline)) {
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(vmcnt_imm(NV) & ~(15 << 8));
+    barrier();
+  };
+  // the second group runs one phase behind the first (and the first waits for it at the end)
+  const bool late = wave >= NW / 2;
+  if (late) barrier();
+  auto step = [&](int st) __attribute__((always_inline)) {
+    const uint4* sA = smem + st * kA;
+    const uint4* sB = smem + 2 * kA + st * kB;
+    bf16x8 af[KS][MI0], bfr[KS][NI];
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+#pragma unroll
+      for (int ni = 0; ni < NI; ++ni) bfr[ks][ni] = read_frag<BN, BKA, TB>(sB, wn * WN + ni * 32, ks, lane);
+#pragma unroll
+      for (int mi = 0; mi < MI0; ++mi) af[ks][mi] = read_frag<R0, BKA, !TA>(sA, wm * (MI0 * 32) + mi * 32, ks, lane);
+    }
+    issue_a1(st ^ 1);
+    walk.advance();
+    settle();
+    __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+      for (int mi = 0; mi < MI0; ++mi)
+#pragma unroll
+        for (int ni = 0; ni < NI; ++ni)
+          acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[ks][ni], af[ks][mi], acc[mi][ni], 0, 0, 0);
+    __builtin_amdgcn_s_setprio(0);
+    barrier();
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+      for (int mi = 0; mi < MI1; ++mi) af[ks][mi] = read_frag<R1, BKA, !TA>(sA + kA0, wm * (MI1 * 32) + mi * 32, ks, lane);
+    issue_b_a0(st);
+    settle();
+    __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+      for (int mi = 0; mi < MI1; ++mi)
+#pragma unroll
+        for (int ni = 0; ni < NI; ++ni)
+          acc[MI0 + mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[ks][ni], af[ks][mi], acc[MI0 + mi][ni], 0, 0, 0);
+    __builtin_amdgcn_s_setprio(0);
+    barrier();
+  };
+  int kt = 0;
+  for (; kt + 2 <= nk; kt += 2) { step(0); step(1); }
+  if (kt < nk) step(0);
+  if (!late) barrier();
+  __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+  __syncthreads();
+  epilogue<MI, NI, WM, WN, EPI>(acc, p_epi, m0, n0, wm, wn, lane, smem, wave, 0, MI);
+}
+
+template <int BM, int BN, int WM, int WN, bool TA, bool TB, int EPI>
+__global__ __launch_bounds__(512) void gemm_bf16_phased_kernel(LaunchParams<EPI> gp) {
+  extern __shared__ uint4 smem[];
+  int wg, g;
+  const BfParams p = select_problem(gp, wg, g);
+  int bm, bn;
+  tile_coords(wg, p.tiles_m, p.tiles_n, bm, bn);
+  // (tiles of half the height, see launch_tiles: their 128 rows on all eight waves)
+  if (BM == 256 && p.tile_m == 128) phased_tile<128, BN, 64, 64, TA, TB, EPI>(p, gp.p[g], bm * 128, bn * BN, smem);   // wave-uniform
+  else phased_tile<BM, BN, WM, WN, TA, TB, EPI>(p, gp.p[g], bm * BM, bn * BN, smem);
+}
 
 // ------------------------------------------------------------------------------------------------
 // Products with few tiles.  A workgroup owns a tile of 32*MB x 32*NB and its kSplit waves share the reduction range: wave w takes
@@ -1256,19 +1433,8 @@ BfParams lower_rows(const BfParams& q, int m_split) {
 // round then takes about 0.6 of a full one (the B tile is still loaded whole).  The halved tiles
 // are the launch's last problems, or the last tile rows of one that is split in two for this;
 // they are dispatched last because the XCD remap treats them as a segment of its own.
-template <int BM, int BN, int WM, int WN, int BKA, int NS, bool TA, bool TB, int EPI>
-hipError_t launch_ring(GroupParams gp, hipStream_t s) {
-  constexpr int NT = (BM / WM) * (BN / WN) * 64;
-  constexpr size_t lds = NS * (BM + BN) * (BKA / 8) * sizeof(uint4);
-  static_assert(lds <= 160 * 1024, "LDS of a CU");
-  auto kern = gemm_bf16_ring_kernel<BM, BN, WM, WN, BKA, NS, TA, TB, EPI>;
-  static bool configured = false;
-  if (!configured) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-    configured = true;
-  }
+template <int BM, int BN, int BKA, bool HALVES, bool TA, int EPI>
+hipError_t launch_tiles(void (*kern)(LaunchParams<EPI>), int threads, size_t lds, GroupParams gp, hipStream_t s) {
   int64_t full = 0;
   for (int g = 0; g < gp.count; ++g) {
     // (seg_tiles arrives as the number of pieces; choose_tile has checked that a piece is whole K tiles)
@@ -1279,7 +1445,7 @@ hipError_t launch_ring(GroupParams gp, hipStream_t s) {
     full += (int64_t)gp.p[g].tiles_m * gp.p[g].tiles_n;
   }
   int first_half = gp.count;   // problems [first_half, count) get tiles of BM/2 rows
-  if (kHalves<BM, BN, WM, WN, BKA>) {
+  if (HALVES) {
     const int n_cu = compute_units();
     int64_t need = full % n_cu;
     if (full > n_cu && need > 0 && need <= n_cu / 2) {
@@ -1318,8 +1484,38 @@ hipError_t launch_ring(GroupParams gp, hipStream_t s) {
   gp.seg0 = full_tiles / 256 * 256;
   gp.seg1 = (full_tiles - gp.seg0) / 8 * 8;
   gp.seg2 = (total - gp.seg0 - gp.seg1) / 8 * 8;
-  hipLaunchKernelGGL(kern, dim3(total), dim3(NT), lds, s, launch_params<EPI>(gp));
+  hipLaunchKernelGGL(kern, dim3(total), dim3(threads), lds, s, launch_params<EPI>(gp));
   return hipGetLastError();
+}
+
+template <int BM, int BN, int WM, int WN, int BKA, int NS, bool TA, bool TB, int EPI>
+hipError_t launch_ring(const GroupParams& gp, hipStream_t s) {
+  constexpr size_t lds = NS * (BM + BN) * (BKA / 8) * sizeof(uint4);
+  static_assert(lds <= 160 * 1024, "LDS of a CU");
+  auto kern = gemm_bf16_ring_kernel<BM, BN, WM, WN, BKA, NS, TA, TB, EPI>;
+  static bool configured = false;
+  if (!configured) {
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+    configured = true;
+  }
+  return launch_tiles<BM, BN, BKA, kHalves<BM, BN, WM, WN, BKA>, TA, EPI>(kern, (BM / WM) * (BN / WN) * 64, lds, gp, s);
+}
+
+template <int BM, int BN, int WM, int WN, bool TA, bool TB, int EPI>
+hipError_t launch_phased(const GroupParams& gp, hipStream_t s) {
+  constexpr size_t lds = 2 * (BM + BN) * (kPhasedK / 8) * sizeof(uint4);
+  static_assert(lds <= 160 * 1024, "LDS of a CU");
+  auto kern = gemm_bf16_phased_kernel<BM, BN, WM, WN, TA, TB, EPI>;
+  static bool configured = false;
+  if (!configured) {
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+    configured = true;
+  }
+  return launch_tiles<BM, BN, kPhasedK, BM == 256, TA, EPI>(kern, 512, lds, gp, s);
 }
 
 template <int BM, int BN, int WM, int WN, int BK, bool TA, bool TB, int EPI, int KSPLIT = 1>
@@ -1382,94 +1578,117 @@ hipError_t launch_split(GroupParams gp, hipStream_t s) {
 
 int g_tile_override = 0;  // 0: heuristic; else force a tile shape (tuning aid)
 
-// Tile choice for a (grouped) problem; ta/tb as in GemmDesc.
+// Estimated time of a launch, in microseconds, with r tiles per CU, R = ceil(r) rounds and K in thousands:
+//   fixed + round R + round_k K R + tile r + (tile_k + off_k [K not a multiple of 64]) K r
+// (a round costs time whether or not its CUs all have a tile; tiles cost memory traffic and, on a full chip, clock).
+// A tile shape is open to a problem if K is at least `whole` (its K tile; 0: any K).
+struct TileCost { int id, bm, bn, whole; double fixed, round, round_k, tile_k, tile, off_k; };
+
+// The tile shapes of the three operand forms and the constants of the estimate.  Fitted, with each shape forced, to 3300 launches of
+// random sizes (48 to 16384 rows and columns, K of 96 to 16384; those within 1.4 of the best shape of their size): 4 to 10 % off the
+// measured times, 64x64 and 32x32 tiles 12 to 16 %.  Time of the choice over the best shape of each size, geometric mean: forward
+// 1.004, both operands along K 1.007, weight gradient 1.004 (with the lines in use before the phased kernels, whose shapes were 23,
+// 24 and the staged ones: 1.025, 1.036, 1.017; slowest against those 1.20, 1.08 and 1.08).
+// What a form does without: the ring's 256x256 tiles are 4 to 17 % behind the phased ones from K = 512 on except in the weight
+// gradient (1.02 below K = 512, then 1.00, 0.97 from 2048: not worth a second instance); 192x256 tiles are even between ring and
+// phased in the forward form, 5 to 14 % behind on the phased kernel in the weight gradient; register-staged 128x128 tiles, two
+// workgroups per CU, win in the weight gradient only, with two K groups only where both operands run along K.
+constexpr TileCost kForwardTiles[] = {
+    {22, 128, 128, 64, 1.8, 2.7, 5.0, 2.2, 0.7, 2.2},    {25, 256, 256, 64, 1.1, 7.6, 10.5, 12.7, 1.8, 0},
+    {24, 192, 256, 32, 2.0, 4.7, 9.6, 9.7, 2.1, 0},      {27, 128, 256, 64, 2.1, 3.4, 8.9, 4.5, 2.0, 0},
+    {64, 64, 64, 0, 1.45, 2.4, 2.7, 2.0, 0, 0},          {32, 32, 32, 0, 1.4, 1.6, 0.97, 1.4, 0, 0},
+    {3, 256, 256, 0, 2.7, 5.5, 18.0, 10.0, 1.8, 1.8}};
+constexpr TileCost kDataTiles[] = {   // both operands along K
+    {22, 128, 128, 64, 1.4, 3.0, 4.5, 2.55, 0.5, 4.1},   {25, 256, 256, 64, 0, 8.1, 12.1, 10.3, 2.8, 0},
+    {26, 192, 256, 64, 2.2, 3.9, 10.2, 7.3, 4.1, 0},     {27, 128, 256, 64, 1.1, 4.6, 7.2, 5.8, 1.7, 0},
+    {64, 64, 64, 0, 1.65, 2.2, 2.5, 2.4, 0, 0},          {32, 32, 32, 0, 1.55, 1.55, 0.83, 1.1, 0, 0},
+    {3, 256, 256, 0, 2.85, 4.6, 17.9, 9.1, 2.8, 2.7},    {6, 128, 128, 0, 1.8, 3.3, 6.7, 1.9, 1.3, 1.5}};
+constexpr TileCost kWeightTiles[] = {
+    {22, 128, 128, 64, 1.0, 4.5, 5.4, 2.3, 2.3, 1.0},    {23, 256, 256, 32, 0.4, 8.8, 13.5, 11.1, 13.0, 0},
+    {24, 192, 256, 32, 0.8, 7.0, 10.1, 7.9, 9.4, 0},     {27, 128, 256, 64, 0.4, 6.8, 8.7, 5.5, 4.6, 0},
+    {64, 64, 64, 0, 1.3, 3.05, 2.6, 1.9, 0, 0},          {32, 32, 32, 0, 1.4, 1.9, 0.93, 1.9, 0, 0},
+    {2, 128, 128, 0, 1.9, 4.0, 7.7, 5.5, 2.4, 0.5}};
+
+// Tile choice for a (grouped) problem; ta/tb as in GemmDesc.  A forced shape that the form has not or that is not open to the problem
+// gives way to the best open one.  -1: no shape is open (a segmented range that is not made of whole K tiles).
 int choose_tile(const BfParams* p, int count, bool ta, bool tb) {
-  int tile = g_tile_override;
-  if (tile == 0) {
-    // Every line below was drawn from launches of 660 random sizes (M, N, K of 8 to 16384, half of them near the lines) with each
-    // tile forced; over these the choice costs 1.3 % over the best tile on average.
-    //
-    // 192x256 where they fit into one round and the forms read B along its rows: against 256x256 tiles 5..14 % less time (4096 x
-    // 2560 x 2560 60.5 -> 55.4 us).  Against two 128x128 workgroups per CU, time of 192x256 over that of 128x128: forward K < 128
-    // 1.05, from there 0.97 (K < 512), 0.89, 0.85, 0.80 (K >= 2048); weight gradient, which pays for C by the tile, K < 512 1.14,
-    // < 1024 1.02, < 2048 0.92, above 0.83.  Beyond two 128x128 tiles per CU, a third round of those, 0.9 down to 0.55.  (With both
-    // operands along K they gain nothing over 256x256: 4096 x 2560 x 10240 198 -> 206 us.)
-    // 256x256 from 144 tiles on.  With both operands along K and a partial K tile the register-staged kernel of that tile: the rows
-    // then start off the 128-byte lines, which the direct-to-LDS loads pay for twice (staged over ring 0.97, elsewhere 1.02..1.2).
-    // More 128x128 tiles than CUs: two register-staged workgroups per CU while their overlap is worth more than the ring; ring over
-    // staged: forward K < 128 1.18, < 512 1.01 (off the lines 1.09), < 1024 0.90 (1.02), above 0.83 (0.93); both along K 1.19, 1.05
-    // (1.16), 0.95 (1.15), 0.87 (1.05); weight gradient K < 512 1.2, < 1024 1.07, < 2048 1.0, above 0.90.
-    // Fewer: the least estimated time of 128x128, of 64x64 and of 32x32 tiles with K split over the waves, below.  Forward | data |
-    // weight gradient, tiles 128 (register-staged), 128 ring, 64, 32 in us: 128 tokens 1024 -> 3072: 17.3|35.0|8.7, 9.9|17.9|7.7,
-    // 7.2|10.6|11.1, 7.9|6.1|24.8; 1000 tokens 768 -> 2304: 14.9|27.3|17.4, 9.8|16.0|13.2, 15.3|10.0|14.0, 26.6|15.5|32.8.
-    int64_t big = 0, t192 = 0, t128 = 0, t64 = 0, t32 = 0;
-    int K = 0;
-    for (int g = 0; g < count; ++g) {
-      big += (int64_t)ceil_div(p[g].M, 256) * ceil_div(p[g].N, 256);
-      t192 += (int64_t)ceil_div(p[g].M, 192) * ceil_div(p[g].N, 256);
-      t128 += (int64_t)ceil_div(p[g].M, 128) * ceil_div(p[g].N, 128);
-      t64 += (int64_t)ceil_div(p[g].M, 64) * ceil_div(p[g].N, 64);
-      t32 += (int64_t)ceil_div(p[g].M, 32) * ceil_div(p[g].N, 32);
-      K = p[g].K > K ? p[g].K : K;
-    }
-    const int cus = compute_units();
-    const bool off_lines = K % 64 != 0;   // rows along K that are not whole 128-byte lines
-    if (!tb && t192 >= 132 && t192 <= cus && big < cus && (big >= 144 || t128 > 2 * cus || K >= (ta ? 1024 : 128))) {
-      tile = 24;
-    } else if (big >= 144) {
-      tile = tb && K % 32 ? 3 : 23;
-    } else if (t128 > cus) {
-      tile = K < (ta ? 1536 : off_lines ? 1024 : 512) || (tb && off_lines) ? 2 : 22;
-    } else {
-      // In microseconds, with R tiles per CU, C = ceil(R) rounds and K in thousands: a fixed part, one per round, and per k a part
-      // by rounds and one by tiles (bytes); 7 to 13 % off the measured times
-      struct TileCost { double c0, round, round_k, tile_k; };
-      static constexpr TileCost kCost[3][3] = {
-          {{2.8, 1.7, 5.6, 3.5}, {1.45, 2.4, 2.7, 2.0}, {1.4, 1.6, 0.97, 1.4}},    // forward
-          {{2.6, 1.8, 5.2, 5.7}, {1.65, 2.2, 2.5, 2.4}, {1.55, 1.55, 0.83, 1.1}},  // both operands along K
-          {{3.2, 2.6, 5.6, 2.6}, {1.3, 3.05, 2.6, 1.9}, {1.4, 1.9, 0.93, 1.9}}};   // weight gradient
-      const int64_t tiles[3] = {t128, t64, t32};
-      double cost[3];
-      for (int e = 0; e < 3; ++e) {
-        const TileCost& q = kCost[ta ? 2 : tb ? 1 : 0][e];
-        const double r = (double)tiles[e] / cus, c = ceil_div(tiles[e], cus);
-        cost[e] = q.c0 + q.round * c + (q.round_k * c + q.tile_k * r) * K * 1e-3;
-      }
-      if (cost[2] < cost[1] && cost[2] < cost[0]) tile = 32;
-      else if (cost[1] < cost[0]) tile = 64;
-      else tile = tb && off_lines && K >= 4096 ? 6 : 22;   // (ring over two K groups: 1.02 there, 0.98 from 2048, below 0.83)
-    }
+  int K = 0;
+  bool segmented = false, odd_pieces = false;
+  for (int g = 0; g < count; ++g) {
+    K = p[g].K > K ? p[g].K : K;
+    segmented = segmented || p[g].seg_tiles > 1;
+    odd_pieces = odd_pieces || (p[g].seg_tiles > 1 && p[g].K / p[g].seg_tiles % 64 != 0);
   }
-  bool segmented = false;
-  for (int g = 0; g < count; ++g) segmented = segmented || p[g].seg_tiles > 1;
-  if (tile == 24 && tb) tile = 23;   // (a forced one)
-  if (segmented && tile != 23 && tile != 24) tile = 22;   // only the ring kernels walk a segmented reduction range
-  if (tile >= 22 && tile <= 24) {   // the ring kernels need a whole K tile (and nothing but whole ones in the pieces of a segmented range)
-    const int bk = tile == 22 ? 64 : 32;
+  const int cus = compute_units();
+  auto cost_of = [&](const TileCost& q) {   // below zero: not open
+    // only the direct-to-LDS kernels walk a segmented reduction range, of whole K tiles
+    const bool direct = q.id >= 22 && q.id <= 27;
+    if (segmented && !direct) return -1.0;
+    int64_t tiles = 0;
     for (int g = 0; g < count; ++g) {
-      const bool ok = p[g].seg_tiles > 1 ? (p[g].K / p[g].seg_tiles) % bk == 0 : p[g].K >= bk;
-      if (!ok) { tile = segmented ? -1 : tile == 22 ? 6 : 3; break; }
+      if (p[g].seg_tiles > 1 ? (p[g].K / p[g].seg_tiles) % q.whole != 0 : p[g].K < q.whole) return -1.0;
+      tiles += (int64_t)ceil_div(p[g].M, q.bm) * ceil_div(p[g].N, q.bn);
     }
-  }
-  return tile;
+    // (the long grouped launches over several microbatches keep square tiles: fewest operand bytes per flop; pieces that are not
+    // multiples of 64, beyond what the interface promises, are taken from 144 square tiles on, or 132 of 192x256 in one round of them)
+    if (segmented && (q.id == 23 || q.id == 24)) {
+      if (q.id == 24 && tiles > cus) return -1.0;
+      if (odd_pieces && tiles < (q.id == 23 ? 144 : 132)) return -1.0;
+    }
+    const int slots = q.id == 2 ? 2 * cus : cus;   // the register-staged workgroups of four waves share a CU
+    double rounds = (double)ceil_div(tiles, (int64_t)slots);
+    // tiles of half the height in the last round (launch_tiles) take 0.6 of a whole one
+    if ((q.id == 23 || q.id == 25) && tiles > cus && tiles % cus > 0 && tiles % cus <= cus / 2) rounds -= 0.4;
+    const double r = (double)tiles / cus, k = K * 1e-3;
+    return q.fixed + q.round * rounds + q.round_k * k * rounds + q.tile * r + (q.tile_k + (K % 64 ? q.off_k : 0.0)) * k * r;
+  };
+  auto pick = [&](const TileCost* list, int n) {
+    int best = -1;
+    double least = 0;
+    for (int i = 0; i < n; ++i) {
+      const double c = cost_of(list[i]);
+      if (c < 0) continue;
+      if (list[i].id == g_tile_override) return list[i].id;
+      if (best < 0 || c < least) { best = list[i].id; least = c; }
+    }
+    return best;
+  };
+  if (ta) return pick(kWeightTiles, sizeof kWeightTiles / sizeof *kWeightTiles);
+  if (tb) return pick(kDataTiles, sizeof kDataTiles / sizeof *kDataTiles);
+  return pick(kForwardTiles, sizeof kForwardTiles / sizeof *kForwardTiles);
 }
 
 template <bool TA, bool TB, int EPI>
 hipError_t pick_tile(const GroupParams& gp, hipStream_t s) {
-  const int tile = choose_tile(gp.p, gp.count, TA, TB);
-  switch (tile) {
-    case 2: return launch<128, 128, 64, 64, 64, TA, TB, EPI>(gp, s);
-    case 3: return launch<256, 256, 128, 64, 64, TA, TB, EPI>(gp, s);   // 8 waves
-    case 6: return launch<128, 128, 64, 64, 64, TA, TB, EPI, 2>(gp, s);   // two K groups of 4 waves
+  switch (choose_tile(gp.p, gp.count, TA, TB)) {   // the instances are those of the tables above
+    case 2:
+      if constexpr (TA) return launch<128, 128, 64, 64, 64, TA, TB, EPI>(gp, s);
+      break;
+    case 3:
+      if constexpr (!TA) return launch<256, 256, 128, 64, 64, TA, TB, EPI>(gp, s);   // 8 waves
+      break;
+    case 6:
+      if constexpr (TB) return launch<128, 128, 64, 64, 64, TA, TB, EPI, 2>(gp, s);   // two K groups of 4 waves
+      break;
     case 22: return launch_ring<128, 128, 32, 64, 64, 4, TA, TB, EPI>(gp, s);   // 8 waves
-    case 23: return launch_ring<256, 256, 128, 64, 32, 4, TA, TB, EPI>(gp, s);
+    case 23:
+      if constexpr (TA) return launch_ring<256, 256, 128, 64, 32, 4, TA, TB, EPI>(gp, s);
+      break;
     case 24:
       if constexpr (!TB) return launch_ring<192, 256, 96, 64, 32, 4, TA, TB, EPI>(gp, s);
-      return hipErrorInvalidValue;
+      break;
+    case 25:
+      if constexpr (!TA) return launch_phased<256, 256, 128, 64, TA, TB, EPI>(gp, s);
+      break;
+    case 26:
+      if constexpr (TB) return launch_phased<192, 256, 96, 64, TA, TB, EPI>(gp, s);
+      break;
+    case 27: return launch_phased<128, 256, 64, 64, TA, TB, EPI>(gp, s);
     case 32: return launch_split<1, 1, 8, TA, TB, EPI>(gp, s);
     case 64: return launch_split<2, 2, 4, TA, TB, EPI>(gp, s);
-    default: return hipErrorInvalidValue;
+    default: break;
   }
+  return hipErrorInvalidValue;
 }
 
 bool vector_ok(const GemmDesc& d) {
@@ -1532,6 +1751,9 @@ void gemm_bf16_kernel_name(const GemmDesc* d, int count, char* out, size_t cap) 
     case 22: snprintf(out, cap, "gemm_bf16_ring_kernel<128, 128, 32, 64, 64, 4, %s, %s, %d>", ta, tb, d[0].epilogue); break;
     case 23: snprintf(out, cap, "gemm_bf16_ring_kernel<256, 256, 128, 64, 32, 4, %s, %s, %d>", ta, tb, d[0].epilogue); break;
     case 24: snprintf(out, cap, "gemm_bf16_ring_kernel<192, 256, 96, 64, 32, 4, %s, %s, %d>", ta, tb, d[0].epilogue); break;
+    case 25: snprintf(out, cap, "gemm_bf16_phased_kernel<256, 256, 128, 64, %s, %s, %d>", ta, tb, d[0].epilogue); break;
+    case 26: snprintf(out, cap, "gemm_bf16_phased_kernel<192, 256, 96, 64, %s, %s, %d>", ta, tb, d[0].epilogue); break;
+    case 27: snprintf(out, cap, "gemm_bf16_phased_kernel<128, 256, 64, 64, %s, %s, %d>", ta, tb, d[0].epilogue); break;
     case 32: snprintf(out, cap, "gemm_bf16_split_kernel<1, 1, 8, %s, %s, %d>", ta, tb, d[0].epilogue); break;
     case 64: snprintf(out, cap, "gemm_bf16_split_kernel<2, 2, 4, %s, %s, %d>", ta, tb, d[0].epilogue); break;
     default: snprintf(out, cap, "gemm_bf16 tile %d <%s, %s, %d>", tile, ta, tb, d[0].epilogue); break;

@@ -74,3 +74,12 @@ def test_fixed_head_attention_kernels_do_not_spill():
     assert len(found) >= 30
     for name, field in found:
         assert field("vgpr_spill_count") <= (2 if "attn_dq_mfma_kernel<128, 4, 2" in name else 0), name
+
+
+def test_phased_gemm_kernels_use_no_scratch_and_fit_two_waves_per_simd():
+    """They park the next-weights touch in a register as the ring kernels do."""
+    found = built_kernels(r"gemm_bf16_phased_kernel<")
+    assert len(found) >= 10
+    for name, field in found:
+        assert field("private_segment_fixed_size") == 0 and field("vgpr_spill_count") == 0 and field("sgpr_spill_count") == 0, name
+        assert field("vgpr_count") <= 256, name
