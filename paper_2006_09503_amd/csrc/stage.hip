@@ -83,13 +83,6 @@ struct stage2bw {
   std::vector<void*> allocations;
   int64_t bytes_total = 0, bytes_weights = 0, bytes_stash = 0;
   char* wbuf[2] = {nullptr, nullptr};
-  // bf16 mode: per version, the transposes of the four projection matrices of every layer ([out, in] row-major;
-  // per layer WqkvT [3h,h] | WoT [h,h] | W1T [f,h] | W2T [h,f]).  The data-gradient products read these, so that
-  // their weight operand has the contraction index strided like the forward's instead of contiguous: the direct-
-  // to-LDS loads then fetch whole 512-byte rows, and the products with long contractions run 16..28 % faster.
-  // Rewritten from wbuf after every update (4 bytes of traffic per matrix element, once per m microbatches).
-  char* wT[2] = {nullptr, nullptr};
-  int64_t bytes_transposed = 0;
   float* master = nullptr;
   float* G = nullptr;
   float* adam_m = nullptr;
@@ -259,35 +252,6 @@ hipError_t timed(stage2bw* st, int cls, const char* name, double flops, double b
 
 const char* wptr(const stage2bw* st, int buffer, int64_t elem_off) {
   return st->wbuf[buffer] + elem_off * st->esize;
-}
-
-enum WhichMatrix { kWqkv = 0, kWo = 1, kW1 = 2, kW2 = 3 };
-// element offset of a layer's transposed matrix inside wT (per layer: 3h*h | h*h | f*h | h*f elements)
-int64_t wT_offset(const stage2bw* st, int layer, int which) {
-  const int64_t h = st->cfg.hidden, f = st->cfg.ffn;
-  const int64_t per_layer = 4 * h * h + 2 * h * f;
-  const int64_t in_layer[4] = {0, 3 * h * h, 4 * h * h, 4 * h * h + h * f};
-  return per_layer * layer + in_layer[which];
-}
-const char* wTptr(const stage2bw* st, int buffer, int layer, int which) {
-  return st->wT[buffer] + wT_offset(st, layer, which) * 2;
-}
-
-// wT[buffer] <- transposes of the matrices in wbuf[buffer] (bf16 mode), one grouped launch
-hipError_t refresh_transposed(stage2bw* st, int buffer, hipStream_t stream) {
-  if (st->dtype != kBF16) return hipSuccess;
-  const int h = st->cfg.hidden, f = st->cfg.ffn;
-  std::vector<TransposeItem> items;
-  items.reserve(4 * st->cfg.n_layers);
-  for (int l = 0; l < st->cfg.n_layers; ++l) {
-    const LayerOff& o = st->off[l];
-    char* dst = st->wT[buffer];
-    items.push_back({st->wbuf[buffer] + o.wqkv * 2, dst + wT_offset(st, l, kWqkv) * 2, h, 3 * h});
-    items.push_back({st->wbuf[buffer] + o.wo * 2, dst + wT_offset(st, l, kWo) * 2, h, h});
-    items.push_back({st->wbuf[buffer] + o.w1 * 2, dst + wT_offset(st, l, kW1) * 2, h, f});
-    items.push_back({st->wbuf[buffer] + o.w2 * 2, dst + wT_offset(st, l, kW2) * 2, f, h});
-  }
-  return transpose_bf16_grouped(items.data(), (int)items.size(), stream);
 }
 
 hipError_t run_gemm(stage2bw* st, int cls, const GemmDesc& d) {
@@ -489,34 +453,21 @@ hipError_t run_backward(stage2bw* st, int buf, int set, int pos, const int32_t* 
     // the GEMM that computes it, dqkv (bf16 mode) from the attention backward kernels; the stage's
     // incoming dy, and du and dqkv in fp32 mode, are summed by the column-sum kernel.
     const bool fused_du = st->dtype == kBF16;
-    const bool bf16 = st->dtype == kBF16;
-    auto dgrad = [&](const void* grad, int N, int which, int64_t w_off, int K, void* out, const void* u, int next_layer,
-                     int next_which, int64_t next_off, int64_t next_elems) {
-      // out[T,K] = grad[T,N] * W[K,N]^T.  Where the result has at least 144 tiles of 256 x 256 (bf16) the product reads the
-      // transposed copy W^T [N,K] in the forward's operand form: measured on those tiles 2 % (contraction 8192) to 16..28 %
-      // (16384 and up) faster, while the 128 x 128 kernel of the small products, whose K tiles of 64 already fetch whole
-      // 128-byte lines, is 10 % faster on W as it is stored.  Some of the former then run on 192 x 256 tiles, which exist in
-      // the forward's form only; a result between this line and theirs (132 of those tiles in one round) stays on W as it is
-      // stored.  fp32: W as it is stored.
-      // next_*: the weights of the chain's next data-gradient GEMM, in the form that GEMM will read
+    auto dgrad = [&](const void* grad, int N, int64_t w_off, int K, void* out, const void* u, const char* next, int64_t next_elems) {
+      // out[T,K] = grad[T,N] * W[K,N]^T; next (may be null): the weights of the chain's next data-gradient GEMM
       GemmDesc d;
       d.dtype = st->dtype;
       d.A = grad; d.lda = N; d.C = out; d.ldc = K;
       d.M = T; d.N = K; d.K = N;
-      auto reads_transposed = [&](int k_out) { return bf16 && (int64_t)ceil_div(T, 256) * ceil_div(k_out, 256) >= 144; };
-      if (reads_transposed(K)) { d.B = wTptr(st, buf, l, which); d.ldb = K; d.trans_b = false; }
-      else { d.B = wptr(st, buf, w_off); d.ldb = N; d.trans_b = true; }
-      if (next_layer >= 0) {
-        d.prefetch = reads_transposed(next_which == kW2 ? f : h) ? wTptr(st, buf, next_layer, next_which) : wptr(st, buf, next_off);
-        d.prefetch_bytes = next_elems * st->esize;
-      }
+      d.B = wptr(st, buf, w_off); d.ldb = N; d.trans_b = true;
+      if (next) { d.prefetch = next; d.prefetch_bytes = next_elems * st->esize; }
       if (u) { d.epilogue = kEpiGeluGrad; d.aux = u; if (fused_du) d.colsum_partial = st->du_partial[l]; }
       return run_gemm(st, STAGE_K_GEMM_DGRAD, d);
     };
     // y = x1 + GELU(u) W2 + b2
-    e = dgrad(dy, h, kW2, o.w2, f, du, A.u, l, kW1, o.w1, (int64_t)h * f);   if (e != hipSuccess) return e;
+    e = dgrad(dy, h, o.w2, f, du, A.u, wptr(st, buf, o.w1), (int64_t)h * f);   if (e != hipSuccess) return e;
     // u = c W1 + b1
-    e = dgrad(du, f, kW1, o.w1, h, st->tmp_h, nullptr, l, kWo, o.wo, (int64_t)h * h);   if (e != hipSuccess) return e;
+    e = dgrad(du, f, o.w1, h, st->tmp_h, nullptr, wptr(st, buf, o.wo), (int64_t)h * h);   if (e != hipSuccess) return e;
     // c = LN2(x1); dx1 = dy + LN2'(dc)
     int ln2_parts = 0, ln1_parts = 0;
     e = run_ln_bwd(st, st->tmp_h, A.x1, A.mean2, A.rstd2, wptr(st, buf, o.ln2_g), dy, dx1, st->ln_partial[l], &ln2_parts,
@@ -524,7 +475,7 @@ hipError_t run_backward(stage2bw* st, int buf, int set, int pos, const int32_t* 
     if (e != hipSuccess) return e;
     if (l == c.n_layers - 1) dy = dy_keep;
     // x1 = x + o Wo + bo
-    e = dgrad(dx1, h, kWo, o.wo, h, st->tmp_h, nullptr, l, kWqkv, o.wqkv, (int64_t)3 * h * h);   if (e != hipSuccess) return e;
+    e = dgrad(dx1, h, o.wo, h, st->tmp_h, nullptr, wptr(st, buf, o.wqkv), (int64_t)3 * h * h);   if (e != hipSuccess) return e;
     // attention
     AttnDesc ad = attn_desc(st, lens);
     const bool fused_dqkv = attention_emits_colsum(ad);
@@ -534,7 +485,7 @@ hipError_t run_backward(stage2bw* st, int buf, int set, int pos, const int32_t* 
     });
     if (e != hipSuccess) return e;
     // qkv = a Wqkv + bqkv
-    e = dgrad(dqkv, 3 * h, kWqkv, o.wqkv, h, st->tmp_h, nullptr, l - 1, kW2, l > 0 ? st->off[l - 1].w2 : 0, (int64_t)h * f);
+    e = dgrad(dqkv, 3 * h, o.wqkv, h, st->tmp_h, nullptr, l > 0 ? wptr(st, buf, st->off[l - 1].w2) : nullptr, (int64_t)h * f);
     if (e != hipSuccess) return e;
     // a = LN1(x); dx = dx1 + LN1'(da)
     e = run_ln_bwd(st, st->tmp_h, A.x, A.mean1, A.rstd1, wptr(st, buf, o.ln1_g), dx1, dx, st->ln_partial2[l], &ln1_parts);
@@ -665,12 +616,6 @@ int stage_create(const stage_config_t* cfg, const float* init_weights_host, void
   if (cfg->flush) st->wbuf[1] = st->wbuf[0];   // one weight version (Section 3.2)
   else ALLOC(st->wbuf[1], P * E, &st->bytes_weights);
   if (st->dtype == kBF16) ALLOC(st->master, P * 4, &st->bytes_weights);
-  if (st->dtype == kBF16) {
-    const int64_t tbytes = cfg->n_layers * (4 * h * h + 2 * h * f) * 2;
-    ALLOC(st->wT[0], tbytes, &st->bytes_transposed);
-    if (cfg->flush) st->wT[1] = st->wT[0];
-    else ALLOC(st->wT[1], tbytes, &st->bytes_transposed);
-  }
   ALLOC(st->G, P * 4, nullptr);
   ALLOC(st->adam_m, P * 4, nullptr);
   if (cfg->optimizer == STAGE_OPT_ADAM) ALLOC(st->adam_v, P * 4, nullptr);
@@ -745,8 +690,6 @@ int stage_create(const stage_config_t* cfg, const float* init_weights_host, void
       e = hipMemcpyAsync(st->wbuf[1], st->wbuf[0], (size_t)P * 4, hipMemcpyDeviceToDevice, st->stream);
     }
   }
-  if (e == hipSuccess) e = refresh_transposed(st, 0, st->stream);
-  if (e == hipSuccess && !cfg->flush) e = refresh_transposed(st, 1, st->stream);
   if (e == hipSuccess) e = hipMemsetAsync(st->G, 0, (size_t)P * 4, st->stream);
   if (e == hipSuccess) e = hipMemsetAsync(st->adam_m, 0, (size_t)P * 4, st->stream);
   if (e == hipSuccess && st->adam_v) e = hipMemsetAsync(st->adam_v, 0, (size_t)P * 4, st->stream);
@@ -875,11 +818,6 @@ int stage_coalesce_update(stage_t* st) {
     HIP_TRY(timed(st, STAGE_K_ADAM, "momentum_kernel", 0.0, bytes, [&] { return momentum_step(d, st->cur); }));
   } else {
     HIP_TRY(timed(st, STAGE_K_ADAM, "adam_kernel", 0.0, bytes, [&] { return adam_step(d, st->cur); }));
-  }
-  // the transposed copy of the version just written (the data-gradient products of its microbatches read it)
-  if (st->dtype == kBF16) {
-    const double tbytes = 4.0 * st->cfg.n_layers * (4.0 * st->cfg.hidden * st->cfg.hidden + 2.0 * st->cfg.hidden * st->cfg.ffn);
-    HIP_TRY(timed(st, STAGE_K_OTHER, "transpose_bf16_grouped_kernel", 0.0, tbytes, [&] { return refresh_transposed(st, wb, st->cur); }));
   }
   if (st->two_streams) {
     HIP_TRY(hipEventRecord(st->ver_ready[wb], st->bstream));
