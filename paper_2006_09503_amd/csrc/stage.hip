@@ -69,9 +69,14 @@ struct stage2bw {
   // two-stream ordering: per stash slot "forward written" / "backward has read"; per version
   // buffer "update has written"
   std::vector<hipEvent_t> fwd_done, bwd_done, set_done;   // per slot, per slot, per activation set
-  std::vector<char> bwd_pending, set_pending;
   hipEvent_t ver_ready[2] = {nullptr, nullptr};
-  bool ver_pending[2] = {false, false};
+  // The events of the backward stream carry the number of their recording (0: none yet).  A stream that has waited for one of them
+  // has waited for all with smaller numbers, so a forward pass waits for the newest of those it depends on, and only if no earlier
+  // one has: a wait across streams costs the host about 8 us here, three kernel launches.
+  std::vector<int64_t> bwd_seq, set_seq;
+  int64_t ver_seq[2] = {0, 0};
+  int64_t b_seq = 0;      // events recorded on the backward stream
+  int64_t f_waited = 0;   // number up to which `stream` has waited for them
   Schedule sched;
   int64_t P = 0;
   int T = 0;
@@ -411,7 +416,7 @@ hipError_t flush_wgrad(stage2bw* st) {
       if (st->two_streams) {
         hipError_t e = hipEventRecord(st->set_done[set], st->cur);
         if (e != hipSuccess) return e;
-        st->set_pending[set] = 1;
+        st->set_seq[set] = ++st->b_seq;
       }
       st->free_sets.push_back(set);
     }
@@ -714,9 +719,13 @@ int stage_forward(stage_t* st, int64_t mb, const void* x_dev, const int32_t* seq
   if (st->two_streams) {
     // the slot's previous occupant has been read by its backward pass, the set's by the weight-gradient
     // launch of its group; the version has been written
-    if (st->bwd_pending[slot]) { HIP_TRY(hipStreamWaitEvent(st->stream, st->bwd_done[slot], 0)); st->bwd_pending[slot] = 0; }
-    if (st->set_pending[set]) { HIP_TRY(hipStreamWaitEvent(st->stream, st->set_done[set], 0)); st->set_pending[set] = 0; }
-    if (st->ver_pending[buf]) { HIP_TRY(hipStreamWaitEvent(st->stream, st->ver_ready[buf], 0)); st->ver_pending[buf] = false; }
+    struct { int64_t seq; hipEvent_t ev; } need = {st->bwd_seq[slot], st->bwd_done[slot]};
+    if (st->set_seq[set] > need.seq) need = {st->set_seq[set], st->set_done[set]};
+    if (st->ver_seq[buf] > need.seq) need = {st->ver_seq[buf], st->ver_ready[buf]};
+    if (need.seq > st->f_waited) {
+      HIP_TRY(hipStreamWaitEvent(st->stream, need.ev, 0));
+      st->f_waited = need.seq;
+    }
   }
   ActSet& acts = st->sets[set];
   // stash the stage input (with recompute it is the only thing kept)
@@ -785,7 +794,7 @@ int stage_backward(stage_t* st, int64_t mb, const void* dy_dev, void* dx_dev) {
   if (st->n_pending == st->wg_j || st->sched.accumulated() == st->cfg.m) HIP_TRY(flush_wgrad(st));
   if (st->two_streams) {
     HIP_TRY(hipEventRecord(st->bwd_done[slot], st->bstream));
-    st->bwd_pending[slot] = 1;
+    st->bwd_seq[slot] = ++st->b_seq;
   }
   return STAGE_OK;
 }
@@ -821,7 +830,7 @@ int stage_coalesce_update(stage_t* st) {
   }
   if (st->two_streams) {
     HIP_TRY(hipEventRecord(st->ver_ready[wb], st->bstream));
-    st->ver_pending[wb] = true;
+    st->ver_seq[wb] = ++st->b_seq;
   }
   return STAGE_OK;
 }
@@ -853,12 +862,13 @@ int stage_set_backward_stream(stage_t* st, void* hip_stream) {
     st->ver_ready[0] = ev[2 * st->cfg.max_inflight];
     st->ver_ready[1] = ev[2 * st->cfg.max_inflight + 1];
     st->set_done.assign(ev.begin() + 2 * st->cfg.max_inflight + 2, ev.end());
-    st->bwd_pending.assign(st->cfg.max_inflight, 0);
-    st->set_pending.assign(n_sets, 0);
+    st->bwd_seq.assign(st->cfg.max_inflight, 0);
+    st->set_seq.assign(n_sets, 0);
   }
-  std::fill(st->bwd_pending.begin(), st->bwd_pending.end(), 0);
-  std::fill(st->set_pending.begin(), st->set_pending.end(), 0);
-  st->ver_pending[0] = st->ver_pending[1] = false;
+  std::fill(st->bwd_seq.begin(), st->bwd_seq.end(), 0);
+  std::fill(st->set_seq.begin(), st->set_seq.end(), 0);
+  st->ver_seq[0] = st->ver_seq[1] = 0;
+  st->b_seq = st->f_waited = 0;
   st->bstream = b;
   st->two_streams = true;
   return STAGE_OK;
