@@ -5,11 +5,11 @@
 // SIMD, and latency below that.  Microbatches of the fp32 mode are small (16 heads x 512 queries are 256 blocks of 32
 // queries), so a workgroup owns only ONE block of 32 rows (queries in the forward and dQ kernels, keys in dK/dV) and
 // its four waves take every fourth tile of 32 rows of the streamed side; their partial results meet in LDS once, at
-// the end, in a fixed order.  Inside the loop nothing is shared: an MFMA of this shape needs one float per lane and
-// operand, which a wave loads from L2 straight into its fragment registers (16 bytes per lane along the head for the
-// row operands, 128-byte rows for the column operands), one step ahead of their use.  No LDS, no barrier.
-// Measured at b=2 s=512 a=8 dh=64, causal, against one thread per row on the vector ALU: forward 520 -> 18 us, dQ with
-// delta 423 -> 26, dK/dV 723 -> 33; the matrix instructions alone are 7, 10 and 14 us of the longest workgroup.
+// the end, in a fixed order.  Inside the loop nothing is shared and there is no barrier: a wave fetches its tiles into LDS of
+// its own (WaveTile), the next one under the last product of the current one.
+// Measured at b=2 s=512 a=8 dh=64, causal: forward 17 us, backward 42 (55 while every fragment came from L2 by itself and dQ
+// and dK/dV were launches of their own; 520 and 1146 with one thread per row on the vector ALU); the matrix instructions alone
+// are 7 and 14 us of the longest workgroups.
 //
 // v_mfma_f32_32x32x2_f32: lane l supplies element (l % 32, l / 32) of the first operand (32 x 2) and (l / 32, l % 32) of
 // the second (2 x 32); it receives column l % 32 of the result, rows 8*(r/4) + 4*(l/32) + (r%4) in register r.  The two
@@ -30,6 +30,8 @@ namespace k2bw {
 namespace {
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef __attribute__((address_space(3))) void lds_void_t;
+typedef __attribute__((address_space(1))) const void glob_void_t;
 
 // Waves per workgroup (NW): four, which split the streamed rows, or one where a launch has blocks enough without that (one_wave)
 constexpr int kManyWaves = 4;
@@ -63,80 +65,80 @@ __device__ __forceinline__ void load_row(const float* __restrict__ row, int dh, 
   }
 }
 
-// Column operand of the 32 rows at `tile` (uniform): f[db][r] = tile[reg_row(r)][32*db + l32]; rows from `rows` on are zero,
-// columns past dh hold a copy of the last one (they only reach result columns that are never stored).  In a whole tile a
-// row's address is scalar and the lane's offset the same for all rows.
+// The 32 rows of a streamed operand that a wave works on, in LDS of its own: fetched once, 16 bytes per lane along the rows and no
+// registers, and read both as rows (16 bytes per lane) and as columns (4 bytes).  Straight from L2 into fragment registers every
+// operand came twice, the second time by 16 loads of two rows each per 32 columns, and a load occupies the CU's address unit for some
+// 16 cycles whatever it brings: 112 of them per tile and wave in dK/dV were as much time as the matrix instructions.
+// Layout: rows of LW floats (16, 32, 64 or 128, what lies past the head is zero), 1 KB blocks of kRowsPer rows as a load instruction
+// writes them, 16-byte chunks XOR-swizzled by row inside a block and kPad floats between blocks: 16 consecutive rows at one chunk then
+// fall on all banks, and the addresses of a lane differ by constants but for two or four.
+__device__ const float4 kZeros = {0.f, 0.f, 0.f, 0.f};
 template <int DH>
-__device__ __forceinline__ void load_cols(const float* __restrict__ tile, int ld, int rows, int dh, int l32, int hf,
-                                          float (&f)[CfgF<DH>::DB][16]) {
-  constexpr int DB = CfgF<DH>::DB;
-  uint32_t col[DB];
+struct WaveTile {
+  static constexpr int LW = DH <= 16 ? 16 : DH <= 32 ? 32 : DH <= 64 ? 64 : 128;
+  static constexpr int CH = LW / 4, kRowsPer = 64 / CH, kInstr = 32 / kRowsPer;
+  static constexpr int kPad = LW == 16 ? 0 : LW == 128 ? 8 : 16;
+  static constexpr int kBlock = 256 + kPad, kFloats = kInstr * kBlock;
+  // swizzle of a row: two bits, one for rows of 512 bytes
+  static __device__ __forceinline__ int swz(int row) { return LW == 128 ? row & 1 : LW == 64 ? row & 3 : LW == 32 ? (row >> 1) & 3 : (row >> 2) & 3; }
+  static __device__ __forceinline__ int at(int row) { return row / kRowsPer * kBlock + row % kRowsPer * LW; }
+  // rows [0, rows) x [0, dh) of the matrix at src (uniform) into t; the rest is zero
+  static __device__ __forceinline__ void issue(const float* __restrict__ src, int64_t ld, int rows, int dh, int lane, float* t) {
+    const int row = lane / CH, c = (lane % CH) ^ swz(row);   // (the swizzle has the period of a block)
+    asm volatile("" : "+s"(src));   // else the loop keeps a pointer per lane and load instruction
+    const float* from = src + row * ld + 4 * c;
+    const bool in_head = 4 * c < dh;
 #pragma unroll
-  for (int db = 0; db < DB; ++db) col[db] = (uint32_t)min(db * 32 + l32, dh - 1);
-  if (rows >= 32) {
-    const uint32_t half = (uint32_t)(4 * hf * ld);
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const float* __restrict__ row = tile + (int64_t)reg_row(r, 0) * ld;
-#pragma unroll
-      for (int db = 0; db < DB; ++db) f[db][r] = row[half + col[db]];
+    for (int q = 0; q < kInstr; ++q) {
+      const float* p = in_head && row < rows - q * kRowsPer ? from + q * kRowsPer * ld : reinterpret_cast<const float*>(&kZeros);
+      __builtin_amdgcn_global_load_lds((glob_void_t*)p, (lds_void_t*)(t + q * kBlock), 16, 0, 0);
     }
-  } else {
+  }
+  // head columns 8j + 4*hf .. +3 of row l32
+  static __device__ __forceinline__ float4 row4(const float* t, int j, int l32, int hf) {
+    return *reinterpret_cast<const float4*>(t + at(l32) + (((2 * (j & 1) + hf) ^ swz(l32)) << 2) + 16 * (j >> 1));
+  }
+  // f[db][r] = row reg_row(r, hf), column 32*db + l32 (columns past DH: zero, or another's if rows have 16; they only reach result
+  // columns that are never stored)
+  static __device__ __forceinline__ void cols(const float* t, int l32, int hf, float (&f)[CfgF<DH>::DB][16]) {
+    const int col = LW == 16 ? l32 & 15 : l32;
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       const int row = reg_row(r, hf);
-      const uint32_t at = (uint32_t)(min(row, rows - 1) * ld);
+      const float* x = t + at(row) + ((((col >> 2) ^ swz(row)) << 2) | (col & 3));
 #pragma unroll
-      for (int db = 0; db < DB; ++db) {
-        const float v = tile[at + col[db]];
-        f[db][r] = row < rows ? v : 0.f;
-      }
+      for (int db = 0; db < CfgF<DH>::DB; ++db) f[db][r] = x[32 * db];
     }
   }
-}
-
-// acc (32 x 32) += A * B over the head dimension
-template <int DH>
-__device__ __forceinline__ void mul_rows(const float (&a)[CfgF<DH>::NF], const float (&b)[CfgF<DH>::NF], f32x16& acc) {
-#pragma unroll
-  for (int i = 0; i < CfgF<DH>::NF; ++i) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[i], acc, 0, 0, 0);
-}
-
-// The operand a workgroup keeps for its own 32 rows (Q and dO in dQ, K and V in dK/dV), the same for all four waves: in
-// fragment registers, or for large heads, where the accumulators and the streamed operands need those, in LDS (rows of
-// DH + 4 floats: the 16-byte reads of 16 consecutive rows fall on all banks).
-template <int DH, int NW, bool IN_LDS>
-struct Resident {
-  float f[CfgF<DH>::NF];
-  __device__ __forceinline__ void load(const float* __restrict__ row, int dh, int, int hf, int, float*) { load_row<DH>(row, dh, hf, f); }
-  __device__ __forceinline__ void mul(const float (&x)[CfgF<DH>::NF], f32x16& acc, const float*, int, int) const { mul_rows<DH>(x, f, acc); }
-};
-template <int DH, int NW>
-struct Resident<DH, NW, true> {
-  static constexpr int LDR = DH + 4;
-  // every wave writes its share of the columns of all 32 rows; the caller synchronises
-  __device__ __forceinline__ void load(const float* __restrict__ row, int dh, int l32, int hf, int wave, float* rows) {
-    for (int j = wave; j < DH / 8; j += NW) {
-      float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (8 * j < dh) v = *reinterpret_cast<const float4*>(row + 8 * j + 4 * hf);
-      *reinterpret_cast<float4*>(rows + l32 * LDR + 8 * j + 4 * hf) = v;
-    }
-  }
-  __device__ __forceinline__ void mul(const float (&x)[CfgF<DH>::NF], f32x16& acc, const float* rows, int l32, int hf) const {
+  // acc += (this tile's rows) * f^T over the head dimension
+  static __device__ __forceinline__ void mul(const float* t, const float (&f)[CfgF<DH>::NF], f32x16& acc, int l32, int hf) {
 #pragma unroll
     for (int j = 0; j < DH / 8; ++j) {
-      const float4 v = *reinterpret_cast<const float4*>(rows + l32 * LDR + 8 * j + 4 * hf);
-      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x[4 * j], v.x, acc, 0, 0, 0);
-      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x[4 * j + 1], v.y, acc, 0, 0, 0);
-      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x[4 * j + 2], v.z, acc, 0, 0, 0);
-      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x[4 * j + 3], v.w, acc, 0, 0, 0);
+      const float4 v = row4(t, j, l32, hf);
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(v.x, f[4 * j], acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(v.y, f[4 * j + 1], acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(v.z, f[4 * j + 2], acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(v.w, f[4 * j + 3], acc, 0, 0, 0);
     }
   }
 };
+// a wave's loads into its tiles have landed / its reads of them are done
+__device__ __forceinline__ void tiles_landed() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+__device__ __forceinline__ void tiles_read() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
+
+// LDS, in floats: every wave's two tiles (the strips of the results re-use them), then what the kernel adds
 template <int DH, int NW> constexpr int strip_floats() { return NW * kRows * CfgF<DH>::LD; }
-template <int DH> constexpr int resident_floats() { return kRows * (DH + 4); }
-template <int DH> constexpr bool kDqLds = DH >= 112;
-template <int DH> constexpr bool kDkvLds = DH >= 48;
+template <int DH, int NW> constexpr int tile_floats() {
+  const int t = NW * 2 * WaveTile<DH>::kFloats, s = strip_floats<DH, NW>();
+  return t > s ? t : s;
+}
+// Waves per SIMD that the registers leave room for: two up to head size 64 (one of 512 registers instead: backward at b=8 s=512 a=16
+// dh=64 332 -> 364 us, forward 96 -> 110)
+template <int DH> constexpr int kPerSimd = DH <= 64 ? 2 : 1;
+__device__ __forceinline__ void wave_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
 
 // out[db] += X^T P over the 32 rows of a tile
 template <int DH>
@@ -158,19 +160,19 @@ __device__ __forceinline__ bool any_not_finite(const float (&x)[CfgF<DH>::DB][16
 }
 
 // mul_cols for a tile in which not every lane's row (query or key) sees every row of the tile, when the tile holds
-// infinities or NaNs: row by row, added only where it is seen (sees(row)).  Rare, so it keeps few registers: the
-// weights pass through `p_lds` (32 x 32 floats of this wave), the rows come from `tile` again.
+// infinities or NaNs: row by row, added only where it is seen (sees(row)).  Rare, so it keeps few registers: the rows
+// come from `tile`, the matrix, again.
 template <int DH, typename Sees>
 __device__ __forceinline__ void accumulate_visible(const float* __restrict__ tile, int64_t ld, int rows, int dh, const f32x16& p,
-                                                   f32x16 (&out)[CfgF<DH>::DB], float* p_lds, int l32, int hf, Sees&& sees) {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-#pragma unroll
-  for (int r = 0; r < 16; ++r) p_lds[reg_row(r, hf) * 32 + l32] = p[r];
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  __builtin_amdgcn_wave_barrier();
+                                                   f32x16 (&out)[CfgF<DH>::DB], int hf, Sees&& sees) {
 #pragma unroll 1
   for (int row = 0; row < rows; ++row) {
-    const float w = p_lds[row * 32 + l32];
+    const int reg = (row >> 3) * 4 + (row & 3);
+    float w = p[0];
+#pragma unroll
+    for (int e = 1; e < 16; ++e) w = e == reg ? p[e] : w;
+    const float other = __shfl_xor(w, 32, 64);
+    w = ((row >> 2) & 1) == hf ? w : other;
     const bool vis = sees(row);
     const float* x = tile + row * ld + 4 * hf;
 #pragma unroll
@@ -223,10 +225,10 @@ __device__ __forceinline__ void sum_strips(const float* strips, float* __restric
 // ------------------------------------------------------------------------------------------------
 // forward: lane = query, registers = keys (S^T = K Q^T, O^T = V^T P^T)
 template <int DH, int NW>
-__global__ __launch_bounds__(NW * 64, 1) void attn_f32_fwd_kernel(const float* __restrict__ qkv, float* __restrict__ o, float* __restrict__ lse,
+__global__ __launch_bounds__(NW * 64, (kPerSimd<DH>)) void attn_f32_fwd_kernel(const float* __restrict__ qkv, float* __restrict__ o, float* __restrict__ lse,
                                                                     int s, int a, int dh, int mask_mode, const int32_t* __restrict__ seqlens) {
   using C = CfgF<DH>;
-  extern __shared__ __attribute__((aligned(16))) float smem[];   // strips, then m[NW][32], l[NW][32]
+  extern __shared__ __attribute__((aligned(16))) float smem[];   // tiles (then strips), m[NW][32], l[NW][32]
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l32 = lane & 31, hf = lane >> 5;
   const int n = blockIdx.y, head = blockIdx.x;
   const bool causal = mask_mode == 1;
@@ -238,7 +240,7 @@ __global__ __launch_bounds__(NW * 64, 1) void attn_f32_fwd_kernel(const float* _
   const int kv_len = mask_mode == 2 ? min(max(seqlens[n], 1), s) : s;
   const float scale = 1.0f / sqrtf((float)dh), c = scale * kLog2e;
 
-  float qf[C::NF], kf[C::NF], vc[C::DB][16];
+  float qf[C::NF], vc[C::DB][16];
   load_row<DH>(base + (int64_t)min(i, s - 1) * ld, dh, hf, qf);
   f32x16 oacc[C::DB];
 #pragma unroll
@@ -246,16 +248,22 @@ __global__ __launch_bounds__(NW * 64, 1) void attn_f32_fwd_kernel(const float* _
   float m_i = -INFINITY, l_i = 0.f;
   const int jend = causal ? min(i0 + kRows, s) : kv_len;
   const int ntiles = (jend + 31) / 32;
-  auto load_k = [&](int t) { load_row<DH>(base + h + (int64_t)min(t * 32 + l32, jend - 1) * ld, dh, hf, kf); };
-  if (wave < ntiles) load_k(wave);
+  float* k_tile = smem + wave * 2 * WaveTile<DH>::kFloats;
+  float* v_tile = k_tile + WaveTile<DH>::kFloats;
+  auto issue = [&](int t) {
+    const float* row = base + h + (int64_t)t * 32 * ld;
+    WaveTile<DH>::issue(row, ld, jend - t * 32, dh, lane, k_tile);
+    WaveTile<DH>::issue(row + h, ld, jend - t * 32, dh, lane, v_tile);
+  };
+  if (wave < ntiles) issue(wave);
   for (int t = wave; t < ntiles; t += NW) {
     const int j0 = t * 32;
-    load_cols<DH>(base + 2 * h + (int64_t)j0 * ld, (int)ld, jend - j0, dh, l32, hf, vc);
-    __builtin_amdgcn_sched_barrier(0);   // V travels while the scores are computed
+    tiles_landed();
     f32x16 sc = zero16();
-    mul_rows<DH>(kf, qf, sc);
-    __builtin_amdgcn_sched_barrier(0);
-    if (t + NW < ntiles) load_k(t + NW);   // the next tile's K travels under the softmax and the second product
+    WaveTile<DH>::mul(k_tile, qf, sc, l32, hf);
+    WaveTile<DH>::cols(v_tile, l32, hf, vc);
+    tiles_read();
+    if (t + NW < ntiles) issue(t + NW);   // the next tile travels under the softmax and the second product
     __builtin_amdgcn_sched_barrier(0);
     const bool diag = causal && j0 + 31 > i0;
     if (diag || j0 + 32 > jend) {
@@ -284,11 +292,11 @@ __global__ __launch_bounds__(NW * 64, 1) void attn_f32_fwd_kernel(const float* _
     for (int db = 0; db < C::DB; ++db)
 #pragma unroll
       for (int r = 0; r < 16; ++r) oacc[db][r] *= alpha;
-    if (diag && any_not_finite<DH>(vc)) accumulate_visible<DH>(base + 2 * h + (int64_t)j0 * ld, ld, min(jend - j0, 32), dh, sc, oacc, smem + wave * kRows * C::LD, l32, hf, [&](int row) { return j0 + row <= i; });
+    if (diag && any_not_finite<DH>(vc)) accumulate_visible<DH>(base + 2 * h + (int64_t)j0 * ld, ld, min(jend - j0, 32), dh, sc, oacc, hf, [&](int row) { return j0 + row <= i; });
     else mul_cols<DH>(vc, sc, oacc);
   }
   // the waves' maxima meet, every partial result is rescaled to the common one
-  float* m_lds = smem + NW * kRows * C::LD;
+  float* m_lds = smem + tile_floats<DH, NW>();
   float* l_lds = m_lds + NW * kRows;
   l_i += __shfl_xor(l_i, 32, 64);
   if (hf == 0) m_lds[wave * kRows + l32] = m_i;
@@ -314,16 +322,13 @@ __global__ __launch_bounds__(NW * 64, 1) void attn_f32_fwd_kernel(const float* _
 // ------------------------------------------------------------------------------------------------
 // dQ (and delta = rowsum(dO * O), which the dK/dV kernel reads): the forward's orientation
 template <int DH, int NW>
-__global__ __launch_bounds__(NW * 64, 1) void attn_f32_dq_kernel(const float* __restrict__ qkv, const float* __restrict__ o,
-                                                                   const float* __restrict__ d_o, const float* __restrict__ lse,
-                                                                   float* __restrict__ delta, float* __restrict__ dqkv, int s, int a, int dh,
-                                                                   int mask_mode, const int32_t* __restrict__ seqlens) {
+__device__ __forceinline__ void attn_f32_dq(const float* __restrict__ qkv, const float* __restrict__ o, const float* __restrict__ d_o,
+                                            const float* __restrict__ lse, float* __restrict__ delta, float* __restrict__ dqkv, int s, int a,
+                                            int dh, int mask_mode, const int32_t* __restrict__ seqlens, int blk, float* smem) {
   using C = CfgF<DH>;
-  extern __shared__ __attribute__((aligned(16))) float smem[];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l32 = lane & 31, hf = lane >> 5;
   const int n = blockIdx.y, head = blockIdx.x;
   const bool causal = mask_mode == 1;
-  const int blk = causal ? (int)(gridDim.z - 1 - blockIdx.z) : (int)blockIdx.z;
   const int i0 = blk * kRows, i = i0 + l32, ic = min(i, s - 1);
   const int h = a * dh;
   const int64_t ld = 3 * (int64_t)h;
@@ -331,19 +336,24 @@ __global__ __launch_bounds__(NW * 64, 1) void attn_f32_dq_kernel(const float* __
   const int kv_len = mask_mode == 2 ? min(max(seqlens[n], 1), s) : s;
   const float scale = 1.0f / sqrtf((float)dh), c = scale * kLog2e;
 
-  float kf[C::NF], vf[C::NF], kc[C::DB][16];
-  Resident<DH, NW, kDqLds<DH>> q, g;
-  float* q_lds = smem + strip_floats<DH, NW>();
-  float* g_lds = q_lds + resident_floats<DH>();
+  float qf[C::NF], gf[C::NF], kc[C::DB][16];
   const float* g_row = d_o + ((int64_t)n * s + ic) * h + head * dh;
-  q.load(base + (int64_t)ic * ld, dh, l32, hf, wave, q_lds);
-  g.load(g_row, dh, l32, hf, wave, g_lds);
-  if (kDqLds<DH>) __syncthreads();
+  const int jend = causal ? min(i0 + kRows, s) : kv_len;
+  const int ntiles = (jend + 31) / 32;
+  float* k_tile = smem + wave * 2 * WaveTile<DH>::kFloats;
+  float* v_tile = k_tile + WaveTile<DH>::kFloats;
+  auto issue = [&](int t) {
+    const float* row = base + h + (int64_t)t * 32 * ld;
+    WaveTile<DH>::issue(row, ld, jend - t * 32, dh, lane, k_tile);
+    WaveTile<DH>::issue(row + h, ld, jend - t * 32, dh, lane, v_tile);
+  };
+  if (wave < ntiles) issue(wave);
+  load_row<DH>(base + (int64_t)ic * ld, dh, hf, qf);
+  load_row<DH>(g_row, dh, hf, gf);
   float delta_i;
   {
-    float of[C::NF], gf[C::NF];
+    float of[C::NF];
     load_row<DH>(o + ((int64_t)n * s + ic) * h + head * dh, dh, hf, of);
-    load_row<DH>(g_row, dh, hf, gf);
     float part = 0.f;
 #pragma unroll
     for (int e = 0; e < C::NF; ++e) part = fmaf(gf[e], of[e], part);
@@ -354,28 +364,15 @@ __global__ __launch_bounds__(NW * 64, 1) void attn_f32_dq_kernel(const float* __
   f32x16 dq[C::DB];
 #pragma unroll
   for (int db = 0; db < C::DB; ++db) dq[db] = zero16();
-  const int jend = causal ? min(i0 + kRows, s) : kv_len;
-  const int ntiles = (jend + 31) / 32;
-  auto load_kv = [&](int t) {
-    const float* row = base + h + (int64_t)min(t * 32 + l32, jend - 1) * ld;
-    load_row<DH>(row, dh, hf, kf);
-    load_row<DH>(row + h, dh, hf, vf);
-  };
-  // large heads: rows of the next tile are not requested ahead, and the column operand only once the rows are used up
-  constexpr bool kAhead = DH <= 96;
-  if (kAhead && wave < ntiles) load_kv(wave);
   for (int t = wave; t < ntiles; t += NW) {
     const int j0 = t * 32;
-    if (!kAhead) load_kv(t);
-    auto load_k_cols = [&] { load_cols<DH>(base + h + (int64_t)j0 * ld, (int)ld, jend - j0, dh, l32, hf, kc); };
-    if (kAhead) load_k_cols();
-    __builtin_amdgcn_sched_barrier(0);
+    tiles_landed();
     f32x16 sc = zero16(), dp = zero16();
-    q.mul(kf, sc, q_lds, l32, hf);
-    g.mul(vf, dp, g_lds, l32, hf);
-    __builtin_amdgcn_sched_barrier(0);
-    if (!kAhead) load_k_cols();
-    if (kAhead && t + NW < ntiles) load_kv(t + NW);
+    WaveTile<DH>::mul(k_tile, qf, sc, l32, hf);
+    WaveTile<DH>::mul(v_tile, gf, dp, l32, hf);
+    WaveTile<DH>::cols(k_tile, l32, hf, kc);
+    tiles_read();
+    if (t + NW < ntiles) issue(t + NW);
     __builtin_amdgcn_sched_barrier(0);
     const bool diag = causal && j0 + 31 > i0;
 #pragma unroll
@@ -385,9 +382,10 @@ __global__ __launch_bounds__(NW * 64, 1) void attn_f32_dq_kernel(const float* __
       const float p = __builtin_amdgcn_exp2f(fmaf(sc[r], scale, -lse_i) * kLog2e);
       sc[r] = vis ? p * (dp[r] - delta_i) : 0.f;   // dS^T (the scale is applied at the end)
     }
-    if (diag && any_not_finite<DH>(kc)) accumulate_visible<DH>(base + h + (int64_t)j0 * ld, ld, min(jend - j0, 32), dh, sc, dq, smem + wave * kRows * C::LD, l32, hf, [&](int row) { return j0 + row <= i; });
+    if (diag && any_not_finite<DH>(kc)) accumulate_visible<DH>(base + h + (int64_t)j0 * ld, ld, min(jend - j0, 32), dh, sc, dq, hf, [&](int row) { return j0 + row <= i; });
     else mul_cols<DH>(kc, sc, dq);
   }
+  __syncthreads();   // every wave is done with its tiles
   put_strip<DH>(dq, scale, smem + wave * kRows * C::LD, l32, hf);
   __syncthreads();
   sum_strips<DH, NW>(smem, dqkv + ((int64_t)n * s + i0) * ld + head * dh, ld, s - i0, dh, tid, [](int) { return 1.0f; });
@@ -395,88 +393,120 @@ __global__ __launch_bounds__(NW * 64, 1) void attn_f32_dq_kernel(const float* __
 
 // ------------------------------------------------------------------------------------------------
 // dK, dV: lane = key, registers = queries (S = Q K^T, dV^T = dO^T P, dK^T = Q^T dS)
-template <int DH, int NW>
-__global__ __launch_bounds__(NW * 64, 1) void attn_f32_dkv_kernel(const float* __restrict__ qkv, const float* __restrict__ d_o,
-                                                                    const float* __restrict__ lse, const float* __restrict__ delta,
-                                                                    float* __restrict__ dqkv, int s, int a, int dh, int mask_mode,
-                                                                    const int32_t* __restrict__ seqlens) {
+// FUSED: delta from dO and O, as the launch that forms it for others is the same one; else it is read.
+// EXACT: the second run of a workgroup that met infinities or NaNs in a tile which not all its keys see in whole (returns true for it);
+// that path inside the one loop costs some 70 spilled registers.
+template <int DH, int NW, bool FUSED, bool EXACT>
+__device__ __forceinline__ bool attn_f32_dkv(const float* __restrict__ qkv, const float* __restrict__ o, const float* __restrict__ d_o,
+                                             const float* __restrict__ lse, const float* __restrict__ delta, float* __restrict__ dqkv, int s, int a, int dh, int mask_mode,
+                                             const int32_t* __restrict__ seqlens, int blk, float* smem) {
   using C = CfgF<DH>;
-  extern __shared__ __attribute__((aligned(16))) float smem[];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l32 = lane & 31, hf = lane >> 5;
-  const int n = blockIdx.y, head = blockIdx.x, blk = blockIdx.z;   // causal: the first keys are seen by the most queries
+  const int n = blockIdx.y, head = blockIdx.x;   // causal: the first keys are seen by the most queries
   const bool causal = mask_mode == 1;
   const int j0 = blk * kRows, j = j0 + l32, jc = min(j, s - 1);
   const int h = a * dh;
   const int64_t ld = 3 * (int64_t)h;
   const float* base = qkv + (int64_t)n * s * ld + head * dh;
   const float* gbase = d_o + (int64_t)n * s * h + head * dh;
+  const float* obase = o + (int64_t)n * s * h + head * dh;
   const float* lse_row = lse + ((int64_t)n * a + head) * s;
   const float* delta_row = delta + ((int64_t)n * a + head) * s;
   const int kv_len = mask_mode == 2 ? min(max(seqlens[n], 1), s) : s;
   const float scale = 1.0f / sqrtf((float)dh);
 
-  float qf[C::NF], gf[C::NF], qc[C::DB][16], gc[C::DB][16];
-  Resident<DH, NW, kDkvLds<DH>> k, v;
-  float* k_lds = smem + strip_floats<DH, NW>();
-  float* v_lds = k_lds + resident_floats<DH>();
-  k.load(base + h + (int64_t)jc * ld, dh, l32, hf, wave, k_lds);
-  v.load(base + 2 * h + (int64_t)jc * ld, dh, l32, hf, wave, v_lds);
-  if (kDkvLds<DH>) __syncthreads();
-  f32x16 dk[C::DB], dv[C::DB];
-#pragma unroll
-  for (int db = 0; db < C::DB; ++db) { dk[db] = zero16(); dv[db] = zero16(); }
   // query tiles that can see a key of the block: none if the block is padding, from the block itself on if causal
   const int t0 = causal ? blk : 0;
   const int t1 = j0 >= kv_len ? t0 : (s + 31) / 32;
-  auto load_qg = [&](int t) {
-    const int i = min(t * 32 + l32, s - 1);
-    load_row<DH>(base + (int64_t)i * ld, dh, hf, qf);
-    load_row<DH>(gbase + (int64_t)i * h, dh, hf, gf);
+  float* q_tile = smem + wave * 2 * WaveTile<DH>::kFloats;
+  float* g_tile = q_tile + WaveTile<DH>::kFloats;
+  auto issue = [&](int t) {
+    WaveTile<DH>::issue(base + (int64_t)t * 32 * ld, ld, s - t * 32, dh, lane, q_tile);
+    WaveTile<DH>::issue(gbase + (int64_t)t * 32 * h, h, s - t * 32, dh, lane, g_tile);
   };
-  // the column operands travel under the first two products, and the next tile's rows under the last two, where the
-  // registers allow it
-  constexpr bool kColsFirst = DH <= 64, kAhead = DH <= 64;
-  if (kAhead && t0 + wave < t1) load_qg(t0 + wave);
+  if (t0 + wave < t1) issue(t0 + wave);
+  float kf[C::NF], vf[C::NF], xc[C::DB][16];
+  load_row<DH>(base + h + (int64_t)jc * ld, dh, hf, kf);
+  load_row<DH>(base + 2 * h + (int64_t)jc * ld, dh, hf, vf);
+  // lse and delta of the tile's queries: a lane has those of its row, the products need them by register
+  float* stat = smem + tile_floats<DH, NW>() + wave * 64;
+  f32x16 dk[C::DB], dv[C::DB];
+#pragma unroll
+  for (int db = 0; db < C::DB; ++db) { dk[db] = zero16(); dv[db] = zero16(); }
+  float lse_i = 0.f, delta_i = 0.f, of[FUSED ? C::NF : 1];
+  bool hidden = false;
+  // (O's row a tile ahead only where the registers allow it)
+  constexpr bool kOAhead = DH <= 32;
+  auto load_o = [&](int t) {
+    if constexpr (FUSED) load_row<DH>(obase + (int64_t)min(t * 32 + l32, s - 1) * h, dh, hf, of);
+  };
+  auto load_stat = [&](int t) {
+    const int i = min(t * 32 + l32, s - 1);
+    lse_i = lse_row[i];
+    if (kOAhead) load_o(t);
+    if (!FUSED) delta_i = delta_row[i];
+  };
+  if (t0 + wave < t1) load_stat(t0 + wave);
   for (int t = t0 + wave; t < t1; t += NW) {
     const int i0 = t * 32;
-    if (!kAhead) load_qg(t);
-    auto load_g_cols = [&] { load_cols<DH>(gbase + (int64_t)i0 * h, h, s - i0, dh, l32, hf, gc); };
-    auto load_q_cols = [&] { load_cols<DH>(base + (int64_t)i0 * ld, (int)ld, s - i0, dh, l32, hf, qc); };
-    if (kColsFirst) { load_g_cols(); load_q_cols(); }
-    float lv[16], dl[16];
+    if (!kOAhead) load_o(t);
+    tiles_landed();
+    if constexpr (FUSED) {
+      float part = 0.f;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int i = min(i0 + reg_row(r, hf), s - 1);
-      lv[r] = lse_row[i];
-      dl[r] = delta_row[i];
+      for (int j2 = 0; j2 < DH / 8; ++j2) {
+        const float4 x = WaveTile<DH>::row4(g_tile, j2, l32, hf);
+        part = fmaf(x.x, of[4 * j2], part); part = fmaf(x.y, of[4 * j2 + 1], part);
+        part = fmaf(x.z, of[4 * j2 + 2], part); part = fmaf(x.w, of[4 * j2 + 3], part);
+      }
+      delta_i = part + __shfl_xor(part, 32, 64);
     }
-    __builtin_amdgcn_sched_barrier(0);
+    stat[lane] = hf == 0 ? lse_i : delta_i;
+    wave_fence();
     f32x16 sc = zero16(), dp = zero16();
-    k.mul(qf, sc, k_lds, l32, hf);
-    v.mul(gf, dp, v_lds, l32, hf);
-    __builtin_amdgcn_sched_barrier(0);
-    if (!kColsFirst) load_g_cols();
-    if (kAhead && t + NW < t1) load_qg(t + NW);
+    WaveTile<DH>::mul(q_tile, kf, sc, l32, hf);
+    __builtin_amdgcn_sched_barrier(0);   // (the fragments of both products together do not fit)
+    WaveTile<DH>::mul(g_tile, vf, dp, l32, hf);
     __builtin_amdgcn_sched_barrier(0);
     const bool diag = causal && i0 < j0 + 31;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int i = i0 + reg_row(r, hf);
-      const bool vis = j < kv_len && i < s && (!causal || j <= i);
-      const float p = vis ? __builtin_amdgcn_exp2f(fmaf(sc[r], scale, -lv[r]) * kLog2e) : 0.f;
-      dp[r] = vis ? p * (dp[r] - dl[r]) : 0.f;
-      sc[r] = p;
+    for (int g = 0; g < 4; ++g) {
+      const float4 l4 = *reinterpret_cast<const float4*>(stat + 8 * g + 4 * hf), d4 = *reinterpret_cast<const float4*>(stat + 32 + 8 * g + 4 * hf);
+      const float lv[4] = {l4.x, l4.y, l4.z, l4.w}, dl[4] = {d4.x, d4.y, d4.z, d4.w};
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int r = 4 * g + e, i = i0 + reg_row(r, hf);
+        const bool vis = j < kv_len && i < s && (!causal || j <= i);
+        const float p = vis ? __builtin_amdgcn_exp2f(fmaf(sc[r], scale, -lv[e]) * kLog2e) : 0.f;
+        dp[r] = vis ? p * (dp[r] - dl[e]) : 0.f;
+        sc[r] = p;
+      }
     }
     // a key past the sequence's length sees no query at all: its lanes must stay zero whatever the tile holds
     const bool partial = diag || j0 + 32 > kv_len;
-    float* p_lds = smem + wave * kRows * C::LD;
     auto sees_len = [&](int row) { return j < kv_len && (!causal || j <= i0 + row); };
-    if (partial && any_not_finite<DH>(gc)) accumulate_visible<DH>(gbase + (int64_t)i0 * h, h, min(s - i0, 32), dh, sc, dv, p_lds, l32, hf, sees_len);
-    else mul_cols<DH>(gc, sc, dv);
-    if (!kColsFirst) { __builtin_amdgcn_sched_barrier(0); load_q_cols(); }
-    if (partial && any_not_finite<DH>(qc)) accumulate_visible<DH>(base + (int64_t)i0 * ld, ld, min(s - i0, 32), dh, dp, dk, p_lds, l32, hf, sees_len);
-    else mul_cols<DH>(qc, dp, dk);
+    __builtin_amdgcn_sched_barrier(0);
+    WaveTile<DH>::cols(g_tile, l32, hf, xc);
+    if (EXACT && partial) {
+      accumulate_visible<DH>(gbase + (int64_t)i0 * h, h, min(s - i0, 32), dh, sc, dv, hf, sees_len);
+    } else {
+      if (partial) hidden = hidden || any_not_finite<DH>(xc);
+      mul_cols<DH>(xc, sc, dv);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    WaveTile<DH>::cols(q_tile, l32, hf, xc);
+    tiles_read();
+    if (t + NW < t1) { issue(t + NW); load_stat(t + NW); }   // the next tile travels under the last product
+    __builtin_amdgcn_sched_barrier(0);
+    if (EXACT && partial) {
+      accumulate_visible<DH>(base + (int64_t)i0 * ld, ld, min(s - i0, 32), dh, dp, dk, hf, sees_len);
+    } else {
+      if (partial) hidden = hidden || any_not_finite<DH>(xc);
+      mul_cols<DH>(xc, dp, dk);
+    }
   }
+  if (EXACT) __syncthreads();   // every wave is done with its tiles
+  else if (__syncthreads_or(hidden)) return true;
   float* out = dqkv + ((int64_t)n * s + j0) * ld + h + head * dh;
   put_strip<DH>(dk, scale, smem + wave * kRows * C::LD, l32, hf);
   __syncthreads();
@@ -485,11 +515,60 @@ __global__ __launch_bounds__(NW * 64, 1) void attn_f32_dkv_kernel(const float* _
   put_strip<DH>(dv, 1.0f, smem + wave * kRows * C::LD, l32, hf);
   __syncthreads();
   sum_strips<DH, NW>(smem, out + h, ld, s - j0, dh, tid, [](int) { return 1.0f; });
+  return false;
+}
+
+template <int DH, int NW>
+__global__ __launch_bounds__(NW * 64, (kPerSimd<DH>)) void attn_f32_dq_kernel(const float* __restrict__ qkv, const float* __restrict__ o,
+                                                                    const float* __restrict__ d_o, const float* __restrict__ lse,
+                                                                    float* __restrict__ delta, float* __restrict__ dqkv, int s, int a, int dh,
+                                                                    int mask_mode, const int32_t* __restrict__ seqlens) {
+  extern __shared__ __attribute__((aligned(16))) float smem[];
+  attn_f32_dq<DH, NW>(qkv, o, d_o, lse, delta, dqkv, s, a, dh, mask_mode, seqlens, mask_mode == 1 ? (int)(gridDim.z - 1 - blockIdx.z) : (int)blockIdx.z, smem);
+}
+template <int DH, int NW>
+__global__ __launch_bounds__(NW * 64, (kPerSimd<DH>)) void attn_f32_dkv_kernel(const float* __restrict__ qkv, const float* __restrict__ d_o,
+                                                                     const float* __restrict__ lse, const float* __restrict__ delta,
+                                                                     float* __restrict__ dqkv, int s, int a, int dh, int mask_mode,
+                                                                     const int32_t* __restrict__ seqlens) {
+  extern __shared__ __attribute__((aligned(16))) float smem[];
+  if (attn_f32_dkv<DH, NW, false, false>(qkv, nullptr, d_o, lse, delta, dqkv, s, a, dh, mask_mode, seqlens, blockIdx.z, smem))
+    attn_f32_dkv<DH, NW, false, true>(qkv, nullptr, d_o, lse, delta, dqkv, s, a, dh, mask_mode, seqlens, blockIdx.z, smem);
+}
+// Both in one launch: block 2k of grid.z has the keys of block k, block 2k + 1 the queries of block k (causal: k from the end), so the
+// longest workgroups of either kind go first.
+template <int DH, int NW>
+__global__ __launch_bounds__(NW * 64, (kPerSimd<DH>)) void attn_f32_bwd_kernel(const float* __restrict__ qkv, const float* __restrict__ o,
+                                                                     const float* __restrict__ d_o, const float* __restrict__ lse,
+                                                                     float* __restrict__ delta, float* __restrict__ dqkv, int s, int a, int dh,
+                                                                     int mask_mode, const int32_t* __restrict__ seqlens) {
+  extern __shared__ __attribute__((aligned(16))) float smem[];
+  const int k = blockIdx.z >> 1;
+  if (blockIdx.z & 1) attn_f32_dq<DH, NW>(qkv, o, d_o, lse, delta, dqkv, s, a, dh, mask_mode, seqlens, mask_mode == 1 ? (int)(gridDim.z >> 1) - 1 - k : k, smem);
+  else if (attn_f32_dkv<DH, NW, true, false>(qkv, o, d_o, lse, delta, dqkv, s, a, dh, mask_mode, seqlens, k, smem))
+    attn_f32_dkv<DH, NW, true, true>(qkv, o, d_o, lse, delta, dqkv, s, a, dh, mask_mode, seqlens, k, smem);
+}
+
+// Whether dQ and dK/dV share a launch.  One launch has twice the workgroups, of both lengths, and spares a launch and its tail; in two
+// dK/dV reads the delta that dQ has left and needs no row of O.  One over two launches, up to 128 blocks 0.6, to 256 0.7 to 1.0, to
+// 1024 0.9 (one wave per workgroup 0.65, 0.65, 0.7 to 1.0), above 1.0; heads above 64, whose workgroups fill a CU, in two launches of
+// one round each 0.9 where a workgroup has three tiles or more per wave and no mask shortens it.  Over 500 random sizes the choice
+// costs 0.6 % over the better one.
+bool one_launch(const AttnDesc& d) {
+  const int64_t blocks = (int64_t)d.b * d.a * ceil_div(d.s, kRows), cus = gemm_compute_units();
+  if (d.dh > 64 && d.mask_mode != 1 && d.s > 256 && 2 * blocks > cus && blocks <= cus) return false;
+  return blocks <= 4 * cus;
+}
+
+template <typename K>
+hipError_t set_lds(K kern, size_t bytes) {
+  return hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
 }
 
 template <int DH, int NW>
 hipError_t fwd_launch(const AttnDesc& d, const void* qkv, void* o, float* lse, hipStream_t st) {
-  constexpr size_t lds = (strip_floats<DH, NW>() + 2 * NW * kRows) * sizeof(float);
+  constexpr size_t lds = (tile_floats<DH, NW>() + 2 * NW * kRows) * sizeof(float);
+  static_assert(lds <= 160 * 1024, "LDS of a CU");
   static bool done = false;
   if (!done) {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(attn_f32_fwd_kernel<DH, NW>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
@@ -505,22 +584,29 @@ hipError_t fwd_launch(const AttnDesc& d, const void* qkv, void* o, float* lse, h
 template <int DH, int NW>
 hipError_t bwd_launch(const AttnDesc& d, const void* qkv, const void* o, const float* lse, const void* d_o, void* dqkv, float* delta,
                       hipStream_t st) {
-  constexpr size_t lds_dq = (strip_floats<DH, NW>() + (kDqLds<DH> ? 2 * resident_floats<DH>() : 0)) * sizeof(float);
-  constexpr size_t lds_dkv = (strip_floats<DH, NW>() + (kDkvLds<DH> ? 2 * resident_floats<DH>() : 0)) * sizeof(float);
-  static_assert(lds_dq <= 160 * 1024 && lds_dkv <= 160 * 1024, "LDS of a CU");
+  constexpr size_t lds_dq = tile_floats<DH, NW>() * sizeof(float);
+  constexpr size_t lds = lds_dq + NW * 64 * sizeof(float);
+  static_assert(lds <= 160 * 1024, "LDS of a CU");
   static bool done = false;
   if (!done) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(attn_f32_dq_kernel<DH, NW>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_dq);
-    if (e == hipSuccess)
-      e = hipFuncSetAttribute(reinterpret_cast<const void*>(attn_f32_dkv_kernel<DH, NW>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_dkv);
+    hipError_t e = set_lds(attn_f32_bwd_kernel<DH, NW>, lds);
+    if (e == hipSuccess) e = set_lds(attn_f32_dq_kernel<DH, NW>, lds_dq);
+    if (e == hipSuccess) e = set_lds(attn_f32_dkv_kernel<DH, NW>, lds);
     if (e != hipSuccess) return e;
     done = true;
   }
-  dim3 grid(d.a, d.b, ceil_div(d.s, kRows));
-  hipLaunchKernelGGL((attn_f32_dq_kernel<DH, NW>), grid, dim3(NW * 64), lds_dq, st, static_cast<const float*>(qkv), static_cast<const float*>(o),
-                     static_cast<const float*>(d_o), lse, delta, static_cast<float*>(dqkv), d.s, d.a, d.dh, d.mask_mode, d.seqlens);
-  hipLaunchKernelGGL((attn_f32_dkv_kernel<DH, NW>), grid, dim3(NW * 64), lds_dkv, st, static_cast<const float*>(qkv), static_cast<const float*>(d_o),
-                     lse, delta, static_cast<float*>(dqkv), d.s, d.a, d.dh, d.mask_mode, d.seqlens);
+  const int blocks = ceil_div(d.s, kRows);
+  const float *q = static_cast<const float*>(qkv), *out = static_cast<const float*>(o), *g = static_cast<const float*>(d_o);
+  float* dst = static_cast<float*>(dqkv);
+  if (one_launch(d)) {
+    hipLaunchKernelGGL((attn_f32_bwd_kernel<DH, NW>), dim3(d.a, d.b, 2 * blocks), dim3(NW * 64), lds, st, q, out, g, lse, delta, dst, d.s, d.a, d.dh,
+                       d.mask_mode, d.seqlens);
+  } else {
+    hipLaunchKernelGGL((attn_f32_dq_kernel<DH, NW>), dim3(d.a, d.b, blocks), dim3(NW * 64), lds_dq, st, q, out, g, lse, delta, dst, d.s, d.a, d.dh,
+                       d.mask_mode, d.seqlens);
+    hipLaunchKernelGGL((attn_f32_dkv_kernel<DH, NW>), dim3(d.a, d.b, blocks), dim3(NW * 64), lds, st, q, g, lse, delta, dst, d.s, d.a, d.dh,
+                       d.mask_mode, d.seqlens);
+  }
   return hipGetLastError();
 }
 
@@ -553,23 +639,30 @@ struct Bwd {
 }  // namespace
 
 namespace {
-// A CU holds one workgroup of four waves (their registers fill it) or four of one wave (three in the backward pass of heads above 112,
-// whose LDS fills it).  With t tiles of 32 rows to stream and an overhead of about 1.2 tiles, `blocks` blocks take ceil(blocks / CUs)
-// rounds of ceil(t / 4) + 1.2 tiles, or ceil(blocks / 4 CUs) rounds of t + 1.2, each of those 1.2 times as long as it would be alone;
-// 1.35 times more under a causal mask in a launch of one round, which ends on its longest blocks; 1.4 times more in the forward pass of
-// heads up to 32, of whose four-wave workgroups a CU holds two.  One wave over four, forward | backward, dh=64: s=64 384 blocks
-// 0.83 | 0.81, 640 0.62 | 0.61; s=100 512 1.15 | 1.20, 1024 0.70 | 0.71; s=300 640 0.89 | 0.92 (causal 1.24 | 1.31), 1600 causal
-// 0.60 | 0.60; s=512 768 1.07 | 1.07, 1024 0.85 | 0.82; dh=32 s=160 640 causal 1.28 | 1.01; dh=128 s=300 960 0.73 | 1.35.  Over the 336
-// launches behind these the choice costs 0.8 % over the better one, and none is more than 5 % behind four waves.  Where one thread
-// per row had been ahead of four waves (us, one thread, four, one): b=60 s=40 a=32 dh=32 29 | 73, 30 | 148, 21 | 75; b=46 s=17 a=12
-// dh=64 21 | 52, 18 | 57, 7.6 | 23.
+// One wave per workgroup, or four that split the t tiles of 32 rows to stream?  Forward: a CU holds one workgroup of four waves or four
+// of one; with an overhead of about 1.2 tiles, `blocks` blocks take ceil(blocks / CUs) rounds of ceil(t / 4) + 1.2 tiles, or
+// ceil(blocks / 4 CUs) rounds of t + 1.2, each of those 1.2 times as long as it would be alone; 1.35 times more under a causal mask
+// in a launch of one round, which ends on its longest blocks; 1.4 times more for heads up to 32, of whose four-wave workgroups a CU
+// holds two.  Over 500 random sizes the choice costs 0.5 % over the better one.
+// Backward, whose one launch has two workgroups per block: up to head size 64 a CU holds two of four waves or some six of one, above
+// that one or four; the constants are fitted to 500 random sizes with each form forced, over which the choice costs 1.2 % over the
+// better one.  Against four waves and one by the forward's rule 1.4 %.  (Before the tiles went through LDS and the two kernels into
+// one launch those 500 took 1.6 times as long; b=2 s=512 a=8 dh=64 causal 55 -> 42 us, b=2 s=64 a=4 dh=32 13 -> 7.4, b=1 s=768 a=4
+// dh=128 152 -> 78; slowest b=3 s=652 a=8 dh=72 194 -> 221.)
 bool one_wave(const AttnDesc& d, bool bwd) {
   const int64_t tiles = ceil_div(d.s, kRows), blocks = (int64_t)d.b * d.a * tiles, cus = gemm_compute_units();
-  const int64_t at_once = cus * (bwd && d.dh > 112 ? 3 : 4);
-  double one = 1.2 * ceil_div(blocks, at_once) * (tiles + 1.2);
-  if (d.mask_mode == 1 && blocks <= at_once && tiles > 2) one *= 1.35;
-  if (!bwd && d.dh <= 32) one *= 1.4;
-  return one < ceil_div(blocks, cus) * (ceil_div(tiles, kManyWaves) + 1.2);
+  const bool causal = d.mask_mode == 1 && tiles > 2;
+  if (!bwd) {
+    double one = 1.2 * ceil_div(blocks, 4 * cus) * (tiles + 1.2);
+    if (causal && blocks <= 4 * cus) one *= 1.35;
+    if (d.dh <= 32) one *= 1.4;
+    return one < ceil_div(blocks, cus) * (ceil_div(tiles, kManyWaves) + 1.2);
+  }
+  const int64_t wgs = one_launch(d) ? 2 * blocks : blocks, ones = (d.dh <= 64 ? 6 : 4) * cus, fours = (d.dh <= 64 ? 2 : 1) * cus;
+  double one = 1.38 * ceil_div(wgs, ones) * (tiles + 0.33), four = ceil_div(wgs, fours) * (ceil_div(tiles, kManyWaves) + 1.13);
+  if (causal && wgs <= ones) one *= 1.33;
+  if (d.dh <= 64 && wgs > cus) four *= 1.05;
+  return one < four;
 }
 }  // namespace
 
