@@ -69,29 +69,32 @@ __device__ __forceinline__ void load_row(const float* __restrict__ row, int dh, 
 // registers, and read both as rows (16 bytes per lane) and as columns (4 bytes).  Straight from L2 into fragment registers every
 // operand came twice, the second time by 16 loads of two rows each per 32 columns, and a load occupies the CU's address unit for some
 // 16 cycles whatever it brings: 112 of them per tile and wave in dK/dV were as much time as the matrix instructions.
-// Layout: rows of LW floats (16, 32, 64 or 128, what lies past the head is zero), 1 KB blocks of kRowsPer rows as a load instruction
-// writes them, 16-byte chunks XOR-swizzled by row inside a block and kPad floats between blocks: 16 consecutive rows at one chunk then
+// Layout: rows of LW floats (what lies past the head is zero) in blocks of kRowsPer rows, as one load instruction writes them (three for
+// rows of 96), 16-byte chunks XOR-swizzled by row inside a block and kPad floats between blocks: 16 consecutive rows at one chunk then
 // fall on all banks, and the addresses of a lane differ by constants but for two or four.
 __device__ const float4 kZeros = {0.f, 0.f, 0.f, 0.f};
 template <int DH>
 struct WaveTile {
-  static constexpr int LW = DH <= 16 ? 16 : DH <= 32 ? 32 : DH <= 64 ? 64 : 128;
-  static constexpr int CH = LW / 4, kRowsPer = 64 / CH, kInstr = 32 / kRowsPer;
+  static constexpr int LW = DH <= 16 ? 16 : DH <= 32 ? 32 : DH <= 64 ? 64 : DH <= 96 ? 96 : 128;
+  static constexpr int CH = LW / 4, kLoads = LW == 96 ? 3 : 1, kRowsPer = 64 * kLoads / CH;
   static constexpr int kPad = LW == 16 ? 0 : LW == 128 ? 8 : 16;
-  static constexpr int kBlock = 256 + kPad, kFloats = kInstr * kBlock;
-  // swizzle of a row: two bits, one for rows of 512 bytes
-  static __device__ __forceinline__ int swz(int row) { return LW == 128 ? row & 1 : LW == 64 ? row & 3 : LW == 32 ? (row >> 1) & 3 : (row >> 2) & 3; }
+  static constexpr int kBlock = kLoads * 256 + kPad, kFloats = 32 / kRowsPer * kBlock;
+  // swizzle of a row: two bits, one for rows of 512 bytes; the same in every block
+  static __device__ __forceinline__ int swz(int row) { return LW == 128 ? row & 1 : LW == 64 ? row & 3 : LW == 16 ? (row >> 2) & 3 : (row >> 1) & 3; }
   static __device__ __forceinline__ int at(int row) { return row / kRowsPer * kBlock + row % kRowsPer * LW; }
   // rows [0, rows) x [0, dh) of the matrix at src (uniform) into t; the rest is zero
   static __device__ __forceinline__ void issue(const float* __restrict__ src, int64_t ld, int rows, int dh, int lane, float* t) {
-    const int row = lane / CH, c = (lane % CH) ^ swz(row);   // (the swizzle has the period of a block)
     asm volatile("" : "+s"(src));   // else the loop keeps a pointer per lane and load instruction
-    const float* from = src + row * ld + 4 * c;
-    const bool in_head = 4 * c < dh;
 #pragma unroll
-    for (int q = 0; q < kInstr; ++q) {
-      const float* p = in_head && row < rows - q * kRowsPer ? from + q * kRowsPer * ld : reinterpret_cast<const float*>(&kZeros);
-      __builtin_amdgcn_global_load_lds((glob_void_t*)p, (lds_void_t*)(t + q * kBlock), 16, 0, 0);
+    for (int u = 0; u < kLoads; ++u) {
+      const int L = u * 64 + lane, row = L / CH, c = (L % CH) ^ swz(row);
+      const float* from = src + row * ld + 4 * c;
+      const bool in_head = 4 * c < dh;
+#pragma unroll
+      for (int q = 0; q < 32 / kRowsPer; ++q) {
+        const float* p = in_head && row < rows - q * kRowsPer ? from + q * kRowsPer * ld : reinterpret_cast<const float*>(&kZeros);
+        __builtin_amdgcn_global_load_lds((glob_void_t*)p, (lds_void_t*)(t + q * kBlock + u * 256), 16, 0, 0);
+      }
     }
   }
   // head columns 8j + 4*hf .. +3 of row l32
@@ -549,15 +552,15 @@ __global__ __launch_bounds__(NW * 64, (kPerSimd<DH>)) void attn_f32_bwd_kernel(c
     attn_f32_dkv<DH, NW, true, true>(qkv, o, d_o, lse, delta, dqkv, s, a, dh, mask_mode, seqlens, k, smem);
 }
 
-// Whether dQ and dK/dV share a launch.  One launch has twice the workgroups, of both lengths, and spares a launch and its tail; in two
-// dK/dV reads the delta that dQ has left and needs no row of O.  One over two launches, up to 128 blocks 0.6, to 256 0.7 to 1.0, to
-// 1024 0.9 (one wave per workgroup 0.65, 0.65, 0.7 to 1.0), above 1.0; heads above 64, whose workgroups fill a CU, in two launches of
-// one round each 0.9 where a workgroup has three tiles or more per wave and no mask shortens it.  Over 500 random sizes the choice
-// costs 0.6 % over the better one.
-bool one_launch(const AttnDesc& d) {
+// Whether dQ and dK/dV, on `waves` waves per workgroup, share a launch.  One launch has twice the workgroups, of both lengths, and spares
+// a launch and its tail; in two dK/dV reads the delta that dQ has left and needs no row of O.  One over two launches, four waves: up
+// to 128 blocks 0.6, to 256 0.7 to 1.0, to 1024 0.9, above 1.0; heads above 64, whose workgroups fill a CU, 1.1 where either half is a
+// full round and long and no mask evens out.  One wave: up to 512 blocks 0.65, to 2048 0.65 to 0.8 under a causal mask, 0.9 with
+// lengths, 1.0 without, beyond 0.9 with a mask.
+bool one_launch(const AttnDesc& d, int waves) {
   const int64_t blocks = (int64_t)d.b * d.a * ceil_div(d.s, kRows), cus = gemm_compute_units();
   if (d.dh > 64 && d.mask_mode != 1 && d.s > 256 && 2 * blocks > cus && blocks <= cus) return false;
-  return blocks <= 4 * cus;
+  return blocks <= 4 * cus || (waves == 1 && d.mask_mode != 0);
 }
 
 template <typename K>
@@ -598,7 +601,7 @@ hipError_t bwd_launch(const AttnDesc& d, const void* qkv, const void* o, const f
   const int blocks = ceil_div(d.s, kRows);
   const float *q = static_cast<const float*>(qkv), *out = static_cast<const float*>(o), *g = static_cast<const float*>(d_o);
   float* dst = static_cast<float*>(dqkv);
-  if (one_launch(d)) {
+  if (one_launch(d, NW)) {
     hipLaunchKernelGGL((attn_f32_bwd_kernel<DH, NW>), dim3(d.a, d.b, 2 * blocks), dim3(NW * 64), lds, st, q, out, g, lse, delta, dst, d.s, d.a, d.dh,
                        d.mask_mode, d.seqlens);
   } else {
@@ -644,11 +647,10 @@ namespace {
 // ceil(blocks / 4 CUs) rounds of t + 1.2, each of those 1.2 times as long as it would be alone; 1.35 times more under a causal mask
 // in a launch of one round, which ends on its longest blocks; 1.4 times more for heads up to 32, of whose four-wave workgroups a CU
 // holds two.  Over 500 random sizes the choice costs 0.5 % over the better one.
-// Backward, whose one launch has two workgroups per block: up to head size 64 a CU holds two of four waves or some six of one, above
-// that one or four; the constants are fitted to 500 random sizes with each form forced, over which the choice costs 1.2 % over the
-// better one.  Against four waves and one by the forward's rule 1.4 %.  (Before the tiles went through LDS and the two kernels into
-// one launch those 500 took 1.6 times as long; b=2 s=512 a=8 dh=64 causal 55 -> 42 us, b=2 s=64 a=4 dh=32 13 -> 7.4, b=1 s=768 a=4
-// dh=128 152 -> 78; slowest b=3 s=652 a=8 dh=72 194 -> 221.)
+// Backward, whose one launch has two workgroups per block: up to head size 64 a CU holds two of four waves or eight of one, above
+// that one or four; the constants are fitted to 500 random sizes with each form forced, over which the choice costs 0.8 % over the
+// better one.  (Before the tiles went through LDS and the two kernels into one launch those 500 took 1.6 times as long; b=2 s=512 a=8
+// dh=64 causal 55 -> 42 us, b=2 s=64 a=4 dh=32 13 -> 7.4, b=1 s=768 a=4 dh=128 152 -> 78.)
 bool one_wave(const AttnDesc& d, bool bwd) {
   const int64_t tiles = ceil_div(d.s, kRows), blocks = (int64_t)d.b * d.a * tiles, cus = gemm_compute_units();
   const bool causal = d.mask_mode == 1 && tiles > 2;
@@ -658,10 +660,12 @@ bool one_wave(const AttnDesc& d, bool bwd) {
     if (d.dh <= 32) one *= 1.4;
     return one < ceil_div(blocks, cus) * (ceil_div(tiles, kManyWaves) + 1.2);
   }
-  const int64_t wgs = one_launch(d) ? 2 * blocks : blocks, ones = (d.dh <= 64 ? 6 : 4) * cus, fours = (d.dh <= 64 ? 2 : 1) * cus;
-  double one = 1.38 * ceil_div(wgs, ones) * (tiles + 0.33), four = ceil_div(wgs, fours) * (ceil_div(tiles, kManyWaves) + 1.13);
-  if (causal && wgs <= ones) one *= 1.33;
-  if (d.dh <= 64 && wgs > cus) four *= 1.05;
+  auto launches = [&](int waves) { return one_launch(d, waves) ? 1 : 2; };
+  const int n1 = launches(1), n4 = launches(kManyWaves);
+  const int64_t ones = (d.dh <= 64 ? 8 : 4) * cus, fours = (d.dh <= 64 ? 2 : 1) * cus, wgs1 = 2 * blocks / n1;
+  double one = 0.93 * n1 * ceil_div(wgs1, ones) * (tiles + 0.34);
+  if (causal && wgs1 <= ones) one *= 1.56;
+  const double four = n4 * ceil_div(2 * blocks / n4, fours) * (ceil_div(tiles, kManyWaves) + 0.34);
   return one < four;
 }
 }  // namespace
