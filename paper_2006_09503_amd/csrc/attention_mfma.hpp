@@ -57,6 +57,7 @@ typedef __attribute__((address_space(1))) const void glob_void_t;
 // dh = 128 causal: forward 270 / 258 / 152 us): more waves share each K/V tile and each barrier.
 // That is with a workgroup for every CU; see shape_for for smaller launches.
 constexpr int kTile = 64;         // rows streamed through LDS per step
+constexpr int kMaxDeltas = 2048;  // longest sequence whose deltas a workgroup holds in LDS
 constexpr float kLog2e = 1.4426950408889634f;
 
 template <int DH, bool ANY = false>
@@ -283,6 +284,17 @@ __device__ __forceinline__ float row16_sum(float v) {
   v = dpp_add(v, std::integral_constant<int, 0x141>{});   // row_half_mirror
   v = dpp_add(v, std::integral_constant<int, 0x140>{});   // row_mirror
   return v;
+}
+
+// ... and over the 8 lanes of half a row
+__device__ __forceinline__ float row8_sum(float v) {
+  auto dpp_add = [](float x, auto ctrl) {
+    const int y = __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), decltype(ctrl)::value, 0xF, 0xF, false);
+    return x + __builtin_bit_cast(float, y);
+  };
+  v = dpp_add(v, std::integral_constant<int, 0xB1>{});
+  v = dpp_add(v, std::integral_constant<int, 0x4E>{});
+  return dpp_add(v, std::integral_constant<int, 0x141>{});
 }
 
 // Column sums over the workgroup's rows of a result held as acc[db][r] (lane = row, registers =
@@ -529,7 +541,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_fwd_mfma_kernel(const bf16_t*
 // ------------------------------------------------------------------------------------------------
 // dQ (and delta = rowsum(dO * O), which the dK/dV kernel reads afterwards)
 template <int DH, int NW, int KSPL, bool ANY, bool EXACT>
-__device__ __forceinline__ bool attn_dq(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ o, const bf16_t* __restrict__ d_o, const float* __restrict__ lse, float* __restrict__ delta, bf16_t* __restrict__ dqkv, int s, int a, int mask_mode, const int32_t* __restrict__ seqlens, float* __restrict__ colsum, int dh_) {
+__device__ __forceinline__ bool attn_dq(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ o, const bf16_t* __restrict__ d_o, const float* __restrict__ lse, float* __restrict__ delta, bf16_t* __restrict__ dqkv, int s, int a, int mask_mode, const int32_t* __restrict__ seqlens, float* __restrict__ colsum, int dh_, int blk, int nblk) {
   using C = Cfg<DH>;
   extern __shared__ uint4 smem[];   // stage st: K tile at st * 2 * kTileU4, V tile behind it
 
@@ -542,7 +554,6 @@ __device__ __forceinline__ bool attn_dq(const bf16_t* __restrict__ qkv, const bf
   // dispatched together, and under a causal mask the blocks with the most keys to visit (the last queries) go
   // first: the workgroups that take longest start earliest and the launch does not end on one of them
   const int n = blockIdx.y, head = blockIdx.x;
-  const int blk = mask_mode == 1 ? (int)(gridDim.z - 1 - blockIdx.z) : (int)blockIdx.z;
   const int i0 = blk * RW * 32;
   const int dh = ANY ? dh_ : DH;
   const int h = a * dh;
@@ -674,7 +685,7 @@ __device__ __forceinline__ bool attn_dq(const bf16_t* __restrict__ qkv, const bf
     __syncthreads();
   }
   if (!ANY && colsum) {   // rows past the end of the sequence hold zeros
-    float* row = colsum + ((int64_t)n * gridDim.z + blk) * ld + head * dh;
+    float* row = colsum + ((int64_t)n * nblk + blk) * ld + head * dh;
     block_column_sums<DH, NW>(dq, scale, reinterpret_cast<float*>(smem), row, tid, lane, wave);
     __syncthreads();   // ... and with the partial rows of the sums
   }
@@ -683,8 +694,9 @@ __device__ __forceinline__ bool attn_dq(const bf16_t* __restrict__ qkv, const bf
 }
 template <int DH, int NW, int KSPL, bool ANY>
 __global__ __launch_bounds__(NW * 64, 2) void attn_dq_mfma_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ o, const bf16_t* __restrict__ d_o, const float* __restrict__ lse, float* __restrict__ delta, bf16_t* __restrict__ dqkv, int s, int a, int mask_mode, const int32_t* __restrict__ seqlens, float* __restrict__ colsum, int dh_) {
-  if (attn_dq<DH, NW, KSPL, ANY, false>(qkv, o, d_o, lse, delta, dqkv, s, a, mask_mode, seqlens, colsum, dh_))
-    if constexpr (ANY) attn_dq<DH, NW, KSPL, ANY, true>(qkv, o, d_o, lse, delta, dqkv, s, a, mask_mode, seqlens, colsum, dh_);
+  const int nblk = gridDim.z, blk = mask_mode == 1 ? nblk - 1 - (int)blockIdx.z : (int)blockIdx.z;
+  if (attn_dq<DH, NW, KSPL, ANY, false>(qkv, o, d_o, lse, delta, dqkv, s, a, mask_mode, seqlens, colsum, dh_, blk, nblk))
+    if constexpr (ANY) attn_dq<DH, NW, KSPL, ANY, true>(qkv, o, d_o, lse, delta, dqkv, s, a, mask_mode, seqlens, colsum, dh_, blk, nblk);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -694,8 +706,10 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_dq_mfma_kernel(const bf16_t* 
 // loop waits for the next tile's loads: backward at b=3 s=1000 a=16 causal, head size 96 119 -> 100 us, 72 145 -> 91); and launches
 // that leave half of the CUs idle gain the second half's work (backward, 64-row blocks: b=1 s=1024 a=8 dh=64 30.2 -> 28.2 us,
 // b=1 s=2048 a=4 causal 51.3 -> 47.4).
+// delta_lds: null, and delta comes from what the dQ kernel left; or LDS for as many floats as the sequence has rows, which the
+// workgroup fills from dO and O while its first tile travels.
 template <int DH, int NW, int KSPL, bool ANY, bool EXACT, int PART>
-__device__ __forceinline__ bool attn_dkv(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ d_o, const float* __restrict__ lse, const float* __restrict__ delta, bf16_t* __restrict__ dqkv, int s, int a, int mask_mode, const int32_t* __restrict__ seqlens, float* __restrict__ colsum, int dh_) {
+__device__ __forceinline__ bool attn_dkv(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ o, const bf16_t* __restrict__ d_o, const float* __restrict__ lse, const float* __restrict__ delta, bf16_t* __restrict__ dqkv, int s, int a, int mask_mode, const int32_t* __restrict__ seqlens, float* __restrict__ colsum, int dh_, int blk, int nblk, float* delta_lds) {
   using C = Cfg<DH>;
   extern __shared__ uint4 smem[];
   // stage st: Q tile, dO tile, 64 lse, 64 delta
@@ -707,7 +721,7 @@ __device__ __forceinline__ bool attn_dkv(const bf16_t* __restrict__ qkv, const b
   // (halves of the waves: see the forward kernel)
   constexpr int RW = NW / KSPL;
   const int kg = KSPL == 1 ? 0 : wave / RW, rw = KSPL == 1 ? wave : wave % RW;
-  const int n = blockIdx.y, head = blockIdx.x, blk = PART ? (int)blockIdx.z >> 1 : (int)blockIdx.z;
+  const int n = blockIdx.y, head = blockIdx.x;
   constexpr bool DV = PART != 2, DK = PART != 1;
   const int j0 = blk * RW * 32;
   const int dh = ANY ? dh_ : DH;
@@ -753,12 +767,45 @@ __device__ __forceinline__ bool attn_dkv(const bf16_t* __restrict__ qkv, const b
   float stat = 0.f;
   auto load_stat = [&](int i0) {
     if (rw < 2) stat = (rw == 0 ? lse_row : delta_row)[min(i0 + lane, s - 1)];
+    if (delta_lds && rw == 1) stat = delta_lds[min(i0 + lane, s - 1)];
   };
   bool hidden = false;
 #pragma unroll
   for (int db = 0; db < C::DB; ++db) { dk[db] = zero16(); dv[db] = zero16(); }
   uint4* const tiles = smem + kg * (2 * kStageU4 + C::kPadU4);
-  if (kg < ntiles) { load_stat(istart + kg * kTile); issue_tile(istart + kg * kTile, tiles); }
+  if (kg < ntiles) issue_tile(istart + kg * kTile, tiles);
+  if (delta_lds && DK && ntiles > 0) {   // (uniform) eight lanes per row, U rows in flight
+    constexpr int NC = (C::CH + 7) / 8, U = NC == 1 ? 8 : 4;
+    for (int r0 = istart + wave * 8; r0 < s; r0 += U * NW * 8) {
+      bf16x8 x[U][NC], y[U][NC];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int64_t at = ((int64_t)n * s + min(r0 + u * NW * 8 + (lane >> 3), s - 1)) * h + head * dh;
+#pragma unroll
+        for (int q = 0; q < NC; ++q) {
+          const int c8 = min(((lane & 7) + q * 8) * 8, dh - 8);   // (past the head: the last chunk, not counted below)
+          x[u][q] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(d_o + at + c8));
+          y[u][q] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(o + at + c8));
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int row = r0 + u * NW * 8 + (lane >> 3);
+        float part = 0.f;
+#pragma unroll
+        for (int q = 0; q < NC; ++q) {
+          float t = 0.f;
+#pragma unroll
+          for (int e = 0; e < 8; ++e) t = fmaf((float)x[u][q][e], (float)y[u][q][e], t);
+          part += ((lane & 7) + q * 8) * 8 < dh ? t : 0.f;
+        }
+        part = row8_sum(part);
+        if ((lane & 7) == 0 && row < s) delta_lds[row] = part;
+      }
+    }
+    __syncthreads();
+  }
+  if (kg < ntiles) load_stat(istart + kg * kTile);
   for (int st = 0; st * KSPL < ntiles; ++st) {
     const int t = st * KSPL + kg, i0 = istart + t * kTile;
     __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
@@ -879,7 +926,7 @@ __device__ __forceinline__ bool attn_dkv(const bf16_t* __restrict__ qkv, const b
     __syncthreads();
   }
   if (!ANY && colsum) {   // masked and non-existent keys hold zeros
-    float* row = colsum + ((int64_t)n * (gridDim.z >> (PART ? 1 : 0)) + blk) * ld + head * dh;
+    float* row = colsum + ((int64_t)n * nblk + blk) * ld + head * dh;
     float* red = reinterpret_cast<float*>(smem);
     if (DK) {
       block_column_sums<DH, NW>(dk, scale, red, row + h, tid, lane, wave);
@@ -898,14 +945,41 @@ __device__ __forceinline__ bool attn_dkv(const bf16_t* __restrict__ qkv, const b
 }
 template <int DH, int NW, int KSPL, bool ANY, bool PARTS>
 __global__ __launch_bounds__(NW * 64, 2) void attn_dkv_mfma_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ d_o, const float* __restrict__ lse, const float* __restrict__ delta, bf16_t* __restrict__ dqkv, int s, int a, int mask_mode, const int32_t* __restrict__ seqlens, float* __restrict__ colsum, int dh_) {
+  const int nblk = gridDim.z >> (PARTS ? 1 : 0), blk = blockIdx.z >> (PARTS ? 1 : 0);
   auto run = [&](auto part) __attribute__((always_inline)) {
     constexpr int PART = decltype(part)::value;
-    if (attn_dkv<DH, NW, KSPL, ANY, false, PART>(qkv, d_o, lse, delta, dqkv, s, a, mask_mode, seqlens, colsum, dh_))
-      if constexpr (ANY) attn_dkv<DH, NW, KSPL, ANY, true, PART>(qkv, d_o, lse, delta, dqkv, s, a, mask_mode, seqlens, colsum, dh_);
+    if (attn_dkv<DH, NW, KSPL, ANY, false, PART>(qkv, nullptr, d_o, lse, delta, dqkv, s, a, mask_mode, seqlens, colsum, dh_, blk, nblk, nullptr))
+      if constexpr (ANY) attn_dkv<DH, NW, KSPL, ANY, true, PART>(qkv, nullptr, d_o, lse, delta, dqkv, s, a, mask_mode, seqlens, colsum, dh_, blk, nblk, nullptr);
   };
   if constexpr (!PARTS) run(std::integral_constant<int, 0>{});
   else if (blockIdx.z & 1) run(std::integral_constant<int, 1>{});
   else run(std::integral_constant<int, 2>{});
+}
+
+// The whole backward pass in one launch.  Of every kRoles consecutive block numbers one has queries (causal: the blocks with the most
+// keys first), the others keys, so the longest workgroups of every kind go first.  delta_at: where the row of deltas lies in LDS.
+template <int DH, int NW, int KSPL, bool ANY, bool PARTS>
+__global__ __launch_bounds__(NW * 64, 2) void attn_bwd_mfma_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ o, const bf16_t* __restrict__ d_o, const float* __restrict__ lse, float* __restrict__ delta, bf16_t* __restrict__ dqkv, int s, int a, int mask_mode, const int32_t* __restrict__ seqlens, float* __restrict__ colsum, int dh_, int delta_at) {
+  extern __shared__ uint4 smem[];
+  constexpr int kRoles = PARTS ? 3 : 2;
+  const int nblk = gridDim.z / kRoles, k = blockIdx.z / kRoles, role = blockIdx.z % kRoles;
+  float* delta_lds = reinterpret_cast<float*>(smem + delta_at);
+  auto run = [&](auto part) __attribute__((always_inline)) {
+    constexpr int PART = decltype(part)::value;
+    if (attn_dkv<DH, NW, KSPL, ANY, false, PART>(qkv, o, d_o, lse, delta, dqkv, s, a, mask_mode, seqlens, colsum, dh_, k, nblk, delta_lds))
+      if constexpr (ANY) attn_dkv<DH, NW, KSPL, ANY, true, PART>(qkv, o, d_o, lse, delta, dqkv, s, a, mask_mode, seqlens, colsum, dh_, k, nblk, delta_lds);
+  };
+  if (role == kRoles - 1) {
+    const int blk = mask_mode == 1 ? nblk - 1 - k : k;
+    if (attn_dq<DH, NW, KSPL, ANY, false>(qkv, o, d_o, lse, delta, dqkv, s, a, mask_mode, seqlens, colsum, dh_, blk, nblk))
+      if constexpr (ANY) attn_dq<DH, NW, KSPL, ANY, true>(qkv, o, d_o, lse, delta, dqkv, s, a, mask_mode, seqlens, colsum, dh_, blk, nblk);
+  } else if constexpr (!PARTS) {
+    run(std::integral_constant<int, 0>{});
+  } else if (role == 1) {
+    run(std::integral_constant<int, 1>{});
+  } else {
+    run(std::integral_constant<int, 2>{});
+  }
 }
 
 template <typename K>
@@ -918,6 +992,23 @@ hipError_t set_lds(K kern, size_t bytes, bool* done) {
 }
 
 constexpr size_t max_of(size_t a, size_t b) { return a > b ? a : b; }
+
+// LDS of the two kernels, in bytes
+template <int DH, int NW, int KSPL>
+constexpr size_t dq_lds() {
+  using C = Cfg<DH>;
+  constexpr size_t out = (size_t)NW * out_strip_u4<DH>() * sizeof(uint4);   // the output strips re-use the tiles' LDS
+  constexpr size_t merge = KSPL == 1 ? 0 : NW / KSPL * C::DB * 16 * 64 * sizeof(float);   // ... and so do the halves' results
+  return max_of(max_of(KSPL * (4 * C::kTileU4 + C::kPadU4) * sizeof(uint4), out), merge);
+}
+template <int DH, int NW, int KSPL, bool ANY, bool PARTS>
+constexpr size_t dkv_lds() {
+  using C = Cfg<DH>;
+  constexpr size_t out = (size_t)NW * out_strip_u4<DH>() * sizeof(uint4);
+  constexpr size_t merge = KSPL == 1 ? 0 : NW / KSPL * (PARTS ? 1 : 2) * C::DB * 16 * 64 * sizeof(float);
+  constexpr size_t tiles = (KSPL * (2 * (2 * C::kTileU4 + 2 * kTile / 4) + C::kPadU4) + (!PARTS && Cfg<DH, ANY>::kDkvVInLds ? NW * C::KS * 64 : 0)) * sizeof(uint4);
+  return max_of(max_of(tiles, out), merge);
+}
 
 template <int DH, int NW, int KSPL, bool ANY>
 hipError_t fwd_launch(const AttnDesc& d, const void* qkv, void* o, float* lse, hipStream_t st) {
@@ -937,12 +1028,7 @@ hipError_t fwd_launch(const AttnDesc& d, const void* qkv, void* o, float* lse, h
 
 template <int DH, int NW, int KSPL, bool ANY, bool PARTS>
 hipError_t dkv_launch(const AttnDesc& d, const void* qkv, const float* lse, const void* d_o, void* dqkv, const float* delta, hipStream_t st) {
-  using C = Cfg<DH>;
-  constexpr size_t lds_out = (size_t)NW * out_strip_u4<DH>() * sizeof(uint4);
-  constexpr size_t lds_merge = KSPL == 1 ? 0 : NW / KSPL * (PARTS ? 1 : 2) * C::DB * 16 * 64 * sizeof(float);
-  constexpr size_t lds_tiles = (KSPL * (2 * (2 * C::kTileU4 + 2 * kTile / 4) + C::kPadU4) +
-                                (!PARTS && Cfg<DH, ANY>::kDkvVInLds ? NW * C::KS * 64 : 0)) * sizeof(uint4);
-  constexpr size_t lds = max_of(max_of(lds_tiles, lds_out), lds_merge);
+  constexpr size_t lds = dkv_lds<DH, NW, KSPL, ANY, PARTS>();
   static_assert(lds <= 160 * 1024, "LDS of a CU");
   static bool done = false;
   hipError_t e = set_lds(attn_dkv_mfma_kernel<DH, NW, KSPL, ANY, PARTS>, lds, &done);
@@ -954,13 +1040,46 @@ hipError_t dkv_launch(const AttnDesc& d, const void* qkv, const float* lse, cons
   return hipGetLastError();
 }
 
+// Whether `wgs` workgroups of both halves together go out in one launch, which spares a launch and its tail but makes dK/dV's
+// workgroups form the deltas they need (their rows of dO and O: some 3 us at 600 rows): where they all run at once, or under a causal
+// mask, whose blocks differ, one and a half times as many.  One over two launches by wgs over what the CUs hold at once, no mask |
+// causal | lengths: up to 0.5 0.65 | 0.64 | 0.65, to 1 0.69 | 0.66 | 0.68, to 1.25 0.84 (at worst 1.04) | 0.82 | 0.91 (1.33), to 1.5
+// 1.05 (1.37) | 0.79 | 0.96 (1.23), to 3 0.92 (1.2) | 0.91 (1.08) | 0.95 (1.29).  By this rule 600 random calls take 0.715 of the time
+// with two launches always, none more than 1.03.
+template <int DH, int NW, bool ANY>
+bool one_launch(const AttnDesc& d, int64_t wgs) {
+  constexpr bool kSmall = DH == 32 && !ANY;                                        // 128 registers
+  constexpr int kPerCu = NW == 4 ? (kSmall ? 4 : DH <= 64 ? 2 : 1) : (kSmall ? 2 : 1);   // by registers and LDS
+  return d.s <= kMaxDeltas && 2 * wgs <= (d.mask_mode == 1 ? 3 : 2) * kPerCu * (int64_t)gemm_compute_units();
+}
+
+// Both halves of the backward pass in one launch
+template <int DH, int NW, int KSPL, bool ANY, bool PARTS>
+hipError_t both_launch(const AttnDesc& d, const void* qkv, const void* o, const float* lse, const void* d_o, void* dqkv, float* delta, hipStream_t st) {
+  constexpr size_t base = max_of(dq_lds<DH, NW, KSPL>(), dkv_lds<DH, NW, KSPL, ANY, PARTS>());
+  const size_t lds = base + ceil_div(d.s, 4) * sizeof(uint4);
+  static bool done = false;
+  hipError_t e = set_lds(attn_bwd_mfma_kernel<DH, NW, KSPL, ANY, PARTS>, base + kMaxDeltas * sizeof(float), &done);
+  if (e != hipSuccess) return e;
+  static_assert(base + kMaxDeltas * sizeof(float) <= 160 * 1024, "LDS of a CU");
+  dim3 grid(d.a, d.b, ceil_div(d.s, NW / KSPL * 32) * (PARTS ? 3 : 2));
+  hipLaunchKernelGGL((attn_bwd_mfma_kernel<DH, NW, KSPL, ANY, PARTS>), grid, dim3(NW * 64), lds, st, static_cast<const bf16_t*>(qkv), static_cast<const bf16_t*>(o),
+                     static_cast<const bf16_t*>(d_o), lse, delta, static_cast<bf16_t*>(dqkv), d.s, d.a, d.mask_mode, d.seqlens, d.colsum_partial, d.dh,
+                     (int)(base / sizeof(uint4)));
+  return hipGetLastError();
+}
+
 template <int DH, int NW, int KSPL, bool ANY>
 hipError_t bwd_launch(const AttnDesc& d, const void* qkv, const void* o, const float* lse, const void* d_o, void* dqkv,
                       float* delta, hipStream_t st) {
-  using C = Cfg<DH>;
-  constexpr size_t lds_out = (size_t)NW * out_strip_u4<DH>() * sizeof(uint4);
-  constexpr size_t lds_merge = KSPL == 1 ? 0 : NW / KSPL * C::DB * 16 * 64 * sizeof(float);
-  constexpr size_t lds = max_of(max_of(KSPL * (4 * C::kTileU4 + C::kPadU4) * sizeof(uint4), lds_out), lds_merge);
+  // (two sets of tiles and the V fragments of head size 128 do not fit in LDS together)
+  constexpr bool kAlways = Cfg<DH, ANY>::kDkvParts || (KSPL == 2 && Cfg<DH, ANY>::kDkvVInLds), kMay = kAlways || (NW == 4 && KSPL == 2);
+  // few blocks: dK and dV in workgroups of their own (see attn_dkv)
+  const int64_t blocks = (int64_t)d.a * d.b * ceil_div(d.s, NW / KSPL * 32);
+  const bool parts = kAlways || (kMay && 2 * blocks <= gemm_compute_units());
+  if (one_launch<DH, NW, ANY>(d, blocks * (parts ? 3 : 2)))
+    return parts ? both_launch<DH, NW, KSPL, ANY, kMay>(d, qkv, o, lse, d_o, dqkv, delta, st) : both_launch<DH, NW, KSPL, ANY, kAlways>(d, qkv, o, lse, d_o, dqkv, delta, st);
+  constexpr size_t lds = dq_lds<DH, NW, KSPL>();
   static_assert(lds <= 160 * 1024, "LDS of a CU");
   static bool done = false;
   hipError_t e = set_lds(attn_dq_mfma_kernel<DH, NW, KSPL, ANY>, lds, &done);
@@ -971,12 +1090,7 @@ hipError_t bwd_launch(const AttnDesc& d, const void* qkv, const void* o, const f
                      static_cast<bf16_t*>(dqkv), d.s, d.a, d.mask_mode, d.seqlens, d.colsum_partial, d.dh);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
-  // (two sets of tiles and the V fragments of head size 128 do not fit in LDS together)
-  constexpr bool kAlways = Cfg<DH, ANY>::kDkvParts || (KSPL == 2 && Cfg<DH, ANY>::kDkvVInLds), kMay = kAlways || (NW == 4 && KSPL == 2);
-  // few blocks: dK and dV in workgroups of their own (see attn_dkv)
-  const int64_t blocks = (int64_t)d.a * d.b * ceil_div(d.s, NW / KSPL * 32);
-  if (kAlways || (kMay && 2 * blocks <= gemm_compute_units())) return dkv_launch<DH, NW, KSPL, ANY, kMay>(d, qkv, lse, d_o, dqkv, delta, st);
-  return dkv_launch<DH, NW, KSPL, ANY, kAlways>(d, qkv, lse, d_o, dqkv, delta, st);
+  return parts ? dkv_launch<DH, NW, KSPL, ANY, kMay>(d, qkv, lse, d_o, dqkv, delta, st) : dkv_launch<DH, NW, KSPL, ANY, kAlways>(d, qkv, lse, d_o, dqkv, delta, st);
 }
 
 // F<DH, NW, KSPL, ANY>::run for the head size of a call
