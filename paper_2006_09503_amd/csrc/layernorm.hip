@@ -267,31 +267,29 @@ __global__ __launch_bounds__(kWg) void ln_bwd_kernel(const T* __restrict__ dy, c
 
 // Backward for long rows (h >= 2048).  With 256 threads the per-column sums of a row of 8192 take 96
 // registers per thread next to the row itself, one wave per SIMD fits, and a CU has too few loads in
-// flight to keep HBM busy.  Here a workgroup has 1024 threads, R = 256, 512 or 1024 of them share a row
-// with one or two 16-byte chunks each, so the sums are 24 or 48 registers and sixteen waves stay resident
-// per CU.  A workgroup is alone on its CU, so nothing else hides its trips to HBM: the U rows per thread
+// flight to keep HBM busy.  Here a workgroup has 768 to 1024 threads, R = 256 to 1024 of them share a row
+// with one or two 16-byte chunks each, so the sums are 24 or 48 registers and twelve to sixteen waves stay
+// resident per CU.  A workgroup is alone on its CU, so nothing else hides its trips to HBM: the U rows per thread
 // of the next step are requested (and held as loaded, 16 bytes per chunk) before the arithmetic of the
 // current step starts, and the row sums of all U rows share one barrier (the exchange buffer alternates
 // between steps, so a wave that runs ahead cannot overwrite sums that a slower one still reads).
 // Same partial-row layout as the kernel above; the grid is one workgroup per CU at most.
-constexpr int kWgWide = 1024;
-
-template <typename T, int R, int CPT, int U, bool KEEP>
-__global__ __launch_bounds__(kWgWide) void ln_bwd_wide_kernel(const T* __restrict__ dy, const T* __restrict__ x,
+template <typename T, int R, int ROWS, int CPT, int U, bool KEEP>
+__global__ __launch_bounds__(R* ROWS) void ln_bwd_wide_kernel(const T* __restrict__ dy, const T* __restrict__ x,
                                                               const float* __restrict__ mean_in,
                                                               const float* __restrict__ rstd_in, const T* __restrict__ gain,
                                                               const T* __restrict__ dres, T* __restrict__ dx,
                                                               float* __restrict__ partial, int rows, int h, T* __restrict__ dres_keep) {
-  constexpr int ROWS = kWgWide / R;
+  constexpr int kThreads = R * ROWS;
   constexpr int W = R / 64;   // waves per row
   // Requesting a step ahead costs 12 registers per chunk next to the 24 of the column sums; the budget of a
-  // 1024-thread workgroup is 128, so it is done for 2-byte elements with one chunk per thread; with one chunk
+  // workgroup of more than 768 threads is 128, so it is done for 2-byte elements with one chunk per thread; with one chunk
   // per thread the sums of the results live in LDS (one 16-byte slot per thread and column quad, touched by
   // its owner only).
   constexpr bool kAhead = sizeof(T) == 2 && CPT == 1;
   constexpr bool kLdsSums = CPT == 1;
   __shared__ float red[2][2 * U][16];
-  __shared__ float4 osum_lds[kLdsSums ? 2 * kWgWide : 1];
+  __shared__ float4 osum_lds[kLdsSums ? 2 * kThreads : 1];
   __shared__ float comb[(ROWS > 1) ? (ROWS - 1) * R * CPT * 8 : 1];
   const int tid = threadIdx.x;
   const int sub = tid % R, rsub = tid / R;
@@ -333,7 +331,7 @@ __global__ __launch_bounds__(kWgWide) void ln_bwd_wide_kernel(const T* __restric
   };
   if (kLdsSums) {
     osum_lds[tid] = make_float4(0.f, 0.f, 0.f, 0.f);
-    osum_lds[kWgWide + tid] = make_float4(0.f, 0.f, 0.f, 0.f);
+    osum_lds[kThreads + tid] = make_float4(0.f, 0.f, 0.f, 0.f);
   }
   if (kAhead && (int)blockIdx.x < n_groups) fetch(blockIdx.x);
   int parity = 0;
@@ -415,10 +413,10 @@ __global__ __launch_bounds__(kWgWide) void ln_bwd_wide_kernel(const T* __restric
               for (int i = 0; i < 8; ++i) o[i] += rv[i];
             }
             if (kLdsSums) {
-              float4 lo = osum_lds[tid], hi = osum_lds[kWgWide + tid];
+              float4 lo = osum_lds[tid], hi = osum_lds[kThreads + tid];
               lo.x += o[0]; lo.y += o[1]; lo.z += o[2]; lo.w += o[3];
               hi.x += o[4]; hi.y += o[5]; hi.z += o[6]; hi.w += o[7];
-              osum_lds[tid] = lo; osum_lds[kWgWide + tid] = hi;
+              osum_lds[tid] = lo; osum_lds[kThreads + tid] = hi;
             } else {
 #pragma unroll
               for (int i = 0; i < 8; ++i) osum[c][i] += o[i];
@@ -431,7 +429,7 @@ __global__ __launch_bounds__(kWgWide) void ln_bwd_wide_kernel(const T* __restric
     parity ^= 1;
   }
   if (kLdsSums) {
-    const float4 lo = osum_lds[tid], hi = osum_lds[kWgWide + tid];
+    const float4 lo = osum_lds[tid], hi = osum_lds[kThreads + tid];
     osum[0][0] = lo.x; osum[0][1] = lo.y; osum[0][2] = lo.z; osum[0][3] = lo.w;
     osum[0][4] = hi.x; osum[0][5] = hi.y; osum[0][6] = hi.z; osum[0][7] = hi.w;
   }
@@ -737,27 +735,42 @@ hipError_t layernorm_bwd(const void* dy, const void* x, const float* mean, const
       (dres && !aligned16(dres)) || (dres_keep && (!dres || !aligned16(dres_keep))))
     return hipErrorInvalidValue;
   if (h >= 2048) {
-    // long rows: 1024-thread workgroups, at most one per CU (256 partial rows)
+    // Long rows: one workgroup per CU at most (256 partial rows); threads per row, rows per workgroup and rows of a step per thread
+    // by the length of a row.  What counts is the rows a CU has in flight.  With 512 threads to a row of 257 to 320 chunks three
+    // to four of the eight waves have none of it and a workgroup takes two rows; 320 threads leave room for three (4096 x 2560 in
+    // bf16 with its finalize launch 29.1 -> 26.4 us, 12000 rows 72.9 -> 59.6; 2056 columns 27.6 -> 24.7; 384 to 600 rows 0.83 to 0.95
+    // of the time, 700 to 1024 rows 0.93 to 1.02, below 384 up to 1.09).  fp32 rows arrive in the step that uses them and gain nothing from a
+    // third row beside the two (0.96 to 1.11); with 384 threads, twelve waves, the registers suffice for three rows per thread and
+    // step instead: 0.86 to 1.00 of the time at every count of 257 to 384 chunks (4096 x 3072 53.1 -> 51.4 us, 1300 rows 25.6 -> 22.0).
+    // That form is within 4 % on either side in bf16, and one row per workgroup on 640 or 768 threads with three per step is 2 to
+    // 28 % behind 1024 threads with two at 513 to 768 chunks.
     const int chunks = h / 8;
-    const int R = chunks <= 256 ? 256 : chunks <= 512 ? 512 : 1024;
-    const int cpt = ceil_div(chunks, R);   // 1, or 2 above h = 8192 (h <= 16384)
-    const int groups = ceil_div(rows, kWgWide / R);
-    const int grid = groups < 256 ? groups : 256;
-#define CALL_WIDE_AS(T_, R_, C_, U_, K_)                                                                     \
-  hipLaunchKernelGGL((ln_bwd_wide_kernel<T_, R_, C_, U_, K_>), dim3(grid), dim3(kWgWide), 0, stream,         \
+#define CALL_WIDE_AS(T_, R_, N_, C_, U_, K_)                                                                 \
+  hipLaunchKernelGGL((ln_bwd_wide_kernel<T_, R_, N_, C_, U_, K_>), dim3(grid), dim3(R_ * N_), 0, stream,     \
                      static_cast<const T_*>(dy), static_cast<const T_*>(x), mean, rstd,                      \
                      static_cast<const T_*>(gain), static_cast<const T_*>(dres), static_cast<T_*>(dx),       \
                      partial, rows, h, static_cast<T_*>(dres_keep))
-#define CALL_WIDE(R_, C_, U_)                                                                                \
-  if (dtype == kBF16 && dres_keep) CALL_WIDE_AS(bf16_t, R_, C_, U_, true);                                   \
-  else if (dtype == kBF16) CALL_WIDE_AS(bf16_t, R_, C_, U_, false);                                          \
-  else if (dres_keep) CALL_WIDE_AS(float, R_, C_, U_, true);                                                 \
-  else CALL_WIDE_AS(float, R_, C_, U_, false)
-    if (cpt == 1 && R == 256) { CALL_WIDE(256, 1, 2); }
-    else if (cpt == 1 && R == 512) { CALL_WIDE(512, 1, 2); }
-    else if (cpt == 1) { CALL_WIDE(1024, 1, 2); }
-    else if (cpt == 2) { CALL_WIDE(1024, 2, 1); }
-    else return hipErrorInvalidValue;
+#define CALL_WIDE(T_, R_, N_, C_, U_)                                                                        \
+  do {                                                                                                       \
+    const int groups = ceil_div(rows, N_);                                                                   \
+    grid = groups < 256 ? groups : 256;                                                                      \
+    if (dres_keep) CALL_WIDE_AS(T_, R_, N_, C_, U_, true);                                                   \
+    else CALL_WIDE_AS(T_, R_, N_, C_, U_, false);                                                            \
+  } while (0)
+    int grid = 0;
+    if (dtype == kBF16) {
+      if (chunks <= 256) CALL_WIDE(bf16_t, 256, 4, 1, 2);
+      else if (chunks <= 320 && rows >= 384) CALL_WIDE(bf16_t, 320, 3, 1, 2);
+      else if (chunks <= 512) CALL_WIDE(bf16_t, 512, 2, 1, 2);
+      else if (chunks <= 1024) CALL_WIDE(bf16_t, 1024, 1, 1, 2);
+      else CALL_WIDE(bf16_t, 1024, 1, 2, 1);
+    } else {
+      if (chunks <= 256) CALL_WIDE(float, 256, 4, 1, 2);
+      else if (chunks <= 384) CALL_WIDE(float, 384, 2, 1, 3);
+      else if (chunks <= 512) CALL_WIDE(float, 512, 2, 1, 2);
+      else if (chunks <= 1024) CALL_WIDE(float, 1024, 1, 1, 2);
+      else CALL_WIDE(float, 1024, 1, 2, 1);
+    }
 #undef CALL_WIDE
 #undef CALL_WIDE_AS
     *parts_out = grid;
