@@ -628,7 +628,7 @@ int stage_create(const stage_config_t* cfg, const float* init_weights_host, void
   // Backward passes per grouped weight-gradient launch: the caller's choice, else what brings the reduction
   // range to 16384 tokens (4 passes of 4096 tokens, 8 of 2048 or fewer: measured, 8 instead of 4 passes of 2048
   // are +3 % on the weight-gradient launches, 8 instead of 4 of 4096 nothing); never more than m (a group stays
-  // inside its batch).  The segmented product exists in the bf16 ring kernels only, whose
+  // inside its batch).  The segmented product exists in the bf16 direct-to-LDS kernels only, whose
   // K tiles must divide a pass's tokens, and a set's number must fit the kernel's 4-bit fields.
   int j = cfg->wgrad_group > 0 ? cfg->wgrad_group : (T <= 2048 ? 8 : 4);
   if (j > cfg->m) j = cfg->m;
