@@ -101,16 +101,17 @@ struct WaveTile {
   static __device__ __forceinline__ float4 row4(const float* t, int j, int l32, int hf) {
     return *reinterpret_cast<const float4*>(t + at(l32) + (((2 * (j & 1) + hf) ^ swz(l32)) << 2) + 16 * (j >> 1));
   }
-  // f[db][r] = row reg_row(r, hf), column 32*db + l32 (columns past DH: zero, or another's if rows have 16; they only reach result
+  // f[db][r] = row reg_row(r, hf), column 32*db + l32 of NB blocks of columns (columns past DH: zero, or another's if rows have 16; they only reach result
   // columns that are never stored)
-  static __device__ __forceinline__ void cols(const float* t, int l32, int hf, float (&f)[CfgF<DH>::DB][16]) {
+  template <int NB>
+  static __device__ __forceinline__ void cols(const float* t, int l32, int hf, float (&f)[NB][16]) {
     const int col = LW == 16 ? l32 & 15 : l32;
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       const int row = reg_row(r, hf);
       const float* x = t + at(row) + ((((col >> 2) ^ swz(row)) << 2) | (col & 3));
 #pragma unroll
-      for (int db = 0; db < CfgF<DH>::DB; ++db) f[db][r] = x[32 * db];
+      for (int db = 0; db < NB; ++db) f[db][r] = x[32 * db];
     }
   }
   // acc += (this tile's rows) * f^T over the head dimension
@@ -144,19 +145,19 @@ __device__ __forceinline__ void wave_fence() {
 }
 
 // out[db] += X^T P over the 32 rows of a tile
-template <int DH>
-__device__ __forceinline__ void mul_cols(const float (&x)[CfgF<DH>::DB][16], const f32x16& p, f32x16 (&out)[CfgF<DH>::DB]) {
+template <int NB>
+__device__ __forceinline__ void mul_cols(const float (&x)[NB][16], const f32x16& p, f32x16 (&out)[NB]) {
 #pragma unroll
   for (int r = 0; r < 16; ++r)
 #pragma unroll
-    for (int db = 0; db < CfgF<DH>::DB; ++db) out[db] = __builtin_amdgcn_mfma_f32_32x32x2f32(x[db][r], p[r], out[db], 0, 0, 0);
+    for (int db = 0; db < NB; ++db) out[db] = __builtin_amdgcn_mfma_f32_32x32x2f32(x[db][r], p[r], out[db], 0, 0, 0);
 }
 
-template <int DH>
-__device__ __forceinline__ bool any_not_finite(const float (&x)[CfgF<DH>::DB][16]) {
+template <int NB>
+__device__ __forceinline__ bool any_not_finite(const float (&x)[NB][16]) {
   bool bad = false;
 #pragma unroll
-  for (int db = 0; db < CfgF<DH>::DB; ++db)
+  for (int db = 0; db < NB; ++db)
 #pragma unroll
     for (int r = 0; r < 16; ++r) bad = bad || !(fabsf(x[db][r]) < INFINITY);
   return __any(bad);
@@ -165,9 +166,9 @@ __device__ __forceinline__ bool any_not_finite(const float (&x)[CfgF<DH>::DB][16
 // mul_cols for a tile in which not every lane's row (query or key) sees every row of the tile, when the tile holds
 // infinities or NaNs: row by row, added only where it is seen (sees(row)).  Rare, so it keeps few registers: the rows
 // come from `tile`, the matrix, again.
-template <int DH, typename Sees>
+template <int NB, typename Sees>
 __device__ __forceinline__ void accumulate_visible(const float* __restrict__ tile, int64_t ld, int rows, int dh, const f32x16& p,
-                                                   f32x16 (&out)[CfgF<DH>::DB], int hf, Sees&& sees) {
+                                                   f32x16 (&out)[NB], int hf, Sees&& sees) {
 #pragma unroll 1
   for (int row = 0; row < rows; ++row) {
     const int reg = (row >> 3) * 4 + (row & 3);
@@ -179,7 +180,7 @@ __device__ __forceinline__ void accumulate_visible(const float* __restrict__ til
     const bool vis = sees(row);
     const float* x = tile + row * ld + 4 * hf;
 #pragma unroll
-    for (int db = 0; db < CfgF<DH>::DB; ++db)
+    for (int db = 0; db < NB; ++db)
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
         if (db * 32 + 8 * g >= dh) continue;   // (a multiple of 8: uniform)
@@ -195,10 +196,10 @@ __device__ __forceinline__ void accumulate_visible(const float* __restrict__ til
 }
 
 // This wave's 32 x DH partial result (lane % 32 = row, registers = head columns), times f, into its strip
-template <int DH>
-__device__ __forceinline__ void put_strip(const f32x16 (&acc)[CfgF<DH>::DB], float f, float* strip, int l32, int hf) {
+template <int DH, int NB>
+__device__ __forceinline__ void put_strip(const f32x16 (&acc)[NB], float f, float* strip, int l32, int hf) {
 #pragma unroll
-  for (int db = 0; db < CfgF<DH>::DB; ++db)
+  for (int db = 0; db < NB; ++db)
 #pragma unroll
     for (int g = 0; g < 4; ++g)
       *reinterpret_cast<float4*>(strip + l32 * CfgF<DH>::LD + db * 32 + 8 * g + 4 * hf) =
@@ -295,8 +296,8 @@ __global__ __launch_bounds__(NW * 64, (kPerSimd<DH>)) void attn_f32_fwd_kernel(c
     for (int db = 0; db < C::DB; ++db)
 #pragma unroll
       for (int r = 0; r < 16; ++r) oacc[db][r] *= alpha;
-    if (diag && any_not_finite<DH>(vc)) accumulate_visible<DH>(base + 2 * h + (int64_t)j0 * ld, ld, min(jend - j0, 32), dh, sc, oacc, hf, [&](int row) { return j0 + row <= i; });
-    else mul_cols<DH>(vc, sc, oacc);
+    if (diag && any_not_finite(vc)) accumulate_visible(base + 2 * h + (int64_t)j0 * ld, ld, min(jend - j0, 32), dh, sc, oacc, hf, [&](int row) { return j0 + row <= i; });
+    else mul_cols(vc, sc, oacc);
   }
   // the waves' maxima meet, every partial result is rescaled to the common one
   float* m_lds = smem + tile_floats<DH, NW>();
@@ -385,8 +386,8 @@ __device__ __forceinline__ void attn_f32_dq(const float* __restrict__ qkv, const
       const float p = __builtin_amdgcn_exp2f(fmaf(sc[r], scale, -lse_i) * kLog2e);
       sc[r] = vis ? p * (dp[r] - delta_i) : 0.f;   // dS^T (the scale is applied at the end)
     }
-    if (diag && any_not_finite<DH>(kc)) accumulate_visible<DH>(base + h + (int64_t)j0 * ld, ld, min(jend - j0, 32), dh, sc, dq, hf, [&](int row) { return j0 + row <= i; });
-    else mul_cols<DH>(kc, sc, dq);
+    if (diag && any_not_finite(kc)) accumulate_visible(base + h + (int64_t)j0 * ld, ld, min(jend - j0, 32), dh, sc, dq, hf, [&](int row) { return j0 + row <= i; });
+    else mul_cols(kc, sc, dq);
   }
   __syncthreads();   // every wave is done with its tiles
   put_strip<DH>(dq, scale, smem + wave * kRows * C::LD, l32, hf);
@@ -397,13 +398,16 @@ __device__ __forceinline__ void attn_f32_dq(const float* __restrict__ qkv, const
 // ------------------------------------------------------------------------------------------------
 // dK, dV: lane = key, registers = queries (S = Q K^T, dV^T = dO^T P, dK^T = Q^T dS)
 // FUSED: delta from dO and O, as the launch that forms it for others is the same one; else it is read.
-// EXACT: the second run of a workgroup that met infinities or NaNs in a tile which not all its keys see in whole (returns true for it);
-// that path inside the one loop costs some 70 spilled registers.
+// EXACT: the second run of a workgroup that met infinities or NaNs in a tile which not all its keys see in whole (returns true for it),
+// for the results' 32 columns from 32 * db0 on.  All columns at once in that run, whose row-by-row path keeps more alive, spill 92 to 302
+// registers at head sizes 48, 64, 112 and 128, some of them inside the loop of the first run (backward without that 0.97 to 0.98 of the
+// time at those heads and 80 and 96, over 2700 random sizes).
 template <int DH, int NW, bool FUSED, bool EXACT>
 __device__ __forceinline__ bool attn_f32_dkv(const float* __restrict__ qkv, const float* __restrict__ o, const float* __restrict__ d_o,
                                              const float* __restrict__ lse, const float* __restrict__ delta, float* __restrict__ dqkv, int s, int a, int dh, int mask_mode,
-                                             const int32_t* __restrict__ seqlens, int blk, float* smem) {
+                                             const int32_t* __restrict__ seqlens, int blk, float* smem, int db0 = 0) {
   using C = CfgF<DH>;
+  constexpr int NB = EXACT ? 1 : C::DB;   // blocks of 32 result columns
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l32 = lane & 31, hf = lane >> 5;
   const int n = blockIdx.y, head = blockIdx.x;   // causal: the first keys are seen by the most queries
   const bool causal = mask_mode == 1;
@@ -424,18 +428,26 @@ __device__ __forceinline__ bool attn_f32_dkv(const float* __restrict__ qkv, cons
   float* q_tile = smem + wave * 2 * WaveTile<DH>::kFloats;
   float* g_tile = q_tile + WaveTile<DH>::kFloats;
   auto issue = [&](int t) {
-    WaveTile<DH>::issue(base + (int64_t)t * 32 * ld, ld, s - t * 32, dh, lane, q_tile);
-    WaveTile<DH>::issue(gbase + (int64_t)t * 32 * h, h, s - t * 32, dh, lane, g_tile);
+    int l = lane;
+    if (DH > 32 && DH <= 64) asm volatile("" : "+v"(l));   // 256 registers have no room for what of the addresses stays the same
+    WaveTile<DH>::issue(base + (int64_t)t * 32 * ld, ld, s - t * 32, dh, l, q_tile);
+    WaveTile<DH>::issue(gbase + (int64_t)t * 32 * h, h, s - t * 32, dh, l, g_tile);
   };
   if (t0 + wave < t1) issue(t0 + wave);
-  float kf[C::NF], vf[C::NF], xc[C::DB][16];
-  load_row<DH>(base + h + (int64_t)jc * ld, dh, hf, kf);
-  load_row<DH>(base + 2 * h + (int64_t)jc * ld, dh, hf, vf);
+  float kf[C::NF], vf[C::NF], xc[NB][16];
+  constexpr bool kAgain = EXACT && C::DB > 1;   // K and V fetched for every tile rather than in registers throughout
+  auto load_kv = [&] {
+    const float* row = base + h + (int64_t)jc * ld;
+    if (kAgain) asm volatile("" : "+v"(row));
+    load_row<DH>(row, dh, hf, kf);
+    load_row<DH>(row + h, dh, hf, vf);
+  };
+  if (!kAgain) load_kv();
   // lse and delta of the tile's queries: a lane has those of its row, the products need them by register
   float* stat = smem + tile_floats<DH, NW>() + wave * 64;
-  f32x16 dk[C::DB], dv[C::DB];
+  f32x16 dk[NB], dv[NB];
 #pragma unroll
-  for (int db = 0; db < C::DB; ++db) { dk[db] = zero16(); dv[db] = zero16(); }
+  for (int db = 0; db < NB; ++db) { dk[db] = zero16(); dv[db] = zero16(); }
   float lse_i = 0.f, delta_i = 0.f, of[FUSED ? C::NF : 1];
   bool hidden = false;
   // (O's row a tile ahead only where the registers allow it)
@@ -467,6 +479,7 @@ __device__ __forceinline__ bool attn_f32_dkv(const float* __restrict__ qkv, cons
     stat[lane] = hf == 0 ? lse_i : delta_i;
     wave_fence();
     f32x16 sc = zero16(), dp = zero16();
+    if (kAgain) load_kv();
     WaveTile<DH>::mul(q_tile, kf, sc, l32, hf);
     __builtin_amdgcn_sched_barrier(0);   // (the fragments of both products together do not fit)
     WaveTile<DH>::mul(g_tile, vf, dp, l32, hf);
@@ -489,36 +502,48 @@ __device__ __forceinline__ bool attn_f32_dkv(const float* __restrict__ qkv, cons
     const bool partial = diag || j0 + 32 > kv_len;
     auto sees_len = [&](int row) { return j < kv_len && (!causal || j <= i0 + row); };
     __builtin_amdgcn_sched_barrier(0);
-    WaveTile<DH>::cols(g_tile, l32, hf, xc);
+    WaveTile<DH>::cols(g_tile + 32 * db0, l32, hf, xc);
     if (EXACT && partial) {
-      accumulate_visible<DH>(gbase + (int64_t)i0 * h, h, min(s - i0, 32), dh, sc, dv, hf, sees_len);
+      accumulate_visible(gbase + (int64_t)i0 * h + 32 * db0, h, min(s - i0, 32), dh - 32 * db0, sc, dv, hf, sees_len);
     } else {
-      if (partial) hidden = hidden || any_not_finite<DH>(xc);
-      mul_cols<DH>(xc, sc, dv);
+      if (partial) hidden = hidden || any_not_finite(xc);
+      mul_cols(xc, sc, dv);
     }
     __builtin_amdgcn_sched_barrier(0);
-    WaveTile<DH>::cols(q_tile, l32, hf, xc);
+    WaveTile<DH>::cols(q_tile + 32 * db0, l32, hf, xc);
     tiles_read();
     if (t + NW < t1) { issue(t + NW); load_stat(t + NW); }   // the next tile travels under the last product
     __builtin_amdgcn_sched_barrier(0);
     if (EXACT && partial) {
-      accumulate_visible<DH>(base + (int64_t)i0 * ld, ld, min(s - i0, 32), dh, dp, dk, hf, sees_len);
+      accumulate_visible(base + (int64_t)i0 * ld + 32 * db0, ld, min(s - i0, 32), dh - 32 * db0, dp, dk, hf, sees_len);
     } else {
-      if (partial) hidden = hidden || any_not_finite<DH>(xc);
-      mul_cols<DH>(xc, dp, dk);
+      if (partial) hidden = hidden || any_not_finite(xc);
+      mul_cols(xc, dp, dk);
     }
   }
   if (EXACT) __syncthreads();   // every wave is done with its tiles
   else if (__syncthreads_or(hidden)) return true;
-  float* out = dqkv + ((int64_t)n * s + j0) * ld + h + head * dh;
+  float* out = dqkv + ((int64_t)n * s + j0) * ld + h + head * dh + 32 * db0;
+  const int cols = EXACT ? min(dh - 32 * db0, 32) : dh;
   put_strip<DH>(dk, scale, smem + wave * kRows * C::LD, l32, hf);
   __syncthreads();
-  sum_strips<DH, NW>(smem, out, ld, s - j0, dh, tid, [](int) { return 1.0f; });
+  sum_strips<DH, NW>(smem, out, ld, s - j0, cols, tid, [](int) { return 1.0f; });
   __syncthreads();
   put_strip<DH>(dv, 1.0f, smem + wave * kRows * C::LD, l32, hf);
   __syncthreads();
-  sum_strips<DH, NW>(smem, out + h, ld, s - j0, dh, tid, [](int) { return 1.0f; });
+  sum_strips<DH, NW>(smem, out + h, ld, s - j0, cols, tid, [](int) { return 1.0f; });
   return false;
+}
+template <int DH, int NW, bool FUSED>
+__device__ __forceinline__ void attn_f32_dkv_all(const float* __restrict__ qkv, const float* __restrict__ o, const float* __restrict__ d_o,
+                                                 const float* __restrict__ lse, const float* __restrict__ delta, float* __restrict__ dqkv, int s, int a, int dh, int mask_mode,
+                                                 const int32_t* __restrict__ seqlens, int blk, float* smem) {
+  if (!attn_f32_dkv<DH, NW, FUSED, false>(qkv, o, d_o, lse, delta, dqkv, s, a, dh, mask_mode, seqlens, blk, smem)) return;
+#pragma unroll 1
+  for (int db0 = 0; db0 < CfgF<DH>::DB; ++db0) {
+    attn_f32_dkv<DH, NW, FUSED, true>(qkv, o, d_o, lse, delta, dqkv, s, a, dh, mask_mode, seqlens, blk, smem, db0);
+    __syncthreads();   // the strips are read, the next tiles may come
+  }
 }
 
 template <int DH, int NW>
@@ -535,8 +560,7 @@ __global__ __launch_bounds__(NW * 64, (kPerSimd<DH>)) void attn_f32_dkv_kernel(c
                                                                      float* __restrict__ dqkv, int s, int a, int dh, int mask_mode,
                                                                      const int32_t* __restrict__ seqlens) {
   extern __shared__ __attribute__((aligned(16))) float smem[];
-  if (attn_f32_dkv<DH, NW, false, false>(qkv, nullptr, d_o, lse, delta, dqkv, s, a, dh, mask_mode, seqlens, blockIdx.z, smem))
-    attn_f32_dkv<DH, NW, false, true>(qkv, nullptr, d_o, lse, delta, dqkv, s, a, dh, mask_mode, seqlens, blockIdx.z, smem);
+  attn_f32_dkv_all<DH, NW, false>(qkv, nullptr, d_o, lse, delta, dqkv, s, a, dh, mask_mode, seqlens, blockIdx.z, smem);
 }
 // Both in one launch: block 2k of grid.z has the keys of block k, block 2k + 1 the queries of block k (causal: k from the end), so the
 // longest workgroups of either kind go first.
@@ -548,8 +572,7 @@ __global__ __launch_bounds__(NW * 64, (kPerSimd<DH>)) void attn_f32_bwd_kernel(c
   extern __shared__ __attribute__((aligned(16))) float smem[];
   const int k = blockIdx.z >> 1;
   if (blockIdx.z & 1) attn_f32_dq<DH, NW>(qkv, o, d_o, lse, delta, dqkv, s, a, dh, mask_mode, seqlens, mask_mode == 1 ? (int)(gridDim.z >> 1) - 1 - k : k, smem);
-  else if (attn_f32_dkv<DH, NW, true, false>(qkv, o, d_o, lse, delta, dqkv, s, a, dh, mask_mode, seqlens, k, smem))
-    attn_f32_dkv<DH, NW, true, true>(qkv, o, d_o, lse, delta, dqkv, s, a, dh, mask_mode, seqlens, k, smem);
+  else attn_f32_dkv_all<DH, NW, true>(qkv, o, d_o, lse, delta, dqkv, s, a, dh, mask_mode, seqlens, k, smem);
 }
 
 // Whether dQ and dK/dV, on `waves` waves per workgroup, share a launch.  One launch has twice the workgroups, of both lengths, and spares

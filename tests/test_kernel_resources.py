@@ -76,6 +76,16 @@ def test_fixed_head_attention_kernels_do_not_spill():
         assert field("vgpr_spill_count") <= (2 if "attn_dq_mfma_kernel<128, 4, 2" in name else 0), name
 
 
+def test_fp32_attention_kernels_do_not_spill():
+    """Their rare second run, for infinities and NaNs that some rows must not see, works on 32 columns of the results at a time; with all at
+    once 92 to 302 registers spilled at head sizes 48, 64, 112 and 128, some in the loop of the first run.  Six of the second run at head
+    size 64, dQ and dK/dV in one launch, are the exception."""
+    found = built_kernels(r"attn_f32_(fwd|dq|dkv|bwd)_kernel<")
+    assert len(found) == 64
+    for name, field in found:
+        assert field("vgpr_spill_count") <= (6 if "attn_f32_bwd_kernel<64" in name else 0), name
+
+
 def test_phased_gemm_kernels_use_no_scratch_and_fit_two_waves_per_simd():
     """They park the next-weights touch in a register as the ring kernels do."""
     found = built_kernels(r"gemm_bf16_phased_kernel<")
