@@ -402,6 +402,8 @@ __device__ __forceinline__ void attn_f32_dq(const float* __restrict__ qkv, const
 // for the results' 32 columns from 32 * db0 on.  All columns at once in that run, whose row-by-row path keeps more alive, spill 92 to 302
 // registers at head sizes 48, 64, 112 and 128, some of them inside the loop of the first run (backward without that 0.97 to 0.98 of the
 // time at those heads and 80 and 96, over 2700 random sizes).
+// In that run, too, only tiles that hold such values are added row by row (a NaN in dO of one query, b=2 s=512 a=8 dh=128 with lengths:
+// 854 -> 321 us; without the NaN 93).
 template <int DH, int NW, bool FUSED, bool EXACT>
 __device__ __forceinline__ bool attn_f32_dkv(const float* __restrict__ qkv, const float* __restrict__ o, const float* __restrict__ d_o,
                                              const float* __restrict__ lse, const float* __restrict__ delta, float* __restrict__ dqkv, int s, int a, int dh, int mask_mode,
@@ -503,10 +505,10 @@ __device__ __forceinline__ bool attn_f32_dkv(const float* __restrict__ qkv, cons
     auto sees_len = [&](int row) { return j < kv_len && (!causal || j <= i0 + row); };
     __builtin_amdgcn_sched_barrier(0);
     WaveTile<DH>::cols(g_tile + 32 * db0, l32, hf, xc);
-    if (EXACT && partial) {
+    if (EXACT && partial && any_not_finite(xc)) {
       accumulate_visible(gbase + (int64_t)i0 * h + 32 * db0, h, min(s - i0, 32), dh - 32 * db0, sc, dv, hf, sees_len);
     } else {
-      if (partial) hidden = hidden || any_not_finite(xc);
+      if (!EXACT && partial) hidden = hidden || any_not_finite(xc);
       mul_cols(xc, sc, dv);
     }
     __builtin_amdgcn_sched_barrier(0);
@@ -514,10 +516,10 @@ __device__ __forceinline__ bool attn_f32_dkv(const float* __restrict__ qkv, cons
     tiles_read();
     if (t + NW < t1) { issue(t + NW); load_stat(t + NW); }   // the next tile travels under the last product
     __builtin_amdgcn_sched_barrier(0);
-    if (EXACT && partial) {
+    if (EXACT && partial && any_not_finite(xc)) {
       accumulate_visible(base + (int64_t)i0 * ld + 32 * db0, ld, min(s - i0, 32), dh - 32 * db0, dp, dk, hf, sees_len);
     } else {
-      if (partial) hidden = hidden || any_not_finite(xc);
+      if (!EXACT && partial) hidden = hidden || any_not_finite(xc);
       mul_cols(xc, dp, dk);
     }
   }
