@@ -33,7 +33,7 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef __attribute__((address_space(3))) void lds_void_t;
 typedef __attribute__((address_space(1))) const void glob_void_t;
 
-// Waves per workgroup (NW): four, which split the streamed rows, or one where a launch has blocks enough without that (one_wave)
+// Waves per workgroup (NW): four, which split the streamed rows, or one where a launch has blocks enough without that (fwd_one_wave, bwd_form)
 constexpr int kManyWaves = 4;
 constexpr int kRows = 32;               // rows a workgroup owns
 constexpr float kLog2e = 1.4426950408889634f;
@@ -577,17 +577,6 @@ __global__ __launch_bounds__(NW * 64, (kPerSimd<DH>)) void attn_f32_bwd_kernel(c
   else attn_f32_dkv_all<DH, NW, true>(qkv, o, d_o, lse, delta, dqkv, s, a, dh, mask_mode, seqlens, k, smem);
 }
 
-// Whether dQ and dK/dV, on `waves` waves per workgroup, share a launch.  One launch has twice the workgroups, of both lengths, and spares
-// a launch and its tail; in two dK/dV reads the delta that dQ has left and needs no row of O.  One over two launches, four waves: up
-// to 128 blocks 0.6, to 256 0.7 to 1.0, to 1024 0.9, above 1.0; heads above 64, whose workgroups fill a CU, 1.1 where either half is a
-// full round and long and no mask evens out.  One wave: up to 512 blocks 0.65, to 2048 0.65 to 0.8 under a causal mask, 0.9 with
-// lengths, 1.0 without, beyond 0.9 with a mask.
-bool one_launch(const AttnDesc& d, int waves) {
-  const int64_t blocks = (int64_t)d.b * d.a * ceil_div(d.s, kRows), cus = gemm_compute_units();
-  if (d.dh > 64 && d.mask_mode != 1 && d.s > 256 && 2 * blocks > cus && blocks <= cus) return false;
-  return blocks <= 4 * cus || (waves == 1 && d.mask_mode != 0);
-}
-
 template <typename K>
 hipError_t set_lds(K kern, size_t bytes) {
   return hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
@@ -610,7 +599,7 @@ hipError_t fwd_launch(const AttnDesc& d, const void* qkv, void* o, float* lse, h
 }
 
 template <int DH, int NW>
-hipError_t bwd_launch(const AttnDesc& d, const void* qkv, const void* o, const float* lse, const void* d_o, void* dqkv, float* delta,
+hipError_t bwd_launch(const AttnDesc& d, bool one_launch, const void* qkv, const void* o, const float* lse, const void* d_o, void* dqkv, float* delta,
                       hipStream_t st) {
   constexpr size_t lds_dq = tile_floats<DH, NW>() * sizeof(float);
   constexpr size_t lds = lds_dq + NW * 64 * sizeof(float);
@@ -626,7 +615,7 @@ hipError_t bwd_launch(const AttnDesc& d, const void* qkv, const void* o, const f
   const int blocks = ceil_div(d.s, kRows);
   const float *q = static_cast<const float*>(qkv), *out = static_cast<const float*>(o), *g = static_cast<const float*>(d_o);
   float* dst = static_cast<float*>(dqkv);
-  if (one_launch(d, NW)) {
+  if (one_launch) {
     hipLaunchKernelGGL((attn_f32_bwd_kernel<DH, NW>), dim3(d.a, d.b, 2 * blocks), dim3(NW * 64), lds, st, q, out, g, lse, delta, dst, d.s, d.a, d.dh,
                        d.mask_mode, d.seqlens);
   } else {
@@ -660,8 +649,8 @@ struct Fwd {
 };
 template <int DH, int NW>
 struct Bwd {
-  static hipError_t run(const AttnDesc& d, const void* qkv, const void* o, const float* lse, const void* d_o, void* dqkv, float* delta, hipStream_t st) {
-    return bwd_launch<DH, NW>(d, qkv, o, lse, d_o, dqkv, delta, st);
+  static hipError_t run(const AttnDesc& d, bool one_launch, const void* qkv, const void* o, const float* lse, const void* d_o, void* dqkv, float* delta, hipStream_t st) {
+    return bwd_launch<DH, NW>(d, one_launch, qkv, o, lse, d_o, dqkv, delta, st);
   }
 };
 }  // namespace
@@ -672,36 +661,71 @@ namespace {
 // ceil(blocks / 4 CUs) rounds of t + 1.2, each of those 1.2 times as long as it would be alone; 1.35 times more under a causal mask
 // in a launch of one round, which ends on its longest blocks; 1.4 times more for heads up to 32, of whose four-wave workgroups a CU
 // holds two.  Over 500 random sizes the choice costs 0.5 % over the better one.
-// Backward, whose one launch has two workgroups per block: up to head size 64 a CU holds two of four waves or eight of one, above
-// that one or four; the constants are fitted to 500 random sizes with each form forced, over which the choice costs 0.8 % over the
-// better one.  (Before the tiles went through LDS and the two kernels into one launch those 500 took 1.6 times as long; b=2 s=512 a=8
-// dh=64 causal 55 -> 42 us, b=2 s=64 a=4 dh=32 13 -> 7.4, b=1 s=768 a=4 dh=128 152 -> 78.)
-bool one_wave(const AttnDesc& d, bool bwd) {
+bool fwd_one_wave(const AttnDesc& d) {
   const int64_t tiles = ceil_div(d.s, kRows), blocks = (int64_t)d.b * d.a * tiles, cus = gemm_compute_units();
-  const bool causal = d.mask_mode == 1 && tiles > 2;
-  if (!bwd) {
-    double one = 1.2 * ceil_div(blocks, 4 * cus) * (tiles + 1.2);
-    if (causal && blocks <= 4 * cus) one *= 1.35;
-    if (d.dh <= 32) one *= 1.4;
-    return one < ceil_div(blocks, cus) * (ceil_div(tiles, kManyWaves) + 1.2);
+  double one = 1.2 * ceil_div(blocks, 4 * cus) * (tiles + 1.2);
+  if (d.mask_mode == 1 && tiles > 2 && blocks <= 4 * cus) one *= 1.35;
+  if (d.dh <= 32) one *= 1.4;
+  return one < ceil_div(blocks, cus) * (ceil_div(tiles, kManyWaves) + 1.2);
+}
+
+// Backward: one wave or four, and dQ and dK/dV in one launch or in two.  One launch has twice the workgroups, of both lengths, and spares
+// a launch and its tail; in two dK/dV reads the delta that dQ has left and needs no row of O.
+// Heads up to 64: a CU holds two workgroups of four waves or eight of one.  One launch over two, four waves: up to 128 blocks 0.6, to
+// 256 0.7 to 1.0, to 1024 0.9, above 1.0; one wave: up to 512 blocks 0.65, to 2048 0.65 to 0.8 under a causal mask, 0.9 with lengths,
+// 1.0 without, beyond 0.9 with a mask.  The constants of one wave against four are fitted to 500 random sizes with each form forced.
+// Longer heads: one of four or four of one, so where the workgroups of one launch are not all there at once, what counts is whole rounds.
+// One launch over two, no mask, by blocks over what the CUs hold: up to 0.5 0.65, to 1 1.0 to 1.2 (sequences of up to 3 tiles 0.8 to
+// 1.0), to 1.5 0.72 to 0.93, to 2 0.92 to 1.16, to 2.5 0.82 to 0.95, to 3 0.97 to 1.1; under a causal mask 0.65 as long as the longest
+// blocks fit side by side.  The constants below, which weigh the four forms in units of a tile, are fitted to 5568 random sizes with each
+// form forced.
+// Over the least time of the forms: up to 64 1.008, above 1.006.  Over the time before the tiles went through LDS and the two halves into
+// one launch: up to 64 0.61, above 0.68, of 5568 calls 13 more than 1.03, the worst b=7 s=88 a=12 dh=80 causal, 28.6 -> 32.0 us.  (With
+// the rule of the shorter heads above 64, too: 1.05 over the least, 235 calls more than 1.03 over that time, at worst 1.26.)
+struct BwdForm { int waves; bool one_launch; };
+BwdForm bwd_form(const AttnDesc& d) {
+  const int64_t tiles = ceil_div(d.s, kRows), blocks = (int64_t)d.b * d.a * tiles, cus = gemm_compute_units();
+  const bool causal = d.mask_mode == 1;
+  if (d.dh <= 64) {
+    const bool few = blocks <= 4 * cus, l1 = few || d.mask_mode != 0;
+    const int64_t wgs1 = l1 ? 2 * blocks : blocks, wgs4 = few ? 2 * blocks : blocks;
+    double one = 0.93 * (l1 ? 1 : 2) * ceil_div(wgs1, 8 * cus) * (tiles + 0.34);
+    if (causal && tiles > 2 && wgs1 <= 8 * cus) one *= 1.56;
+    const double four = (few ? 1 : 2) * ceil_div(wgs4, 2 * cus) * (ceil_div(tiles, kManyWaves) + 0.34);
+    return one < four ? BwdForm{1, l1} : BwdForm{kManyWaves, few};
   }
-  auto launches = [&](int waves) { return one_launch(d, waves) ? 1 : 2; };
-  const int n1 = launches(1), n4 = launches(kManyWaves);
-  const int64_t ones = (d.dh <= 64 ? 8 : 4) * cus, fours = (d.dh <= 64 ? 2 : 1) * cus, wgs1 = 2 * blocks / n1;
-  double one = 0.93 * n1 * ceil_div(wgs1, ones) * (tiles + 0.34);
-  if (causal && wgs1 <= ones) one *= 1.56;
-  const double four = n4 * ceil_div(2 * blocks / n4, fours) * (ceil_div(tiles, kManyWaves) + 0.34);
-  return one < four;
+  BwdForm best = {0, false};
+  double least = 0;
+  for (int waves : {1, kManyWaves})
+    for (bool one : {false, true}) {
+      const int64_t wgs = one ? 2 * blocks : blocks, slots = (waves == 1 ? 4 : 1) * cus;
+      const int64_t steps = ceil_div(tiles, waves), whole = tiles / waves;
+      const double x = (double)wgs / slots, over = waves == 1 ? 0.14 : 0.46;   // what a workgroup costs beside its steps
+      double rounds;
+      if (causal) {   // blocks of all lengths, the longest first
+        const double mean = (waves * whole * (whole + 1) / 2 + (tiles - waves * whole) * steps) / (double)tiles;
+        rounds = x * (mean + over) / (steps + over) + (x > 0.5 ? 0.3 : 0.0);
+      } else {   // in one launch the last round starts as the shorter half of the one before ends
+        const double part = !one ? 0.0 : tiles <= 3 ? 1.0 : d.mask_mode == 2 ? 0.4 : 0.3;
+        rounds = (1 - part) * ceil_div(wgs, slots) + part * x;
+      }
+      if (rounds < 1) rounds = 1;
+      const double length = (waves == 1 ? 0.91 : 1.0) * (steps + over);   // of dQ and dK/dV together
+      const double time = one ? 0.14 + length * (0.16 + 0.51 * rounds) : 0.28 + length * rounds;
+      if (best.waves == 0 || time < least) { best = {waves, one}; least = time; }
+    }
+  return best;
 }
 }  // namespace
 
 hipError_t attention_fwd_f32(const AttnDesc& d, const void* qkv, void* o, float* lse, hipStream_t st) {
-  return one_wave(d, false) ? by_head<Fwd, 1>(d, qkv, o, lse, st) : by_head<Fwd, kManyWaves>(d, qkv, o, lse, st);
+  return fwd_one_wave(d) ? by_head<Fwd, 1>(d, qkv, o, lse, st) : by_head<Fwd, kManyWaves>(d, qkv, o, lse, st);
 }
 
 hipError_t attention_bwd_f32(const AttnDesc& d, const void* qkv, const void* o, const float* lse, const void* d_o, void* dqkv, float* delta,
                              hipStream_t st) {
-  return one_wave(d, true) ? by_head<Bwd, 1>(d, qkv, o, lse, d_o, dqkv, delta, st) : by_head<Bwd, kManyWaves>(d, qkv, o, lse, d_o, dqkv, delta, st);
+  const BwdForm f = bwd_form(d);
+  return f.waves == 1 ? by_head<Bwd, 1>(d, f.one_launch, qkv, o, lse, d_o, dqkv, delta, st) : by_head<Bwd, kManyWaves>(d, f.one_launch, qkv, o, lse, d_o, dqkv, delta, st);
 }
 
 }  // namespace k2bw
