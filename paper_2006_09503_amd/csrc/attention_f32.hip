@@ -582,16 +582,27 @@ hipError_t set_lds(K kern, size_t bytes) {
   return hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
 }
 
+// Long causal sequences whose blocks are more than the CUs and no more than twice: all start at once where a CU holds two workgroups of
+// four waves, and the CUs that got one idle when it ends.  With one at a time the longest blocks go first and the others follow where a CU
+// comes free (two over one: from 13 tiles on 1.02 to 1.23, b=2 s=700 a=8 dh=56 25.6 -> 20.9 us; 9 to 12 tiles up to 320 blocks 1.0 to
+// 1.16, beyond 0.84 to 1.0; fewer 0.7 to 0.96; above 512 blocks 0.8 to 0.91).  Head sizes up to 32 are even up to 256 blocks and behind above.
+template <int DH, int NW>
+bool one_at_a_time(const AttnDesc& d) {
+  const int64_t tiles = ceil_div(d.s, kRows), blocks = (int64_t)d.b * d.a * tiles, cus = gemm_compute_units();
+  return NW > 1 && DH > 32 && DH <= 64 && d.mask_mode == 1 && blocks > cus && blocks <= 2 * cus && (tiles >= 13 || (tiles >= 9 && 4 * blocks <= 5 * cus));
+}
+
 template <int DH, int NW>
 hipError_t fwd_launch(const AttnDesc& d, const void* qkv, void* o, float* lse, hipStream_t st) {
-  constexpr size_t lds = (tile_floats<DH, NW>() + 2 * NW * kRows) * sizeof(float);
-  static_assert(lds <= 160 * 1024, "LDS of a CU");
+  constexpr size_t need = (tile_floats<DH, NW>() + 2 * NW * kRows) * sizeof(float), most = need > 81 * 1024 ? need : 81 * 1024;
+  static_assert(need <= 160 * 1024, "LDS of a CU");
   static bool done = false;
   if (!done) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(attn_f32_fwd_kernel<DH, NW>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    hipError_t e = set_lds(attn_f32_fwd_kernel<DH, NW>, most);
     if (e != hipSuccess) return e;
     done = true;
   }
+  const size_t lds = one_at_a_time<DH, NW>(d) ? most : need;
   dim3 grid(d.a, d.b, ceil_div(d.s, kRows));
   hipLaunchKernelGGL((attn_f32_fwd_kernel<DH, NW>), grid, dim3(NW * 64), lds, st, static_cast<const float*>(qkv), static_cast<float*>(o), lse,
                      d.s, d.a, d.dh, d.mask_mode, d.seqlens);

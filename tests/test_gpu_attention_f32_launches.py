@@ -1,5 +1,6 @@
 """fp32 attention, backward in one launch and in two: sizes on both sides of that rule, on one and on four waves per workgroup (all
-four forms at heads above 64), head sizes of every row width in LDS; and what a position that nobody may see holds must not show in either form."""
+four forms at heads above 64), head sizes of every row width in LDS; forward
+with one workgroup per CU at a time; and what a position that nobody may see holds must not show in either form."""
 import pytest
 import torch
 
@@ -10,7 +11,7 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("dh", [8, 24, 48, 64, 80, 104, 128])
 @pytest.mark.parametrize("b,s,a,mask", [(1, 65, 2, 1), (2, 290, 8, 0), (2, 290, 8, 2), (2, 290, 8, 1), (2, 250, 9, 2), (9, 97, 30, 1), (40, 33, 13, 2),
-                                        (3, 520, 24, 2), (4, 60, 72, 0), (13, 100, 12, 0), (19, 108, 16, 0)])
+                                        (3, 520, 24, 2), (4, 60, 72, 0), (13, 100, 12, 0), (19, 108, 16, 0), (2, 430, 10, 1), (1, 300, 32, 1)])
 def test_backward_on_both_sides_of_the_launch_rule(dh, b, s, a, mask):
     h = a * dh
     qkv, d_o, lens = inputs(F32, b, s, a, dh, mask)
