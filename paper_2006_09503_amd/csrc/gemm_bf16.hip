@@ -876,7 +876,7 @@ constexpr int vmcnt_imm(int n) { return (n & 15) | ((n >> 4) << 14) | (7 << 4) |
 // the other 24).  With more than two stages the stage that tile kt+NS-1 goes to is already free
 // during the whole of step kt, so its loads are issued one at a time between the MFMAs of all
 // sub-steps and the queue never fills; a load has NS-2 steps to land.  256x256 tiles: four stages
-// of K = 32 (128 KB); the phased kernel took over their forms with an operand along K.  128x128 tiles: four stages of K = 64; with K = 32 (half a 128-byte line per
+// of K = 32 (128 KB); with an operand along K the phased kernel is ahead of them from K = 512 on.  128x128 tiles: four stages of K = 64; with K = 32 (half a 128-byte line per
 // row and load) that tile is 10..15 % slower once the operands come from HBM, as they do inside
 // the stage, with four stages or with eight.
 // Whether a launch of such tiles may end with tiles of half the height (see launch_tiles): 256x256 ones, whose loads divide evenly
@@ -1581,37 +1581,48 @@ int g_tile_override = 0;  // 0: heuristic; else force a tile shape (tuning aid)
 // Estimated time of a launch, in microseconds, with r tiles per CU, R = ceil(r) rounds and K in thousands:
 //   fixed + round R + round_k K R + tile r + (tile_k + off_k [K not a multiple of 64]) K r
 // (a round costs time whether or not its CUs all have a tile; tiles cost memory traffic and, on a full chip, clock).
-// A tile shape is open to a problem if K is at least `whole` (its K tile; 0: any K).
-struct TileCost { int id, bm, bn, whole; double fixed, round, round_k, tile_k, tile, off_k; };
+// A tile shape is open to a problem if K is at least `whole` (its K tile; 0: any K); by itself it is taken for K below `below` only.
+struct TileCost { int id, bm, bn, whole; double fixed, round, round_k, tile_k, tile, off_k; int below = 1 << 30; };
 
-// The tile shapes of the three operand forms and the constants of the estimate.  Fitted, with each shape forced, to 3300 launches of
-// random sizes (48 to 16384 rows and columns, K of 96 to 16384; those within 1.4 of the best shape of their size): 4 to 10 % off the
-// measured times, 64x64 and 32x32 tiles 12 to 16 %.  Time of the choice over the best shape of each size, geometric mean: forward
-// 1.004, both operands along K 1.007, weight gradient 1.004 (with the lines in use before the phased kernels, whose shapes were 23,
-// 24 and the staged ones: 1.025, 1.036, 1.017; slowest against those 1.20, 1.08 and 1.08).
+// The tile shapes of the operand forms and the constants of the estimate.  Fitted, with each shape forced, to 3300 launches of random
+// sizes (48 to 16384 rows and columns, K of 96 to 16384), and those of the shapes that meet at short K again to 4600, of which a third
+// with K of 40 to 700 and wide outputs.  Time of the choice over the best shape of each of the 4600, geometric mean: forward 1.0025, both
+// operands along K 1.003 (with the GELU' epilogue 1.004), weight gradient 1.001.  Over the lines in use before the phased kernels, whose
+// shapes were 23, 24 and the staged ones: 0.978, 0.970 (0.962) and 0.982; of 3309 other sizes of more than 6 us 97
+// above 1.03, at worst 1.11, 1.10 (1.10) and 1.12.  (Without shape 2 in the first two forms and 23 in the first, and with one table for
+// both epilogues, 171, at worst 1.41; K below 64 up to 1.58: 1302 x 4736, K = 56, 11.9 -> 18.3.)
 // What a form does without: the ring's 256x256 tiles are 4 to 17 % behind the phased ones from K = 512 on except in the weight
-// gradient (1.02 below K = 512, then 1.00, 0.97 from 2048: not worth a second instance); 192x256 tiles are even between ring and
-// phased in the forward form, 5 to 14 % behind on the phased kernel in the weight gradient; register-staged 128x128 tiles, two
-// workgroups per CU, win in the weight gradient only, with two K groups only where both operands run along K.
+// gradient (phased over ring 1.02 below K = 512, then 1.00, 0.97 from 2048: not worth a second instance), and ahead by up to 15 %
+// below, where K is not a multiple of 64; in the data gradient that is the choice for too few sizes (4 of 758) and worth no instance.
+// 192x256 tiles are even between ring and phased in the forward form, 5 to 14 % behind on the phased kernel in the weight gradient; two
+// K groups win only where both operands run along K.
 constexpr TileCost kForwardTiles[] = {
-    {22, 128, 128, 64, 1.8, 2.7, 5.0, 2.2, 0.7, 2.2},    {25, 256, 256, 64, 1.1, 7.6, 10.5, 12.7, 1.8, 0},
-    {24, 192, 256, 32, 2.0, 4.7, 9.6, 9.7, 2.1, 0},      {27, 128, 256, 64, 2.1, 3.4, 8.9, 4.5, 2.0, 0},
-    {64, 64, 64, 0, 1.45, 2.4, 2.7, 2.0, 0, 0},          {32, 32, 32, 0, 1.4, 1.6, 0.97, 1.4, 0, 0},
-    {3, 256, 256, 0, 2.7, 5.5, 18.0, 10.0, 1.8, 1.8}};
+    {22, 128, 128, 64, 1.8, 2.7, 5.0, 2.2, 0.7, 2.2},          {25, 256, 256, 64, 1.5, 9.08, 14.12, 8.24, 1.71, 0.11},
+    {24, 192, 256, 32, 2.46, 4.82, 8.76, 9.7, 1.9, 0.16},      {27, 128, 256, 64, 2.1, 3.4, 8.9, 4.5, 2.0, 0},
+    {64, 64, 64, 0, 1.45, 2.4, 2.7, 2.0, 0, 0},                {32, 32, 32, 0, 1.4, 1.6, 0.97, 1.4, 0, 0},
+    {3, 256, 256, 0, 3.59, 4.95, 28.17, 12.85, 2.44, 1.43},    {2, 128, 128, 0, 3.95, 0.41, 10.06, 5.05, 1.97, 1.16},
+    {23, 256, 256, 32, 3.7, 5.82, 8.71, 14.87, 2.6, 0.71, 512}};
 constexpr TileCost kDataTiles[] = {   // both operands along K
-    {22, 128, 128, 64, 1.4, 3.0, 4.5, 2.55, 0.5, 4.1},   {25, 256, 256, 64, 0, 8.1, 12.1, 10.3, 2.8, 0},
-    {26, 192, 256, 64, 2.2, 3.9, 10.2, 7.3, 4.1, 0},     {27, 128, 256, 64, 1.1, 4.6, 7.2, 5.8, 1.7, 0},
-    {64, 64, 64, 0, 1.65, 2.2, 2.5, 2.4, 0, 0},          {32, 32, 32, 0, 1.55, 1.55, 0.83, 1.1, 0, 0},
-    {3, 256, 256, 0, 2.85, 4.6, 17.9, 9.1, 2.8, 2.7},    {6, 128, 128, 0, 1.8, 3.3, 6.7, 1.9, 1.3, 1.5}};
+    {22, 128, 128, 64, 1.4, 3.0, 4.5, 2.55, 0.5, 4.1},         {25, 256, 256, 64, 0.06, 7.62, 12.1, 10.3, 2.66, 0},
+    {26, 192, 256, 64, 1.77, 3.79, 9.46, 7.26, 3.74, 0.41},    {27, 128, 256, 64, 1.1, 4.6, 7.2, 5.8, 1.7, 0},
+    {64, 64, 64, 0, 1.65, 2.2, 2.5, 2.4, 0, 0},                {32, 32, 32, 0, 1.55, 1.55, 0.83, 1.1, 0, 0},
+    {3, 256, 256, 0, 2.85, 4.55, 19.84, 8.1, 2.49, 2.44},      {6, 128, 128, 0, 4.2, 5.44, 4.5, 1.85, 1.61, 1.26},
+    {2, 128, 128, 0, 4.12, 0.49, 9.23, 6.12, 1.61, 1.07}};
+constexpr TileCost kDataGeluTiles[] = {   // the same with the GELU' epilogue, which reads a matrix more; two workgroups per CU hide that
+    {22, 128, 128, 64, 0.94, 4.2, 4.39, 2.22, 0.21, 4.1},      {25, 256, 256, 64, 0, 10.72, 12.59, 9.09, 2.43, 0.56},
+    {26, 192, 256, 64, 1.38, 5.15, 10.2, 6.52, 4.54, 0.46},    {27, 128, 256, 64, 1.25, 4.67, 7.39, 4.03, 3.52, 0},
+    {64, 64, 64, 0, 1.65, 2.2, 2.5, 2.4, 0, 0},                {32, 32, 32, 0, 1.55, 1.55, 0.83, 1.1, 0, 0},
+    {3, 256, 256, 0, 2.24, 5.84, 21.48, 11.77, 3.24, 4.54},    {6, 128, 128, 0, 2.52, 4.83, 6.65, 1.4, 1.41, 0.72},
+    {2, 128, 128, 0, 4.45, 0.63, 7.78, 5.33, 1.7, 0.18}};
 constexpr TileCost kWeightTiles[] = {
-    {22, 128, 128, 64, 1.0, 4.5, 5.4, 2.3, 2.3, 1.0},    {23, 256, 256, 32, 0.4, 8.8, 13.5, 11.1, 13.0, 0},
-    {24, 192, 256, 32, 0.8, 7.0, 10.1, 7.9, 9.4, 0},     {27, 128, 256, 64, 0.4, 6.8, 8.7, 5.5, 4.6, 0},
-    {64, 64, 64, 0, 1.3, 3.05, 2.6, 1.9, 0, 0},          {32, 32, 32, 0, 1.4, 1.9, 0.93, 1.9, 0, 0},
-    {2, 128, 128, 0, 1.9, 4.0, 7.7, 5.5, 2.4, 0.5}};
+    {22, 128, 128, 64, 1.0, 4.5, 5.4, 2.3, 2.3, 1.0},          {23, 256, 256, 32, 0.4, 8.8, 13.5, 11.1, 13.0, 0},
+    {24, 192, 256, 32, 0.8, 7.0, 10.1, 7.9, 9.4, 0},           {27, 128, 256, 64, 0.4, 6.8, 8.7, 5.5, 4.6, 0},
+    {64, 64, 64, 0, 1.3, 3.05, 2.6, 1.9, 0, 0},                {32, 32, 32, 0, 1.4, 1.9, 0.93, 1.9, 0, 0},
+    {2, 128, 128, 0, 1.48, 4.28, 15.16, 2.93, 2.12, 0.4}};
 
-// Tile choice for a (grouped) problem; ta/tb as in GemmDesc.  A forced shape that the form has not or that is not open to the problem
+// Tile choice for a (grouped) problem; ta/tb and epilogue as in GemmDesc.  A forced shape that the form has not or that is not open to the problem
 // gives way to the best open one.  -1: no shape is open (a segmented range that is not made of whole K tiles).
-int choose_tile(const BfParams* p, int count, bool ta, bool tb) {
+int choose_tile(const BfParams* p, int count, bool ta, bool tb, int epilogue) {
   int K = 0;
   bool segmented = false, odd_pieces = false;
   for (int g = 0; g < count; ++g) {
@@ -1635,6 +1646,9 @@ int choose_tile(const BfParams* p, int count, bool ta, bool tb) {
       if (q.id == 24 && tiles > cus) return -1.0;
       if (odd_pieces && tiles < (q.id == 23 ? 144 : 132)) return -1.0;
     }
+    // an accumulator larger than the memory-side cache (256 MB): 128x128 tiles, two at a time on a CU, lose up to 12 % to 256x256 ones
+    // there (4648 x 14232, K = 128: 112 us against 101; smaller ones win 3 to 10 %)
+    if (ta && q.id == 2 && tiles > 15 * cus && g_tile_override != 2) return -1.0;
     const int slots = q.id == 2 ? 2 * cus : cus;   // the register-staged workgroups of four waves share a CU
     double rounds = (double)ceil_div(tiles, (int64_t)slots);
     // tiles of half the height in the last round (launch_tiles) take 0.6 of a whole one
@@ -1649,21 +1663,21 @@ int choose_tile(const BfParams* p, int count, bool ta, bool tb) {
       const double c = cost_of(list[i]);
       if (c < 0) continue;
       if (list[i].id == g_tile_override) return list[i].id;
+      if (K >= list[i].below) continue;
       if (best < 0 || c < least) { best = list[i].id; least = c; }
     }
     return best;
   };
   if (ta) return pick(kWeightTiles, sizeof kWeightTiles / sizeof *kWeightTiles);
+  if (tb && epilogue == kEpiGeluGrad) return pick(kDataGeluTiles, sizeof kDataGeluTiles / sizeof *kDataGeluTiles);
   if (tb) return pick(kDataTiles, sizeof kDataTiles / sizeof *kDataTiles);
   return pick(kForwardTiles, sizeof kForwardTiles / sizeof *kForwardTiles);
 }
 
 template <bool TA, bool TB, int EPI>
 hipError_t pick_tile(const GroupParams& gp, hipStream_t s) {
-  switch (choose_tile(gp.p, gp.count, TA, TB)) {   // the instances are those of the tables above
-    case 2:
-      if constexpr (TA) return launch<128, 128, 64, 64, 64, TA, TB, EPI>(gp, s);
-      break;
+  switch (choose_tile(gp.p, gp.count, TA, TB, EPI)) {   // the instances are those of the tables above
+    case 2: return launch<128, 128, 64, 64, 64, TA, TB, EPI>(gp, s);
     case 3:
       if constexpr (!TA) return launch<256, 256, 128, 64, 64, TA, TB, EPI>(gp, s);   // 8 waves
       break;
@@ -1672,7 +1686,7 @@ hipError_t pick_tile(const GroupParams& gp, hipStream_t s) {
       break;
     case 22: return launch_ring<128, 128, 32, 64, 64, 4, TA, TB, EPI>(gp, s);   // 8 waves
     case 23:
-      if constexpr (TA) return launch_ring<256, 256, 128, 64, 32, 4, TA, TB, EPI>(gp, s);
+      if constexpr (!TB) return launch_ring<256, 256, 128, 64, 32, 4, TA, TB, EPI>(gp, s);
       break;
     case 24:
       if constexpr (!TB) return launch_ring<192, 256, 96, 64, 32, 4, TA, TB, EPI>(gp, s);
@@ -1741,7 +1755,7 @@ int gemm_compute_units() { return compute_units(); }
 void gemm_bf16_kernel_name(const GemmDesc* d, int count, char* out, size_t cap) {
   BfParams p[kMaxGroup];
   for (int g = 0; g < count && g < kMaxGroup; ++g) p[g] = to_params(d[g]);
-  const int tile = choose_tile(p, count < kMaxGroup ? count : kMaxGroup, d[0].trans_a, d[0].trans_b);
+  const int tile = choose_tile(p, count < kMaxGroup ? count : kMaxGroup, d[0].trans_a, d[0].trans_b, d[0].epilogue);
   const char* ta = d[0].trans_a ? "true" : "false";
   const char* tb = d[0].trans_b ? "true" : "false";
   switch (tile) {

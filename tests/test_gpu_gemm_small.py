@@ -136,10 +136,10 @@ def test_bf16_weight_gradient_of_any_number_of_tokens(tile, M, N, K):
 
 
 @pytest.mark.parametrize("M,N,K", [(200, 17000, 72), (1168, 3304, 1544), (648, 11960, 40), (4104, 2056, 96), (968, 5944, 520), (392, 8536, 1032),
-                                   (1000, 2312, 2104), (3080, 3592, 40), (136, 10296, 264)])
+                                   (1000, 2312, 2104), (3080, 3592, 40), (136, 10296, 264), (1304, 4736, 56), (1592, 8976, 96), (1752, 1320, 48)])
 def test_bf16_products_on_both_sides_of_the_tile_rule(M, N, K):
     """The tile the library picks, around its lines: 128 x 128 tiles in several rounds of short and long reductions, 192 x 256 and
-    256 x 256 tiles, reductions that are whole 128-byte lines and that are not; the partial K tiles and NaNs of the tests above."""
+    256 x 256 tiles, reductions that are whole 128-byte lines and that are not, or less than one; the partial K tiles and NaNs of the tests above."""
     for k in (K, K + (-K) % 64):
         test_bf16_partial_k_tiles(0, M, N, k)
         test_bf16_weight_gradient_of_any_number_of_tokens(0, M, N, k - 3)
