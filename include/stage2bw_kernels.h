@@ -44,7 +44,7 @@ int k2bw_gemm(int dtype, int trans_a, int trans_b, int epilogue, int M, int N, i
  * microbatches of a batch, taken inside the reduction): C[M,N] (fp32) = (accumulate ? C : 0) +
  * sum over s < n_seg of X_s^T dY_s, X_s: [T, M] (ld = lda) at A0 + a_idx[s] * a_stride_bytes,
  * dY_s: [T, N] (ld = ldb) at B0 + b_idx[s] * b_stride_bytes.  n_seg 1..8, indices 0..15 (host arrays of
- * n_seg bytes), strides multiples of 256 bytes, T a multiple of 64; INVALID_ARG otherwise. */
+ * n_seg bytes), strides multiples of 256 bytes, T a multiple of 32 (any T for n_seg 1); INVALID_ARG otherwise. */
 int k2bw_gemm_wgrad_segmented(int M, int N, int T, int n_seg, const void* A0, int lda,
                               int64_t a_stride_bytes, const uint8_t* a_idx_host, const void* B0, int ldb,
                               int64_t b_stride_bytes, const uint8_t* b_idx_host, float* C, int ldc,

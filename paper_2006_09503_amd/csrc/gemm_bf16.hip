@@ -1624,11 +1624,10 @@ constexpr TileCost kWeightTiles[] = {
 // gives way to the best open one.  -1: no shape is open (a segmented range that is not made of whole K tiles).
 int choose_tile(const BfParams* p, int count, bool ta, bool tb, int epilogue) {
   int K = 0;
-  bool segmented = false, odd_pieces = false;
+  bool segmented = false;
   for (int g = 0; g < count; ++g) {
     K = p[g].K > K ? p[g].K : K;
     segmented = segmented || p[g].seg_tiles > 1;
-    odd_pieces = odd_pieces || (p[g].seg_tiles > 1 && p[g].K / p[g].seg_tiles % 64 != 0);
   }
   const int cus = compute_units();
   auto cost_of = [&](const TileCost& q) {   // below zero: not open
@@ -1640,12 +1639,8 @@ int choose_tile(const BfParams* p, int count, bool ta, bool tb, int epilogue) {
       if (p[g].seg_tiles > 1 ? (p[g].K / p[g].seg_tiles) % q.whole != 0 : p[g].K < q.whole) return -1.0;
       tiles += (int64_t)ceil_div(p[g].M, q.bm) * ceil_div(p[g].N, q.bn);
     }
-    // (the long grouped launches over several microbatches keep square tiles: fewest operand bytes per flop; pieces that are not
-    // multiples of 64, beyond what the interface promises, are taken from 144 square tiles on, or 132 of 192x256 in one round of them)
-    if (segmented && (q.id == 23 || q.id == 24)) {
-      if (q.id == 24 && tiles > cus) return -1.0;
-      if (odd_pieces && tiles < (q.id == 23 ? 144 : 132)) return -1.0;
-    }
+    // (the long grouped launches over several microbatches keep square tiles: fewest operand bytes per flop)
+    if (segmented && q.id == 24 && tiles > cus) return -1.0;
     // an accumulator larger than the memory-side cache (256 MB): 128x128 tiles, two at a time on a CU, lose up to 12 % to 256x256 ones
     // there (4648 x 14232, K = 128: 112 us against 101; smaller ones win 3 to 10 %)
     if (ta && q.id == 2 && tiles > 15 * cus && g_tile_override != 2) return -1.0;

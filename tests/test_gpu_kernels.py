@@ -338,6 +338,8 @@ def test_bias_gradient_column_sums(dtype, rows, n):
     (3080, 3072, 96, [5, 1, 4, 0], [3, 2, 1, 0]),          # 204 tiles of 192x256 (K tiles of 32), ragged M: one round
     (3080, 4352, 96, [5, 1, 4, 0], [3, 2, 1, 0]),          # 289 of those would not fit a round: 256x256 ring tiles, ragged M
     (2048, 2304, 64, [0, 1, 2, 3, 4, 5, 6, 7], [7, 6, 5, 4, 3, 2, 1, 0]),   # the maximum number of pieces
+    (136, 520, 96, [1, 4], [2, 0]),                        # pieces of an odd number of K tiles of 32 into a small output
+    (520, 264, 32, [3, 0, 2], [0, 1, 2]),                  # ... and of one
 ])
 def test_gemm_weight_gradient_over_several_microbatches(M, N, T, idx_a, idx_b):
     """sum_s X_s^T dY_s with the pieces in separate buffers at a constant stride, in one product."""
