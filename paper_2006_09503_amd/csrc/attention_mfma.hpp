@@ -539,8 +539,8 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_fwd_mfma_kernel(const bf16_t*
 }
 
 // ------------------------------------------------------------------------------------------------
-// dQ (and delta = rowsum(dO * O), which the dK/dV kernel reads afterwards)
-template <int DH, int NW, int KSPL, bool ANY, bool EXACT>
+// dQ (and, if SAVE, delta = rowsum(dO * O), which the dK/dV kernel reads afterwards)
+template <int DH, int NW, int KSPL, bool ANY, bool EXACT, bool SAVE>
 __device__ __forceinline__ bool attn_dq(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ o, const bf16_t* __restrict__ d_o, const float* __restrict__ lse, float* __restrict__ delta, bf16_t* __restrict__ dqkv, int s, int a, int mask_mode, const int32_t* __restrict__ seqlens, float* __restrict__ colsum, int dh_, int blk, int nblk) {
   using C = Cfg<DH>;
   extern __shared__ uint4 smem[];   // stage st: K tile at st * 2 * kTileU4, V tile behind it
@@ -590,7 +590,7 @@ __device__ __forceinline__ bool attn_dq(const bf16_t* __restrict__ qkv, const bf
 #pragma unroll
       for (int e = 0; e < 8; ++e) part = fmaf((float)dof[ks][e], (float)of[ks][e], part);
     delta_i = part + __shfl_xor(part, 32, 64);
-    if (row_ok && hf == 0 && kg == 0) delta[((int64_t)n * a + head) * s + i] = delta_i;
+    if (SAVE && row_ok && hf == 0 && kg == 0) delta[((int64_t)n * a + head) * s + i] = delta_i;
   }
   const float lse_i = row_ok ? lse[((int64_t)n * a + head) * s + i] * (ANY ? 1.f : kLog2e) : INFINITY;
   // dP - delta comes out of the product, whose accumulators start at -delta; at head size 32 delta is subtracted afterwards: the
@@ -695,8 +695,8 @@ __device__ __forceinline__ bool attn_dq(const bf16_t* __restrict__ qkv, const bf
 template <int DH, int NW, int KSPL, bool ANY>
 __global__ __launch_bounds__(NW * 64, 2) void attn_dq_mfma_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ o, const bf16_t* __restrict__ d_o, const float* __restrict__ lse, float* __restrict__ delta, bf16_t* __restrict__ dqkv, int s, int a, int mask_mode, const int32_t* __restrict__ seqlens, float* __restrict__ colsum, int dh_) {
   const int nblk = gridDim.z, blk = mask_mode == 1 ? nblk - 1 - (int)blockIdx.z : (int)blockIdx.z;
-  if (attn_dq<DH, NW, KSPL, ANY, false>(qkv, o, d_o, lse, delta, dqkv, s, a, mask_mode, seqlens, colsum, dh_, blk, nblk))
-    if constexpr (ANY) attn_dq<DH, NW, KSPL, ANY, true>(qkv, o, d_o, lse, delta, dqkv, s, a, mask_mode, seqlens, colsum, dh_, blk, nblk);
+  if (attn_dq<DH, NW, KSPL, ANY, false, true>(qkv, o, d_o, lse, delta, dqkv, s, a, mask_mode, seqlens, colsum, dh_, blk, nblk))
+    if constexpr (ANY) attn_dq<DH, NW, KSPL, ANY, true, true>(qkv, o, d_o, lse, delta, dqkv, s, a, mask_mode, seqlens, colsum, dh_, blk, nblk);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -706,10 +706,10 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_dq_mfma_kernel(const bf16_t* 
 // loop waits for the next tile's loads: backward at b=3 s=1000 a=16 causal, head size 96 119 -> 100 us, 72 145 -> 91); and launches
 // that leave half of the CUs idle gain the second half's work (backward, 64-row blocks: b=1 s=1024 a=8 dh=64 30.2 -> 28.2 us,
 // b=1 s=2048 a=4 causal 51.3 -> 47.4).
-// delta_lds: null, and delta comes from what the dQ kernel left; or LDS for as many floats as the sequence has rows, which the
-// workgroup fills from dO and O while its first tile travels.
-template <int DH, int NW, int KSPL, bool ANY, bool EXACT, int PART>
-__device__ __forceinline__ bool attn_dkv(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ o, const bf16_t* __restrict__ d_o, const float* __restrict__ lse, const float* __restrict__ delta, bf16_t* __restrict__ dqkv, int s, int a, int mask_mode, const int32_t* __restrict__ seqlens, float* __restrict__ colsum, int dh_, int blk, int nblk, float* delta_lds) {
+// OWN: delta comes from own_delta, LDS for as many floats as the sequence has rows, which the workgroup fills from dO and O while its
+// first tile travels (a workgroup that only makes dV has no use for it); else from what the dQ kernel left in memory.
+template <int DH, int NW, int KSPL, bool ANY, bool EXACT, int PART, bool OWN>
+__device__ __forceinline__ bool attn_dkv(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ o, const bf16_t* __restrict__ d_o, const float* __restrict__ lse, const float* __restrict__ delta, bf16_t* __restrict__ dqkv, int s, int a, int mask_mode, const int32_t* __restrict__ seqlens, float* __restrict__ colsum, int dh_, int blk, int nblk, float* own_delta) {
   using C = Cfg<DH>;
   extern __shared__ uint4 smem[];
   // stage st: Q tile, dO tile, 64 lse, 64 delta
@@ -730,7 +730,7 @@ __device__ __forceinline__ bool attn_dkv(const bf16_t* __restrict__ qkv, const b
   const bf16_t* base = qkv + (int64_t)n * s * ld + head * dh;
   const bf16_t* dobase = d_o + (int64_t)n * s * h + head * dh;
   const float* lse_row = lse + ((int64_t)n * a + head) * s;
-  const float* delta_row = delta + ((int64_t)n * a + head) * s;
+  const float* delta_row = OWN ? nullptr : delta + ((int64_t)n * a + head) * s;
   const int kv_len = mask_mode == 2 ? min(max(seqlens[n], 1), s) : s;   // lengths outside [1, s] are clamped: no read past the sequence, no empty row
   const bool causal = mask_mode == 1;
   const int jw0 = j0 + rw * 32;
@@ -766,15 +766,21 @@ __device__ __forceinline__ bool attn_dkv(const bf16_t* __restrict__ qkv, const b
   // loop uses: -lse * log2(e) (ANY: -lse), and -delta, the starting value of the accumulators of dP
   float stat = 0.f;
   auto load_stat = [&](int i0) {
-    if (rw < 2) stat = (rw == 0 ? lse_row : delta_row)[min(i0 + lane, s - 1)];
-    if (delta_lds && rw == 1) stat = delta_lds[min(i0 + lane, s - 1)];
+    const int i = min(i0 + lane, s - 1);
+    if constexpr (!OWN) {
+      if (rw < 2) stat = (rw == 0 ? lse_row : delta_row)[i];
+    } else if (rw == 0) {
+      stat = lse_row[i];
+    } else if (DK && rw == 1) {
+      stat = own_delta[i];
+    }
   };
   bool hidden = false;
 #pragma unroll
   for (int db = 0; db < C::DB; ++db) { dk[db] = zero16(); dv[db] = zero16(); }
   uint4* const tiles = smem + kg * (2 * kStageU4 + C::kPadU4);
   if (kg < ntiles) issue_tile(istart + kg * kTile, tiles);
-  if (delta_lds && DK && ntiles > 0) {   // (uniform) eight lanes per row, U rows in flight
+  if (OWN && DK && ntiles > 0) {   // (uniform) eight lanes per row, U rows in flight
     constexpr int NC = (C::CH + 7) / 8, U = NC == 1 ? 8 : 4;
     for (int r0 = istart + wave * 8; r0 < s; r0 += U * NW * 8) {
       bf16x8 x[U][NC], y[U][NC];
@@ -800,7 +806,7 @@ __device__ __forceinline__ bool attn_dkv(const bf16_t* __restrict__ qkv, const b
           part += ((lane & 7) + q * 8) * 8 < dh ? t : 0.f;
         }
         part = row8_sum(part);
-        if ((lane & 7) == 0 && row < s) delta_lds[row] = part;
+        if ((lane & 7) == 0 && row < s) own_delta[row] = part;
       }
     }
     __syncthreads();
@@ -948,8 +954,8 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_dkv_mfma_kernel(const bf16_t*
   const int nblk = gridDim.z >> (PARTS ? 1 : 0), blk = blockIdx.z >> (PARTS ? 1 : 0);
   auto run = [&](auto part) __attribute__((always_inline)) {
     constexpr int PART = decltype(part)::value;
-    if (attn_dkv<DH, NW, KSPL, ANY, false, PART>(qkv, nullptr, d_o, lse, delta, dqkv, s, a, mask_mode, seqlens, colsum, dh_, blk, nblk, nullptr))
-      if constexpr (ANY) attn_dkv<DH, NW, KSPL, ANY, true, PART>(qkv, nullptr, d_o, lse, delta, dqkv, s, a, mask_mode, seqlens, colsum, dh_, blk, nblk, nullptr);
+    if (attn_dkv<DH, NW, KSPL, ANY, false, PART, false>(qkv, nullptr, d_o, lse, delta, dqkv, s, a, mask_mode, seqlens, colsum, dh_, blk, nblk, nullptr))
+      if constexpr (ANY) attn_dkv<DH, NW, KSPL, ANY, true, PART, false>(qkv, nullptr, d_o, lse, delta, dqkv, s, a, mask_mode, seqlens, colsum, dh_, blk, nblk, nullptr);
   };
   if constexpr (!PARTS) run(std::integral_constant<int, 0>{});
   else if (blockIdx.z & 1) run(std::integral_constant<int, 1>{});
@@ -957,22 +963,23 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_dkv_mfma_kernel(const bf16_t*
 }
 
 // The whole backward pass in one launch.  Of every kRoles consecutive block numbers one has queries (causal: the blocks with the most
-// keys first), the others keys, so the longest workgroups of every kind go first.  delta_at: where the row of deltas lies in LDS.
+// keys first), the others keys, so the longest workgroups of every kind go first.  Nothing is handed from one to another: dK/dV form
+// their deltas themselves, in LDS at delta_at.
 template <int DH, int NW, int KSPL, bool ANY, bool PARTS>
-__global__ __launch_bounds__(NW * 64, 2) void attn_bwd_mfma_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ o, const bf16_t* __restrict__ d_o, const float* __restrict__ lse, float* __restrict__ delta, bf16_t* __restrict__ dqkv, int s, int a, int mask_mode, const int32_t* __restrict__ seqlens, float* __restrict__ colsum, int dh_, int delta_at) {
+__global__ __launch_bounds__(NW * 64, 2) void attn_bwd_mfma_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ o, const bf16_t* __restrict__ d_o, const float* __restrict__ lse, bf16_t* __restrict__ dqkv, int s, int a, int mask_mode, const int32_t* __restrict__ seqlens, float* __restrict__ colsum, int dh_, int delta_at) {
   extern __shared__ uint4 smem[];
   constexpr int kRoles = PARTS ? 3 : 2;
   const int nblk = gridDim.z / kRoles, k = blockIdx.z / kRoles, role = blockIdx.z % kRoles;
-  float* delta_lds = reinterpret_cast<float*>(smem + delta_at);
+  float* own_delta = reinterpret_cast<float*>(smem + delta_at);
   auto run = [&](auto part) __attribute__((always_inline)) {
     constexpr int PART = decltype(part)::value;
-    if (attn_dkv<DH, NW, KSPL, ANY, false, PART>(qkv, o, d_o, lse, delta, dqkv, s, a, mask_mode, seqlens, colsum, dh_, k, nblk, delta_lds))
-      if constexpr (ANY) attn_dkv<DH, NW, KSPL, ANY, true, PART>(qkv, o, d_o, lse, delta, dqkv, s, a, mask_mode, seqlens, colsum, dh_, k, nblk, delta_lds);
+    if (attn_dkv<DH, NW, KSPL, ANY, false, PART, true>(qkv, o, d_o, lse, nullptr, dqkv, s, a, mask_mode, seqlens, colsum, dh_, k, nblk, own_delta))
+      if constexpr (ANY) attn_dkv<DH, NW, KSPL, ANY, true, PART, true>(qkv, o, d_o, lse, nullptr, dqkv, s, a, mask_mode, seqlens, colsum, dh_, k, nblk, own_delta);
   };
   if (role == kRoles - 1) {
     const int blk = mask_mode == 1 ? nblk - 1 - k : k;
-    if (attn_dq<DH, NW, KSPL, ANY, false>(qkv, o, d_o, lse, delta, dqkv, s, a, mask_mode, seqlens, colsum, dh_, blk, nblk))
-      if constexpr (ANY) attn_dq<DH, NW, KSPL, ANY, true>(qkv, o, d_o, lse, delta, dqkv, s, a, mask_mode, seqlens, colsum, dh_, blk, nblk);
+    if (attn_dq<DH, NW, KSPL, ANY, false, false>(qkv, o, d_o, lse, nullptr, dqkv, s, a, mask_mode, seqlens, colsum, dh_, blk, nblk))
+      if constexpr (ANY) attn_dq<DH, NW, KSPL, ANY, true, false>(qkv, o, d_o, lse, nullptr, dqkv, s, a, mask_mode, seqlens, colsum, dh_, blk, nblk);
   } else if constexpr (!PARTS) {
     run(std::integral_constant<int, 0>{});
   } else if (role == 1) {
@@ -1055,7 +1062,7 @@ bool one_launch(const AttnDesc& d, int64_t wgs) {
 
 // Both halves of the backward pass in one launch
 template <int DH, int NW, int KSPL, bool ANY, bool PARTS>
-hipError_t both_launch(const AttnDesc& d, const void* qkv, const void* o, const float* lse, const void* d_o, void* dqkv, float* delta, hipStream_t st) {
+hipError_t both_launch(const AttnDesc& d, const void* qkv, const void* o, const float* lse, const void* d_o, void* dqkv, hipStream_t st) {
   constexpr size_t base = max_of(dq_lds<DH, NW, KSPL>(), dkv_lds<DH, NW, KSPL, ANY, PARTS>());
   const size_t lds = base + ceil_div(d.s, 4) * sizeof(uint4);
   static bool done = false;
@@ -1064,7 +1071,7 @@ hipError_t both_launch(const AttnDesc& d, const void* qkv, const void* o, const 
   static_assert(base + kMaxDeltas * sizeof(float) <= 160 * 1024, "LDS of a CU");
   dim3 grid(d.a, d.b, ceil_div(d.s, NW / KSPL * 32) * (PARTS ? 3 : 2));
   hipLaunchKernelGGL((attn_bwd_mfma_kernel<DH, NW, KSPL, ANY, PARTS>), grid, dim3(NW * 64), lds, st, static_cast<const bf16_t*>(qkv), static_cast<const bf16_t*>(o),
-                     static_cast<const bf16_t*>(d_o), lse, delta, static_cast<bf16_t*>(dqkv), d.s, d.a, d.mask_mode, d.seqlens, d.colsum_partial, d.dh,
+                     static_cast<const bf16_t*>(d_o), lse, static_cast<bf16_t*>(dqkv), d.s, d.a, d.mask_mode, d.seqlens, d.colsum_partial, d.dh,
                      (int)(base / sizeof(uint4)));
   return hipGetLastError();
 }
@@ -1078,7 +1085,7 @@ hipError_t bwd_launch(const AttnDesc& d, const void* qkv, const void* o, const f
   const int64_t blocks = (int64_t)d.a * d.b * ceil_div(d.s, NW / KSPL * 32);
   const bool parts = kAlways || (kMay && 2 * blocks <= gemm_compute_units());
   if (one_launch<DH, NW, ANY>(d, blocks * (parts ? 3 : 2)))
-    return parts ? both_launch<DH, NW, KSPL, ANY, kMay>(d, qkv, o, lse, d_o, dqkv, delta, st) : both_launch<DH, NW, KSPL, ANY, kAlways>(d, qkv, o, lse, d_o, dqkv, delta, st);
+    return parts ? both_launch<DH, NW, KSPL, ANY, kMay>(d, qkv, o, lse, d_o, dqkv, st) : both_launch<DH, NW, KSPL, ANY, kAlways>(d, qkv, o, lse, d_o, dqkv, st);
   constexpr size_t lds = dq_lds<DH, NW, KSPL>();
   static_assert(lds <= 160 * 1024, "LDS of a CU");
   static bool done = false;

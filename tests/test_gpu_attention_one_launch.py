@@ -50,3 +50,24 @@ def test_what_nobody_sees_does_not_show(dh, b, s, a, pos, bad):
     poisoned[:, pos] = bad                           # the gradient of one query
     _, _, d2 = run(BF16, b, s, a, dh, 1, qkv, poisoned, None)
     assert same(d2[:, pos + 1:, h:], d0[:, pos + 1:, h:])
+
+
+@pytest.mark.parametrize("dh", [32, 64, 96, 128])
+@pytest.mark.parametrize("b,s,a,mask,one", [(2, 65, 3, 1, True), (1, 300, 4, 0, True), (2, 150, 2, 2, True), (2, 2049, 1, 1, False), (8, 900, 16, 0, False)])
+def test_one_launch_hands_nothing_through_the_scratch_array(dh, b, s, a, mask, one):
+    """Its workgroups run side by side, so what some of them left in delta others must not use: they get no pointer to it, and the caller's
+    scratch array stays as it was.  In two launches it holds the row sums of dO * O afterwards."""
+    h = a * dh
+    qkv, d_o, lens = inputs(BF16, b, s, a, dh, mask)
+    L, p = B.lib(), lambda t: None if t is None else t.data_ptr()
+    o, dqkv = torch.empty_like(d_o), torch.empty_like(qkv)
+    lse, delta = torch.empty((b, a, s), device="cuda"), torch.full((b, a, s), float("nan"), device="cuda")
+    assert L.k2bw_attention_fwd(BF16, b, s, a, dh, mask, p(lens), p(qkv), p(o), p(lse), None) == 0
+    assert L.k2bw_attention_bwd(BF16, b, s, a, dh, mask, p(lens), p(qkv), p(o), p(lse), p(d_o), p(dqkv), p(delta), None, 0, None, None) == 0
+    torch.cuda.synchronize()
+    assert bool(torch.isfinite(dqkv).all())
+    if one:
+        assert bool(torch.isnan(delta).all())
+    else:
+        want = (d_o.float() * o.float()).reshape(b, s, a, dh).sum(-1).transpose(1, 2)
+        assert float((delta - want).abs().max()) < 1e-4 * math.sqrt(dh)
