@@ -223,3 +223,19 @@ def compare_stage(cfg, gpu, tr: tb.Trace, tol=None, check_dw=True, check_weights
     for s in gpu["snaps"]:
         ck.snapshot(s)
     return ck.finish()
+
+
+# The operand forms (forward, data gradient, weight gradient) that have a tile variant of the bf16 GEMM, and the least K it takes: where
+# either does not hold a forced variant gives way to the built-in choice.  test_kernel_resources.py compares this with the kernels built.
+GEMM_TILE_FORMS = {2: "fdw", 3: "fd", 6: "d", 22: "fdw", 23: "fw", 24: "fw", 25: "fd", 26: "d", 27: "fdw", 32: "fdw", 64: "fdw"}
+GEMM_TILE_K = {22: 64, 23: 32, 24: 32, 25: 64, 26: 64, 27: 64}
+
+
+def gemm_tile_runs(tile, form, K):
+    """Whether a product of this form runs on the forced tile (0: on the library's choice)."""
+    return tile == 0 or (form in GEMM_TILE_FORMS[tile] and K >= GEMM_TILE_K.get(tile, 0))
+
+
+def gemm_tile_cases(tiles, shapes, forms="fdw"):
+    """(tile, M, N, K) for every shape that at least one of the forms runs on that tile."""
+    return [(t, *s) for s in shapes for t in tiles if any(gemm_tile_runs(t, f, s[2]) for f in forms)]

@@ -25,11 +25,12 @@ def test_weight_gradient(M, N, K):
 
 @pytest.mark.parametrize("M,N,K", [(4360, 4096, 64), (4096, 4360, 136)])
 def test_tiles_of_half_the_height_end_a_launch(M, N, K):
-    """18 x 16 and 16 x 18 tiles of 256 x 256: the last rows of tiles run as tiles of 128 rows."""
+    """18 x 16 and 16 x 18 tiles of 256 x 256: the last rows of tiles run as tiles of 128 rows.  (Their partial sums of the fused bias
+    gradient: test_gemm_gelu_gradient_with_fused_bias_gradient.)"""
     every_form(25, M, N, K)
 
 
-@pytest.mark.parametrize("M,N,T,idx_a,idx_b", [(520, 264, 64, [3, 0, 2], [0, 1, 2]), (136, 520, 192, [1, 4], [2, 0])])
+@pytest.mark.parametrize("M,N,T,idx_a,idx_b", [(520, 264, 64, [3, 0, 2], [0, 1, 2]), (136, 520, 192, [1, 4], [2, 0])])   # (pieces of whole K tiles)
 def test_weight_gradient_over_pieces_in_several_buffers(M, N, T, idx_a, idx_b):
     L = B.lib()
     assert L.k2bw_tune_gemm_tile(27) == 0

@@ -14,7 +14,7 @@ from paper_2006_09503_amd import binding as B
 
 from paper_2006_09503_amd.synth import round_to_bf16
 
-from gpu_util import rel, to_host
+from gpu_util import gemm_tile_cases, gemm_tile_runs, rel, to_host
 
 pytestmark = pytest.mark.gpu
 
@@ -76,9 +76,10 @@ def bf16_matrix(rng, rows, cols, ld, scale=1.0):
     return a.astype(np.float64), d
 
 
-@pytest.mark.parametrize("tile", [0, 22, 23, 24, 32, 64])
-@pytest.mark.parametrize("M,N,K", [(8, 8, 8), (40, 72, 40), (264, 136, 72), (136, 264, 104), (96, 520, 200), (328, 272, 1016), (72, 64, 2056)])
+@pytest.mark.parametrize("tile,M,N,K", gemm_tile_cases([0, 2, 22, 23, 24, 32, 64], [(8, 8, 8), (40, 72, 40), (264, 136, 72), (136, 264, 104),
+                                                                                 (96, 520, 200), (328, 272, 1016), (72, 64, 2056)], "fd"))
 def test_bf16_partial_k_tiles(tile, M, N, K):
+    """Forward and data gradient in the forms that have the tile."""
     rng = np.random.default_rng(M + N + K + tile)
     L = B.lib()
     assert L.k2bw_tune_gemm_tile(tile) == 0
@@ -91,6 +92,8 @@ def test_bf16_partial_k_tiles(tile, M, N, K):
         C = torch.empty((M, N), device="cuda", dtype=torch.bfloat16)
         G = torch.empty_like(C)
         for tb, (m, dev, ld) in ((0, (w, W, N + 8)), (1, (wt.T, Wt, K + 8))):
+            if not gemm_tile_runs(tile, "fd"[tb], K):
+                continue
             want = x @ m
             for epi in (0, 1, 2):
                 if tb and epi == 1:
@@ -103,6 +106,8 @@ def test_bf16_partial_k_tiles(tile, M, N, K):
                 assert rel(to_host(C), full) < 3e-3      # one rounding to bf16: 2^-9 / sqrt(3), and the fast GELU
                 if epi == 1:
                     assert rel(to_host(G), ob.gelu(full)) < 3e-3
+        if not gemm_tile_runs(tile, "d", K):
+            return
         # the fused bias gradient: column sums of the unrounded values
         db = torch.full((N,), float("nan"), device="cuda")
         ws = torch.empty(L.k2bw_gemm_dgrad_gelu_bias_workspace(M, N), device="cuda")
@@ -115,9 +120,10 @@ def test_bf16_partial_k_tiles(tile, M, N, K):
         assert L.k2bw_tune_gemm_tile(0) == 0
 
 
-@pytest.mark.parametrize("tile", [0, 22, 23, 24, 32, 64])
-@pytest.mark.parametrize("M,N,K", [(72, 40, 1), (136, 264, 33), (264, 136, 65), (256, 520, 127), (520, 264, 1000), (64, 64, 4099)])
+@pytest.mark.parametrize("tile,M,N,K", gemm_tile_cases([0, 2, 22, 23, 24, 32, 64], [(72, 40, 1), (136, 264, 33), (264, 136, 65), (256, 520, 127),
+                                                                                 (520, 264, 1000), (64, 64, 4099)], "w"))
 def test_bf16_weight_gradient_of_any_number_of_tokens(tile, M, N, K):
+    assert gemm_tile_runs(tile, "w", K)
     rng = np.random.default_rng(M + N + K + tile)
     L = B.lib()
     assert L.k2bw_tune_gemm_tile(tile) == 0

@@ -12,7 +12,7 @@ from oracle import twobw as tb
 from paper_2006_09503_amd import binding as B
 from paper_2006_09503_amd.synth import round_to_bf16
 
-from gpu_util import rel, to_dev, to_host
+from gpu_util import gemm_tile_cases, gemm_tile_runs, rel, to_dev, to_host
 
 pytestmark = pytest.mark.gpu
 
@@ -97,8 +97,8 @@ def test_gemm_data_gradient_form(dtype, M, N, K, epi):
 @pytest.mark.parametrize("dtype", [F32, BF16])
 @pytest.mark.parametrize("M,N,K", GEMM_SHAPES)
 def test_gemm_data_gradient_through_gelu_on_a_transposed_weight_copy(dtype, M, N, K):
-    """(dY[M,K'] Wt[K',N]) * GELU'(u): the form the bf16 stage issues, reading its transposed copy of the weights
-    (the forward's operand form with the data-gradient epilogue)."""
+    """(dY[M,K'] Wt[K',N]) * GELU'(u): the forward's operand form with the data-gradient epilogue, for callers that keep the weights
+    transposed (the stage reads them as they are stored)."""
     rng = np.random.default_rng(11 * M + N + K)
     dy, wt = rnd(rng, (M, K), dtype), rnd(rng, (K, N), dtype, 0.1)
     u = rnd(rng, (M, N), dtype)
@@ -132,11 +132,11 @@ def test_gemm_weight_gradient_form_coalesces_in_place(dtype, M, N, K):
     assert rel(to_host(G), g1 + x2.astype(np.float64).T @ d2.astype(np.float64)) < 2e-6
 
 
-@pytest.mark.parametrize("tile", [2, 3, 6, 22, 23])
-@pytest.mark.parametrize("M,N,K", [(296, 264, 200), (328, 272, 192), (136, 520, 64), (264, 136, 96), (136, 264, 32)])
+@pytest.mark.parametrize("tile,M,N,K", gemm_tile_cases([2, 3, 6, 22, 23], [(296, 264, 200), (328, 272, 192), (136, 520, 64), (264, 136, 96),
+                                                                           (136, 264, 32)]))
 def test_gemm_every_tile_variant(tile, M, N, K):
-    """Each tile shape / staging variant of the bf16 kernel, forced, on ragged shapes in all three forms:
-    K = 200 is not a multiple of the K step (the direct-to-LDS variants fall back), K = 192 is three K
+    """Each tile shape / staging variant of the bf16 kernel, forced, on ragged shapes in the forms that have it:
+    K = 200 is not a multiple of the K step (a partial K tile), K = 192 is three K
     steps (uneven halves for the variant with two K groups), K = 64 leaves its second group empty;
     K = 96 and 32 are three tiles and one tile of the four-stage ring (fewer than it prefetches)."""
     rng = np.random.default_rng(tile * 1000 + M + N + K)
@@ -145,31 +145,33 @@ def test_gemm_every_tile_variant(tile, M, N, K):
     try:
         x, w, b = rnd(rng, (M, K), BF16), rnd(rng, (K, N), BF16, 0.1), rnd(rng, (N,), BF16)
         X, W, Bv = dev(x, BF16), dev(w, BF16), dev(b, BF16)
-        U, Gl = empty((M, N), BF16), empty((M, N), BF16)
-        assert L.k2bw_gemm(BF16, 0, 0, 1, M, N, K, X.data_ptr(), K, W.data_ptr(), N, U.data_ptr(), N, Bv.data_ptr(),
-                           None, Gl.data_ptr(), 0, None) == 0
-        sync()
-        want_u = x.astype(np.float64) @ w.astype(np.float64) + b
-        assert rel(to_host(U), want_u) < TIGHT[BF16]
-        assert rel(to_host(Gl), ob.gelu(want_u)) < TIGHT[BF16]
+        if gemm_tile_runs(tile, "f", K):
+            U, Gl = empty((M, N), BF16), empty((M, N), BF16)
+            assert L.k2bw_gemm(BF16, 0, 0, 1, M, N, K, X.data_ptr(), K, W.data_ptr(), N, U.data_ptr(), N, Bv.data_ptr(),
+                               None, Gl.data_ptr(), 0, None) == 0
+            sync()
+            want_u = x.astype(np.float64) @ w.astype(np.float64) + b
+            assert rel(to_host(U), want_u) < TIGHT[BF16]
+            assert rel(to_host(Gl), ob.gelu(want_u)) < TIGHT[BF16]
 
-        wt = rnd(rng, (N, K), BF16, 0.1)
-        Wt, Cc = dev(wt, BF16), empty((M, N), BF16)
-        u_host = to_host(U)
-        assert L.k2bw_gemm(BF16, 0, 1, 2, M, N, K, X.data_ptr(), K, Wt.data_ptr(), K, Cc.data_ptr(), N, None,
-                           U.data_ptr(), None, 0, None) == 0
-        sync()
-        want = (x.astype(np.float64) @ wt.astype(np.float64).T) * ob.gelu_grad(u_host.astype(np.float64))
-        assert rel(to_host(Cc), want) < TIGHT[BF16]
+        if gemm_tile_runs(tile, "d", K):
+            wt, u = rnd(rng, (N, K), BF16, 0.1), rnd(rng, (M, N), BF16)
+            Wt, Uv, Cc = dev(wt, BF16), dev(u, BF16), empty((M, N), BF16)
+            assert L.k2bw_gemm(BF16, 0, 1, 2, M, N, K, X.data_ptr(), K, Wt.data_ptr(), K, Cc.data_ptr(), N, None,
+                               Uv.data_ptr(), None, 0, None) == 0
+            sync()
+            want = (x.astype(np.float64) @ wt.astype(np.float64).T) * ob.gelu_grad(u.astype(np.float64))
+            assert rel(to_host(Cc), want) < TIGHT[BF16]
 
-        xt, dy = rnd(rng, (K, M), BF16), rnd(rng, (K, N), BF16)
-        G = torch.full((M, N), float("nan"), device="cuda", dtype=torch.float32)
-        Xt, DY = dev(xt, BF16), dev(dy, BF16)
-        for acc in (0, 1):
-            assert L.k2bw_gemm(BF16, 1, 0, 3, M, N, K, Xt.data_ptr(), M, DY.data_ptr(), N, G.data_ptr(), N, None,
-                               None, None, acc, None) == 0
-        sync()
-        assert rel(to_host(G), 2.0 * (xt.astype(np.float64).T @ dy.astype(np.float64))) < 2e-6
+        if gemm_tile_runs(tile, "w", K):
+            xt, dy = rnd(rng, (K, M), BF16), rnd(rng, (K, N), BF16)
+            G = torch.full((M, N), float("nan"), device="cuda", dtype=torch.float32)
+            Xt, DY = dev(xt, BF16), dev(dy, BF16)
+            for acc in (0, 1):
+                assert L.k2bw_gemm(BF16, 1, 0, 3, M, N, K, Xt.data_ptr(), M, DY.data_ptr(), N, G.data_ptr(), N, None,
+                                   None, None, acc, None) == 0
+            sync()
+            assert rel(to_host(G), 2.0 * (xt.astype(np.float64).T @ dy.astype(np.float64))) < 2e-6
     finally:
         assert L.k2bw_tune_gemm_tile(0) == 0
 
@@ -178,8 +180,8 @@ def test_gemm_every_tile_variant(tile, M, N, K):
 def test_gemm_balanced_tail_of_a_256_tile_launch(M, N, K):
     """A launch whose last round of 256x256 tiles would leave most CUs idle gives the rows of those tiles to
     half-height tiles: 4360 x 4096 is 18 x 16 = 288 tiles (the last two tile rows, 264 rows, are split off and
-    halved: 128 + 128 + 8 rows); 4096 x 4360 is 16 x 18 (the last tile row halved).  All three forms, the
-    two-output epilogue and in-place accumulation."""
+    halved: 128 + 128 + 8 rows); 4096 x 4360 is 16 x 18 (the last tile row halved).  Forward with the two-output
+    epilogue and weight gradient with in-place accumulation, the forms that have these tiles."""
     test_gemm_every_tile_variant(23, M, N, K)
 
 
@@ -228,11 +230,14 @@ def test_gemm_random_shapes_with_the_built_in_tile_choice(M, N, K):
     assert rel(to_host(G), 2.0 * (xt.astype(np.float64).T @ dy.astype(np.float64))) < 2e-6
 
 
-@pytest.mark.parametrize("M,N,K", [(296, 264, 200), (4096, 1032, 136), (520, 4096, 64), (4360, 4096, 64)])
-def test_gemm_gelu_gradient_with_fused_bias_gradient(M, N, K):
+@pytest.mark.parametrize("tile,M,N,K", [(0, 296, 264, 200), (0, 4096, 1032, 136), (0, 520, 4096, 64), (0, 4360, 4096, 64),
+                                        (25, 4360, 4096, 64), (25, 4096, 4360, 72)])
+def test_gemm_gelu_gradient_with_fused_bias_gradient(tile, M, N, K):
     """du = (dy W^T) * GELU'(u) and db = colsum(du) from the same pass (bf16), overwrite then accumulate.
-    The last shape is 288 tiles of 256x256: its last two tile rows (264 rows) run as five rows of
-    half-height tiles, split off as a problem of their own with its own partial-sum rows."""
+    The last two shapes are 18 x 16 and 16 x 18 tiles of 256x256, forced: their last two tile rows (264 rows), or
+    the last one, run as five or two rows of half-height tiles, split off as a problem of their own with its own
+    partial-sum rows."""
+    assert gemm_tile_runs(tile, "d", K)
     rng = np.random.default_rng(M + N + K)
     dy, w, u = rnd(rng, (M, K), BF16), rnd(rng, (N, K), BF16, 0.1), rnd(rng, (M, N), BF16)
     want = (dy.astype(np.float64) @ w.astype(np.float64).T) * ob.gelu_grad(u.astype(np.float64))
@@ -240,11 +245,15 @@ def test_gemm_gelu_gradient_with_fused_bias_gradient(M, N, K):
     DY, W, U = dev(dy, BF16), dev(w, BF16), dev(u, BF16)
     DU = empty((M, N), BF16)
     db = torch.full((N,), float("nan"), device="cuda")
-    ws = torch.empty(L.k2bw_gemm_dgrad_gelu_bias_workspace(M, N), device="cuda")
-    for acc in (0, 1):
-        assert L.k2bw_gemm_dgrad_gelu_bias(M, N, K, DY.data_ptr(), K, W.data_ptr(), K, DU.data_ptr(), N, U.data_ptr(),
-                                           db.data_ptr(), acc, ws.data_ptr(), None) == 0
-    sync()
+    ws = torch.full((L.k2bw_gemm_dgrad_gelu_bias_workspace(M, N),), float("nan"), device="cuda")
+    assert L.k2bw_tune_gemm_tile(tile) == 0
+    try:
+        for acc in (0, 1):
+            assert L.k2bw_gemm_dgrad_gelu_bias(M, N, K, DY.data_ptr(), K, W.data_ptr(), K, DU.data_ptr(), N, U.data_ptr(),
+                                               db.data_ptr(), acc, ws.data_ptr(), None) == 0
+        sync()
+    finally:
+        assert L.k2bw_tune_gemm_tile(0) == 0
     assert rel(to_host(DU), want) < TIGHT[BF16]
     scale = np.sqrt((want ** 2).sum(0)).max()
     assert np.abs(to_host(db) - 2.0 * want.sum(0)).max() < 1e-5 * scale * np.sqrt(M)

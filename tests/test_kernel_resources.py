@@ -10,6 +10,8 @@ import tempfile
 
 from paper_2006_09503_amd import build as B
 
+from gpu_util import GEMM_TILE_FORMS
+
 
 def test_ring_gemm_kernels_use_no_scratch_and_fit_two_waves_per_simd():
     src = os.path.join(B.CSRC, "gemm_bf16.hip")
@@ -76,6 +78,21 @@ def test_fixed_head_attention_kernels_do_not_spill():
     allowed = {"attn_dq_mfma_kernel<128, 4, 2": 2, "attn_bwd_mfma_kernel<128, 4, 2": 4}
     for name, field in found:
         assert field("vgpr_spill_count") <= sum(n for kernel, n in allowed.items() if kernel in name), name
+
+
+def test_every_operand_form_has_the_tile_variants_that_the_tests_force():
+    """A forced variant that a form has not gives way to the built-in choice without a word: what the tests take for granted is what is
+    built."""
+    shapes = {"gemm_bf16_kernel<128, 128, 64, 64, 64, {}, 1>": 2, "gemm_bf16_kernel<256, 256, 128, 64, 64, {}, 1>": 3,
+              "gemm_bf16_kernel<128, 128, 64, 64, 64, {}, 2>": 6, "gemm_bf16_ring_kernel<128, 128, 32, 64, 64, 4, {}>": 22,
+              "gemm_bf16_ring_kernel<256, 256, 128, 64, 32, 4, {}>": 23, "gemm_bf16_ring_kernel<192, 256, 96, 64, 32, 4, {}>": 24,
+              "gemm_bf16_phased_kernel<256, 256, 128, 64, {}>": 25, "gemm_bf16_phased_kernel<192, 256, 96, 64, {}>": 26,
+              "gemm_bf16_phased_kernel<128, 256, 64, 64, {}>": 27, "gemm_bf16_split_kernel<1, 1, 8, {}>": 32,
+              "gemm_bf16_split_kernel<2, 2, 4, {}>": 64}
+    forms = {"f": [("false, false, %d" % e) for e in (0, 1, 2)], "d": [("false, true, %d" % e) for e in (0, 2)], "w": ["true, false, 3"]}
+    expected = {pattern.format(args) for pattern, tile in shapes.items() for form in GEMM_TILE_FORMS[tile] for args in forms[form]}
+    built = {re.search(r"gemm_bf16\w*<[^>]*>", name).group(0) for name, _ in built_kernels(r"gemm_bf16\w*<")}
+    assert built == expected, built ^ expected
 
 
 def test_fp32_attention_kernels_do_not_spill():
