@@ -1588,9 +1588,11 @@ struct TileCost { int id, bm, bn, whole; double fixed, round, round_k, tile_k, t
 // sizes (48 to 16384 rows and columns, K of 96 to 16384), and those of the shapes that meet at short K again to 4600, of which a third
 // with K of 40 to 700 and wide outputs.  Time of the choice over the best shape of each of the 4600, geometric mean: forward 1.0025, both
 // operands along K 1.003 (with the GELU' epilogue 1.004), weight gradient 1.001.  Over the lines in use before the phased kernels, whose
-// shapes were 23, 24 and the staged ones: 0.978, 0.970 (0.962) and 0.982; of 3309 other sizes of more than 6 us 97
-// above 1.03, at worst 1.11, 1.10 (1.10) and 1.12.  (Without shape 2 in the first two forms and 23 in the first, and with one table for
-// both epilogues, 171, at worst 1.41; K below 64 up to 1.58: 1302 x 4736, K = 56, 11.9 -> 18.3.)
+// shapes were 23, 24 and the staged ones: 0.978, 0.971 (0.962) and 0.982.  Of 3253 other sizes of more than 6 us, half of them with K of
+// 40 to 700, 106 take more than 1.03 of their time then, at worst 1.16, 1.19 (1.11) and 1.17: data gradients of wide outputs whose K is
+// short and no multiple of 64 (3232 x 7248, K = 136: 24.2 -> 28.9 us), weight gradients of some wide outputs and short K (14464 x 896,
+// K = 256: 24.9 -> 27.1).  (Without shape 2 in the first two forms and 23 in the first, and with one table for both epilogues: 225, at
+// worst 1.39, 1.30 (1.50) and 1.12; K below 64 up to 1.58: 1302 x 4736, K = 56, 11.9 -> 18.3.)
 // What a form does without: the ring's 256x256 tiles are 4 to 17 % behind the phased ones from K = 512 on except in the weight
 // gradient (phased over ring 1.02 below K = 512, then 1.00, 0.97 from 2048: not worth a second instance), and ahead by up to 15 %
 // below, where K is not a multiple of 64; in the data gradient that is the choice for too few sizes (4 of 758) and worth no instance.
@@ -1606,11 +1608,11 @@ constexpr TileCost kDataTiles[] = {   // both operands along K
     {22, 128, 128, 64, 1.4, 3.0, 4.5, 2.55, 0.5, 4.1},         {25, 256, 256, 64, 0.06, 7.62, 12.1, 10.3, 2.66, 0},
     {26, 192, 256, 64, 1.77, 3.79, 9.46, 7.26, 3.74, 0.41},    {27, 128, 256, 64, 1.1, 4.6, 7.2, 5.8, 1.7, 0},
     {64, 64, 64, 0, 1.65, 2.2, 2.5, 2.4, 0, 0},                {32, 32, 32, 0, 1.55, 1.55, 0.83, 1.1, 0, 0},
-    {3, 256, 256, 0, 2.85, 4.55, 19.84, 8.1, 2.49, 2.44},      {6, 128, 128, 0, 4.2, 5.44, 4.5, 1.85, 1.61, 1.26},
+    {3, 256, 256, 0, 2.85, 4.55, 19.84, 8.1, 2.49, 2.44},      {6, 128, 128, 0, 1.8, 3.3, 6.7, 1.9, 1.3, 1.5},
     {2, 128, 128, 0, 4.12, 0.49, 9.23, 6.12, 1.61, 1.07}};
 constexpr TileCost kDataGeluTiles[] = {   // the same with the GELU' epilogue, which reads a matrix more; two workgroups per CU hide that
     {22, 128, 128, 64, 0.94, 4.2, 4.39, 2.22, 0.21, 4.1},      {25, 256, 256, 64, 0, 10.72, 12.59, 9.09, 2.43, 0.56},
-    {26, 192, 256, 64, 1.38, 5.15, 10.2, 6.52, 4.54, 0.46},    {27, 128, 256, 64, 1.25, 4.67, 7.39, 4.03, 3.52, 0},
+    {26, 192, 256, 64, 1.38, 5.15, 10.2, 6.52, 4.54, 0.46},    {27, 128, 256, 64, 1.25, 4.67, 7.39, 5.4, 2.8, 0},
     {64, 64, 64, 0, 1.65, 2.2, 2.5, 2.4, 0, 0},                {32, 32, 32, 0, 1.55, 1.55, 0.83, 1.1, 0, 0},
     {3, 256, 256, 0, 2.24, 5.84, 21.48, 11.77, 3.24, 4.54},    {6, 128, 128, 0, 2.52, 4.83, 6.65, 1.4, 1.41, 0.72},
     {2, 128, 128, 0, 4.45, 0.63, 7.78, 5.33, 1.7, 0.18}};
