@@ -40,38 +40,38 @@ TRAFFIC_BYTES_PER_LAUNCH = {
     "C5": {
         # weight-gradient GEMM launches: the 8 products of the stage's 2 layers over 8 microbatches' tokens each
         # (reduction length 16384) go out in 6 launches of 16 rounds of tiles (FC2; FC1; out-projection + QKV, per
-        # layer); average per launch: L2-miss read traffic 1.99e10 (the operand panels of products this size pass
+        # layer); average per launch: L2-miss read traffic 2.04e10 (the operand panels of products this size pass
         # through the 4 MB L2 of every XCD once per block of 32 tiles; the counter sees what misses L2, whether HBM or
-        # the memory-side cache serves it; 1.65e10 to 1.99e10 from run to run) + 1.07e9 written.  Algorithmic minimum
+        # the memory-side cache serves it; 1.65e10 to 2.04e10 from run to run) + 1.07e9 written.  Algorithmic minimum
         # 3.58e9: operands once + fp32 accumulator read-modify-write.  (4 microbatches and all 8 products in one launch
         # of 96 rounds: 8.75e10 .. 9.93e10 per 4 microbatches instead of 5.3e10, see the stage's flush of pending products.)
-        "gemm_bf16_ring_kernel<256, 256, 128, 64, 32, 4, true, false, 3>": 2.0944e+10,
+        "gemm_bf16_ring_kernel<256, 256, 128, 64, 32, 4, true, false, 3>": 2.1485e+10,
         # forward projections, and the data gradients on the weights as stored: averages over the three shapes each
         # plain instance serves
-        "gemm_bf16_phased_kernel<256, 256, 128, 64, false, false, 0>": 1.3419e+09,
-        "gemm_bf16_phased_kernel<256, 256, 128, 64, false, true, 0>": 1.1891e+09,
-        "gemm_bf16_phased_kernel<256, 256, 128, 64, false, false, 1>": 2.1373e+09,
-        "gemm_bf16_phased_kernel<256, 256, 128, 64, false, true, 2>": 2.0470e+09,
+        "gemm_bf16_phased_kernel<256, 256, 128, 64, false, false, 0>": 1.3301e+09,
+        "gemm_bf16_phased_kernel<256, 256, 128, 64, false, true, 0>": 1.1898e+09,
+        "gemm_bf16_phased_kernel<256, 256, 128, 64, false, false, 1>": 2.1344e+09,
+        "gemm_bf16_phased_kernel<256, 256, 128, 64, false, true, 2>": 2.0482e+09,
     },
     "C4": {
         # (activation recomputation: the forward GEMMs run twice per microbatch; 4 layers x 4 products over 4 passes,
         # reduction length 16384, in 6 weight-gradient launches of 8 rounds)
-        "gemm_bf16_ring_kernel<256, 256, 128, 64, 32, 4, true, false, 3>": 8.3963e+09,
-        "gemm_bf16_phased_kernel<256, 256, 128, 64, false, false, 0>": 6.6635e+08,
-        "gemm_bf16_phased_kernel<256, 256, 128, 64, false, true, 0>": 5.8163e+08,
-        "gemm_bf16_phased_kernel<256, 256, 128, 64, false, false, 1>": 1.0811e+09,
-        "gemm_bf16_phased_kernel<256, 256, 128, 64, false, true, 2>": 1.0822e+09,
+        "gemm_bf16_ring_kernel<256, 256, 128, 64, 32, 4, true, false, 3>": 8.3900e+09,
+        "gemm_bf16_phased_kernel<256, 256, 128, 64, false, false, 0>": 6.6729e+08,
+        "gemm_bf16_phased_kernel<256, 256, 128, 64, false, true, 0>": 5.8525e+08,
+        "gemm_bf16_phased_kernel<256, 256, 128, 64, false, false, 1>": 1.0813e+09,
+        "gemm_bf16_phased_kernel<256, 256, 128, 64, false, true, 2>": 1.0821e+09,
     },
     "C2": {
         # grouped weight-gradient GEMM (the 24 products of the stage's 6 layers over 4 microbatches' tokens each,
         # reduction length 16384): FETCH_SIZE x 1.997 (copy-kernel factor) + WRITE_SIZE x 1.000; algorithmic minimum
         # 3.825e9 (operands once + fp32 accumulator read-modify-write)
-        "gemm_bf16_ring_kernel<256, 256, 128, 64, 32, 4, true, false, 3>": 4.3737e+09,
+        "gemm_bf16_ring_kernel<256, 256, 128, 64, 32, 4, true, false, 3>": 4.3756e+09,
         # the other GEMM instances (averages over the shapes each serves)
         "gemm_bf16_phased_kernel<256, 256, 128, 64, false, true, 2>": 1.2830e+08,
-        "gemm_bf16_phased_kernel<256, 256, 128, 64, false, false, 1>": 1.2617e+08,
+        "gemm_bf16_phased_kernel<256, 256, 128, 64, false, false, 1>": 1.2615e+08,
         "gemm_bf16_ring_kernel<128, 128, 32, 64, 64, 4, false, false, 0>": 8.6550e+07,
-        "gemm_bf16_ring_kernel<128, 128, 32, 64, 64, 4, false, true, 0>": 8.0663e+07,
+        "gemm_bf16_ring_kernel<128, 128, 32, 64, 64, 4, false, true, 0>": 8.0662e+07,
         "gemm_bf16_phased_kernel<256, 256, 128, 64, false, false, 0>": 7.3580e+07,
     },
 }

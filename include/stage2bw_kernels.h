@@ -32,7 +32,7 @@ extern "C" {
  *          1: u = acc + bias[n]; C = u; aux_out = GELU(u)  (FC1)
  *          2: C = acc * GELU'(aux[m,n])                     (data gradient through GELU)
  *          3: C fp32: C = (accumulate ? C : 0) + acc        (weight gradient, coalesced in place)
- * bf16 supports the pairs the stage issues: (trans_a,trans_b,epilogue) in
+ * bf16 supports the pairs the stage issues, and the data gradient on weights kept transposed: (trans_a,trans_b,epilogue) in
  * {(0,0,0),(0,0,1),(0,0,2),(0,1,0),(0,1,2),(1,0,3)}; fp32 supports all.  bf16: A and B each smaller than
  * 2 GiB (rows * ld * 2 bytes), INVALID_ARG otherwise.
  */

@@ -7,7 +7,7 @@
 // its four waves take every fourth tile of 32 rows of the streamed side; their partial results meet in LDS once, at
 // the end, in a fixed order.  Inside the loop nothing is shared and there is no barrier: a wave fetches its tiles into LDS of
 // its own (WaveTile), the next one under the last product of the current one.
-// Measured at b=2 s=512 a=8 dh=64, causal: forward 17 us, backward 42 (55 while every fragment came from L2 by itself and dQ
+// Measured at b=2 s=512 a=8 dh=64, causal: forward 17 us, backward 41 (55 while every fragment came from L2 by itself and dQ
 // and dK/dV were launches of their own; 520 and 1146 with one thread per row on the vector ALU); the matrix instructions alone
 // are 7 and 14 us of the longest workgroups.
 //
@@ -667,11 +667,12 @@ struct Bwd {
 }  // namespace
 
 namespace {
-// One wave per workgroup, or four that split the t tiles of 32 rows to stream?  Forward: a CU holds one workgroup of four waves or four
-// of one; with an overhead of about 1.2 tiles, `blocks` blocks take ceil(blocks / CUs) rounds of ceil(t / 4) + 1.2 tiles, or
-// ceil(blocks / 4 CUs) rounds of t + 1.2, each of those 1.2 times as long as it would be alone; 1.35 times more under a causal mask
-// in a launch of one round, which ends on its longest blocks; 1.4 times more for heads up to 32, of whose four-wave workgroups a CU
-// holds two.  Over 500 random sizes the choice costs 0.5 % over the better one.
+// One wave per workgroup, or four that split the t tiles of 32 rows to stream?  Forward, an empirical rule: four waves cost a round of
+// ceil(t / 4) + 1.2 tiles per block on each CU, one wave a round of t + 1.2 per four blocks, times 1.2; 1.35 times more under a causal
+// mask in a launch of up to four blocks per CU, which ends on its longest blocks; 1.4 times more for heads up to 32.  (It counts one or
+// four workgroups on a CU at every head size; up to 64 a CU holds two or eight.)  Over 2700 random sizes the choice costs 0.7 % (heads up
+// to 32) and 0.3 % (above) over the better one.  Over the time before the tiles went through LDS: heads up to 32 0.90, 64 0.92, 96 0.98,
+// 128 0.96, at worst 1.07 to 1.09 (b=3 s=685 a=12 dh=80 92 -> 97 us: one wave, four workgroups on every CU).
 bool fwd_one_wave(const AttnDesc& d) {
   const int64_t tiles = ceil_div(d.s, kRows), blocks = (int64_t)d.b * d.a * tiles, cus = gemm_compute_units();
   double one = 1.2 * ceil_div(blocks, 4 * cus) * (tiles + 1.2);

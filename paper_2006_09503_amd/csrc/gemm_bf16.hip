@@ -3,12 +3,14 @@
 // One workgroup computes a BM x BN tile of C.  The kernel families share the tile order, the
 // fragment layout and the epilogue:
 //
-//   * the ring kernel (gemm_bf16_ring_kernel, further down): operand tiles go from HBM straight
-//     into LDS (global_load_lds) through a ring of four stages, K-strided operands stay in their
-//     HBM form and are transposed by the LDS read.  It serves every launch with enough tiles and at least one whole
-//     K tile; launches with few tiles run on the same scheme with tiles of 64 or 32 and the reduction range split over
-//     the waves (gemm_bf16_split_kernel);
-//   * the register-staged kernel (gemm_bf16_kernel): K steps of 64 through two LDS stages, any K, two workgroups per CU.
+//   * the direct-to-LDS kernels (further down): operand tiles go from HBM straight into LDS (global_load_lds), K-strided
+//     operands stay in their HBM form and are transposed by the LDS read.  The phased kernel (gemm_bf16_phased_kernel: K tiles
+//     of 64 in two stages, two groups of waves in turns) has the large tiles of the forward and data-gradient forms, the ring
+//     kernel (gemm_bf16_ring_kernel: a ring of four stages) those of the weight gradient, of short reductions, and the 128x128
+//     ones; launches with few tiles run with tiles of 64 or 32 and the reduction range split over the waves
+//     (gemm_bf16_split_kernel).  All but the last take at least one whole K tile;
+//   * the register-staged kernel (gemm_bf16_kernel): K steps of 64 through two LDS stages, any K, two workgroups of 128x128
+//     tiles per CU: short reductions.
 //     Both operand tiles are staged in one common form -- [row][64 k] bf16, 128-byte rows, 16-byte
 //     chunks XOR-swizzled by row -- whatever the operand's layout in HBM:
 //       - K contiguous in HBM (activations as A, W read for the data gradient): 16-byte global
@@ -51,10 +53,10 @@ struct BfParams {
   float* colsum;   // GELU' epilogue: partial[ceil(M/32)][N] column sums of the result, or null
   int accumulate;
   int tiles_m, tiles_n;
-  int tile_m;      // rows of C per tile: the kernel's BM, or BM/2 in the balanced tail of a ring launch
-  const void* prefetch;        // lines to touch for a later launch, or null (ring kernels)
+  int tile_m;      // rows of C per tile: the kernel's BM, or BM/2 in the balanced tail of a launch (launch_tiles)
+  const void* prefetch;        // lines to touch for a later launch, or null (ring and phased kernels)
   uint32_t prefetch_bytes;     // multiple of 4, below 2^31
-  // segmented reduction range (ring kernels): K tiles per piece (the launcher fills it in; K / tile for
+  // segmented reduction range (ring and phased kernels): K tiles per piece (the launcher fills it in; K / tile for
   // a plain problem), the buffer index of every piece in 4-bit fields (piece 0 lowest) and the
   // distance between consecutive buffer indices in units of 256 bytes
   int seg_tiles;
@@ -1791,14 +1793,14 @@ hipError_t gemm_bf16_grouped(const GemmDesc* d, int count, hipStream_t stream) {
   if (!f.trans_a && !f.trans_b) {
     if (f.epilogue == kEpiStore) return pick_tile<false, false, kEpiStore>(gp, stream);
     if (f.epilogue == kEpiGelu) return pick_tile<false, false, kEpiGelu>(gp, stream);
-    if (f.epilogue == kEpiGeluGrad) return pick_tile<false, false, kEpiGeluGrad>(gp, stream);
+    if (f.epilogue == kEpiGeluGrad) return pick_tile<false, false, kEpiGeluGrad>(gp, stream);   // (for callers of the C ABI; the stage reads W as stored)
   } else if (!f.trans_a && f.trans_b) {
     if (f.epilogue == kEpiStore) return pick_tile<false, true, kEpiStore>(gp, stream);
     if (f.epilogue == kEpiGeluGrad) return pick_tile<false, true, kEpiGeluGrad>(gp, stream);
   } else if (f.trans_a && !f.trans_b) {
     if (f.epilogue == kEpiAccum) return pick_tile<true, false, kEpiAccum>(gp, stream);
   }
-  return hipErrorInvalidValue;  // form/epilogue pair the stage never issues
+  return hipErrorInvalidValue;  // a form/epilogue pair without instances
 }
 
 hipError_t gemm_bf16(const GemmDesc& d, hipStream_t stream) { return gemm_bf16_grouped(&d, 1, stream); }

@@ -148,7 +148,8 @@ def test_what_nobody_sees_does_not_show_in_any_launch_shape(shape, rows, pos, dh
 @pytest.mark.parametrize("b,s,a,mask", [(40, 31, 8, 1), (33, 1, 8, 2), (40, 32, 8, 0), (40, 29, 7, 2), (40, 33, 8, 1),
                                         (30, 100, 8, 2), (30, 97, 8, 1), (20, 70, 8, 1), (8, 40, 8, 2)])
 def test_fp32_launches_of_many_blocks_on_one_wave(dh, b, s, a, mask):
-    """Enough blocks of 32 rows for every SIMD, one to four tiles each (the last two: too few, four waves)."""
+    """Enough blocks of 32 rows for every SIMD, one to four tiles each (too few, four waves: the last, and the two before it in the
+    backward pass of heads up to 64)."""
     h = a * dh
     qkv, d_o, lens = inputs(F32, b, s, a, dh, mask)
     o, lse, dqkv = run(F32, b, s, a, dh, mask, qkv, d_o, lens)
