@@ -866,6 +866,21 @@ __device__ __forceinline__ bf16x8 read_frag(const uint4* tile, int row0, int ks,
   }
 }
 
+// Lines of the operand a later launch will read (GemmDesc::prefetch): every wave of the launch touches 64 of them, 128 bytes apart,
+// with one 4-byte load each.  The words go to LDS, to 256 bytes per wave at `lds_free`, and not to a register: the compiler takes an
+// asm block's output as written when the block ends and may move or re-use that register while the load is still in flight.  The
+// caller names a place that nothing is loaded into, or read from, before the first wait that covers the touch and a barrier behind it.
+__device__ __forceinline__ void touch_ahead(const BfParams& p, int wave, int waves, int lane, uint32_t lds_free) {
+  if (p.prefetch == nullptr) return;   // uniform
+  const uint32_t line = ((uint32_t)blockIdx.x * (uint32_t)waves + (uint32_t)wave) * 64u + (uint32_t)lane;
+  const uint32_t off = min(line * 128u, p.prefetch_bytes - 4u);
+  const uint32_t dst = __builtin_amdgcn_readfirstlane(lds_free + (uint32_t)wave * 256u);
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2"
+               :
+               : "s"(dst), "v"(off), "s"(uniform_address(p.prefetch))
+               : "memory");
+}
+
 // s_waitcnt immediate for "at most n vector-memory operations outstanding" (gfx9 encoding:
 // vmcnt = bits 3:0 and 15:14; expcnt and lgkmcnt fields left at their maxima = no wait)
 constexpr int vmcnt_imm(int n) { return (n & 15) | ((n >> 4) << 14) | (7 << 4) | (15 << 8); }
@@ -941,18 +956,10 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void gemm_bf16_ring_ker
     if (v < IPA) ld_a.issue_one_untracked(v, walk.a_addr, stage_bytes);
     else ld_b.issue_one_untracked(v - IPA, walk.b_addr, stage_bytes + (uint32_t)(BM * CHK) * 16u);
   };
-  // Lines of the operand a later launch will read (GemmDesc::prefetch): every wave of the launch
-  // touches 64 of them, 128 bytes apart, with one 4-byte load in front of its own first loads.  The
-  // load is older than every tile load, so the waits below (which count the newest operations that
-  // may still be outstanding) stay sufficient whenever it returns.  The compiler does not know that the
-  // value arrives late: its destination register is kept out of other use up to the first wait below,
-  // after which the load has returned (vector-memory loads return in order) and the register is free.
-  uint32_t touched = 0;
-  if (p.prefetch != nullptr) {
-    const uint32_t line = ((uint32_t)blockIdx.x * NW + (uint32_t)wave) * 64u + (uint32_t)lane;
-    const uint32_t off = min(line * 128u, p.prefetch_bytes - 4u);
-    asm volatile("global_load_dword %0, %1, %2" : "=v"(touched) : "v"(off), "s"(uniform_address(p.prefetch)) : "memory");
-  }
+  // In front of a wave's own first loads.  The touch lands in the last stage, which is first loaded into after the barrier below, and
+  // being older than every tile load it has returned by the wait in front of that barrier.
+  static_assert(NW * 256 <= kStage * 16, "the touches of all waves fit in a stage");
+  touch_ahead(p, wave, NW, lane, lds_base + (uint32_t)((NS - 1) * kStage) * 16u);
 #pragma unroll
   for (int t = 0; t < NS - 1; ++t) {
     if (t == 0 && rem > 0) {   // uniform
@@ -971,7 +978,6 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void gemm_bf16_ring_ker
   }
   if (extra) __builtin_amdgcn_s_waitcnt(vmcnt_imm((NS - 2) * NV));
   else __builtin_amdgcn_s_waitcnt(vmcnt_imm((NS - 2) * (NV - 1)));
-  asm volatile("" : "+v"(touched));   // the touch has landed: last use of its register
   __syncthreads();
   if (rem > 0) {
     decltype(ld_a)::zero_past_end(smem, rem, tid, NW * 64);
@@ -1129,12 +1135,9 @@ __device__ __forceinline__ void phased_tile(const BfParams& p, const BfParams& p
 #pragma unroll
     for (int v = 0; v < IP1; ++v) ld_a1.issue_one_untracked(v, walk.a_addr, lds_a + (uint32_t)(st * kA + kA0) * 16u);
   };
-  uint32_t touched = 0;   // as in the ring kernel
-  if (p.prefetch != nullptr) {
-    const uint32_t line = ((uint32_t)blockIdx.x * NW + (uint32_t)wave) * 64u + (uint32_t)lane;
-    const uint32_t off = min(line * 128u, p.prefetch_bytes - 4u);
-    asm volatile("global_load_dword %0, %1, %2" : "=v"(touched) : "v"(off), "s"(uniform_address(p.prefetch)) : "memory");
-  }
+  // as in the ring kernel; what step 0 loads first, the second part of A in stage 1, is the free place here
+  static_assert(R1 > 0 && NW * 256 <= R1 * CHK * 16, "the touches of all waves fit there");
+  touch_ahead(p, wave, NW, lane, lds_a + (uint32_t)(kA + kA0) * 16u);
   if (rem > 0) {   // uniform; the partial tile comes first, as in the ring kernel
     const uint64_t a_tail = walk.a_addr + (uint64_t)walk.a_step * (uint32_t)nk_whole, b_tail = walk.b_addr + (uint64_t)walk.b_step * (uint32_t)nk_whole;
 #pragma unroll
@@ -1151,7 +1154,6 @@ __device__ __forceinline__ void phased_tile(const BfParams& p, const BfParams& p
   issue_b_a0(1);
   if (rem > 0) __builtin_amdgcn_s_waitcnt(vmcnt_imm(IPB + IP0));   // all of tile 0
   else __builtin_amdgcn_s_waitcnt(vmcnt_imm(NV));                  // its B and first A part
-  asm volatile("" : "+v"(touched));   // the touch has landed: last use of its register
   __syncthreads();
   if (rem > 0) {
     decltype(ld_a0)::zero_past_end(smem, rem, tid, NW * 64);

@@ -1,7 +1,6 @@
-"""The ring GEMM kernels must not spill: their next-weights touch parks a value in a register that
-the compiler believes is already written, and a spill of it (or of anything else in the K loop) would
-go unnoticed at run time.  Compiles the kernel file to gfx950 assembly (no GPU needed) and reads the
-resource usage the compiler reports per kernel."""
+"""What the compiler makes of the kernels, read without a GPU.  The GEMM kernels must not spill: a spill in the K loop would go
+unnoticed at run time, and its reload would wait for the tile loads that the kernel counts by itself.  The kernel file is compiled to
+gfx950 assembly, or the built library's notes are read, for the resource usage that the compiler reports per kernel."""
 import os
 import re
 import struct
@@ -29,6 +28,29 @@ def test_ring_gemm_kernels_use_no_scratch_and_fit_two_waves_per_simd():
         assert field("private_segment_fixed_size") == 0, name       # no scratch: nothing spilled
         assert field("vgpr_spill_count") == 0 and field("sgpr_spill_count") == 0, name
         assert field("vgpr_count") <= 256, name                     # 8 waves per workgroup = 2 per SIMD
+
+
+def test_no_asm_load_leaves_a_register_in_flight():
+    """The compiler takes the output of an asm block as written when the block ends.  A load whose register is written later may
+    therefore only be issued by a block that waits for it as well."""
+    blocks = []
+    for name in sorted(os.listdir(B.CSRC)):
+        if name.endswith((".hip", ".hpp", ".h")):
+            text = open(os.path.join(B.CSRC, name)).read()
+            blocks += [(name, b) for b in re.findall(r"\basm\s+(?:volatile\s*)?\((.*?)\);", text, flags=re.S)]
+    assert any("global_load_lds" in b for _, b in blocks)      # the search finds the blocks there are
+    for name, b in blocks:
+        code = "".join(re.findall(r'"((?:[^"\\]|\\.)*)"', b.split("\n")[0]))
+        loads = re.search(r"\b(?:global|buffer|flat|scratch|ds|s)_(?:load|read|buffer_load)\w*", code)
+        if loads and "_lds" not in loads.group(0):
+            assert "s_waitcnt" in code, (name, b)
+
+
+def test_phased_gemm_kernels_do_not_spill():
+    kernels = built_kernels("gemm_bf16_phased_kernel")
+    assert len(kernels) >= 10
+    for name, field in kernels:
+        assert field("private_segment_fixed_size") == 0 and field("vgpr_spill_count") == 0 and field("sgpr_spill_count") == 0, name
 
 
 def built_kernels(pattern):
