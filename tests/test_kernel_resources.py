@@ -51,6 +51,7 @@ def test_phased_gemm_kernels_do_not_spill():
     assert len(kernels) >= 10
     for name, field in kernels:
         assert field("private_segment_fixed_size") == 0 and field("vgpr_spill_count") == 0 and field("sgpr_spill_count") == 0, name
+        assert field("vgpr_count") <= 256, name                     # 8 waves per workgroup = 2 per SIMD
 
 
 def built_kernels(pattern):
