@@ -11,7 +11,7 @@
 // dimension or base address do not allow 16-byte loads take guarded 4-byte loads instead.
 //
 // Products whose 128 x 128 tiles do not fill the chip run on gemm_f32_split_kernel (further down): tiles of 64 x 64 or 32 x 32 whose reduction range
-// is split over the workgroup's waves.
+// is split over the workgroup's waves; the smallest ones on gemm_f32_narrow_kernel, tiles of 16 x 16.
 //
 // Lane layout of v_mfma_f32_32x32x2_f32: lane l supplies element (l % 32, l / 32) of the first operand
 // (32 x 2) and (l / 32, l % 32) of the second (2 x 32); it receives column l % 32 of D, rows
@@ -27,6 +27,7 @@ namespace k2bw {
 namespace {
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int BM = 128, BN = 128, BK = 16, LDT = 128 + 32;   // LDT: floats per k row of a staged tile
 constexpr int kThreads = 256;
@@ -348,6 +349,95 @@ __global__ __launch_bounds__(kSplit * 64) void gemm_f32_split_kernel(GroupOfF32<
 }
 
 // ------------------------------------------------------------------------------------------------
+// The smallest products (fewer 32 x 32 tiles than a quarter of the CUs): tiles of 16 x 16 on v_mfma_f32_16x16x4_f32, so that four times
+// as many CUs share the operands' way in and the products themselves (a 32 x 32 tile with K = 1024 is 3.5 us of one CU's matrix cores).
+// The eight waves take every eighth chunk of 16 k; up to NC chunks of a wave are in flight at once.
+// Lane layout: lane l supplies row l % 16 of either operand at k = l / 16 and receives column l % 16, rows 4 * (l / 16) + r.
+// k-slots: instruction i of a chunk takes k = 4 * (l / 16) + i in lane l.
+template <bool ROW_CONTIG>
+struct NarrowLoader {
+  const float* base;
+  int ld;
+  __device__ __forceinline__ void init(const float* X, int ld_, int row0, int rows, int l16, int quarter) {
+    ld = ld_;
+    const int r = min(row0 + l16, rows - 1);   // rows past the matrix: a copy, never stored
+    base = ROW_CONTIG ? X + r + (int64_t)(4 * quarter) * ld : X + (int64_t)r * ld + 4 * quarter;
+  }
+  __device__ __forceinline__ void load(int k0, float (&f)[4]) const {
+    if (ROW_CONTIG) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) f[i] = base[(int64_t)(k0 + i) * ld];
+    } else {
+      const float4 v = *reinterpret_cast<const float4*>(base + k0);
+      f[0] = v.x; f[1] = v.y; f[2] = v.z; f[3] = v.w;
+    }
+  }
+};
+constexpr int kNarrow = 16, kNarrowWaves = 8;
+
+// The waves' partial sums of a 16 x 16 tile (a lane owns row l16 and four consecutive columns) to the epilogue
+template <int EPI>
+__device__ __forceinline__ void finish_narrow(const F32Params& p, const f32x4& acc, float* part, int m0, int n0, int tid, int wave) {
+  constexpr int T = kNarrow, LDS_LD = T + 4;
+  const int lane = tid & 63;
+  *reinterpret_cast<float4*>(part + (wave * T + (lane & 15)) * LDS_LD + 4 * (lane >> 4)) = make_float4(acc[0], acc[1], acc[2], acc[3]);
+  __syncthreads();
+  if (tid < T * T / 4) {
+    const int row = tid / (T / 4), col = tid % (T / 4) * 4;
+    if (m0 + row >= p.M || n0 + col >= p.N) return;
+    float4 s = *reinterpret_cast<const float4*>(part + row * LDS_LD + col);
+#pragma unroll
+    for (int w = 1; w < kNarrowWaves; ++w) {
+      const float4 v = *reinterpret_cast<const float4*>(part + (w * T + row) * LDS_LD + col);
+      s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
+    }
+    const float v[4] = {s.x, s.y, s.z, s.w};
+    finish4<EPI>(p, m0 + row, n0 + col, v);
+  }
+}
+
+template <int NC, bool TB, int EPI>
+__global__ __launch_bounds__(kNarrowWaves * 64) void gemm_f32_narrow_kernel(F32Params p) {
+  constexpr int W = kNarrowWaves, T = kNarrow;
+  __shared__ __attribute__((aligned(16))) float part[W * T * (T + 4)];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l16 = lane & 15, quarter = lane >> 4;
+  const int tiles_n = (p.N + T - 1) / T, m0 = (int)blockIdx.x / tiles_n * T, n0 = (int)blockIdx.x % tiles_n * T;
+  NarrowLoader<false> la;
+  NarrowLoader<!TB> lb;
+  la.init(p.A, p.lda, m0, p.M, l16, quarter);
+  lb.init(p.B, p.ldb, n0, p.N, l16, quarter);
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  const int chunks = p.K / kChunk;
+  for (int c0 = wave; c0 < chunks; c0 += NC * W) {
+    float a[NC][4], b[NC][4];
+#pragma unroll
+    for (int i = 0; i < NC; ++i) {
+      const int c = min(c0 + i * W, chunks - 1);   // past the end: the last one again, not multiplied
+      la.load(c * kChunk, a[i]);
+      lb.load(c * kChunk, b[i]);
+    }
+    __builtin_amdgcn_sched_barrier(0);   // (else the loads sink to their uses)
+#pragma unroll
+    for (int i = 0; i < NC; ++i) {
+      if (c0 + i * W >= chunks) break;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(b[i][e], a[i][e], acc, 0, 0, 0);
+    }
+  }
+  const int rem = p.K % kChunk;   // a multiple of 4: whole quarters of a chunk
+  if (rem > 0 && chunks % W == wave) {
+    float a[4], b[4];
+    const bool in = 4 * quarter < rem;
+    const int k0 = chunks * kChunk - (in ? 0 : 4 * quarter);   // (the chunk's first quarter in place of one that is not there)
+    la.load(k0, a);
+    lb.load(k0, b);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(in ? b[e] : 0.f, in ? a[e] : 0.f, acc, 0, 0, 0);
+  }
+  finish_narrow<EPI>(p, acc, part, m0, n0, tid, wave);
+}
+
+// ------------------------------------------------------------------------------------------------
 template <int MB, int NB, int kSplit, bool TA, bool TB, int EPI>
 hipError_t launch_split(GroupF32& gp, hipStream_t s) {
   constexpr size_t lds = (size_t)kSplit * 32 * MB * (32 * NB + 4) * sizeof(float);
@@ -374,6 +464,16 @@ hipError_t launch_split(GroupF32& gp, hipStream_t s) {
 
 // The split kernels load a K-contiguous operand 16 bytes at a time
 bool split_ok(const F32Params& p, bool ta, bool tb) { return (ta || p.vec_a) && (!tb || p.vec_b); }
+
+int64_t narrow_tiles(const F32Params& p) { return (int64_t)ceil_div(p.M, kNarrow) * ceil_div(p.N, kNarrow); }
+int narrow_chunks(const F32Params& p) { return p.K <= 2 * kNarrowWaves * kChunk ? 2 : 8; }   // of a wave, in flight at once
+template <bool TB, int EPI>
+hipError_t launch_narrow(const F32Params& p, hipStream_t s) {
+  const dim3 grid((int)narrow_tiles(p)), block(kNarrowWaves * 64);
+  if (narrow_chunks(p) == 2) hipLaunchKernelGGL((gemm_f32_narrow_kernel<2, TB, EPI>), grid, block, 0, s, p);
+  else hipLaunchKernelGGL((gemm_f32_narrow_kernel<8, TB, EPI>), grid, block, 0, s, p);
+  return hipGetLastError();
+}
 
 // Tile edge for `count` products of one form (128: one product per launch on the staged kernel): the one with the least estimated
 // time.  In microseconds, with R tiles per CU, C = ceil(R) rounds and K in thousands: a launch has a fixed part, a part per tile of a
@@ -405,7 +505,13 @@ int choose_f32(const F32Params* p, int count, bool ta, bool tb) {
   }
   const double c64 = q.t64_0 + q.t64_tile * r64 + q.t64_k * std::ceil(r64) * (k64 / r64);
   const double c32 = q.t32_0 + q.t32_tile * r32 + q.t32_k * std::ceil(r32) * (k32 / r32);
-  return c128 <= c64 && c128 <= c32 ? 128 : c64 <= c32 ? 64 : 32;
+  if (c128 <= c64 && c128 <= c32) return 128;
+  if (c64 <= c32) return 64;
+  // 16 x 16 tiles halve the time of long reductions as long as every CU has one tile at most; a second one takes as long again, and each
+  // brings twice the bytes of a 32 x 32 tile's share.  Tiles per CU, 32 x 32 | 16 x 16 in us: (tokens, in, out) forward (128,1024,256) 0.5
+  // 9.2 | 5.5; (100,2048,128) 0.22 15.9 | 8.5; (128,4096,512) 1.0 30.1 | 16.6; (925,80,712) data gradient 1.13 7.4 | 7.9;
+  // (51,2320,1352) 1.33 19.7 | 25.1; (926,120,1416) data gradient 1.81 11.4 | 14.9.  Up to K = 256 they are level.
+  return !ta && count == 1 && p[0].K % 4 == 0 && narrow_tiles(p[0]) <= cus ? 16 : 32;
 }
 
 template <bool TA, bool TB, int EPI>
@@ -414,6 +520,9 @@ hipError_t launch_form(GroupF32& gp, hipStream_t s) {
   switch (choose_f32(gp.p, gp.count, TA, TB)) {
     case 64: return launch_split<2, 2, 4, TA, TB, EPI>(gp, s);
     case 32: return launch_split<1, 1, 8, TA, TB, EPI>(gp, s);
+    case 16:
+      if constexpr (!TA) return launch_narrow<TB, EPI>(gp.p[0], s);
+      return hipErrorInvalidValue;
   }
   for (int g = 0; g < gp.count; ++g) {
     const F32Params& p = gp.p[g];
@@ -473,6 +582,7 @@ void gemm_f32_kernel_name(const GemmDesc* d, int count, char* out, size_t cap) {
   switch (choose_f32(p, n, d[0].trans_a, d[0].trans_b)) {
     case 64: snprintf(out, cap, "gemm_f32_split_kernel<2, 2, 4, %s, %s, %d>", ta, tb, d[0].epilogue); break;
     case 32: snprintf(out, cap, "gemm_f32_split_kernel<1, 1, 8, %s, %s, %d>", ta, tb, d[0].epilogue); break;
+    case 16: snprintf(out, cap, "gemm_f32_narrow_kernel<%d, %s, %d>", narrow_chunks(p[0]), tb, d[0].epilogue); break;
     default: snprintf(out, cap, "gemm_f32_mfma_kernel<%s, %s, %d>", ta, tb, d[0].epilogue); break;
   }
 }
