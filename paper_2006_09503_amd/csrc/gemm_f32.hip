@@ -20,6 +20,7 @@
 // per register quad: the epilogue's accesses are 16-byte vectors.
 #include <cmath>
 #include <cstdio>
+#include <type_traits>
 
 #include "kernels.hpp"
 
@@ -438,6 +439,166 @@ __global__ __launch_bounds__(kNarrowWaves * 64) void gemm_f32_narrow_kernel(F32P
 }
 
 // ------------------------------------------------------------------------------------------------
+// A LayerNorm and the product that reads its result, in one launch: 16 x 16 tiles as above, the A operand made on the way from the rows
+// the LayerNorm reads.  A wave's chunks of A are pieces of all the tile's 16 rows, so each wave adds up its part of the rows' sums, the
+// parts meet in LDS, and the wave turns its fragments into the normalised ones (BWD: into the LayerNorm's input gradient) in
+// registers.  What the LayerNorm leaves behind for later launches is written by the workgroup whose columns of C have the same numbers:
+// its 16 columns of the result, of the copies and of the column sums over its 16 rows.  A stage of few tokens is bound by the number of
+// its launches: 3 to 5 us each for LayerNorms of 128 x 128, whatever they compute (lines at ln_fits).
+struct LnArgs {
+  const float *x, *gain;
+  float *mean, *rstd, *y;      // y: the LayerNorm's result, BWD: its input gradient
+  float* keep;                 // a copy of x (BWD: of dres), or null
+  const float* shift;          // forward
+  float eps;
+  const int32_t* n_in; int32_t* n_out; int n;   // integers to copy
+  const float *dy, *dres; float* partial;       // BWD; partial: [ceil(M / 16)][3 K]
+};
+constexpr int kLnMaxChunks = 4;   // chunks per wave
+
+// sum over the 16 lanes of a DPP row
+__device__ __forceinline__ float row16_sum(float v) {
+  auto dpp_add = [](float x, auto ctrl) {
+    const int y = __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), decltype(ctrl)::value, 0xF, 0xF, false);
+    return x + __builtin_bit_cast(float, y);
+  };
+  v = dpp_add(v, std::integral_constant<int, 0xB1>{});      // quad_perm [1,0,3,2]
+  v = dpp_add(v, std::integral_constant<int, 0x4E>{});      // quad_perm [2,3,0,1]
+  v = dpp_add(v, std::integral_constant<int, 0x141>{});     // row_half_mirror
+  return dpp_add(v, std::integral_constant<int, 0x140>{});  // row_mirror
+}
+
+template <bool BWD, int NC, bool TB, int EPI>
+__global__ __launch_bounds__(kNarrowWaves * 64) void gemm_f32_ln_kernel(F32Params p, LnArgs q) {
+  constexpr int W = kNarrowWaves, T = kNarrow;
+  __shared__ __attribute__((aligned(16))) float part[W * T * (T + 4)];
+  __shared__ float row_part[2][W][T];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l16 = lane & 15, quarter = lane >> 4;
+  const int tiles_n = (p.N + T - 1) / T, mt = (int)blockIdx.x / tiles_n, nt = (int)blockIdx.x % tiles_n;
+  const int m0 = mt * T, n0 = nt * T;
+  const bool row_ok = m0 + l16 < p.M;
+  const int row = min(m0 + l16, p.M - 1);   // rows past the matrix: a copy, never stored
+  const int chunks = p.K / kChunk;
+  if (blockIdx.x == 0)
+    for (int i = tid; i < q.n; i += W * 64) q.n_out[i] = q.n_in[i];
+
+  NarrowLoader<!TB> lb;
+  lb.init(p.B, p.ldb, n0, p.N, l16, quarter);
+  float x[NC][4], a[NC][4], g[NC][4], r[NC][4], b[NC][4];   // a: dy (BWD); r: shift (BWD: dres)
+  auto load = [&](const float* from, float (&f)[4]) __attribute__((always_inline)) {
+    const float4 v = *reinterpret_cast<const float4*>(from);
+    f[0] = v.x; f[1] = v.y; f[2] = v.z; f[3] = v.w;
+  };
+  auto store = [&](float* to, const float (&f)[4]) __attribute__((always_inline)) { *reinterpret_cast<float4*>(to) = make_float4(f[0], f[1], f[2], f[3]); };
+  float s1 = 0.f, s2 = 0.f, mean = 0.f, rstd = 0.f;
+  if (BWD) { mean = q.mean[row]; rstd = q.rstd[row]; }
+#pragma unroll
+  for (int i = 0; i < NC; ++i) {
+    const int c = wave + i * W;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) x[i][e] = a[i][e] = g[i][e] = r[i][e] = b[i][e] = 0.f;
+    if (c >= chunks) continue;   // wave-uniform
+    const int col = c * kChunk + 4 * quarter;
+    const int64_t at = (int64_t)row * p.K + col;
+    load(q.x + at, x[i]);
+    load(q.gain + col, g[i]);
+    if (BWD) {
+      load(q.dy + at, a[i]);
+      load(q.dres + at, r[i]);
+    } else {
+      load(q.shift + col, r[i]);
+    }
+    lb.load(c * kChunk, b[i]);
+  }
+  // sums over the rows: own pieces, the wave's other quarters, the other waves
+  auto row_sum = [&](float v, int slot) __attribute__((always_inline)) {
+    v += __shfl_xor(v, 16, 64);
+    v += __shfl_xor(v, 32, 64);
+    if (quarter == 0) row_part[slot][wave][l16] = v;
+  };
+  auto total = [&](int slot) __attribute__((always_inline)) {
+    float t = 0.f;
+#pragma unroll
+    for (int w = 0; w < W; ++w) t += row_part[slot][w][l16];
+    return t;
+  };
+  if constexpr (!BWD) {
+#pragma unroll
+    for (int i = 0; i < NC; ++i)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) s1 += x[i][e];
+    row_sum(s1, 0);
+    __syncthreads();
+    mean = total(0) / (float)p.K;
+#pragma unroll
+    for (int i = 0; i < NC; ++i)
+      if (wave + i * W < chunks)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) { const float d = x[i][e] - mean; s2 += d * d; }
+    row_sum(s2, 1);
+    __syncthreads();
+    rstd = 1.0f / sqrtf(total(1) / (float)p.K + q.eps);
+#pragma unroll
+    for (int i = 0; i < NC; ++i)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) a[i][e] = g[i][e] * ((x[i][e] - mean) * rstd) + r[i][e];
+    if (nt == 0 && wave == 0 && quarter == 0 && row_ok) { q.mean[row] = mean; q.rstd[row] = rstd; }
+  } else {
+    // x becomes xhat, g the gradient dy * gain of xhat; dy stays for the sums
+#pragma unroll
+    for (int i = 0; i < NC; ++i)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        x[i][e] = wave + i * W < chunks ? (x[i][e] - mean) * rstd : 0.f;
+        g[i][e] *= a[i][e];
+        s1 += g[i][e];
+        s2 += g[i][e] * x[i][e];
+      }
+    row_sum(s1, 0);
+    row_sum(s2, 1);
+    __syncthreads();
+    const float c1 = total(0) / (float)p.K, c2 = total(1) / (float)p.K;
+#pragma unroll
+    for (int i = 0; i < NC; ++i) {
+      if (wave + i * W == nt && nt < chunks && row_ok && q.keep) store(q.keep + (int64_t)row * p.K + nt * kChunk + 4 * quarter, r[i]);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) r[i][e] += rstd * (g[i][e] - c1 - x[i][e] * c2);
+    }
+  }
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int i = 0; i < NC; ++i) {
+    if (wave + i * W >= chunks) continue;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(b[i][e], BWD ? r[i][e] : a[i][e], acc, 0, 0, 0);
+  }
+  // what the LayerNorm leaves behind in the columns nt * 16 .. + 15, from the wave that has them
+#pragma unroll
+  for (int i = 0; i < NC; ++i) {
+    if (wave + i * W != nt || nt >= chunks) continue;   // wave-uniform
+    const int col = nt * kChunk + 4 * quarter;
+    const int64_t at = (int64_t)row * p.K + col;
+    if (row_ok) store(q.y + at, BWD ? r[i] : a[i]);
+    if constexpr (!BWD) {
+      if (row_ok && q.keep) store(q.keep + at, x[i]);
+    } else {
+      float v[3][4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float dy = row_ok ? a[i][e] : 0.f;
+        v[0][e] = row16_sum(row_ok ? dy * x[i][e] : 0.f);
+        v[1][e] = row16_sum(dy);
+        v[2][e] = row16_sum(row_ok ? r[i][e] : 0.f);
+      }
+      if (l16 == 0)
+#pragma unroll
+        for (int k = 0; k < 3; ++k) store(q.partial + ((int64_t)mt * 3 + k) * p.K + col, v[k]);
+    }
+  }
+  finish_narrow<EPI>(p, acc, part, m0, n0, tid, wave);
+}
+
+// ------------------------------------------------------------------------------------------------
 template <int MB, int NB, int kSplit, bool TA, bool TB, int EPI>
 hipError_t launch_split(GroupF32& gp, hipStream_t s) {
   constexpr size_t lds = (size_t)kSplit * 32 * MB * (32 * NB + 4) * sizeof(float);
@@ -557,6 +718,27 @@ F32Params to_params(const GemmDesc& d) {
   return p;
 }
 
+// Whether the LayerNorm in front of product d goes into its launch: small products only, since every workgroup makes the LayerNorm of its
+// rows again.  Three batches of 4 microbatches of an fp32 stage with and without, us (tokens x h, f = 4 h): 128 x 128 1800 -> 1499, 300 x 128
+// 1822 -> 1486, 1024 x 128 1205 -> 1109 (one layer), 180 x 192 2205 -> 2014, 1000 x 64 2054 -> 1845, 128 x 256 1805 -> 1494, 128 x 512 1812 ->
+// 1781; with the output projection's data gradient too (64 x 16 tiles of K = 256) 1024 x 256 3370 -> 3435, so the line is below that.
+bool ln_fits(const GemmDesc& d) {
+  if (d.dtype != kF32 || d.trans_a || d.n_seg != 1 || d.K % kChunk || d.K > gemm_ln_row_max() || d.N < d.K) return false;
+  const F32Params p = to_params(d);
+  return p.vec_b && choose_f32(&p, 1, false, d.trans_b) <= 32 && narrow_tiles(p) * d.K <= 200000;
+}
+
+template <bool BWD, bool TB, int EPI>
+hipError_t launch_ln(const F32Params& p, const LnArgs& q, hipStream_t s) {
+  const dim3 grid((int)narrow_tiles(p)), block(kNarrowWaves * 64);
+  switch (ceil_div(p.K, kNarrowWaves * kChunk)) {
+    case 1: hipLaunchKernelGGL((gemm_f32_ln_kernel<BWD, 1, TB, EPI>), grid, block, 0, s, p, q); break;
+    case 2: hipLaunchKernelGGL((gemm_f32_ln_kernel<BWD, 2, TB, EPI>), grid, block, 0, s, p, q); break;
+    default: hipLaunchKernelGGL((gemm_f32_ln_kernel<BWD, kLnMaxChunks, TB, EPI>), grid, block, 0, s, p, q); break;
+  }
+  return hipGetLastError();
+}
+
 }  // namespace
 
 // `count` products of the same form and epilogue (1..kGemmMaxGroup); small ones share a launch
@@ -571,6 +753,30 @@ hipError_t gemm_f32_grouped(const GemmDesc* d, int count, hipStream_t stream) {
   }
   if (d[0].trans_a) return d[0].trans_b ? launch_epi<true, true>(gp, d[0].epilogue, stream) : launch_epi<true, false>(gp, d[0].epilogue, stream);
   return d[0].trans_b ? launch_epi<false, true>(gp, d[0].epilogue, stream) : launch_epi<false, false>(gp, d[0].epilogue, stream);
+}
+
+int gemm_ln_row_max() { return kLnMaxChunks * kNarrowWaves * kChunk; }
+bool gemm_ln_fwd_fits(const GemmDesc& d) { return !d.trans_b && (d.epilogue == kEpiStore || d.epilogue == kEpiGelu) && ln_fits(d); }
+bool gemm_ln_bwd_fits(const GemmDesc& d) { return d.trans_b && d.M <= kNarrow * ln_bwd_max_parts() && (d.epilogue == kEpiStore || d.epilogue == kEpiGeluGrad) && ln_fits(d); }
+
+hipError_t gemm_ln_fwd(const GemmDesc& d, const LnForward& ln, hipStream_t stream) {
+  if (!gemm_ln_fwd_fits(d)) return hipErrorInvalidValue;
+  LnArgs q{};
+  q.x = static_cast<const float*>(ln.x); q.gain = static_cast<const float*>(ln.gain); q.shift = static_cast<const float*>(ln.shift);
+  q.y = static_cast<float*>(ln.y); q.mean = ln.mean; q.rstd = ln.rstd; q.eps = ln.eps;
+  if (ln.keep) { q.keep = static_cast<float*>(ln.keep->x); q.n_in = ln.keep->n_in; q.n_out = ln.keep->n_out; q.n = ln.keep->n; }
+  const F32Params p = to_params(d);
+  return d.epilogue == kEpiGelu ? launch_ln<false, false, kEpiGelu>(p, q, stream) : launch_ln<false, false, kEpiStore>(p, q, stream);
+}
+
+hipError_t gemm_ln_bwd(const GemmDesc& d, const LnBackward& ln, hipStream_t stream) {
+  if (!gemm_ln_bwd_fits(d)) return hipErrorInvalidValue;
+  LnArgs q{};
+  q.x = static_cast<const float*>(ln.x); q.gain = static_cast<const float*>(ln.gain); q.mean = const_cast<float*>(ln.mean);
+  q.rstd = const_cast<float*>(ln.rstd); q.y = static_cast<float*>(ln.dx); q.keep = static_cast<float*>(ln.dres_keep);
+  q.dy = static_cast<const float*>(ln.dy); q.dres = static_cast<const float*>(ln.dres); q.partial = ln.partial;
+  const F32Params p = to_params(d);
+  return d.epilogue == kEpiGeluGrad ? launch_ln<true, true, kEpiGeluGrad>(p, q, stream) : launch_ln<true, true, kEpiStore>(p, q, stream);
 }
 
 void gemm_f32_kernel_name(const GemmDesc* d, int count, char* out, size_t cap) {

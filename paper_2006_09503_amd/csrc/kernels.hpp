@@ -83,6 +83,28 @@ hipError_t layernorm_bwd(const void* dy, const void* x, const float* mean, const
                          const void* gain, const void* dres, void* dx, float* partial,
                          int* parts_out, int rows, int h, int dtype, hipStream_t stream, void* dres_keep = nullptr);
 
+// A LayerNorm (forward or backward, as above) whose result is the A operand of product d, in the product's launch (fp32 products of few
+// tiles with K = the row length; d.A is not read).  d.C must be none of the matrices that the LayerNorm reads.
+// LayerNorm backward leaves ceil(M / 16) partial rows.
+struct LnForward {
+  const void *x = nullptr, *gain = nullptr, *shift = nullptr;
+  void* y = nullptr;
+  float *mean = nullptr, *rstd = nullptr;
+  float eps = 0.f;
+  const LnKeep* keep = nullptr;
+};
+struct LnBackward {
+  const void *dy = nullptr, *x = nullptr, *gain = nullptr, *dres = nullptr;   // (dres: not null)
+  const float *mean = nullptr, *rstd = nullptr;
+  void *dx = nullptr, *dres_keep = nullptr;
+  float* partial = nullptr;
+};
+int gemm_ln_row_max();   // no longer rows than that
+bool gemm_ln_fwd_fits(const GemmDesc& d);
+bool gemm_ln_bwd_fits(const GemmDesc& d);
+hipError_t gemm_ln_fwd(const GemmDesc& d, const LnForward& ln, hipStream_t stream);
+hipError_t gemm_ln_bwd(const GemmDesc& d, const LnBackward& ln, hipStream_t stream);
+
 // ---------------------------------------------------------------------------- column sums
 // partial[parts][n] = per-slab column sums of y[rows, n] (ld = ldy); parts <= colsum_max_parts().
 int colsum_max_parts();

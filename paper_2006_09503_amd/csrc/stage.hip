@@ -109,10 +109,11 @@ struct stage2bw {
   int pending_set[kGemmMaxSegments] = {};   // the set of each pending pass, in order
 
   // backward workspace
-  // tmp_h is transient; the gradients that the weight-gradient products read (dx1, du, dqkv and
-  // each layer's input gradient dchain) exist once per layer, because those products run after
-  // the data-gradient chain of the whole stage
+  // tmp_h and tmp_o are transient (one buffer where no launch reads the one and writes the other); the gradients that the
+  // weight-gradient products read (dx1, du, dqkv and each layer's input gradient dchain) exist once per layer, because those
+  // products run after the data-gradient chain of the whole stage
   char* tmp_h = nullptr;
+  char* tmp_o = nullptr;
   std::vector<char*> dx1, dchain, du, dqkv;   // wg_j copies each, one per position in the pending group
   char* dy_top = nullptr;     // wg_j copies of the stage's incoming gradient (only when wg_j > 1)
   float* delta = nullptr;
@@ -273,6 +274,15 @@ hipError_t run_ln_fwd(stage2bw* st, const void* x, const void* gain, const void*
   });
 }
 
+// A LayerNorm and the product that reads its result: one launch where that pays, else two.
+hipError_t run_ln_gemm_fwd(stage2bw* st, const LnForward& ln, const GemmDesc& g) {
+  if (!gemm_ln_fwd_fits(g)) {
+    hipError_t e = run_ln_fwd(st, ln.x, ln.gain, ln.shift, ln.y, ln.mean, ln.rstd, ln.keep);
+    return e != hipSuccess ? e : run_gemm(st, STAGE_K_GEMM_FWD, g);
+  }
+  return timed(st, STAGE_K_GEMM_FWD, "gemm_f32_ln_kernel", 2.0 * g.M * g.N * g.K, 0.0, [&] { return gemm_ln_fwd(g, ln, st->cur); });
+}
+
 // LayerNorm backward; its two parameter gradients (gain | shift are adjacent in G) are left as
 // per-workgroup partial rows in `partial` and reduced at the end of the layer.
 hipError_t run_ln_bwd(stage2bw* st, const void* dy, const void* x, const float* mean, const float* rstd,
@@ -282,6 +292,16 @@ hipError_t run_ln_bwd(stage2bw* st, const void* dy, const void* x, const float* 
   return timed(st, STAGE_K_LN_BWD, h >= 2048 ? "ln_bwd_wide_kernel" : "ln_bwd_kernel", 0.0, bytes, [&] {
     return layernorm_bwd(dy, x, mean, rstd, gain, dres, dx, partial, parts, st->T, h, st->dtype, st->cur, dres_keep);
   });
+}
+
+// ... and the product that reads dx, in the same launch where that pays
+hipError_t run_ln_bwd_gemm(stage2bw* st, const LnBackward& ln, const GemmDesc& g, int* parts) {
+  if (!gemm_ln_bwd_fits(g)) {
+    hipError_t e = run_ln_bwd(st, ln.dy, ln.x, ln.mean, ln.rstd, ln.gain, ln.dres, ln.dx, ln.partial, parts, ln.dres_keep);
+    return e != hipSuccess ? e : run_gemm(st, STAGE_K_GEMM_DGRAD, g);
+  }
+  *parts = (g.M + 15) / 16;
+  return timed(st, STAGE_K_GEMM_DGRAD, "gemm_f32_ln_kernel", 2.0 * g.M * g.N * g.K, 0.0, [&] { return gemm_ln_bwd(g, ln, st->cur); });
 }
 
 AttnDesc attn_desc(const stage2bw* st, const int32_t* lens) {
@@ -305,14 +325,12 @@ hipError_t run_forward(stage2bw* st, int buf, ActSet& acts, const int32_t* lens,
     LayerActs& A = acts.layer[l];
     void* y = (l == c.n_layers - 1) ? y_out : static_cast<void*>(acts.layer[l + 1].x);
     hipError_t e;
-    e = run_ln_fwd(st, l == 0 && keep ? x_in : A.x, wptr(st, buf, o.ln1_g), wptr(st, buf, o.ln1_b), A.a, A.mean1, A.rstd1, l == 0 ? keep : nullptr);
-    if (e != hipSuccess) return e;
     GemmDesc g;
     g.dtype = st->dtype;
     g.A = A.a; g.lda = h; g.B = wptr(st, buf, o.wqkv); g.ldb = 3 * h; g.C = A.qkv; g.ldc = 3 * h;
     g.M = T; g.N = 3 * h; g.K = h; g.bias = wptr(st, buf, o.bqkv);
     g.prefetch = wptr(st, buf, o.wo); g.prefetch_bytes = (int64_t)h * h * st->esize;   // the next GEMM's weights
-    e = run_gemm(st, STAGE_K_GEMM_FWD, g);
+    e = run_ln_gemm_fwd(st, {l == 0 && keep ? x_in : A.x, wptr(st, buf, o.ln1_g), wptr(st, buf, o.ln1_b), A.a, A.mean1, A.rstd1, c.ln_eps, l == 0 ? keep : nullptr}, g);
     if (e != hipSuccess) return e;
     e = timed(st, STAGE_K_ATTN_FWD, st->dtype == kBF16 ? "attn_fwd_mfma_kernel" : "attn_f32_fwd_kernel", attn_flops, 0.0, [&] {
       return attention_fwd(attn_desc(st, lens), A.qkv, A.o, A.lse, st->cur);
@@ -325,14 +343,12 @@ hipError_t run_forward(stage2bw* st, int buf, ActSet& acts, const int32_t* lens,
     g.prefetch = wptr(st, buf, o.w1); g.prefetch_bytes = (int64_t)h * f * st->esize;
     e = run_gemm(st, STAGE_K_GEMM_FWD, g);
     if (e != hipSuccess) return e;
-    e = run_ln_fwd(st, A.x1, wptr(st, buf, o.ln2_g), wptr(st, buf, o.ln2_b), A.c, A.mean2, A.rstd2);
-    if (e != hipSuccess) return e;
     g = GemmDesc();
     g.dtype = st->dtype;
     g.A = A.c; g.lda = h; g.B = wptr(st, buf, o.w1); g.ldb = f; g.C = A.u; g.ldc = f;
     g.M = T; g.N = f; g.K = h; g.bias = wptr(st, buf, o.b1); g.epilogue = kEpiGelu; g.aux_out = A.g;
     g.prefetch = wptr(st, buf, o.w2); g.prefetch_bytes = (int64_t)h * f * st->esize;
-    e = run_gemm(st, STAGE_K_GEMM_FWD, g);
+    e = run_ln_gemm_fwd(st, {A.x1, wptr(st, buf, o.ln2_g), wptr(st, buf, o.ln2_b), A.c, A.mean2, A.rstd2, c.ln_eps, nullptr}, g);
     if (e != hipSuccess) return e;
     if (y == nullptr) break;
     g = GemmDesc();
@@ -444,6 +460,9 @@ hipError_t run_backward(stage2bw* st, int buf, int set, int pos, const int32_t* 
   std::vector<FinalizeItem> fin;
   fin.reserve(8 * c.n_layers);
   double fin_elems = 0.0;
+  std::vector<int> parts(2 * c.n_layers, 0);   // partial rows that LN1 and LN2 of each layer left
+  LnBackward above;                            // LN1 of the layer above, still to be launched
+  int* above_parts = nullptr;
   for (int l = c.n_layers - 1; l >= 0; --l) {
     const LayerOff& o = st->off[l];
     LayerActs& A = acts.layer[l];
@@ -458,7 +477,7 @@ hipError_t run_backward(stage2bw* st, int buf, int set, int pos, const int32_t* 
     // the GEMM that computes it, dqkv (bf16 mode) from the attention backward kernels; the stage's
     // incoming dy, and du and dqkv in fp32 mode, are summed by the column-sum kernel.
     const bool fused_du = st->dtype == kBF16;
-    auto dgrad = [&](const void* grad, int N, int64_t w_off, int K, void* out, const void* u, const char* next, int64_t next_elems) {
+    auto dgrad_desc = [&](const void* grad, int N, int64_t w_off, int K, void* out, const void* u, const char* next, int64_t next_elems) {
       // out[T,K] = grad[T,N] * W[K,N]^T; next (may be null): the weights of the chain's next data-gradient GEMM
       GemmDesc d;
       d.dtype = st->dtype;
@@ -467,34 +486,40 @@ hipError_t run_backward(stage2bw* st, int buf, int set, int pos, const int32_t* 
       d.B = wptr(st, buf, w_off); d.ldb = N; d.trans_b = true;
       if (next) { d.prefetch = next; d.prefetch_bytes = next_elems * st->esize; }
       if (u) { d.epilogue = kEpiGeluGrad; d.aux = u; if (fused_du) d.colsum_partial = st->du_partial[l]; }
-      return run_gemm(st, STAGE_K_GEMM_DGRAD, d);
+      return d;
     };
+    auto dgrad = [&](auto... args) { return run_gemm(st, STAGE_K_GEMM_DGRAD, dgrad_desc(args...)); };
     // y = x1 + GELU(u) W2 + b2
-    e = dgrad(dy, h, o.w2, f, du, A.u, wptr(st, buf, o.w1), (int64_t)h * f);   if (e != hipSuccess) return e;
+    const GemmDesc d_u = dgrad_desc(dy, h, o.w2, f, du, A.u, wptr(st, buf, o.w1), (int64_t)h * f);
+    if (above.dx) e = run_ln_bwd_gemm(st, above, d_u, above_parts);
+    else e = run_gemm(st, STAGE_K_GEMM_DGRAD, d_u);
+    if (e != hipSuccess) return e;
     // u = c W1 + b1
     e = dgrad(du, f, o.w1, h, st->tmp_h, nullptr, wptr(st, buf, o.wo), (int64_t)h * h);   if (e != hipSuccess) return e;
-    // c = LN2(x1); dx1 = dy + LN2'(dc)
-    int ln2_parts = 0, ln1_parts = 0;
-    e = run_ln_bwd(st, st->tmp_h, A.x1, A.mean2, A.rstd2, wptr(st, buf, o.ln2_g), dy, dx1, st->ln_partial[l], &ln2_parts,
-                   l == c.n_layers - 1 ? dy_keep : nullptr);
+    // c = LN2(x1); dx1 = dy + LN2'(dc); x1 = x + o Wo + bo
+    int& ln2_parts = parts[2 * l + 1];
+    const LnBackward ln2{st->tmp_h, A.x1, wptr(st, buf, o.ln2_g), dy, A.mean2, A.rstd2, dx1, l == c.n_layers - 1 ? dy_keep : nullptr, st->ln_partial[l]};
+    e = run_ln_bwd_gemm(st, ln2, dgrad_desc(dx1, h, o.wo, h, st->tmp_o, nullptr, wptr(st, buf, o.wqkv), (int64_t)3 * h * h), &ln2_parts);
     if (e != hipSuccess) return e;
     if (l == c.n_layers - 1) dy = dy_keep;
-    // x1 = x + o Wo + bo
-    e = dgrad(dx1, h, o.wo, h, st->tmp_h, nullptr, wptr(st, buf, o.wqkv), (int64_t)3 * h * h);   if (e != hipSuccess) return e;
     // attention
     AttnDesc ad = attn_desc(st, lens);
     const bool fused_dqkv = attention_emits_colsum(ad);
     if (fused_dqkv) ad.colsum_partial = st->attn_partial[l];
     e = timed(st, STAGE_K_ATTN_BWD, "attention backward (dq + dkv kernels)", attn_flops, 0.0, [&] {
-      return attention_bwd(ad, A.qkv, A.o, A.lse, st->tmp_h, dqkv, st->delta, st->cur);
+      return attention_bwd(ad, A.qkv, A.o, A.lse, st->tmp_o, dqkv, st->delta, st->cur);
     });
     if (e != hipSuccess) return e;
     // qkv = a Wqkv + bqkv
     e = dgrad(dqkv, 3 * h, o.wqkv, h, st->tmp_h, nullptr, l > 0 ? wptr(st, buf, st->off[l - 1].w2) : nullptr, (int64_t)h * f);
     if (e != hipSuccess) return e;
-    // a = LN1(x); dx = dx1 + LN1'(da)
-    e = run_ln_bwd(st, st->tmp_h, A.x, A.mean1, A.rstd1, wptr(st, buf, o.ln1_g), dx1, dx, st->ln_partial2[l], &ln1_parts);
-    if (e != hipSuccess) return e;
+    // a = LN1(x); dx = dx1 + LN1'(da): the first product of the layer below reads it, and goes out with it
+    above = LnBackward{st->tmp_h, A.x, wptr(st, buf, o.ln1_g), dx1, A.mean1, A.rstd1, dx, nullptr, st->ln_partial2[l]};
+    above_parts = &parts[2 * l];
+    if (l == 0) {
+      e = run_ln_bwd(st, above.dy, above.x, above.mean, above.rstd, above.gain, above.dres, above.dx, above.partial, above_parts);
+      if (e != hipSuccess) return e;
+    }
     ColsumItem cs[3];
     int n_cs = 0, col_dqkv = -1, col_du = -1, col_dy = -1, cols = 0;
     // fp32 mode, few tokens: the matrices themselves are partial rows that the stage's last reduction can sum, no more of them
@@ -530,9 +555,13 @@ hipError_t run_backward(stage2bw* st, int buf, int set, int pos, const int32_t* 
     }
     add_fin(st->ln_partial[l], ln2_parts, 3 * h, 2 * h, st->G + o.ln2_g);
     add_fin(st->ln_partial[l] + 2 * h, ln2_parts, 3 * h, h, st->G + o.bo);
-    add_fin(st->ln_partial2[l], ln1_parts, 3 * h, 2 * h, st->G + o.ln1_g);
-    if (l > 0) add_fin(st->ln_partial2[l] + 2 * h, ln1_parts, 3 * h, h, st->G + st->off[l - 1].b2);
     dy = dx;
+  }
+  for (int l = 0; l < c.n_layers; ++l) {   // (LN1 of a layer is launched with the layer below)
+    const float* partial = st->ln_partial2[l];
+    fin.push_back({partial, parts[2 * l], 3 * h, 2 * h, st->G + st->off[l].ln1_g});
+    if (l > 0) fin.push_back({partial + 2 * h, parts[2 * l], 3 * h, h, st->G + st->off[l - 1].b2});
+    fin_elems += (double)parts[2 * l] * (l > 0 ? 3 : 2) * h;
   }
   // every layer left its partial rows in buffers of its own: one reduction launch finishes the
   // bias, gain and shift gradients of the whole stage
@@ -651,6 +680,9 @@ int stage_create(const stage_config_t* cfg, const float* init_weights_host, void
     if (cfg->recompute) ALLOC(st->slot_x0[i], T * h * E, &st->bytes_stash);
   }
   ALLOC(st->tmp_h, T * h * E, nullptr);
+  // (LayerNorm backward and the output projection's data gradient in one launch: one buffer read, the other written)
+  st->tmp_o = st->tmp_h;
+  if (st->dtype == kF32 && gemm_ln_row_max() >= h) ALLOC(st->tmp_o, T * h * E, nullptr);
   st->dx1.assign(cfg->n_layers, nullptr);
   st->dchain.assign(cfg->n_layers, nullptr);
   st->du.assign(cfg->n_layers, nullptr);

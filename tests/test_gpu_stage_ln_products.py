@@ -1,0 +1,39 @@
+"""fp32 stages whose LayerNorms go out with the product that reads their result: rows of one, two and up to four chunks of 16 per wave
+(and some waves without one), token counts that fill no tile, one token, an FFN narrower than the rows (its LayerNorms have launches of
+their own), both sides of the line on tiles x row length, recomputation (the copy of the input is the only one kept)."""
+import numpy as np
+import pytest
+
+from paper_2006_09503_amd import synth
+
+from gpu_util import rel, run_stage_gpu, run_stage_oracle
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("hidden,heads,ffn,seq,micro,layers,recompute",
+                         [(16, 1, 64, 1, 1, 1, 0), (64, 2, 256, 33, 1, 2, 0), (80, 2, 72, 17, 2, 3, 0), (128, 4, 512, 64, 2, 2, 1),
+                          (144, 3, 576, 31, 1, 2, 0), (256, 4, 256, 50, 1, 2, 1), (272, 17, 1088, 15, 1, 2, 0), (512, 8, 520, 16, 1, 2, 0),
+                          (528, 11, 528, 16, 1, 2, 0), (128, 2, 512, 260, 3, 2, 0), (128, 2, 512, 264, 4, 1, 0), (72, 1, 288, 20, 2, 2, 0)])
+def test_layernorms_in_the_products_launch(hidden, heads, ffn, seq, micro, layers, recompute):
+    cfg = synth.StageConfig(layers, hidden, heads, ffn, seq, micro, 2, 2, synth.MASK_PADDING if micro % 2 else synth.MASK_CAUSAL, synth.PREC_FP32,
+                            recompute=recompute, min_len=1)
+    gen = synth.StageInputs(cfg, 11)
+    w0 = gen.weights()
+    # gains and shifts that are no ones and zeros, and rows with a mean far from zero: the order of the operations shows
+    for layer in synth.param_slices(cfg):
+        for name in ("ln1_g", "ln1_b", "ln2_g", "ln2_b"):
+            off, (n,) = layer[name]
+            w0[off:off + n] += np.linspace(-0.5, 0.5, n, dtype=np.float32)
+    mbs = [(x + 3.0, dy, lens) for x, dy, lens in gen.microbatches(2)]
+    gpu = run_stage_gpu(cfg, w0, mbs, 2, two_streams=True)
+    want = run_stage_oracle(cfg, w0, mbs)
+    for k in want.Y:
+        assert rel(gpu["Y"][k], want.Y[k]) < 5e-6 and rel(gpu["dX"][k], want.dX[k]) < 5e-6
+    G = gpu["snaps"][0]["G"]
+    for slices in synth.param_slices(cfg):
+        for name, (off, shape) in slices.items():
+            n = int(np.prod(shape))
+            g, w = G[off:off + n], want.G[0][off:off + n]
+            # (the key part of the QKV bias has a gradient of zero but for rounding: relative to the whole)
+            assert np.abs(g - w).max() < 2e-5 * np.abs(w).max(), name
