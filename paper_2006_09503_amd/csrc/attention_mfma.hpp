@@ -375,7 +375,7 @@ __device__ __forceinline__ void store_rows(const f32x16 (&acc)[Cfg<DH>::DB], flo
 // MFMA results in ordinary VGPRs.  With 512 available it parks them in the accumulator file and copies every score to a
 // VGPR and back around the softmax arithmetic, which costs more than the MFMAs.)
 template <int DH, int NW, int KSPL, bool ANY, bool EXACT>
-__device__ __forceinline__ bool attn_fwd(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ o, float* __restrict__ lse, int s, int a, int mask_mode, const int32_t* __restrict__ seqlens, int dh_) {
+__device__ __forceinline__ bool attn_fwd(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ o, float* __restrict__ lse, int s, int a, int mask_mode, const int32_t* __restrict__ seqlens, int dh_, int blk) {
   using C = Cfg<DH>;
   extern __shared__ uint4 smem[];   // stage st: K tile at st * 2 * kTileU4, V tile behind it
 
@@ -386,9 +386,8 @@ __device__ __forceinline__ bool attn_fwd(const bf16_t* __restrict__ qkv, bf16_t*
   const int kg = KSPL == 1 ? 0 : wave / RW, rw = KSPL == 1 ? wave : wave % RW;
   // grid = (heads, sequences, row blocks): the row block varies slowest, so all heads' copies of a block are
   // dispatched together, and under a causal mask the blocks with the most keys to visit (the last queries) go
-  // first: the workgroups that take longest start earliest and the launch does not end on one of them
+  // first: the workgroups that take longest start earliest and the launch does not end on one of them (where all start at once: Fold)
   const int n = blockIdx.y, head = blockIdx.x;
-  const int blk = mask_mode == 1 ? (int)(gridDim.z - 1 - blockIdx.z) : (int)blockIdx.z;
   const int i0 = blk * RW * 32;
   const int dh = ANY ? dh_ : DH;
   const int h = a * dh;
@@ -533,9 +532,10 @@ __device__ __forceinline__ bool attn_fwd(const bf16_t* __restrict__ qkv, bf16_t*
   return false;
 }
 template <int DH, int NW, int KSPL, bool ANY>
-__global__ __launch_bounds__(NW * 64, 2) void attn_fwd_mfma_kernel(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ o, float* __restrict__ lse, int s, int a, int mask_mode, const int32_t* __restrict__ seqlens, int dh_) {
-  if (attn_fwd<DH, NW, KSPL, ANY, false>(qkv, o, lse, s, a, mask_mode, seqlens, dh_))
-    if constexpr (ANY) attn_fwd<DH, NW, KSPL, ANY, true>(qkv, o, lse, s, a, mask_mode, seqlens, dh_);
+__global__ __launch_bounds__(NW * 64, 2) void attn_fwd_mfma_kernel(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ o, float* __restrict__ lse, int s, int a, int mask_mode, const int32_t* __restrict__ seqlens, int dh_, Fold fold) {
+  const int z = folded_z(fold), blk = mask_mode == 1 ? (int)gridDim.z - 1 - z : z;
+  if (attn_fwd<DH, NW, KSPL, ANY, false>(qkv, o, lse, s, a, mask_mode, seqlens, dh_, blk))
+    if constexpr (ANY) attn_fwd<DH, NW, KSPL, ANY, true>(qkv, o, lse, s, a, mask_mode, seqlens, dh_, blk);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -1024,12 +1024,14 @@ hipError_t fwd_launch(const AttnDesc& d, const void* qkv, void* o, float* lse, h
   constexpr size_t lds_merge = KSPL == 1 ? 0 : NW / KSPL * (C::DB * 16 + 2) * 64 * sizeof(float);   // ... and so do the halves' results
   constexpr size_t lds = max_of(max_of(KSPL * (4 * C::kTileU4 + C::kPadU4) * sizeof(uint4), lds_out), lds_merge);
   static_assert(lds <= 160 * 1024, "LDS of a CU");
+  constexpr int kPerCu = NW == 4 ? (DH <= 32 ? 4 : DH <= 64 ? 2 : 1) : DH <= (ANY ? 32 : 64) ? 2 : 1;   // workgroups, by registers and LDS
   static bool done = false;
   hipError_t e = set_lds(attn_fwd_mfma_kernel<DH, NW, KSPL, ANY>, lds, &done);
   if (e != hipSuccess) return e;
   dim3 grid(d.a, d.b, ceil_div(d.s, NW / KSPL * 32));
   hipLaunchKernelGGL((attn_fwd_mfma_kernel<DH, NW, KSPL, ANY>), grid, dim3(NW * 64), lds, st, static_cast<const bf16_t*>(qkv),
-                     static_cast<bf16_t*>(o), lse, d.s, d.a, d.mask_mode, d.seqlens, d.dh);
+                     static_cast<bf16_t*>(o), lse, d.s, d.a, d.mask_mode, d.seqlens, d.dh,
+                     fold_of(d, grid.z, kPerCu));
   return hipGetLastError();
 }
 

@@ -150,6 +150,17 @@ hipError_t attention_fwd(const AttnDesc& d, const void* qkv, void* o, float* lse
 hipError_t attention_bwd(const AttnDesc& d, const void* qkv, const void* o, const float* lse,
                          const void* d_o, void* dqkv, float* delta, hipStream_t stream);
 
+// Causal launches whose workgroups all start at once, up to `per_cu` on a CU: grid.z holds the blocks from the longest to the shortest, and
+// workgroup p shares its CU with p + CUs, so what follows the first workgroup of every CU counts its blocks from the end: the longest
+// blocks sit beside the shortest and not beside the middle ones.
+struct Fold { int at, last; };   // z from `at` on stands for last - z
+inline Fold fold_of(const AttnDesc& d, int nz, int per_cu) {
+  const int64_t per_z = (int64_t)d.a * d.b, cus = gemm_compute_units();
+  const int at = d.mask_mode == 1 && nz * per_z > cus && nz * per_z <= per_cu * cus ? (int)((cus + per_z - 1) / per_z) : nz;
+  return {at, nz - 1 + at};
+}
+__device__ __forceinline__ int folded_z(const Fold& f) { return (int)blockIdx.z < f.at ? (int)blockIdx.z : f.last - (int)blockIdx.z; }
+
 // ---------------------------------------------------------------------------- optimizer
 // One Adam step on n parameters with the coalesced gradient sum G (g = G * inv_m):
 //   m <- b1 m + (1-b1) g;  v <- b2 v + (1-b2) g^2;
