@@ -275,13 +275,12 @@ using GroupF32 = GroupOfF32<kGroupF32>;   // on the host
 template <int EPI>
 constexpr int kLaunchCap = EPI == kEpiAccum ? kGroupF32 : 1;
 
-template <int MB, int NB, int kSplit, bool TA, bool TB, int EPI>
-__global__ __launch_bounds__(kSplit * 64) void gemm_f32_split_kernel(GroupOfF32<kLaunchCap<EPI>> gp) {
+template <int MB, int NB, int kSplit, bool TA, bool TB, int EPI, int CAP>
+__device__ __forceinline__ void split_tile(const GroupOfF32<CAP>& gp, float* part) {   // part: [kSplit][TM][TN + 4]
   constexpr int TM = 32 * MB, TN = 32 * NB, LDS_LD = TN + 4;
-  extern __shared__ __attribute__((aligned(16))) float part[];   // [kSplit][TM][LDS_LD]
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l32 = lane & 31, hf = lane >> 5;
   int g = 0;
-  if (kLaunchCap<EPI> > 1)
+  if (CAP > 1)
     for (int q = 1; q < gp.count; ++q) g = (int)blockIdx.x >= gp.tile_start[q] ? q : g;
   const F32Params& p = gp.p[g];
   const int t = (int)blockIdx.x - gp.tile_start[g], tiles_n = (p.N + TN - 1) / TN;
@@ -346,6 +345,62 @@ __global__ __launch_bounds__(kSplit * 64) void gemm_f32_split_kernel(GroupOfF32<
     }
     const float v[4] = {s.x, s.y, s.z, s.w};
     finish4<EPI>(p, m0 + row, n0 + col, v);
+  }
+}
+template <int MB, int NB, int kSplit, bool TA, bool TB, int EPI>
+__global__ __launch_bounds__(kSplit * 64) void gemm_f32_split_kernel(GroupOfF32<kLaunchCap<EPI>> gp) {
+  extern __shared__ __attribute__((aligned(16))) float part[];
+  split_tile<MB, NB, kSplit, TA, TB, EPI>(gp, part);
+}
+
+// Weight gradients in 32 x 32 tiles and, in the workgroups behind theirs, sums over the rows of matrices (the bias, gain and shift gradients of
+// the same pass: colsum_finalize_grouped), which have nothing to do with them but to be due at the same time: one launch less per pass of a
+// stage that is bound by its launches (two layers of 128 tokens, h = 128: 23.3 -> 22.3 per microbatch; a launch of few products also carries
+// 2 instead of 4.3 KB of arguments).  A workgroup owns 64 columns: 16 threads x 16 bytes along a row, 32 such groups walk the rows.
+constexpr int kSumProducts = 16, kSumItems = 24;
+struct SumItems {
+  const float* in[kSumItems];
+  float* out[kSumItems];
+  int rows[kSumItems], n[kSumItems], ld[kSumItems], block0[kSumItems];
+  int count, accumulate;
+};
+__global__ __launch_bounds__(512) void gemm_f32_wgrad_sums_kernel(GroupOfF32<kSumProducts> gp, SumItems g) {
+  extern __shared__ __attribute__((aligned(16))) float part[];
+  const int block = (int)blockIdx.x - gp.tile_start[kSumProducts];
+  if (block < 0) {
+    split_tile<1, 1, 8, true, false, kEpiAccum>(gp, part);
+    return;
+  }
+  float4 (*red)[17] = reinterpret_cast<float4 (*)[17]>(part);   // [32][17]
+  int q = 0;
+  for (int i = 1; i < g.count; ++i) q = block >= g.block0[i] ? i : q;
+  const float* in = g.in[q];
+  const int rows = g.rows[q], n = g.n[q], ld = g.ld[q];
+  const int c = threadIdx.x & 15, pl = threadIdx.x >> 4, col = ((block - g.block0[q]) * 16 + c) * 4;
+  auto add = [](float4& a, const float4& b) { a.x += b.x; a.y += b.y; a.z += b.z; a.w += b.w; };
+  auto at = [&](int r) { return *reinterpret_cast<const float4*>(in + (int64_t)r * ld + col); };
+  float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+  if (col < n) {
+    int r = pl;
+    for (; r + 3 * 32 < rows; r += 4 * 32) {   // four rows in flight, added as a tree
+      float4 v[4] = {at(r), at(r + 32), at(r + 64), at(r + 96)};
+      add(v[0], v[2]); add(v[1], v[3]); add(v[0], v[1]); add(s, v[0]);
+    }
+    for (; r < rows; r += 32) add(s, at(r));
+  }
+  red[pl][c] = s;
+  __syncthreads();
+  if (pl == 0 && col < n) {
+    float4 v[32];
+#pragma unroll
+    for (int i = 0; i < 32; ++i) v[i] = red[i][c];
+#pragma unroll
+    for (int w = 16; w > 0; w /= 2)
+#pragma unroll
+      for (int i = 0; i < w; ++i) add(v[i], v[i + w]);
+    float4* out = reinterpret_cast<float4*>(g.out[q] + col);
+    if (g.accumulate) add(v[0], *out);
+    *out = v[0];
   }
 }
 
@@ -718,6 +773,8 @@ F32Params to_params(const GemmDesc& d) {
   return p;
 }
 
+bool aligned16(const void* ptr) { return (reinterpret_cast<uintptr_t>(ptr) & 15) == 0; }
+
 // Whether the LayerNorm in front of product d goes into its launch: small products only, since every workgroup makes the LayerNorm of its
 // rows again.  Three batches of 4 microbatches of an fp32 stage with and without, us (tokens x h, f = 4 h): 128 x 128 1800 -> 1499, 300 x 128
 // 1822 -> 1486, 1024 x 128 1205 -> 1109 (one layer), 180 x 192 2205 -> 2014, 1000 x 64 2054 -> 1845, 128 x 256 1805 -> 1494, 128 x 512 1812 ->
@@ -777,6 +834,45 @@ hipError_t gemm_ln_bwd(const GemmDesc& d, const LnBackward& ln, hipStream_t stre
   q.dy = static_cast<const float*>(ln.dy); q.dres = static_cast<const float*>(ln.dres); q.partial = ln.partial;
   const F32Params p = to_params(d);
   return d.epilogue == kEpiGeluGrad ? launch_ln<true, true, kEpiGeluGrad>(p, q, stream) : launch_ln<true, true, kEpiStore>(p, q, stream);
+}
+
+bool gemm_sums_fit(const GemmDesc* d, int count, const FinalizeItem* items, int n) {
+  if (count < 1 || count > kSumProducts || n < 1 || n > kSumItems) return false;
+  F32Params p[kSumProducts];
+  for (int g = 0; g < count; ++g) {
+    if (d[g].dtype != kF32 || !d[g].trans_a || d[g].trans_b || d[g].epilogue != kEpiAccum || d[g].n_seg != 1) return false;
+    p[g] = to_params(d[g]);
+  }
+  for (int i = 0; i < n; ++i)
+    if (items[i].parts <= 0 || items[i].n <= 0 || items[i].n % 4 || items[i].ld % 4 || items[i].ld < items[i].n || !aligned16(items[i].partial) || !aligned16(items[i].out))
+      return false;
+  return choose_f32(p, count, true, false) == 32;
+}
+
+hipError_t gemm_with_sums(const GemmDesc* d, int count, const FinalizeItem* items, int n, bool accumulate, hipStream_t stream) {
+  if (!gemm_sums_fit(d, count, items, n)) return hipErrorInvalidValue;
+  GroupOfF32<kSumProducts> gp;
+  gp.count = count;
+  int total = 0;
+  for (int g = 0; g <= kSumProducts; ++g) {
+    gp.tile_start[g] = total;
+    if (g >= count) continue;
+    gp.p[g] = to_params(d[g]);
+    total += ceil_div(d[g].M, 32) * ceil_div(d[g].N, 32);
+  }
+  SumItems s;
+  s.count = n;
+  s.accumulate = accumulate ? 1 : 0;
+  int blocks = 0;
+  for (int i = 0; i < n; ++i) {
+    s.in[i] = items[i].partial; s.out[i] = items[i].out; s.rows[i] = items[i].parts; s.n[i] = items[i].n; s.ld[i] = items[i].ld;
+    s.block0[i] = blocks;
+    blocks += ceil_div(items[i].n, 64);
+  }
+  constexpr size_t lds = 8 * 32 * (32 + 4) * sizeof(float);
+  static_assert(lds >= 32 * 17 * sizeof(float4) && lds <= 64 * 1024, "");
+  hipLaunchKernelGGL(gemm_f32_wgrad_sums_kernel, dim3(total + blocks), dim3(512), lds, stream, gp, s);
+  return hipGetLastError();
 }
 
 void gemm_f32_kernel_name(const GemmDesc* d, int count, char* out, size_t cap) {

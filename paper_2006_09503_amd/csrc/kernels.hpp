@@ -126,6 +126,9 @@ hipError_t colsum_partial_grouped(const ColsumItem* items, int count, int rows, 
 struct FinalizeItem { const float* partial; int parts; int ld; int n; float* out; };
 constexpr int kFinalizeMaxItems = 64;   // segments per launch (the launch's arguments stay under 4 KB)
 hipError_t colsum_finalize_grouped(const FinalizeItem* items, int count, bool accumulate, hipStream_t stream);
+// The same beside `count` weight-gradient products, in their launch (fp32 products of few tiles, few items).
+bool gemm_sums_fit(const GemmDesc* d, int count, const FinalizeItem* items, int n);
+hipError_t gemm_with_sums(const GemmDesc* d, int count, const FinalizeItem* items, int n, bool accumulate, hipStream_t stream);
 
 // ---------------------------------------------------------------------------- attention
 // qkv: [b*s, 3h] rows = tokens, columns Q|K|V each head-major (head size dh = h/a).

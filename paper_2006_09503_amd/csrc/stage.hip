@@ -119,6 +119,10 @@ struct stage2bw {
   float* delta = nullptr;
   // per layer: partial rows of the bias / gain / shift gradients, reduced by one launch per backward pass
   std::vector<float*> ln_partial, ln_partial2, cs_partial, du_partial, attn_partial;
+  // ... and what that launch is to sum
+  std::vector<FinalizeItem> fin;
+  double fin_elems = 0.0;
+  bool fin_accumulate = false;
 
   // timing
   bool timing = false;
@@ -362,6 +366,20 @@ hipError_t run_forward(stage2bw* st, int buf, ActSet& acts, const int32_t* lens,
   return hipSuccess;
 }
 
+// The sums that the last backward pass left
+hipError_t flush_sums(stage2bw* st) {
+  const std::vector<FinalizeItem>& fin = st->fin;
+  for (size_t i0 = 0; i0 < fin.size(); i0 += kFinalizeMaxItems) {
+    const int n = (int)std::min<size_t>(kFinalizeMaxItems, fin.size() - i0);
+    hipError_t e = timed(st, STAGE_K_BIAS_GRAD, "colsum_finalize_grouped_kernel", 0.0, 4.0 * st->fin_elems * n / fin.size(), [&] {
+      return colsum_finalize_grouped(&fin[i0], n, st->fin_accumulate, st->cur);
+    });
+    if (e != hipSuccess) return e;
+  }
+  st->fin.clear();
+  return hipSuccess;
+}
+
 // The grouped weight-gradient launch(es) for the pending backward passes: per layer the four products
 // G_W (+)= [X_1; ..; X_n]^T [dY_1; ..; dY_n] over the n = n_pending passes' tokens.  The activation
 // operand of pass s lies in activation set pending_set[s], its gradient operand in copy s of the
@@ -419,18 +437,29 @@ hipError_t flush_wgrad(stage2bw* st) {
     const int cnt = (int)(i1 - i0);
     double flops = 0.0;
     for (int i = 0; i < cnt; ++i) flops += 2.0 * wg[i0 + i].M * (double)wg[i0 + i].N * wg[i0 + i].K;
+    if (!st->fin.empty() && gemm_sums_fit(&wg[i0], cnt, st->fin.data(), (int)st->fin.size())) {   // (fp32: one pass per group)
+      hipError_t e = timed(st, STAGE_K_GEMM_WGRAD, "gemm_f32_wgrad_sums_kernel", flops, 0.0, [&] {
+        return gemm_with_sums(&wg[i0], cnt, st->fin.data(), (int)st->fin.size(), st->fin_accumulate, st->cur);
+      });
+      if (e != hipSuccess) return e;
+      st->fin.clear();
+      i0 = i1;
+      continue;
+    }
     char wg_name[96] = "";
     if (st->timing) gemm_kernel_name(&wg[i0], cnt, wg_name, sizeof(wg_name));
     hipError_t e = timed(st, STAGE_K_GEMM_WGRAD, wg_name, flops, 0.0, [&] { return gemm_grouped(&wg[i0], cnt, st->cur); });
     if (e != hipSuccess) return e;
     i0 = i1;
   }
+  hipError_t e = flush_sums(st);
+  if (e != hipSuccess) return e;
   // the sets are free again once this launch has run
   if (!c.recompute) {
     for (int s = 0; s < n; ++s) {
       const int set = st->pending_set[s];
       if (st->two_streams) {
-        hipError_t e = hipEventRecord(st->set_done[set], st->cur);
+        e = hipEventRecord(st->set_done[set], st->cur);
         if (e != hipSuccess) return e;
         st->set_seq[set] = ++st->b_seq;
       }
@@ -563,16 +592,12 @@ hipError_t run_backward(stage2bw* st, int buf, int set, int pos, const int32_t* 
     if (l > 0) fin.push_back({partial + 2 * h, parts[2 * l], 3 * h, h, st->G + st->off[l - 1].b2});
     fin_elems += (double)parts[2 * l] * (l > 0 ? 3 : 2) * h;
   }
-  // every layer left its partial rows in buffers of its own: one reduction launch finishes the
-  // bias, gain and shift gradients of the whole stage
-  for (size_t i0 = 0; i0 < fin.size(); i0 += kFinalizeMaxItems) {
-    const int n = (int)std::min<size_t>(kFinalizeMaxItems, fin.size() - i0);
-    hipError_t e = timed(st, STAGE_K_BIAS_GRAD, "colsum_finalize_grouped_kernel", 0.0, 4.0 * fin_elems * n / fin.size(), [&] {
-      return colsum_finalize_grouped(&fin[i0], n, acc, st->cur);
-    });
-    if (e != hipSuccess) return e;
-  }
-  return hipSuccess;
+  // every layer left its partial rows in buffers of its own: one reduction launch finishes the bias, gain and shift gradients of the whole
+  // stage, in fp32 mode the one of this pass's weight gradients
+  st->fin.swap(fin);
+  st->fin_elems = fin_elems;
+  st->fin_accumulate = acc;
+  return st->dtype == kF32 ? hipSuccess : flush_sums(st);
 }
 
 int free_all(stage2bw* st) {

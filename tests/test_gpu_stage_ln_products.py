@@ -1,6 +1,7 @@
 """fp32 stages whose LayerNorms go out with the product that reads their result: rows of one, two and up to four chunks of 16 per wave
 (and some waves without one), token counts that fill no tile, one token, an FFN narrower than the rows (its LayerNorms have launches of
-their own), both sides of the line on tiles x row length, recomputation (the copy of the input is the only one kept)."""
+their own), both sides of the line on tiles x row length, recomputation (the copy of the input is the only one kept); the sums
+of the small gradients in the launch of the weight gradients (up to three layers) and in one of their own (more)."""
 import numpy as np
 import pytest
 
@@ -14,7 +15,7 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("hidden,heads,ffn,seq,micro,layers,recompute",
                          [(16, 1, 64, 1, 1, 1, 0), (64, 2, 256, 33, 1, 2, 0), (80, 2, 72, 17, 2, 3, 0), (128, 4, 512, 64, 2, 2, 1),
                           (144, 3, 576, 31, 1, 2, 0), (256, 4, 256, 50, 1, 2, 1), (272, 17, 1088, 15, 1, 2, 0), (512, 8, 520, 16, 1, 2, 0),
-                          (528, 11, 528, 16, 1, 2, 0), (128, 2, 512, 260, 3, 2, 0), (128, 2, 512, 264, 4, 1, 0), (72, 1, 288, 20, 2, 2, 0)])
+                          (528, 11, 528, 16, 1, 2, 0), (128, 2, 512, 260, 3, 2, 0), (128, 2, 512, 264, 4, 1, 0), (72, 1, 288, 20, 2, 2, 0), (48, 2, 96, 10, 1, 4, 0), (48, 2, 96, 10, 1, 5, 0)])
 def test_layernorms_in_the_products_launch(hidden, heads, ffn, seq, micro, layers, recompute):
     cfg = synth.StageConfig(layers, hidden, heads, ffn, seq, micro, 2, 2, synth.MASK_PADDING if micro % 2 else synth.MASK_CAUSAL, synth.PREC_FP32,
                             recompute=recompute, min_len=1)
