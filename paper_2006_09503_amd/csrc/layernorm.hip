@@ -133,6 +133,61 @@ __global__ __launch_bounds__(kWg) void ln_fwd_kernel(const T* __restrict__ x, co
   if (sub == 0) { mean_out[row] = mean; rstd_out[row] = rstd; }
 }
 
+// The end of a backward workgroup: the column sums of its ROWS sub-rows (R threads each, chunks of 8 columns at (sub + c * R) * 8) added in
+// the order of the rows and stored to row = [3][h].  The matrices go through LDS as 16-byte pieces [which][CPT][2][thread] and every thread
+// takes its share of the adding and storing; all three at once, unless two workgroups would no longer fit into a CU's LDS.
+// (One matrix after the other, added and stored by the threads of the first sub-row alone: bf16 4096 x 1024 12.1 -> 11.6 us, 4096 x 2560 21.4 -> 21.0,
+// fp32 1428 x 1920 14.2 -> 13.4; all three at once there, one workgroup per CU, 16.9.)
+// IN_LDS: the third matrix is there already.
+constexpr int row_sums_at_once(int cpt) { return cpt < 4 ? 3 : 1; }
+template <int R, int ROWS, int CPT, bool IN_LDS = false>
+__device__ __forceinline__ void store_row_sums(float4* sums, const float (&gsum)[CPT][8], const float (&bsum)[CPT][8],
+                                               const float (&osum)[CPT][8], float* __restrict__ row, int h) {
+  constexpr int kThreads = R * ROWS;
+  const int tid = threadIdx.x;
+  if constexpr (ROWS == 1) {
+#pragma unroll
+    for (int c = 0; c < CPT; ++c) {
+      const int col = (tid + c * R) * 8;
+      if (col < h) {
+        store8(row + col, gsum[c]);
+        store8(row + h + col, bsum[c]);
+        store8(row + 2 * h + col, osum[c]);
+      }
+    }
+  } else {
+    constexpr int kTurn = row_sums_at_once(CPT), kPieces = kTurn * CPT * 2 * R;   // pieces of a turn, in the order of their addresses within a matrix
+    static_assert(!IN_LDS || kTurn == 3, "the third matrix lies behind the first two");
+#pragma unroll
+    for (int w0 = 0; w0 < 3; w0 += kTurn) {
+      if (w0 > 0) __syncthreads();   // the last turn's pieces are read
+#pragma unroll
+      for (int w = 0; w < kTurn; ++w) {
+        if (IN_LDS && w == 2) break;
+        const float (&v)[CPT][8] = w0 + w == 0 ? gsum : w0 + w == 1 ? bsum : osum;
+#pragma unroll
+        for (int c = 0; c < CPT; ++c)
+#pragma unroll
+          for (int q = 0; q < 2; ++q)
+            sums[((w * CPT + c) * 2 + q) * kThreads + tid] = make_float4(v[c][4 * q], v[c][4 * q + 1], v[c][4 * q + 2], v[c][4 * q + 3]);
+      }
+      __syncthreads();
+#pragma unroll
+      for (int k0 = 0; k0 < kPieces; k0 += kThreads) {
+        const int k = k0 + tid;
+        if (kPieces % kThreads != 0 && k >= kPieces) break;
+        const int q = k & 1, sub = (k >> 1) % R, wc = (k >> 1) / R, col = (sub + (wc % CPT) * R) * 8 + 4 * q;
+        if (col >= h) continue;
+        const float4* at = sums + (wc * 2 + q) * kThreads + sub;
+        float4 t = at[0];
+#pragma unroll
+        for (int rr = 1; rr < ROWS; ++rr) { const float4 v = at[rr * R]; t.x += v.x; t.y += v.y; t.z += v.z; t.w += v.w; }
+        *reinterpret_cast<float4*>(row + (w0 + wc / CPT) * h + col) = t;
+      }
+    }
+  }
+}
+
 // Backward.  Workgroups stride over row groups and keep per-column sums of dy*xhat, dy and of the
 // result dx in registers; each workgroup writes one row of partial[parts][3h] (dy*xhat | dy | dx).
 // The third block is the bias gradient of the projection that produced this kernel's residual
@@ -145,7 +200,7 @@ __global__ __launch_bounds__(kWg) void ln_bwd_kernel(const T* __restrict__ dy, c
                                                       T* __restrict__ dx, float* __restrict__ partial, int rows, int h, T* __restrict__ dres_keep) {
   constexpr int ROWS = kWg / R;
   __shared__ float red[4];
-  __shared__ float comb[(ROWS > 1) ? (ROWS - 1) * R * CPT * 8 : 1];
+  __shared__ float4 sums[ROWS > 1 ? row_sums_at_once(CPT) * 2 * CPT * kWg : 1];
   const int tid = threadIdx.x;
   const int sub = tid % R, rsub = tid / R;
   float gsum[CPT][8], bsum[CPT][8], osum[CPT][8], gn[CPT][8];
@@ -233,36 +288,8 @@ __global__ __launch_bounds__(kWg) void ln_bwd_kernel(const T* __restrict__ dy, c
       }
     }
   }
-  // combine the ROWS sub-rows of this workgroup, then one partial row per workgroup
-#pragma unroll
-  for (int which = 0; which < 3; ++which) {
-    if (ROWS > 1) {
-      __syncthreads();
-      if (rsub > 0) {
-#pragma unroll
-        for (int c = 0; c < CPT; ++c)
-#pragma unroll
-          for (int i = 0; i < 8; ++i)
-            comb[(((rsub - 1) * CPT + c) * 8 + i) * R + sub] = which == 0 ? gsum[c][i] : which == 1 ? bsum[c][i] : osum[c][i];
-      }
-      __syncthreads();
-    }
-    if (rsub == 0) {
-#pragma unroll
-      for (int c = 0; c < CPT; ++c) {
-        const int col = (sub + c * R) * 8;
-        if (col < h) {
-          float o[8];
-#pragma unroll
-          for (int i = 0; i < 8; ++i) {
-            o[i] = which == 0 ? gsum[c][i] : which == 1 ? bsum[c][i] : osum[c][i];
-            for (int rr = 1; rr < ROWS; ++rr) o[i] += comb[(((rr - 1) * CPT + c) * 8 + i) * R + sub];
-          }
-          store8(partial + (int64_t)blockIdx.x * 3 * h + which * h + col, o);
-        }
-      }
-    }
-  }
+  // one partial row per workgroup: the sums of its ROWS sub-rows
+  store_row_sums<R, ROWS, CPT>(sums, gsum, bsum, osum, partial + (int64_t)blockIdx.x * 3 * h, h);
 }
 
 // Backward for long rows (h >= 2048).  With 256 threads the per-column sums of a row of 8192 take 96
@@ -289,8 +316,9 @@ __global__ __launch_bounds__(R* ROWS) void ln_bwd_wide_kernel(const T* __restric
   constexpr bool kAhead = sizeof(T) == 2 && CPT == 1;
   constexpr bool kLdsSums = CPT == 1;
   __shared__ float red[2][2 * U][16];
-  __shared__ float4 osum_lds[kLdsSums ? 2 * kThreads : 1];
-  __shared__ float comb[(ROWS > 1) ? (ROWS - 1) * R * CPT * 8 : 1];
+  __shared__ float4 sums[ROWS > 1 ? 6 * kThreads : kLdsSums ? 2 * kThreads : 1];   // of gain, shift and results, [3][2][thread]; with one row the last only
+  float4* osum_lds = sums + (ROWS > 1 ? 4 * kThreads : 0);
+  static_assert(ROWS == 1 || kLdsSums, "store_row_sums takes the sums of the results from LDS");
   const int tid = threadIdx.x;
   const int sub = tid % R, rsub = tid / R;
   const int wave = tid >> 6, first_wave = (wave / W) * W;
@@ -428,40 +456,16 @@ __global__ __launch_bounds__(R* ROWS) void ln_bwd_wide_kernel(const T* __restric
     }
     parity ^= 1;
   }
-  if (kLdsSums) {
-    const float4 lo = osum_lds[tid], hi = osum_lds[kThreads + tid];
-    osum[0][0] = lo.x; osum[0][1] = lo.y; osum[0][2] = lo.z; osum[0][3] = lo.w;
-    osum[0][4] = hi.x; osum[0][5] = hi.y; osum[0][6] = hi.z; osum[0][7] = hi.w;
-  }
-  // combine the ROWS sub-rows of this workgroup, then one partial row per workgroup
-#pragma unroll
-  for (int which = 0; which < 3; ++which) {
-    if (ROWS > 1) {
-      __syncthreads();
-      if (rsub > 0) {
-#pragma unroll
-        for (int c = 0; c < CPT; ++c)
-#pragma unroll
-          for (int i = 0; i < 8; ++i)
-            comb[(((rsub - 1) * CPT + c) * 8 + i) * R + sub] = which == 0 ? gsum[c][i] : which == 1 ? bsum[c][i] : osum[c][i];
-      }
-      __syncthreads();
+  float* row = partial + (int64_t)blockIdx.x * 3 * h;
+  if constexpr (ROWS > 1) {
+    store_row_sums<R, ROWS, CPT, true>(sums, gsum, bsum, osum, row, h);
+  } else {
+    if (kLdsSums) {
+      const float4 lo = osum_lds[tid], hi = osum_lds[kThreads + tid];
+      osum[0][0] = lo.x; osum[0][1] = lo.y; osum[0][2] = lo.z; osum[0][3] = lo.w;
+      osum[0][4] = hi.x; osum[0][5] = hi.y; osum[0][6] = hi.z; osum[0][7] = hi.w;
     }
-    if (rsub == 0) {
-#pragma unroll
-      for (int c = 0; c < CPT; ++c) {
-        const int col = (sub + c * R) * 8;
-        if (col < h) {
-          float o[8];
-#pragma unroll
-          for (int i = 0; i < 8; ++i) {
-            o[i] = which == 0 ? gsum[c][i] : which == 1 ? bsum[c][i] : osum[c][i];
-            for (int rr = 1; rr < ROWS; ++rr) o[i] += comb[(((rr - 1) * CPT + c) * 8 + i) * R + sub];
-          }
-          store8(partial + (int64_t)blockIdx.x * 3 * h + which * h + col, o);
-        }
-      }
-    }
+    store_row_sums<R, 1, CPT>(sums, gsum, bsum, osum, row, h);
   }
 }
 
@@ -504,6 +508,8 @@ __global__ __launch_bounds__(512) void colsum_direct_kernel(const T* __restrict_
   __shared__ float part[128][33], part2[16][32];
   const int tid = threadIdx.x, cc = tid & 3, rl = tid >> 2;
   const int col = blockIdx.x * 32 + cc * 8;
+  const int oc = blockIdx.x * 32 + tid;
+  const float before = accumulate && tid < 32 && oc < n ? out[oc] : 0.f;
   float s[8] = {0, 0, 0, 0, 0, 0, 0, 0};
   if (col < n) {
     int r = rl;
@@ -536,7 +542,6 @@ __global__ __launch_bounds__(512) void colsum_direct_kernel(const T* __restrict_
     for (int k = 0; k < w; ++k) t[k] += t[k + w];
   part2[g][c] = t[0];
   __syncthreads();
-  const int oc = blockIdx.x * 32 + tid;
   if (tid < 32 && oc < n) {
 #pragma unroll
     for (int k = 0; k < 16; ++k) t[k] = part2[k][tid];
@@ -544,35 +549,55 @@ __global__ __launch_bounds__(512) void colsum_direct_kernel(const T* __restrict_
     for (int w = 8; w > 0; w /= 2)
 #pragma unroll
       for (int k = 0; k < w; ++k) t[k] += t[k + w];
-    out[oc] = accumulate ? out[oc] + t[0] : t[0];
+    out[oc] = before + t[0];
   }
 }
 
-// 16 columns x 16 part-lanes per workgroup: 64-byte segments per part row, 8 loads in flight per
-// thread, then an LDS tree over the part-lanes.
+__device__ __forceinline__ void plus(float& a, float b) { a += b; }
+__device__ __forceinline__ void plus(float4& a, const float4& b) { a.x += b.x; a.y += b.y; a.z += b.z; a.w += b.w; }
+// Sum of N numbers (a power of two) as a tree: log2 N roundings deep
+template <int N, typename T>
+__device__ __forceinline__ T pairwise(T (&v)[N]) {
+#pragma unroll
+  for (int w = N / 2; w > 0; w /= 2)
+#pragma unroll
+    for (int i = 0; i < w; ++i) plus(v[i], v[i + w]);
+  return v[0];
+}
+
+// s += rows p, p + 16, .. below `parts` (ld apart): 8, 4, 2 and 1 of them in flight at a time.  One after the other, the last seven
+// cost as many trips to memory (119 rows of 3 x 1920 fp32 columns 6.0 -> 5.0 us); all of them at once behind conditions is code that every
+// short call has to fetch (22 rows 3.7 -> 4.2).
+template <int N, typename T>
+__device__ __forceinline__ void add_rows(T& s, const float* __restrict__ at, int64_t step) {
+  T v[N];
+#pragma unroll
+  for (int i = 0; i < N; ++i) v[i] = *reinterpret_cast<const T*>(at + i * step);
+  plus(s, pairwise(v));
+}
+template <typename T>
+__device__ __forceinline__ T sum_rows(const float* __restrict__ partial, int p, int parts, int64_t ld) {
+  T s = T{};
+  for (; p + 7 * 16 < parts; p += 8 * 16) add_rows<8>(s, partial + p * ld, 16 * ld);
+  if (p + 3 * 16 < parts) { add_rows<4>(s, partial + p * ld, 16 * ld); p += 4 * 16; }
+  if (p + 16 < parts) { add_rows<2>(s, partial + p * ld, 16 * ld); p += 2 * 16; }
+  if (p < parts) add_rows<1>(s, partial + p * ld, 16 * ld);
+  return s;
+}
+
+// 16 columns x 16 part-lanes per workgroup: 64-byte segments per part row, then an LDS tree over the part-lanes.
 __global__ __launch_bounds__(kWg) void colsum_finalize_kernel(const float* __restrict__ partial, int parts, int n,
                                                                int ld, float* __restrict__ out, int accumulate) {
   __shared__ float red[16][17];
   const int c = threadIdx.x & 15, pl = threadIdx.x >> 4;
   const int col = blockIdx.x * 16 + c;
-  float s = 0.f;
-  if (col < n) {
-    int p = pl;
-    for (; p + 7 * 16 < parts; p += 8 * 16) {
-      float v[8];
-#pragma unroll
-      for (int i = 0; i < 8; ++i) v[i] = partial[(int64_t)(p + i * 16) * ld + col];
-#pragma unroll
-      for (int i = 0; i < 8; ++i) s += v[i];
-    }
-    for (; p < parts; p += 16) s += partial[(int64_t)p * ld + col];
-  }
-  red[pl][c] = s;
+  red[pl][c] = col < n ? sum_rows<float>(partial + col, pl, parts, ld) : 0.f;
   __syncthreads();
   if (pl == 0 && col < n) {
-    float t = 0.f;
+    float v[16];
 #pragma unroll
-    for (int i = 0; i < 16; ++i) t += red[i][c];
+    for (int i = 0; i < 16; ++i) v[i] = red[i][c];
+    const float t = pairwise(v);
     out[col] = accumulate ? out[col] + t : t;
   }
 }
@@ -617,19 +642,10 @@ __global__ __launch_bounds__(kWg) void colsum_partial_grouped_kernel(ColsumGroup
   }
 }
 
-// Sum of N float4 (a power of two) as a tree: log2 N roundings deep
-template <int N>
-__device__ __forceinline__ float4 pairwise(float4 (&v)[N]) {
-#pragma unroll
-  for (int w = N / 2; w > 0; w /= 2)
-#pragma unroll
-    for (int i = 0; i < w; ++i) { v[i].x += v[i + w].x; v[i].y += v[i + w].y; v[i].z += v[i + w].z; v[i].w += v[i + w].w; }
-  return v[0];
-}
-
 // out_s[n_s] (+)= sum over parts_s rows of partial_s, for up to kFinalizeMaxItems segments in one launch.
 // A workgroup owns 64 columns: 16 threads x 16 bytes cover 256 contiguous bytes of a row (whole cache lines; with
-// one float per thread a workgroup used half of every line it touched), 16 such groups walk the rows.
+// one float per thread a workgroup used half of every line it touched), 16 such groups walk the rows.  (32 columns and 32 groups, twice
+// the workgroups: 256 rows x 19512 columns 6.7 -> 7.9 us; 64 columns and 32 groups 7.4.)
 __global__ __launch_bounds__(kWg) void colsum_finalize_grouped_kernel(FinalizeGroup g) {
   __shared__ float4 red[16][17];
   int sidx = 0;
@@ -640,20 +656,7 @@ __global__ __launch_bounds__(kWg) void colsum_finalize_grouped_kernel(FinalizeGr
   const int c = threadIdx.x & 15, pl = threadIdx.x >> 4;
   const int col = ((blockIdx.x - g.block0[sidx]) * 16 + c) * 4;
   float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
-  if (col < n) {
-    int p = pl;
-    for (; p + 7 * 16 < parts; p += 8 * 16) {
-      float4 v[8];
-#pragma unroll
-      for (int i = 0; i < 8; ++i) v[i] = *reinterpret_cast<const float4*>(partial + (int64_t)(p + i * 16) * ld + col);
-      const float4 t = pairwise(v);
-      s.x += t.x; s.y += t.y; s.z += t.z; s.w += t.w;
-    }
-    for (; p < parts; p += 16) {
-      const float4 v = *reinterpret_cast<const float4*>(partial + (int64_t)p * ld + col);
-      s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
-    }
-  }
+  if (col < n) s = sum_rows<float4>(partial + col, pl, parts, ld);
   red[pl][c] = s;
   __syncthreads();
   if (pl == 0 && col < n) {
@@ -662,7 +665,7 @@ __global__ __launch_bounds__(kWg) void colsum_finalize_grouped_kernel(FinalizeGr
     for (int i = 0; i < 16; ++i) v[i] = red[i][c];
     float4 t = pairwise(v);
     float4* out = reinterpret_cast<float4*>(g.out[sidx] + col);
-    if (g.accumulate) { const float4 o = *out; t.x += o.x; t.y += o.y; t.z += o.z; t.w += o.w; }
+    if (g.accumulate) plus(t, *out);   // (asked for ahead of the rows, its branch holds them up: 22 rows 3.5 -> 4.0 us)
     *out = t;
   }
 }
@@ -776,20 +779,25 @@ hipError_t layernorm_bwd(const void* dy, const void* x, const float* mean, const
     *parts_out = grid;
     return hipGetLastError();
   }
-  const RowShape rs = row_shape(h);
-  const int groups = ceil_div(rows, kWg / rs.R);
+  const int cpt = ceil_div(h, 64 * 8);   // 1 to 4: 64 threads to a row (as row_shape has it)
+  const int groups = ceil_div(rows, kWg / 64);
   const int grid = groups < ln_bwd_max_parts() ? groups : ln_bwd_max_parts();
-#define CALL_BWD_AS(T_, R_, C_, K_)                                                                         \
-  hipLaunchKernelGGL((ln_bwd_kernel<T_, R_, C_, K_>), dim3(grid), dim3(kWg), 0, stream,                     \
+#define CALL_BWD_AS(T_, C_, K_)                                                                         \
+  hipLaunchKernelGGL((ln_bwd_kernel<T_, 64, C_, K_>), dim3(grid), dim3(kWg), 0, stream,                     \
                      static_cast<const T_*>(dy), static_cast<const T_*>(x), mean, rstd,                     \
                      static_cast<const T_*>(gain), static_cast<const T_*>(dres), static_cast<T_*>(dx),      \
                      partial, rows, h, static_cast<T_*>(dres_keep))
-#define CALL_BWD(R_, C_)                                                                                    \
-  if (dtype == kBF16 && dres_keep) CALL_BWD_AS(bf16_t, R_, C_, true);                                       \
-  else if (dtype == kBF16) CALL_BWD_AS(bf16_t, R_, C_, false);                                              \
-  else if (dres_keep) CALL_BWD_AS(float, R_, C_, true);                                                     \
-  else CALL_BWD_AS(float, R_, C_, false)
-  LN_DISPATCH(CALL_BWD)
+#define CALL_BWD(C_)                                                                                    \
+  if (dtype == kBF16 && dres_keep) CALL_BWD_AS(bf16_t, C_, true);                                       \
+  else if (dtype == kBF16) CALL_BWD_AS(bf16_t, C_, false);                                              \
+  else if (dres_keep) CALL_BWD_AS(float, C_, true);                                                     \
+  else CALL_BWD_AS(float, C_, false)
+  switch (cpt) {
+    case 1: CALL_BWD(1); break;
+    case 2: CALL_BWD(2); break;
+    case 3: CALL_BWD(3); break;
+    default: CALL_BWD(4); break;
+  }
 #undef CALL_BWD
 #undef CALL_BWD_AS
   *parts_out = grid;
