@@ -7,9 +7,9 @@
 // its four waves take every fourth tile of 32 rows of the streamed side; their partial results meet in LDS once, at
 // the end, in a fixed order.  Inside the loop nothing is shared and there is no barrier: a wave fetches its tiles into LDS of
 // its own (WaveTile), the next one under the last product of the current one.
-// Measured at b=2 s=512 a=8 dh=64, causal: forward 17 us, backward 41 (55 while every fragment came from L2 by itself and dQ
-// and dK/dV were launches of their own; 520 and 1146 with one thread per row on the vector ALU); the matrix instructions alone
-// are 7 and 14 us of the longest workgroups.
+// Measured at b=2 s=512 a=8 dh=64, causal: forward 17 us, backward 38 (41 in the plain order of blocks, see attn_f32_bwd_folded_kernel;
+// 55 while every fragment came from L2 by itself and dQ and dK/dV were launches of their own; 520 and 1146 with one thread per row on
+// the vector ALU); the matrix instructions alone are 7 and 14 us of the longest workgroups.
 //
 // v_mfma_f32_32x32x2_f32: lane l supplies element (l % 32, l / 32) of the first operand (32 x 2) and (l / 32, l % 32) of
 // the second (2 x 32); it receives column l % 32 of the result, rows 8*(r/4) + 4*(l/32) + (r%4) in register r.  The two
