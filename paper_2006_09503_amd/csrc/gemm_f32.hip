@@ -405,9 +405,12 @@ __global__ __launch_bounds__(512) void gemm_f32_wgrad_sums_kernel(GroupOfF32<kSu
 }
 
 // ------------------------------------------------------------------------------------------------
-// The smallest products (fewer 32 x 32 tiles than a quarter of the CUs): tiles of 16 x 16 on v_mfma_f32_16x16x4_f32, so that four times
-// as many CUs share the operands' way in and the products themselves (a 32 x 32 tile with K = 1024 is 3.5 us of one CU's matrix cores).
-// The eight waves take every eighth chunk of 16 k; up to NC chunks of a wave are in flight at once.
+// The smallest products (at most one tile of 16 x 16 per CU): v_mfma_f32_16x16x4_f32, so that four times as many CUs as with 32 x 32 share
+// the operands' way in and the products themselves (a 32 x 32 tile with K = 1024 is 3.5 us of one CU's matrix cores).
+// The eight waves take every eighth chunk of 16 k, two chunks of a wave in flight at once.  With more of them a wave asks for chunks that
+// it has not got whenever its share is no multiple, and starts on its first one later.  2 | 4 | 8 chunks in us, means over 650 random
+// sizes by K: 256 to 384 3.1 | 3.3 | 4.1; 1200 to 1700 5.3 | 6.0 | 7.3; 4800 to 6800 15.0 | 16.6 | 19.5; operands from memory instead of L2,
+// 256 to 360 3.8 | 3.9 | 4.5, 2048 to 2900 11.4 | 11.4 | 12.5.
 // Lane layout: lane l supplies row l % 16 of either operand at k = l / 16 and receives column l % 16, rows 4 * (l / 16) + r.
 // k-slots: instruction i of a chunk takes k = 4 * (l / 16) + i in lane l.
 template <bool ROW_CONTIG>
@@ -429,7 +432,7 @@ struct NarrowLoader {
     }
   }
 };
-constexpr int kNarrow = 16, kNarrowWaves = 8;
+constexpr int kNarrow = 16, kNarrowWaves = 8, kNarrowChunks = 2;
 
 // The waves' partial sums of a 16 x 16 tile (a lane owns row l16 and four consecutive columns) to the epilogue
 template <int EPI>
@@ -452,9 +455,9 @@ __device__ __forceinline__ void finish_narrow(const F32Params& p, const f32x4& a
   }
 }
 
-template <int NC, bool TB, int EPI>
+template <bool TB, int EPI>
 __global__ __launch_bounds__(kNarrowWaves * 64) void gemm_f32_narrow_kernel(F32Params p) {
-  constexpr int W = kNarrowWaves, T = kNarrow;
+  constexpr int W = kNarrowWaves, T = kNarrow, NC = kNarrowChunks;
   __shared__ __attribute__((aligned(16))) float part[W * T * (T + 4)];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l16 = lane & 15, quarter = lane >> 4;
   const int tiles_n = (p.N + T - 1) / T, m0 = (int)blockIdx.x / tiles_n * T, n0 = (int)blockIdx.x % tiles_n * T;
@@ -682,12 +685,9 @@ hipError_t launch_split(GroupF32& gp, hipStream_t s) {
 bool split_ok(const F32Params& p, bool ta, bool tb) { return (ta || p.vec_a) && (!tb || p.vec_b); }
 
 int64_t narrow_tiles(const F32Params& p) { return (int64_t)ceil_div(p.M, kNarrow) * ceil_div(p.N, kNarrow); }
-int narrow_chunks(const F32Params& p) { return p.K <= 2 * kNarrowWaves * kChunk ? 2 : 8; }   // of a wave, in flight at once
 template <bool TB, int EPI>
 hipError_t launch_narrow(const F32Params& p, hipStream_t s) {
-  const dim3 grid((int)narrow_tiles(p)), block(kNarrowWaves * 64);
-  if (narrow_chunks(p) == 2) hipLaunchKernelGGL((gemm_f32_narrow_kernel<2, TB, EPI>), grid, block, 0, s, p);
-  else hipLaunchKernelGGL((gemm_f32_narrow_kernel<8, TB, EPI>), grid, block, 0, s, p);
+  hipLaunchKernelGGL((gemm_f32_narrow_kernel<TB, EPI>), dim3((int)narrow_tiles(p)), dim3(kNarrowWaves * 64), 0, s, p);
   return hipGetLastError();
 }
 
@@ -723,10 +723,12 @@ int choose_f32(const F32Params* p, int count, bool ta, bool tb) {
   const double c32 = q.t32_0 + q.t32_tile * r32 + q.t32_k * std::ceil(r32) * (k32 / r32);
   if (c128 <= c64 && c128 <= c32) return 128;
   if (c64 <= c32) return 64;
-  // 16 x 16 tiles halve the time of long reductions as long as every CU has one tile at most; a second one takes as long again, and each
-  // brings twice the bytes of a 32 x 32 tile's share.  Tiles per CU, 32 x 32 | 16 x 16 in us: (tokens, in, out) forward (128,1024,256) 0.5
-  // 9.2 | 5.5; (100,2048,128) 0.22 15.9 | 8.5; (128,4096,512) 1.0 30.1 | 16.6; (925,80,712) data gradient 1.13 7.4 | 7.9;
-  // (51,2320,1352) 1.33 19.7 | 25.1; (926,120,1416) data gradient 1.81 11.4 | 14.9.  Up to K = 256 they are level.
+  // 16 x 16 tiles take 0.4 to 0.7 of the time as long as every CU has one tile at most; a second one takes as long again, and each brings
+  // twice the bytes of a 32 x 32 tile's share.  Tiles of 16 per CU, 32 x 32 | 16 x 16 in us: (tokens, in, out) forward (128,256,256) 0.5
+  // 4.1 | 2.8; (128,1024,256) 0.5 9.2 | 4.5; (100,2048,128) 0.22 15.9 | 6.6; (128,4096,512) 1.0 29.8 | 11.7; (16,1024,4096) 1.0 8.6 | 5.5;
+  // (16,4096,4096) 1.0 30.4 | 22.7, one token 28.3 | 21.2; (51,2320,1352) 1.33 20.0 | 19.8; data gradient 16 x 4096, K = 4096 1.0 26.5 | 17.0;
+  // 15 x 672, K = 288 0.16 4.1 | 3.2; 925 x 80, K = 712 1.13 7.3 | 5.7; 926 x 120, K = 1416 1.81 11.2 | 11.2.  1200 random sizes below the line:
+  // 0.60 of the time of 32 x 32, at worst 1.02 (14 x 72, K = 128).
   return !ta && count == 1 && p[0].K % 4 == 0 && narrow_tiles(p[0]) <= cus ? 16 : 32;
 }
 
@@ -884,7 +886,7 @@ void gemm_f32_kernel_name(const GemmDesc* d, int count, char* out, size_t cap) {
   switch (choose_f32(p, n, d[0].trans_a, d[0].trans_b)) {
     case 64: snprintf(out, cap, "gemm_f32_split_kernel<2, 2, 4, %s, %s, %d>", ta, tb, d[0].epilogue); break;
     case 32: snprintf(out, cap, "gemm_f32_split_kernel<1, 1, 8, %s, %s, %d>", ta, tb, d[0].epilogue); break;
-    case 16: snprintf(out, cap, "gemm_f32_narrow_kernel<%d, %s, %d>", narrow_chunks(p[0]), tb, d[0].epilogue); break;
+    case 16: snprintf(out, cap, "gemm_f32_narrow_kernel<%s, %d>", tb, d[0].epilogue); break;
     default: snprintf(out, cap, "gemm_f32_mfma_kernel<%s, %s, %d>", ta, tb, d[0].epilogue); break;
   }
 }

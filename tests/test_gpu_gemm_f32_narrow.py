@@ -14,3 +14,10 @@ pytestmark = pytest.mark.gpu
 def test_products_of_16x16_tiles(M, N, K, pad):
     for tb in (0, 1):
         products(M, N, K, 0, tb, pad)
+
+
+@pytest.mark.parametrize("M,N,K", [(16, 4096, 300), (1, 4088, 272), (15, 672, 288), (570, 20, 320), (33, 1350, 508), (4096, 12, 260)])
+def test_flat_products_and_reductions_just_above_two_chunks_per_wave(M, N, K):
+    """One row or column of tiles, up to one tile per CU; waves with two and with three chunks."""
+    for tb in (0, 1):
+        products(M, N, K, 0, tb, 4)

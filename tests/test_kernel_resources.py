@@ -135,3 +135,12 @@ def test_phased_gemm_kernels_use_no_scratch_and_fit_two_waves_per_simd():
     for name, field in found:
         assert field("private_segment_fixed_size") == 0 and field("vgpr_spill_count") == 0 and field("sgpr_spill_count") == 0, name
         assert field("vgpr_count") <= 256, name
+
+
+def test_narrow_fp32_gemm_kernels_have_one_instance_per_form_and_do_not_spill():
+    """16 x 16 tiles: one number of chunks in flight at every K (a second instance for long K was slower than 32 x 32 tiles from K = 257 to
+    about 450, and than the first one everywhere)."""
+    found = built_kernels(r"gemm_f32_narrow_kernel<")
+    assert {re.search(r"<([^>]*)>", name).group(1) for name, _ in found} == {f"{tb}, {epi}" for tb in ("false", "true") for epi in range(4)}
+    for name, field in found:
+        assert field("private_segment_fixed_size") == 0 and field("vgpr_spill_count") == 0 and field("sgpr_spill_count") == 0, name
