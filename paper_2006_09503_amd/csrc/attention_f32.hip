@@ -590,6 +590,17 @@ __global__ __launch_bounds__(kManyWaves * 64, (kPerSimd<DH>)) void attn_f32_bwd_
   else attn_f32_dkv_all<DH, kManyWaves, true>(qkv, o, d_o, lse, delta, dqkv, s, a, dh, 1, nullptr, k, smem);
 }
 
+// The fold where it pays.  Where it would turn only the last two positions, the dK/dV and the dQ workgroups of the shortest block change
+// places.  That gains or is level, except where blocks take more than one step of the four waves and heads x sequences divides the CUs, so that the
+// two stand exactly beside the longest dK/dV and the longest dQ: the longer of the long ones gets the longer of the short ones.  Folded over
+// plain, means and worst of 30 random calls each by heads x sequences: 4 1.006, 1.024; 8 1.022, 1.053; 16 1.032, 1.063; 32 1.044, 1.082
+// (b=4 s=138 a=8 dh=64 19.7 -> 21.0 us); one step, 64 0.952, 0.993; no divisor 0.989, 1.024.  (300 random folded calls with this rule:
+// 0.987, three positions and more 0.978, at worst 1.013.)
+bool folds(const AttnDesc& d, const Fold& fold, int blocks) {
+  const int turned = 2 * blocks - fold.at;
+  return turned > 2 || (turned == 2 && (blocks <= kManyWaves || gemm_compute_units() % (d.a * d.b) != 0));
+}
+
 template <typename K>
 hipError_t set_lds(K kern, size_t bytes) {
   return hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
@@ -642,7 +653,7 @@ hipError_t bwd_launch(const AttnDesc& d, bool one_launch, const void* qkv, const
   const float *q = static_cast<const float*>(qkv), *out = static_cast<const float*>(o), *g = static_cast<const float*>(d_o);
   float* dst = static_cast<float*>(dqkv);
   const Fold fold = fold_of(d, 2 * blocks, kFolds ? 2 : 1);
-  if (one_launch && kFolds && fold.at < 2 * blocks) {
+  if (one_launch && kFolds && folds(d, fold, blocks)) {
     if constexpr (kFolds)
       hipLaunchKernelGGL((attn_f32_bwd_folded_kernel<DH>), dim3(d.a, d.b, 2 * blocks), dim3(NW * 64), lds, st, q, out, g, lse, delta, dst, d.s, d.a, d.dh, blocks,
                          fold);

@@ -19,3 +19,11 @@ def test_fp32_backward(dh, b, s, a):
 @pytest.mark.parametrize("b,s,a", [(4, 1024, 16), (5, 513, 11), (8, 300, 17), (9, 1025, 13), (3, 1153, 12), (2, 2048, 24)])
 def test_bf16_forward(dh, b, s, a):
     bf16(dh, b, s, a, 1)
+
+
+@pytest.mark.parametrize("dh", [16, 32, 48, 64])
+@pytest.mark.parametrize("b,s,a", [(4, 138, 8), (1, 286, 16), (1, 537, 8), (4, 77, 16), (2, 128, 24), (2, 224, 11), (1, 150, 30), (2, 128, 26)])
+def test_fp32_backward_with_one_two_and_three_positions_turned(dh, b, s, a):
+    """Two positions stay as they are where blocks take more than one step and heads x sequences divides the CUs (the first three), and are
+    turned elsewhere; one and three."""
+    fp32(dh, b, s, a, 1)
