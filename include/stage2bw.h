@@ -208,7 +208,12 @@ enum {
  * (launches beyond the pool are not timed).  enable == 0: stop and free the pool. */
 int stage_timing_enable(stage_t* st, int enable, int32_t capacity);
 /* Synchronise, then add up elapsed milliseconds and launch counts per class since the last
- * call, and the FLOPs / bytes the launches were issued for.  Arrays of STAGE_K_COUNT. */
+ * call, and the FLOPs / bytes the launches were issued for.  Arrays of STAGE_K_COUNT.
+ * A launch that does the work of two classes is counted once, with its whole time, under the product's: in
+ * fp32 stages of few tokens a LayerNorm runs in the launch of the product that reads its result (GEMM_FWD,
+ * GEMM_DGRAD instead of LN_FWD, LN_BWD) and the bias, gain and shift sums in that of the weight
+ * gradients (GEMM_WGRAD instead of BIAS_GRAD).  Its FLOPs are the product's, its bytes those that the
+ * LayerNorm or the sums move (a product alone counts 0 bytes). */
 int stage_timing_collect(stage_t* st, double* ms_out, int64_t* launches_out, double* flops_out,
                          double* bytes_out);
 

@@ -787,10 +787,14 @@ bool ln_fits(const GemmDesc& d) {
   return p.vec_b && choose_f32(&p, 1, false, d.trans_b) <= 32 && narrow_tiles(p) * d.K <= 200000;
 }
 
+int ln_chunks(int K) {   // of a wave
+  const int c = ceil_div(K, kNarrowWaves * kChunk);
+  return c <= 2 ? c : kLnMaxChunks;
+}
 template <bool BWD, bool TB, int EPI>
 hipError_t launch_ln(const F32Params& p, const LnArgs& q, hipStream_t s) {
   const dim3 grid((int)narrow_tiles(p)), block(kNarrowWaves * 64);
-  switch (ceil_div(p.K, kNarrowWaves * kChunk)) {
+  switch (ln_chunks(p.K)) {
     case 1: hipLaunchKernelGGL((gemm_f32_ln_kernel<BWD, 1, TB, EPI>), grid, block, 0, s, p, q); break;
     case 2: hipLaunchKernelGGL((gemm_f32_ln_kernel<BWD, 2, TB, EPI>), grid, block, 0, s, p, q); break;
     default: hipLaunchKernelGGL((gemm_f32_ln_kernel<BWD, kLnMaxChunks, TB, EPI>), grid, block, 0, s, p, q); break;
@@ -836,6 +840,11 @@ hipError_t gemm_ln_bwd(const GemmDesc& d, const LnBackward& ln, hipStream_t stre
   q.dy = static_cast<const float*>(ln.dy); q.dres = static_cast<const float*>(ln.dres); q.partial = ln.partial;
   const F32Params p = to_params(d);
   return d.epilogue == kEpiGeluGrad ? launch_ln<true, true, kEpiGeluGrad>(p, q, stream) : launch_ln<true, true, kEpiStore>(p, q, stream);
+}
+
+void gemm_ln_kernel_name(const GemmDesc& d, char* out, size_t cap) {
+  const char* tb = d.trans_b ? "true" : "false";
+  snprintf(out, cap, "gemm_f32_ln_kernel<%s, %d, %s, %d>", tb, ln_chunks(d.K), tb, d.epilogue);
 }
 
 bool gemm_sums_fit(const GemmDesc* d, int count, const FinalizeItem* items, int n) {

@@ -104,6 +104,7 @@ bool gemm_ln_fwd_fits(const GemmDesc& d);
 bool gemm_ln_bwd_fits(const GemmDesc& d);
 hipError_t gemm_ln_fwd(const GemmDesc& d, const LnForward& ln, hipStream_t stream);
 hipError_t gemm_ln_bwd(const GemmDesc& d, const LnBackward& ln, hipStream_t stream);
+void gemm_ln_kernel_name(const GemmDesc& d, char* out, size_t cap);   // as a kernel trace prints it; trans_b: of LayerNorm backward
 
 // ---------------------------------------------------------------------------- column sums
 // partial[parts][n] = per-slab column sums of y[rows, n] (ld = ldy); parts <= colsum_max_parts().

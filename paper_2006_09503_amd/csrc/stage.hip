@@ -270,10 +270,13 @@ hipError_t run_gemm(stage2bw* st, int cls, const GemmDesc& d) {
   return timed(st, cls, name, 2.0 * d.M * d.N * d.K, 0.0, [&] { return gemm(d, st->cur); });
 }
 
+// Bytes that a LayerNorm moves (copy: it also leaves one of its input, backward of the residual gradient)
+double ln_fwd_bytes(const stage2bw* st, bool copy) { return (copy ? 3.0 : 2.0) * st->T * st->cfg.hidden * st->esize + 8.0 * st->T; }
+double ln_bwd_bytes(const stage2bw* st, bool copy) { return (copy ? 5.0 : 4.0) * st->T * st->cfg.hidden * st->esize + 8.0 * st->T; }
+
 hipError_t run_ln_fwd(stage2bw* st, const void* x, const void* gain, const void* shift, void* y, float* mean,
                       float* rstd, const LnKeep* keep = nullptr) {
-  const double bytes = (keep ? 3.0 : 2.0) * st->T * st->cfg.hidden * st->esize + 8.0 * st->T;
-  return timed(st, STAGE_K_LN_FWD, "ln_fwd_kernel", 0.0, bytes, [&] {
+  return timed(st, STAGE_K_LN_FWD, "ln_fwd_kernel", 0.0, ln_fwd_bytes(st, keep), [&] {
     return layernorm_fwd(x, gain, shift, y, mean, rstd, st->T, st->cfg.hidden, st->cfg.ln_eps, st->dtype, st->cur, keep);
   });
 }
@@ -284,7 +287,9 @@ hipError_t run_ln_gemm_fwd(stage2bw* st, const LnForward& ln, const GemmDesc& g)
     hipError_t e = run_ln_fwd(st, ln.x, ln.gain, ln.shift, ln.y, ln.mean, ln.rstd, ln.keep);
     return e != hipSuccess ? e : run_gemm(st, STAGE_K_GEMM_FWD, g);
   }
-  return timed(st, STAGE_K_GEMM_FWD, "gemm_f32_ln_kernel", 2.0 * g.M * g.N * g.K, 0.0, [&] { return gemm_ln_fwd(g, ln, st->cur); });
+  char name[96] = "";
+  if (st->timing) gemm_ln_kernel_name(g, name, sizeof(name));
+  return timed(st, STAGE_K_GEMM_FWD, name, 2.0 * g.M * g.N * g.K, ln_fwd_bytes(st, ln.keep), [&] { return gemm_ln_fwd(g, ln, st->cur); });
 }
 
 // LayerNorm backward; its two parameter gradients (gain | shift are adjacent in G) are left as
@@ -292,8 +297,7 @@ hipError_t run_ln_gemm_fwd(stage2bw* st, const LnForward& ln, const GemmDesc& g)
 hipError_t run_ln_bwd(stage2bw* st, const void* dy, const void* x, const float* mean, const float* rstd,
                       const void* gain, const void* dres, void* dx, float* partial, int* parts, void* dres_keep = nullptr) {
   const int h = st->cfg.hidden;
-  const double bytes = (dres_keep ? 5.0 : 4.0) * st->T * h * st->esize + 8.0 * st->T;
-  return timed(st, STAGE_K_LN_BWD, h >= 2048 ? "ln_bwd_wide_kernel" : "ln_bwd_kernel", 0.0, bytes, [&] {
+  return timed(st, STAGE_K_LN_BWD, h >= 2048 ? "ln_bwd_wide_kernel" : "ln_bwd_kernel", 0.0, ln_bwd_bytes(st, dres_keep), [&] {
     return layernorm_bwd(dy, x, mean, rstd, gain, dres, dx, partial, parts, st->T, h, st->dtype, st->cur, dres_keep);
   });
 }
@@ -305,7 +309,9 @@ hipError_t run_ln_bwd_gemm(stage2bw* st, const LnBackward& ln, const GemmDesc& g
     return e != hipSuccess ? e : run_gemm(st, STAGE_K_GEMM_DGRAD, g);
   }
   *parts = (g.M + 15) / 16;
-  return timed(st, STAGE_K_GEMM_DGRAD, "gemm_f32_ln_kernel", 2.0 * g.M * g.N * g.K, 0.0, [&] { return gemm_ln_bwd(g, ln, st->cur); });
+  char name[96] = "";
+  if (st->timing) gemm_ln_kernel_name(g, name, sizeof(name));
+  return timed(st, STAGE_K_GEMM_DGRAD, name, 2.0 * g.M * g.N * g.K, ln_bwd_bytes(st, ln.dres_keep), [&] { return gemm_ln_bwd(g, ln, st->cur); });
 }
 
 AttnDesc attn_desc(const stage2bw* st, const int32_t* lens) {
@@ -438,7 +444,7 @@ hipError_t flush_wgrad(stage2bw* st) {
     double flops = 0.0;
     for (int i = 0; i < cnt; ++i) flops += 2.0 * wg[i0 + i].M * (double)wg[i0 + i].N * wg[i0 + i].K;
     if (!st->fin.empty() && gemm_sums_fit(&wg[i0], cnt, st->fin.data(), (int)st->fin.size())) {   // (fp32: one pass per group)
-      hipError_t e = timed(st, STAGE_K_GEMM_WGRAD, "gemm_f32_wgrad_sums_kernel", flops, 0.0, [&] {
+      hipError_t e = timed(st, STAGE_K_GEMM_WGRAD, "gemm_f32_wgrad_sums_kernel", flops, 4.0 * st->fin_elems, [&] {
         return gemm_with_sums(&wg[i0], cnt, st->fin.data(), (int)st->fin.size(), st->fin_accumulate, st->cur);
       });
       if (e != hipSuccess) return e;
@@ -473,7 +479,8 @@ hipError_t flush_wgrad(stage2bw* st) {
 
 // Backward of all layers on weight buffer `buf` for the pass at position `pos` of the pending group,
 // whose activations are in set `set`.  Leaves the operands of the weight-gradient products in place
-// (flush_wgrad launches them); bias, gain and shift gradients go into G here (overwrite when `first`).
+// (flush_wgrad launches them); bias, gain and shift gradients go into G here (overwrite when `first`), in fp32 mode, where every pass is
+// a group of its own, in flush_wgrad too.
 hipError_t run_backward(stage2bw* st, int buf, int set, int pos, const int32_t* lens, const void* dy_in, void* dx_out,
                         bool first) {
   const stage_config_t& c = st->cfg;
