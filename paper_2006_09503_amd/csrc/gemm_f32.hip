@@ -782,7 +782,7 @@ bool aligned16(const void* ptr) { return (reinterpret_cast<uintptr_t>(ptr) & 15)
 // 1822 -> 1486, 1024 x 128 1205 -> 1109 (one layer), 180 x 192 2205 -> 2014, 1000 x 64 2054 -> 1845, 128 x 256 1805 -> 1494, 128 x 512 1812 ->
 // 1781; with the output projection's data gradient too (64 x 16 tiles of K = 256) 1024 x 256 3370 -> 3435, so the line is below that.
 bool ln_fits(const GemmDesc& d) {
-  if (d.dtype != kF32 || d.trans_a || d.n_seg != 1 || d.K % kChunk || d.K > gemm_ln_row_max() || d.N < d.K) return false;
+  if (d.dtype != kF32 || d.trans_a || d.n_seg != 1 || d.K % kChunk || d.K > kLnMaxChunks * kNarrowWaves * kChunk || d.N < d.K) return false;
   const F32Params p = to_params(d);
   return p.vec_b && choose_f32(&p, 1, false, d.trans_b) <= 32 && narrow_tiles(p) * d.K <= 200000;
 }
@@ -818,7 +818,6 @@ hipError_t gemm_f32_grouped(const GemmDesc* d, int count, hipStream_t stream) {
   return d[0].trans_b ? launch_epi<false, true>(gp, d[0].epilogue, stream) : launch_epi<false, false>(gp, d[0].epilogue, stream);
 }
 
-int gemm_ln_row_max() { return kLnMaxChunks * kNarrowWaves * kChunk; }
 bool gemm_ln_fwd_fits(const GemmDesc& d) { return !d.trans_b && (d.epilogue == kEpiStore || d.epilogue == kEpiGelu) && ln_fits(d); }
 bool gemm_ln_bwd_fits(const GemmDesc& d) { return d.trans_b && d.M <= kNarrow * ln_bwd_max_parts() && (d.epilogue == kEpiStore || d.epilogue == kEpiGeluGrad) && ln_fits(d); }
 

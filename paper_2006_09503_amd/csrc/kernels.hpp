@@ -99,7 +99,6 @@ struct LnBackward {
   void *dx = nullptr, *dres_keep = nullptr;
   float* partial = nullptr;
 };
-int gemm_ln_row_max();   // no longer rows than that
 bool gemm_ln_fwd_fits(const GemmDesc& d);
 bool gemm_ln_bwd_fits(const GemmDesc& d);
 hipError_t gemm_ln_fwd(const GemmDesc& d, const LnForward& ln, hipStream_t stream);

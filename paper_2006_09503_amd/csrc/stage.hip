@@ -302,9 +302,9 @@ hipError_t run_ln_bwd(stage2bw* st, const void* dy, const void* x, const float* 
   });
 }
 
-// ... and the product that reads dx, in the same launch where that pays
+// ... and the product that reads dx, in the same launch where that pays and the product writes none of the matrices read
 hipError_t run_ln_bwd_gemm(stage2bw* st, const LnBackward& ln, const GemmDesc& g, int* parts) {
-  if (!gemm_ln_bwd_fits(g)) {
+  if (g.C == ln.dy || !gemm_ln_bwd_fits(g)) {
     hipError_t e = run_ln_bwd(st, ln.dy, ln.x, ln.mean, ln.rstd, ln.gain, ln.dres, ln.dx, ln.partial, parts, ln.dres_keep);
     return e != hipSuccess ? e : run_gemm(st, STAGE_K_GEMM_DGRAD, g);
   }
@@ -312,6 +312,20 @@ hipError_t run_ln_bwd_gemm(stage2bw* st, const LnBackward& ln, const GemmDesc& g
   char name[96] = "";
   if (st->timing) gemm_ln_kernel_name(g, name, sizeof(name));
   return timed(st, STAGE_K_GEMM_DGRAD, name, 2.0 * g.M * g.N * g.K, ln_bwd_bytes(st, ln.dres_keep), [&] { return gemm_ln_bwd(g, ln, st->cur); });
+}
+
+// Data gradient of a projection: out[T,K] = grad[T,N] * W[K,N]^T, W at offset w_off of buffer `buf`
+GemmDesc dgrad_desc(const stage2bw* st, int buf, const void* grad, int N, int64_t w_off, int K, void* out) {
+  GemmDesc d;
+  d.dtype = st->dtype;
+  d.A = grad; d.lda = N; d.C = out; d.ldc = K;
+  d.M = st->T; d.N = K; d.K = N;
+  d.B = wptr(st, buf, w_off); d.ldb = N; d.trans_b = true;
+  return d;
+}
+// ... of the output projection of layer l
+GemmDesc out_dgrad_desc(const stage2bw* st, int buf, int l, const void* dx1, void* out) {
+  return dgrad_desc(st, buf, dx1, st->cfg.hidden, st->off[l].wo, st->cfg.hidden, out);
 }
 
 AttnDesc attn_desc(const stage2bw* st, const int32_t* lens) {
@@ -513,29 +527,27 @@ hipError_t run_backward(stage2bw* st, int buf, int set, int pos, const int32_t* 
     // the GEMM that computes it, dqkv (bf16 mode) from the attention backward kernels; the stage's
     // incoming dy, and du and dqkv in fp32 mode, are summed by the column-sum kernel.
     const bool fused_du = st->dtype == kBF16;
-    auto dgrad_desc = [&](const void* grad, int N, int64_t w_off, int K, void* out, const void* u, const char* next, int64_t next_elems) {
-      // out[T,K] = grad[T,N] * W[K,N]^T; next (may be null): the weights of the chain's next data-gradient GEMM
-      GemmDesc d;
-      d.dtype = st->dtype;
-      d.A = grad; d.lda = N; d.C = out; d.ldc = K;
-      d.M = T; d.N = K; d.K = N;
-      d.B = wptr(st, buf, w_off); d.ldb = N; d.trans_b = true;
+    // next (may be null): the weights of the chain's next data-gradient GEMM
+    auto ahead = [&](GemmDesc d, const char* next, int64_t next_elems) {
       if (next) { d.prefetch = next; d.prefetch_bytes = next_elems * st->esize; }
-      if (u) { d.epilogue = kEpiGeluGrad; d.aux = u; if (fused_du) d.colsum_partial = st->du_partial[l]; }
       return d;
     };
-    auto dgrad = [&](auto... args) { return run_gemm(st, STAGE_K_GEMM_DGRAD, dgrad_desc(args...)); };
+    auto dgrad = [&](const void* grad, int N, int64_t w_off, int K, void* out, const char* next, int64_t next_elems) {
+      return run_gemm(st, STAGE_K_GEMM_DGRAD, ahead(dgrad_desc(st, buf, grad, N, w_off, K, out), next, next_elems));
+    };
     // y = x1 + GELU(u) W2 + b2
-    const GemmDesc d_u = dgrad_desc(dy, h, o.w2, f, du, A.u, wptr(st, buf, o.w1), (int64_t)h * f);
+    GemmDesc d_u = ahead(dgrad_desc(st, buf, dy, h, o.w2, f, du), wptr(st, buf, o.w1), (int64_t)h * f);
+    d_u.epilogue = kEpiGeluGrad; d_u.aux = A.u;
+    if (fused_du) d_u.colsum_partial = st->du_partial[l];
     if (above.dx) e = run_ln_bwd_gemm(st, above, d_u, above_parts);
     else e = run_gemm(st, STAGE_K_GEMM_DGRAD, d_u);
     if (e != hipSuccess) return e;
     // u = c W1 + b1
-    e = dgrad(du, f, o.w1, h, st->tmp_h, nullptr, wptr(st, buf, o.wo), (int64_t)h * h);   if (e != hipSuccess) return e;
+    e = dgrad(du, f, o.w1, h, st->tmp_h, wptr(st, buf, o.wo), (int64_t)h * h);   if (e != hipSuccess) return e;
     // c = LN2(x1); dx1 = dy + LN2'(dc); x1 = x + o Wo + bo
     int& ln2_parts = parts[2 * l + 1];
     const LnBackward ln2{st->tmp_h, A.x1, wptr(st, buf, o.ln2_g), dy, A.mean2, A.rstd2, dx1, l == c.n_layers - 1 ? dy_keep : nullptr, st->ln_partial[l]};
-    e = run_ln_bwd_gemm(st, ln2, dgrad_desc(dx1, h, o.wo, h, st->tmp_o, nullptr, wptr(st, buf, o.wqkv), (int64_t)3 * h * h), &ln2_parts);
+    e = run_ln_bwd_gemm(st, ln2, ahead(out_dgrad_desc(st, buf, l, dx1, st->tmp_o), wptr(st, buf, o.wqkv), (int64_t)3 * h * h), &ln2_parts);
     if (e != hipSuccess) return e;
     if (l == c.n_layers - 1) dy = dy_keep;
     // attention
@@ -547,7 +559,7 @@ hipError_t run_backward(stage2bw* st, int buf, int set, int pos, const int32_t* 
     });
     if (e != hipSuccess) return e;
     // qkv = a Wqkv + bqkv
-    e = dgrad(dqkv, 3 * h, o.wqkv, h, st->tmp_h, nullptr, l > 0 ? wptr(st, buf, st->off[l - 1].w2) : nullptr, (int64_t)h * f);
+    e = dgrad(dqkv, 3 * h, o.wqkv, h, st->tmp_h, l > 0 ? wptr(st, buf, st->off[l - 1].w2) : nullptr, (int64_t)h * f);
     if (e != hipSuccess) return e;
     // a = LN1(x); dx = dx1 + LN1'(da): the first product of the layer below reads it, and goes out with it
     above = LnBackward{st->tmp_h, A.x, wptr(st, buf, o.ln1_g), dx1, A.mean1, A.rstd1, dx, nullptr, st->ln_partial2[l]};
@@ -712,9 +724,9 @@ int stage_create(const stage_config_t* cfg, const float* init_weights_host, void
     if (cfg->recompute) ALLOC(st->slot_x0[i], T * h * E, &st->bytes_stash);
   }
   ALLOC(st->tmp_h, T * h * E, nullptr);
-  // (LayerNorm backward and the output projection's data gradient in one launch: one buffer read, the other written)
+  // (where LayerNorm backward and the output projection's data gradient are one launch: one buffer read, the other written)
   st->tmp_o = st->tmp_h;
-  if (st->dtype == kF32 && gemm_ln_row_max() >= h) ALLOC(st->tmp_o, T * h * E, nullptr);
+  if (gemm_ln_bwd_fits(out_dgrad_desc(st, 0, 0, nullptr, nullptr))) ALLOC(st->tmp_o, T * h * E, nullptr);
   st->dx1.assign(cfg->n_layers, nullptr);
   st->dchain.assign(cfg->n_layers, nullptr);
   st->du.assign(cfg->n_layers, nullptr);

@@ -59,3 +59,26 @@ def test_report_of_fused_launches(hidden, heads, ffn, seq, layers, fused):
     # the instances of a fused stage are told apart: forward, with GELU, backward, and (where a layer has one below) with GELU'
     ln = [k for k in named if k.startswith("gemm_f32_ln_kernel")]
     assert len(ln) == (3 + (n > 1) if fused else 0), ln
+
+
+@pytest.mark.parametrize("hidden,heads,tokens", [(128, 4, (64, 256, 1024, 2048, 4096)), (256, 4, (64, 512, 1024, 2048)), (72, 1, (64, 128, 512)),
+                                                 (512, 8, (64, 256, 384, 1024))])
+def test_second_gradient_buffer_only_where_a_launch_needs_it(hidden, heads, tokens):
+    """Between two numbers of tokens the device bytes of a stage grow by as much per token, but for the buffer that the output projection's
+    data gradient has for itself where it runs in LayerNorm's launch: that one appears and goes with the launch."""
+    had, rest = [], []
+    for T in tokens:
+        cfg = synth.StageConfig(1, hidden, heads, 2 * hidden, T, 1, 1, 1, synth.MASK_NONE, synth.PREC_FP32)
+        st = B.Stage(cfg, synth.StageInputs(cfg, 3).weights())
+        dy = torch.zeros((1, T, hidden), device="cuda")
+        y, dx = torch.empty_like(dy), torch.empty_like(dy)
+        torch.cuda.synchronize()
+        st.timing_enable(True, 64)
+        st.forward(1, dy, None, y)
+        st.backward(1, dy, dx)
+        had.append(any(re.match(r"gemm_f32_ln_kernel<true, \d, true, 0>", k) for k in st.timing_collect_kernels()))
+        rest.append(st.query(B.Q_BYTES_ALLOCATED) - (T * hidden * 4 if had[-1] else 0))
+        st.close()
+    per_token = [(rest[i + 1] - rest[i]) / (tokens[i + 1] - tokens[i]) for i in range(len(tokens) - 1)]
+    assert len(set(per_token)) == 1, (had, per_token)
+    assert had[0] == (hidden % 16 == 0) and not had[-1], had
