@@ -144,3 +144,20 @@ def test_narrow_fp32_gemm_kernels_have_one_instance_per_form_and_do_not_spill():
     assert {re.search(r"<([^>]*)>", name).group(1) for name, _ in found} == {f"{tb}, {epi}" for tb in ("false", "true") for epi in range(4)}
     for name, field in found:
         assert field("private_segment_fixed_size") == 0 and field("vgpr_spill_count") == 0 and field("sgpr_spill_count") == 0, name
+
+
+def test_folded_fp32_attention_backward_does_not_spill_in_its_loops():
+    """The causal backward launch in the folded order, of the head sizes of which a CU holds two workgroups: as its plain form, it spills at head
+    size 64 only, four registers of the rare second run, and has a few bytes of scratch at 32."""
+    found = built_kernels(r"attn_f32_bwd_folded_kernel<")
+    assert sorted(int(re.search(r"<(\d+)>", name).group(1)) for name, _ in found) == [16, 32, 48, 64]
+    for name, field in found:
+        assert field("vgpr_spill_count") <= (4 if "<64>" in name else 0), name
+        assert field("private_segment_fixed_size") <= {"<64>": 44, "<32>": 36}.get(re.search(r"<\d+>", name).group(0), 0), name
+
+
+def test_fp32_gemm_kernels_that_hold_a_layernorm_or_the_sums_do_not_spill():
+    found = built_kernels(r"gemm_f32_(ln|wgrad_sums)_kernel")
+    assert len(found) == 13      # forward (plain, GELU) and backward (plain, GELU') of 1, 2 and 4 chunks; the weight gradients
+    for name, field in found:
+        assert field("private_segment_fixed_size") == 0 and field("vgpr_spill_count") == 0 and field("sgpr_spill_count") == 0, name
