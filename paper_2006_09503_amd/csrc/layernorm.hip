@@ -193,14 +193,13 @@ __device__ __forceinline__ void store_row_sums(float4* sums, const float (&gsum)
 // The third block is the bias gradient of the projection that produced this kernel's residual
 // operand (its output gradient is exactly dx), so no separate pass over dx is needed for it.
 // KEEP: also writes the rows of dres as they came to dres_keep (see the forward kernel).
-template <typename T, int R, int CPT, bool KEEP>
+template <typename T, int CPT, bool KEEP>
 __global__ __launch_bounds__(kWg) void ln_bwd_kernel(const T* __restrict__ dy, const T* __restrict__ x,
                                                       const float* __restrict__ mean_in, const float* __restrict__ rstd_in,
                                                       const T* __restrict__ gain, const T* __restrict__ dres,
                                                       T* __restrict__ dx, float* __restrict__ partial, int rows, int h, T* __restrict__ dres_keep) {
-  constexpr int ROWS = kWg / R;
-  __shared__ float red[4];
-  __shared__ float4 sums[ROWS > 1 ? row_sums_at_once(CPT) * 2 * CPT * kWg : 1];
+  constexpr int R = 64, ROWS = kWg / R;   // a wave to a row
+  __shared__ float4 sums[row_sums_at_once(CPT) * 2 * CPT * kWg];
   const int tid = threadIdx.x;
   const int sub = tid % R, rsub = tid / R;
   float gsum[CPT][8], bsum[CPT][8], osum[CPT][8], gn[CPT][8];
@@ -266,8 +265,8 @@ __global__ __launch_bounds__(kWg) void ln_bwd_kernel(const T* __restrict__ dy, c
           }
         }
       }
-      const float c1 = group_sum<R>(s1, red, tid) / (float)h;
-      const float c2 = group_sum<R>(s2, red, tid) / (float)h;
+      const float c1 = wave_sum(s1) / (float)h;
+      const float c2 = wave_sum(s2) / (float)h;
       if (row_ok[u]) {
 #pragma unroll
         for (int c = 0; c < CPT; ++c) {
@@ -781,11 +780,11 @@ hipError_t layernorm_bwd(const void* dy, const void* x, const float* mean, const
     *parts_out = grid;
     return hipGetLastError();
   }
-  const int cpt = ceil_div(h, 64 * 8);   // 1 to 4: 64 threads to a row (as row_shape has it)
-  const int groups = ceil_div(rows, kWg / 64);
+  const int cpt = ceil_div(h, 64 * 8);   // 1 to 4
+  const int groups = ceil_div(rows, kWg / 64);   // rows of a workgroup: one per wave
   const int grid = groups < ln_bwd_max_parts() ? groups : ln_bwd_max_parts();
 #define CALL_BWD_AS(T_, C_, K_)                                                                         \
-  hipLaunchKernelGGL((ln_bwd_kernel<T_, 64, C_, K_>), dim3(grid), dim3(kWg), 0, stream,                     \
+  hipLaunchKernelGGL((ln_bwd_kernel<T_, C_, K_>), dim3(grid), dim3(kWg), 0, stream,                     \
                      static_cast<const T_*>(dy), static_cast<const T_*>(x), mean, rstd,                     \
                      static_cast<const T_*>(gain), static_cast<const T_*>(dres), static_cast<T_*>(dx),      \
                      partial, rows, h, static_cast<T_*>(dres_keep))
