@@ -1,7 +1,7 @@
 """fp32 stages whose LayerNorms go out with the product that reads their result: rows of one, two and up to four chunks of 16 per wave
 (and some waves without one), token counts that fill no tile, one token, an FFN narrower than the rows (its LayerNorms have launches of
 their own), both sides of the line on tiles x row length, recomputation (the copy of the input is the only one kept); the sums
-of the small gradients in the launch of the weight gradients (up to three layers) and in one of their own (more)."""
+of the small gradients in the launch of the weight gradients (up to four layers) and in one of their own (more)."""
 import numpy as np
 import pytest
 
@@ -38,3 +38,32 @@ def test_layernorms_in_the_products_launch(hidden, heads, ffn, seq, micro, layer
             g, w = G[off:off + n], want.G[0][off:off + n]
             # (the key part of the QKV bias has a gradient of zero but for rounding: relative to the whole)
             assert np.abs(g - w).max() < 2e-5 * np.abs(w).max(), name
+
+
+@pytest.mark.parametrize("bad", [float("nan"), float("inf"), float("-inf")])
+@pytest.mark.parametrize("hidden,heads,seq,pos", [(16, 1, 20, 19), (128, 4, 20, 3), (272, 17, 20, 19), (512, 8, 33, 32)])
+def test_infinities_and_nans_stay_with_their_tokens(hidden, heads, seq, pos, bad):
+    """One token of the second of two sequences holds infinities or NaNs, in its input or in its output gradient: rows of the first sequence in
+    the same tiles, and later or earlier tokens that a causal mask keeps apart, come out as without it.  (seq 20: the first 16 rows end
+    inside the first sequence; pos = seq - 1: the row that the rows past the matrix are copies of.)"""
+    cfg = synth.StageConfig(2, hidden, heads, 2 * hidden, seq, 2, 1, 1, synth.MASK_CAUSAL, synth.PREC_FP32)
+    gen = synth.StageInputs(cfg, 7)
+    w0 = gen.weights()
+    x, dy, lens = gen.microbatches(1)[0]
+    run = lambda x, dy: run_stage_gpu(cfg, w0, [(x, dy, lens)], 1, snapshot=False)
+    clean = run(x, dy)
+    px, pdy = x.copy(), dy.copy()
+    px[1, pos] = bad
+    pdy[1, pos] = bad
+    got = run(px, dy)
+    y, dx = got["Y"][1], got["dX"][1]
+    assert np.array_equal(y[0], clean["Y"][1][0]) and np.array_equal(dx[0], clean["dX"][1][0])
+    if pos > 0:
+        assert rel(y[1, :pos], clean["Y"][1][1, :pos]) < 2e-6
+    assert np.isnan(y[1, pos]).all()
+    got = run(x, pdy)
+    y, dx = got["Y"][1], got["dX"][1]
+    assert np.array_equal(y, clean["Y"][1]) and np.array_equal(dx[0], clean["dX"][1][0])
+    if pos + 1 < seq:
+        assert rel(dx[1, pos + 1:], clean["dX"][1][1, pos + 1:]) < 2e-6
+    assert np.isnan(dx[1, pos]).all()
