@@ -722,7 +722,9 @@ bool fwd_one_wave(const AttnDesc& d) {
 // 1.0), to 1.5 0.72 to 0.93, to 2 0.92 to 1.16, to 2.5 0.82 to 0.95, to 3 0.97 to 1.1; under a causal mask 0.65 as long as the longest
 // blocks fit side by side.  The constants below, which weigh the four forms in units of a tile, are fitted to 5568 random sizes with each
 // form forced.
-// Over the least time of the forms: up to 64 1.008, above 1.006.  Over the time before the tiles went through LDS and the two halves into
+// Over the least time of the forms: up to 64 1.008, above 1.006.  (The folded order, later than the fit, makes four waves faster where it applies;
+// 500 random causal calls of up to 700 blocks with heads up to 64, one wave and four forced: 1.004, 15 calls more than 1.03, all of them of 480 to
+// 672 blocks of short sequences, where nothing is folded, the worst b=7 s=96 a=24 dh=48 23.7 | 28.8.)  Over the time before the tiles went through LDS and the two halves into
 // one launch: up to 64 0.61, above 0.68, of 5568 calls 13 more than 1.03, the worst b=7 s=88 a=12 dh=80 causal, 28.6 -> 32.0 us.  (With
 // the rule of the shorter heads above 64, too: 1.05 over the least, 235 calls more than 1.03 over that time, at worst 1.26.)
 struct BwdForm { int waves; bool one_launch; };

@@ -39,8 +39,11 @@ hipError_t attention_bwd_mfma_4x2(const AttnDesc& d, const void* qkv, const void
 // the CUs has no block of 256 rows.  At head size 128 the backward's dK and dV are workgroups of their own in these shapes, so two
 // rounds begin at half as many rows.  4 x 2 while 8 x 2 would not fill half of the CUs.  Sequences of one tile have nothing to split:
 // 4 x 2 there only packs more workgroups into a CU, where the registers allow it (backward; forward up to head size 64: at 80
-// b=36 s=52 a=12 8.7 -> 9.6 us).  Over 700 random sizes the choice costs 3 % over the best shape, and no call of 491 with a fixed head
-// size that takes more than 6 us is slower than on 8 x 1 by more than 2 %.
+// b=36 s=52 a=12 8.7 -> 9.6 us).  Over 700 random sizes of all masks the choice costs 3 % over the best shape, and no call of 491 with a fixed
+// head size that takes more than 6 us is slower than on 8 x 1 by more than 2 %.  Under a causal mask alone, where the lines are coarsest,
+// the forward pass is 9 % over the best shape (600 random calls of 60 to 1100 workgroups of 256 rows, every shape forced: 1.094, at worst 1.7;
+// in the plain order of blocks 1.099, so the folded order has not moved the lines): mostly 4 x 2 where 8 x 2 is taken, or, for
+// heads up to 48, 8 x 1.
 namespace {
 enum Shape { k8x1, k8x2, k4x2 };
 Shape shape_for(const AttnDesc& d, bool bwd) {

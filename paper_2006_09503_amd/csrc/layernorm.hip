@@ -136,8 +136,9 @@ __global__ __launch_bounds__(kWg) void ln_fwd_kernel(const T* __restrict__ x, co
 // The end of a backward workgroup: the column sums of its ROWS sub-rows (R threads each, chunks of 8 columns at (sub + c * R) * 8) added in
 // the order of the rows and stored to row = [3][h].  The matrices go through LDS as 16-byte pieces [which][CPT][2][thread] and every thread
 // takes its share of the adding and storing; all three at once, unless two workgroups would no longer fit into a CU's LDS.
-// (One matrix after the other, added and stored by the threads of the first sub-row alone: bf16 4096 x 1024 12.1 -> 11.6 us, 4096 x 2560 21.4 -> 21.0,
-// fp32 1428 x 1920 14.2 -> 13.4; all three at once there, one workgroup per CU, 16.9.)
+// (One matrix after the other, added and stored by the threads of the first sub-row alone: bf16 4096 x 1024 12.0 -> 11.3 us, 1024 x 512 4.9 -> 4.6,
+// fp32 1428 x 1920 14.2 -> 12.9, 476 x 1920 8.6 -> 7.6; rows of 2048 columns and more, 4096 x 2560 21.4, are level.  All three at once for
+// fp32 1428 x 1920, one workgroup per CU, 16.9.)
 // IN_LDS: the third matrix is there already.
 constexpr int row_sums_at_once(int cpt) { return cpt < 4 ? 3 : 1; }
 template <int R, int ROWS, int CPT, bool IN_LDS = false>
