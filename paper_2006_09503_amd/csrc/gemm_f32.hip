@@ -781,6 +781,8 @@ bool aligned16(const void* ptr) { return (reinterpret_cast<uintptr_t>(ptr) & 15)
 // rows again.  Three batches of 4 microbatches of an fp32 stage with and without, us (tokens x h, f = 4 h): 128 x 128 1800 -> 1499, 300 x 128
 // 1822 -> 1486, 1024 x 128 1205 -> 1109 (one layer), 180 x 192 2205 -> 2014, 1000 x 64 2054 -> 1845, 128 x 256 1805 -> 1494, 128 x 512 1812 ->
 // 1781; with the output projection's data gradient too (64 x 16 tiles of K = 256) 1024 x 256 3370 -> 3435, so the line is below that.
+// (Above K = 256 the products alone have become faster since, two chunks in flight: 60 random stages of two layers with h = 256 to 512 and up to
+// 500 tokens 0.90 of the time of the separate launches, at worst 1.01.)
 bool ln_fits(const GemmDesc& d) {
   if (d.dtype != kF32 || d.trans_a || d.n_seg != 1 || d.K % kChunk || d.K > kLnMaxChunks * kNarrowWaves * kChunk || d.N < d.K) return false;
   const F32Params p = to_params(d);
